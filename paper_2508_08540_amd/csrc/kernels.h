@@ -47,6 +47,8 @@ __device__ __forceinline__ void fixsum_flush(fixsum_t* dst, long long sum, bool 
     if (poisoned) atomicMax(reinterpret_cast<long long*>(dst), FIX_POISON);
     else atomicAdd(dst, (fixsum_t)sum);
 }
+// erf form of the GELU
+__device__ __forceinline__ float gelu_f32(float v) { return 0.5f * v * (1.f + erff(v * 0.70710678118654752f)); }
 // ReLU that keeps NaN (the hardware maximum returns the other operand): a poisoned statistic or a diverged weight has to
 // reach the losses instead of being clamped to zero on the way.
 __device__ __forceinline__ float relu_keep_nan(float t) { return t < 0.f ? 0.f : t; }
@@ -281,7 +283,9 @@ int launch_wconv(hipStream_t s, int act, int taps, int B, int h_in, int h_out, i
 // ---- gemm_tiled.hip -----------------------------------------------------------------------------------
 // C[m][n] = alpha * sum_k A(m,k) B(n,k) [+ bias[n]] [+ R[m][n]]; A(m,k) = a_kmajor ? A[k*lda + m] : A[m*lda + k], same for B.
 // Batched over z = z1 * inner + z2 (z1 < batch / inner): pointer offsets z1*s?1 + z2*s?2 (R uses C's).  splits > 1 splits
-// K into partials in `part` (batch must be 1) that are added in order.  Fields below the line are filled by the launcher.
+// K into partials in `part` that are added in order (a batch then needs inner == 1); it is the most the launcher may use
+// (unaligned products use it as it is).  k_seg > 0 (a multiple of 16): the contraction runs over
+// K / k_seg pairs of matrices, sa_seg and sb_seg apart.  Fields below the line are filled by the launcher.
 struct GemmDesc {
     const float *A, *B;
     float* C;
@@ -292,9 +296,12 @@ struct GemmDesc {
     int a_kmajor, b_kmajor;
     int batch, inner, splits;
     int64_t sa1, sa2, sb1, sb2, sc1, sc2;
+    int64_t sbias1;   // floats between the bias vectors of consecutive z1
+    int k_seg;
+    int64_t sa_seg, sb_seg;
     float alpha;
     // ----
-    int k_chunk, a_vec, b_vec;
+    int k_chunk, a_vec, b_vec, c_vec;
     int64_t part_stride;
 };
 size_t gemm_tiled_partial_floats(int M, int N, int splits);

@@ -76,9 +76,11 @@ int wgrad_splits(int M, int N, int64_t K, int batch = 1) {
 
 // Splits of a long contraction whose output has too few tiles to keep three workgroups on every compute unit (what
 // hides the load latency of the K loop); only for fp32 outputs, since the partial sums are added by a second kernel.
+// The fp32 products choose for themselves below a limit (16 parts, none shorter than 256).
 #define DGRAD_SPLIT_MIN_K 4096
-int dgrad_splits(int64_t M, int N, int K) {
+int dgrad_splits(bool bf, int64_t M, int N, int K) {
     const int64_t tiles = ceil_div(M, 128) * ceil_div(N, 128);
+    if (!bf) return tiles >= 512 || K < 512 ? 1 : K / 256 < 16 ? K / 256 : 16;
     if (K < DGRAD_SPLIT_MIN_K || tiles >= 512) return 1;
     int64_t s = ceil_div(768, tiles);
     if (s > K / 1024) s = K / 1024;
@@ -139,6 +141,13 @@ SeqScratch carve(Carver& c, const bls_model* m, int B, bool train) {
     s.ce_rows = bf ? c.take<float>(2 * T) : nullptr;
     s.tok_loss = c.take<float>(T);
     s.loss = c.take<float>(B);
+    size_t part = 0;   // split contractions of the main stream (fp32 mode: the forward products too)
+    for (int n_out : {D, 3 * D, F, V})
+        for (int n_in : {D, F}) {
+            const size_t f = gemm_tiled_partial_floats((int)T, n_in, dgrad_splits(bf, T, n_in, n_out));
+            part = (train || !bf) && f > part ? f : part;
+        }
+    s.part_main = c.take<float>(part ? part : 1);
     if (!train) return s;
     if (bf) s.dlogits.h = c.take<uint16_t>(T * V);
     else s.dlogits.f = s.logits;
@@ -153,7 +162,7 @@ SeqScratch carve(Carver& c, const bls_model* m, int B, bool train) {
         s.df[l] = take(c, bf, BOTH, T * F);
         take3(c, bf, BOTH, T * D, s.dq[l], s.dk[l], s.dv[l]);
     }
-    size_t part = 0;
+    part = 0;
     auto need = [&](int M, int N) {
         const size_t f = gemm_tiled_partial_floats(M, N, wgrad_splits(M, N, T));
         part = f > part ? f : part;
@@ -167,13 +176,6 @@ SeqScratch carve(Carver& c, const bls_model* m, int B, bool train) {
     need(D, F);
     need(V, D);
     s.part = c.take<float>(part ? part : 1);
-    part = 0;
-    for (int n_out : {D, F, V})
-        for (int n_in : {D, F}) {
-            const size_t f = gemm_tiled_partial_floats((int)T, n_in, dgrad_splits(T, n_in, n_out));
-            part = f > part ? f : part;
-        }
-    s.part_main = c.take<float>(part ? part : 1);
     // partial column sums of one backward pass: per layer five D-wide and one F-wide bias gradient and two layer norms
     const size_t per_layer = 3 * colsum_partial_floats(T, D) + colsum_partial_floats(T, F) + gelu_bwd_colsum_floats(T, F) + 2 * layernorm_bwd_partial_floats(T, D) + (size_t)12 * B * D;
     const size_t pos = colsum_partial_floats(B, L * D);
@@ -200,6 +202,8 @@ struct Product {
     bool a_kmajor = false, b_kmajor = false;
     int batch = 1, inner = 1, splits = 1;
     int64_t sa1 = 0, sa2 = 0, sb1 = 0, sb2 = 0, sc1 = 0, sc2 = 0, sbias1 = 0;
+    int k_seg = 0;                         // fp32 mode: the contraction runs over K / k_seg pairs of matrices
+    int64_t sa_seg = 0, sb_seg = 0;
     float alpha = 1.f;
     const int32_t* ce_targets = nullptr;   // bf16 mode only: leave softmax statistics of the rows behind
     float *ce_part = nullptr, *ce_tlogit = nullptr;
@@ -227,6 +231,8 @@ void multiply(bls_ctx* ctx, hipStream_t st, bool bf, const Product& p, int prof_
         d.a_kmajor = p.a_kmajor; d.b_kmajor = p.b_kmajor;
         d.batch = p.batch; d.inner = p.inner; d.splits = p.splits;
         d.sa1 = p.sa1; d.sa2 = p.sa2; d.sb1 = p.sb1; d.sb2 = p.sb2; d.sc1 = p.sc1; d.sc2 = p.sc2;
+        d.sbias1 = p.sbias1;
+        d.k_seg = p.k_seg; d.sa_seg = p.sa_seg; d.sb_seg = p.sb_seg;
         d.alpha = p.alpha;
         launch_gemm_tiled(st, d);
     }
@@ -251,6 +257,10 @@ struct Net {
         p.bias = b_off >= 0 ? params + b_off : nullptr;
         p.R = R;
         p.M = (int)T; p.N = n_out; p.K = n_in;
+        if (!s->bf && !gelu.f) {
+            p.splits = dgrad_splits(false, T, n_out, n_in);
+            p.part = s->part_main;
+        }
         multiply(ctx, st, s->bf, p, PROF_GEMM);
     }
     // Per-token losses of the encoder output hf against `targets`; with keep_logits the logits stay in s->logits (and,
@@ -281,7 +291,7 @@ struct Net {
         p.R = R;
         p.M = (int)T; p.N = n_in; p.K = n_out;
         if (s->bf && !dx.h) {
-            p.splits = dgrad_splits(T, n_in, n_out);
+            p.splits = dgrad_splits(s->bf, T, n_in, n_out);
             p.part = s->part_main;
         }
         multiply(ctx, st, s->bf, p, PROF_GEMM);
@@ -301,8 +311,8 @@ struct Net {
     // equally spaced; three products otherwise
     void qkv(Mat x, int64_t T, const EncLayer& e, const LayerAct& a) const {
         const int D = m->enc_D;
-        const int64_t sw = e.wk - e.wq, so = a.k.h - a.q.h;
-        if (s->bf && e.wv - e.wk == sw && e.bk - e.bq == sw && e.bv - e.bk == sw && a.v.h - a.k.h == so) {
+        const int64_t sw = e.wk - e.wq, so = s->bf ? a.k.h - a.q.h : a.k.f - a.q.f;
+        if (e.wv - e.wk == sw && e.bk - e.bq == sw && e.bv - e.bk == sw && (s->bf ? a.v.h - a.k.h : a.v.f - a.k.f) == so) {
             Product p;
             p.A = x; p.lda = D;
             p.B = weight(e.wq); p.ldb = D; p.sb1 = sw;
@@ -310,7 +320,7 @@ struct Net {
             p.bias = params + e.bq; p.sbias1 = sw;
             p.M = (int)T; p.N = D; p.K = D;
             p.batch = 3;
-            multiply(ctx, st, true, p, PROF_GEMM);
+            multiply(ctx, st, s->bf, p, PROF_GEMM);
             return;
         }
         linear(x, T, D, e.wq, e.bq, D, a.q);
@@ -320,8 +330,8 @@ struct Net {
     // Weight gradients of the same three projections from dq, dk, dv
     void qkv_wgrad(Mat dq, Mat dk, Mat dv, Mat x, int64_t T, const EncLayer& e) const {
         const int D = m->enc_D;
-        const int64_t sw = e.wk - e.wq, sd = dk.h - dq.h;
-        if (s->bf && e.wv - e.wk == sw && dv.h - dk.h == sd) {
+        const int64_t sw = e.wk - e.wq, sd = s->bf ? dk.h - dq.h : dk.f - dq.f;
+        if (e.wv - e.wk == sw && (s->bf ? dv.h - dk.h : dv.f - dk.f) == sd) {
             Product p;
             p.A = dq; p.lda = D; p.a_kmajor = true; p.sa1 = sd;
             p.B = x; p.ldb = D; p.b_kmajor = true;
@@ -330,12 +340,34 @@ struct Net {
             p.batch = 3;
             p.splits = wgrad_splits(D, D, T, 3);
             p.part = s->part;
-            multiply(ctx, st, true, p, PROF_CONV_WGRAD);
+            multiply(ctx, st, s->bf, p, PROF_CONV_WGRAD);
             return;
         }
         linear_wgrad(dq, x, T, D, D, e.wq);
         linear_wgrad(dk, x, T, D, D, e.wk);
         linear_wgrad(dv, x, T, D, D, e.wv);
+    }
+    // dx = dq Wq + dk Wk + dv Wv + R: in fp32 mode one contraction over the three pairs
+    void qkv_dgrad(Mat dq, Mat dk, Mat dv, int64_t T, const EncLayer& e, Mat dx, const float* R) const {
+        const int D = m->enc_D;
+        const int64_t sw = e.wk - e.wq;
+        // (segments need the 16-byte rows of the direct kernel)
+        if (!s->bf && e.wv - e.wk == sw && sw % 4 == 0 && dv.f - dk.f == dk.f - dq.f && D % 16 == 0 && (reinterpret_cast<uintptr_t>(params + e.wq) & 15) == 0) {
+            Product p;
+            p.A = dq; p.lda = D; p.sa_seg = dk.f - dq.f;
+            p.B = weight(e.wq); p.ldb = D; p.b_kmajor = true; p.sb_seg = sw;
+            p.k_seg = D;
+            p.out = dx; p.ldc = D;
+            p.R = R;
+            p.M = (int)T; p.N = D; p.K = 3 * D;
+            p.splits = dgrad_splits(false, T, D, 3 * D);
+            p.part = s->part_main;
+            multiply(ctx, st, false, p, PROF_GEMM);
+            return;
+        }
+        linear_dgrad(dq, T, D, e.wq, D, dx, R);    // starting from the residual path
+        linear_dgrad(dk, T, D, e.wk, D, dx, dx.f);
+        linear_dgrad(dv, T, D, e.wv, D, dx, dx.f);
     }
     // Batched product over (sample, head): factors and result are slices of [T][D] activations (row pitch D, head
     // offset D/H) or of a [B][H][L][L] tensor (probs).
@@ -586,9 +618,7 @@ int seq_local_step(bls_ctx* ctx, const bls_model* m, float* params, float* momen
                 bias_grad(dk.f, D, e.bk);
                 bias_grad(dv.f, D, e.bv);
             }
-            net.linear_dgrad(dq, T, D, e.wq, D, da, db1.f);    // da = dx, starting from the residual path
-            net.linear_dgrad(dk, T, D, e.wk, D, da, s.da);
-            net.linear_dgrad(dv, T, D, e.wv, D, da, s.da);
+            net.qkv_dgrad(dq, dk, dv, T, e, da, db1.f);    // da = dx
         }
         // embeddings: position gradient = sum over samples, token gradient = scatter by id
         flush_sums();
