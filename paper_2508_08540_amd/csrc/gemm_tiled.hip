@@ -198,7 +198,7 @@ __global__ __launch_bounds__(256) void gemm_tiled_kernel(GemmDesc d) {
 //
 // Tile choice (launcher): the tile for which the busiest compute unit has least to do.  3100 tokens x 512 outputs are 100
 // tiles of 128 x 128 for 256 compute units but 196 of 64 x 128.
-#define GD_STAGES 4
+#define GD_STAGES 3
 typedef __attribute__((address_space(1))) const void gd_global_ptr;
 typedef __attribute__((address_space(3))) void gd_lds_ptr;
 

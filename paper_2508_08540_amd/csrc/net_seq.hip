@@ -141,13 +141,13 @@ SeqScratch carve(Carver& c, const bls_model* m, int B, bool train) {
     s.ce_rows = bf ? c.take<float>(2 * T) : nullptr;
     s.tok_loss = c.take<float>(T);
     s.loss = c.take<float>(B);
-    size_t part = 0;   // split contractions of the main stream (fp32 mode: the forward products too)
+    size_t part = 0;   // split contractions of the main stream
     for (int n_out : {D, 3 * D, F, V})
         for (int n_in : {D, F}) {
             const size_t f = gemm_tiled_partial_floats((int)T, n_in, dgrad_splits(bf, T, n_in, n_out));
-            part = (train || !bf) && f > part ? f : part;
+            part = train && f > part ? f : part;
         }
-    s.part_main = c.take<float>(part ? part : 1);
+    s.part_main = train ? c.take<float>(part ? part : 1) : nullptr;
     if (!train) return s;
     if (bf) s.dlogits.h = c.take<uint16_t>(T * V);
     else s.dlogits.f = s.logits;
@@ -257,7 +257,7 @@ struct Net {
         p.bias = b_off >= 0 ? params + b_off : nullptr;
         p.R = R;
         p.M = (int)T; p.N = n_out; p.K = n_in;
-        if (!s->bf && !gelu.f) {
+        if (!s->bf && !gelu.f && s->part_main) {   // training only: a score is the same bits whatever it is scored with
             p.splits = dgrad_splits(false, T, n_out, n_in);
             p.part = s->part_main;
         }
@@ -290,7 +290,7 @@ struct Net {
         p.out = dx; p.ldc = n_in;
         p.R = R;
         p.M = (int)T; p.N = n_in; p.K = n_out;
-        if (s->bf && !dx.h) {
+        if (!dx.h) {   // partial sums are added into fp32 only
             p.splits = dgrad_splits(s->bf, T, n_in, n_out);
             p.part = s->part_main;
         }
