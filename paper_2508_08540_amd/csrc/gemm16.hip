@@ -12,6 +12,8 @@
 // global loads (16 bytes = 8 bf16 per lane) are in flight in registers while the matrix instructions run.  The B tile is passed as the first MFMA operand, so
 // that lane (r, g) holds C[m = r][n = 4g .. 4g+3] of a block: four adjacent outputs, stored with one 16-byte (fp32)
 // or 8-byte (bf16) store.
+#include <type_traits>
+
 #include "act.h"
 #include "kernels.h"
 
@@ -128,6 +130,33 @@ __device__ __forceinline__ void g16_put(bf16_t* __restrict__ S, const u32x4 (&v)
     }
 }
 
+// GELU (erf form) for results that are rounded to bf16: x Phi(x) with Phi(-|x|) = exp(-x^2 / 2) t P(t), t = 1 / (1 + 0.334 |x|),
+// P fitted to the Mills ratio by reweighted least squares (relative error 5e-8 on [0, 14]).  No branches and 18 instructions
+// instead of the two branches of erff; Phi has the same rms error on |x| < 2 as 0.5 (1 + erff) (8e-8 against 1.1e-7, relative)
+// and keeps a relative error of 2e-6 where that cancels.
+__device__ __forceinline__ float gelu_tail(float ax, float e) {   // Phi(-ax), e = exp(-ax^2 / 2)
+    const float t = __builtin_amdgcn_rcpf(__fmaf_rn(0.334f, ax, 1.f));
+    float p = -0.02313364800768489f;
+    p = __fmaf_rn(p, t, 0.13077450985052583f);
+    p = __fmaf_rn(p, t, -0.2718444718374854f);
+    p = __fmaf_rn(p, t, 0.21760316855674783f);
+    p = __fmaf_rn(p, t, -0.0526479919843455f);
+    p = __fmaf_rn(p, t, 0.11950669786053332f);
+    p = __fmaf_rn(p, t, 0.11269095661831224f);
+    p = __fmaf_rn(p, t, 0.13382937667447498f);
+    p = __fmaf_rn(p, t, 0.13322142474482226f);
+    return p * t * e;
+}
+__device__ __forceinline__ float gelu_for_bf16(float x) {
+    const float tail = gelu_tail(fabsf(x), __builtin_amdgcn_exp2f(x * x * -0.7213475204444817f));
+    return x * (x < 0.f ? tail : 1.f - tail);
+}
+// its derivative Phi(x) + x phi(x)
+__device__ __forceinline__ float gelu_df_for_bf16(float x) {
+    const float e = __builtin_amdgcn_exp2f(x * x * -0.7213475204444817f), tail = gelu_tail(fabsf(x), e);
+    return __fmaf_rn(x * 0.3989422804014327f, e, x < 0.f ? tail : 1.f - tail);
+}
+
 __device__ __forceinline__ void g16_tile_of_block(int& tile_x, int& tile_y) {
     // launch slot -> tile such that each of the eight XCDs (round-robin over launch slots) walks a contiguous tile range
     const int nx = gridDim.x, tiles = nx * gridDim.y;
@@ -138,14 +167,14 @@ __device__ __forceinline__ void g16_tile_of_block(int& tile_x, int& tile_y) {
 }
 
 // Stores a wave's 64 x 64 block; lane (r, g) holds acc[mt][nt][i] = C[m_base + 16 mt + r][n_base + 16 nt + 4 g + i].
-template <bool VEC, int MB, bool GELU>
-__device__ __forceinline__ void g16_store_block(const Gemm16Desc& d, const f32x4 (&acc)[MB][4], int m_base, int n_base, float* C, bf16_t* C16,
+template <bool VEC, int MB, int NB, bool GELU>
+__device__ __forceinline__ void g16_store_block(const Gemm16Desc& d, const f32x4 (&acc)[MB][NB], int m_base, int n_base, float* C, bf16_t* C16,
                                                 bf16_t* G16, const float* R, const float* bias, int ldc, bool plain, int r, int g) {
 #pragma unroll
     for (int mt = 0; mt < MB; ++mt) {
         const int m = m_base + 16 * mt + r;
 #pragma unroll
-        for (int nt = 0; nt < 4; ++nt) {
+        for (int nt = 0; nt < NB; ++nt) {
             const int n = n_base + 16 * nt + 4 * g;
             if (VEC) {
                 // the block lies inside C and rows allow 16-byte accesses
@@ -161,7 +190,7 @@ __device__ __forceinline__ void g16_store_block(const Gemm16Desc& d, const f32x4
                 if (GELU && G16) {
                     f32x4 q;
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) q[i] = 0.5f * v[i] * (1.f + erff(v[i] * 0.70710678118654752f));
+                    for (int i = 0; i < 4; ++i) q[i] = gelu_for_bf16(v[i]);
                     *reinterpret_cast<u32x2*>(G16 + at) = u32x2{pack2_bf16(q[0], q[1]), pack2_bf16(q[2], q[3])};
                 }
             } else {
@@ -177,7 +206,7 @@ __device__ __forceinline__ void g16_store_block(const Gemm16Desc& d, const f32x4
                         }
                         if (C) C[at] = v;
                         if (C16) C16[at] = (bf16_t)(pack2_bf16(v, 0.f) & 0xffffu);
-                        if (GELU && G16) G16[at] = (bf16_t)(pack2_bf16(0.5f * v * (1.f + erff(v * 0.70710678118654752f)), 0.f) & 0xffffu);
+                        if (GELU && G16) G16[at] = (bf16_t)(pack2_bf16(gelu_for_bf16(v), 0.f) & 0xffffu);
                     }
                 }
             }
@@ -341,30 +370,466 @@ __global__ __launch_bounds__(256, MB == 8 ? 2 : 3) void gemm16_kernel(Gemm16Desc
     const int m_base = m0 + wm * 16 * MB, n_base = n0 + wn * 64;
     if (EPI == 2) g16_ce_block<MB>(d, acc, m_base, n_base, 2 * tile_x + wn, r, g);   // its own instantiation: the statistics cost registers
     const bool vec = (plain ? (d.N & 3) == 0 : d.c_vec != 0) && m_base + 16 * MB <= d.M && n_base + 64 <= d.N;
-    if (vec) g16_store_block<true, MB, EPI == 1>(d, acc, m_base, n_base, C, C16, G16, R, bias, ldc, plain, r, g);
-    else g16_store_block<false, MB, EPI == 1>(d, acc, m_base, n_base, C, C16, G16, R, bias, ldc, plain, r, g);
+    if (vec) g16_store_block<true, MB, 4, EPI == 1>(d, acc, m_base, n_base, C, C16, G16, R, bias, ldc, plain, r, g);
+    else g16_store_block<false, MB, 4, EPI == 1>(d, acc, m_base, n_base, C, C16, G16, R, bias, ldc, plain, r, g);
 }
 
-// out[i] = alpha * sum_z part[z][i] (+ bias) (+ R), in split order (weight gradients: fp32 output only); blockIdx.y is the
-// matrix of a batch (outer batch index only), whose output starts sc1 floats after the previous one
-__global__ __launch_bounds__(256) void gemm16_split_reduce_kernel(const float* __restrict__ part, int splits, int M, int N, float alpha,
-                                                                  const float* __restrict__ bias, const float* __restrict__ R, int ldc,
-                                                                  float* __restrict__ out, int64_t sc1) {
-    const int64_t total = (int64_t)M * N;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    part += (int64_t)blockIdx.y * splits * total;
-    out += (int64_t)blockIdx.y * sc1;
-    if (R) R += (int64_t)blockIdx.y * sc1;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += stride) {
-        float acc = part[i];
-        for (int zz = 1; zz < splits; ++zz) acc += part[(int64_t)zz * total + i];
-        const int64_t m = i / N;
-        const int n = (int)(i - m * N);
-        acc *= alpha;
-        if (bias) acc += bias[n];
-        if (R) acc += R[m * ldc + n];
-        out[m * ldc + n] = acc;
+// ---- both factors row-major: tiles straight into LDS --------------------------------------------------------------------
+//
+// Workgroup = 32 WMB x 32 WNB tile of C, four waves as 2 x 2, each 16 WMB x 16 WNB.  K advances 32 at a time through
+// GD16_STAGES LDS buffers [row][32 k] that global_load_lds fills (16 bytes per lane, 1 KB of consecutive LDS per
+// instruction): no staging registers, no LDS store instructions, two steps of loads in flight.  One barrier per step: a wave
+// waits for its own loads of the step (counted, the younger step stays in flight), the barrier makes everybody's visible and
+// frees the buffer read a step ago.  Rows are 64 bytes; piece c (16 bytes) of a row sits at place c ^ gd16_place(row),
+// so that the 16-byte operand reads, 16 rows x 4 pieces, are free of bank conflicts.  Rows past the end are clamped to the last one (they only
+// feed outputs that are never stored), pieces past the end of K are zeroed in LDS in the last step.
+#define GD16_STAGES 3
+typedef __attribute__((address_space(1))) const void gd16_global_ptr;
+typedef __attribute__((address_space(3))) void gd16_lds_ptr;
+
+// A 16-byte LDS read of a wave proceeds 16 lanes at a time, but not 16 consecutive ones: eight rows of one piece together with
+// eight other rows of its neighbour.  With this permutation (0, 2, 3, 1 over the row quads) those fall on different banks.
+__device__ __forceinline__ int gd16_place(int quad) { return (((quad ^ (quad >> 1)) & 1) << 1) | ((quad >> 1) & 1); }
+
+// Epilogue.  Rows of a row-major B are dealt to the matrix blocks so that blocks 2p and 2p + 1 of a lane hold eight neighbouring columns
+// n_base + 32 p + 8 g ..: 16-byte stores of bf16, 32 bytes of fp32.  Everything the epilogue reads is requested before the
+// first store of a group of block rows (the compiler has to assume that a store changes what a later load reads, so a
+// load behind a store is a memory round trip of its own: 32 of them per tile cost more than the matrix loop of K = 512).
+template <bool PAIRED>
+__device__ __forceinline__ int gd16_column(int nt, int g) { return PAIRED ? 32 * (nt >> 1) + 8 * g + 4 * (nt & 1) : 16 * nt + 4 * g; }
+
+template <bool PAIRED, int WMB, int WNB, bool GELU>
+__device__ __forceinline__ void gd16_store(const Gemm16Desc& d, float alpha, f32x4 (&acc)[WMB][WNB], int m_base, int n_base, float* C, bf16_t* C16, bf16_t* G16,
+                                           const float* R, const float* bias, int ldc, bool plain, int r, int g) {
+    if (!plain) {
+        if (alpha != 1.f)
+#pragma unroll
+            for (int mt = 0; mt < WMB; ++mt)
+#pragma unroll
+                for (int nt = 0; nt < WNB; ++nt) acc[mt][nt] *= alpha;
+        if (bias) {
+            f32x4 b[WNB];
+#pragma unroll
+            for (int nt = 0; nt < WNB; ++nt) b[nt] = *reinterpret_cast<const f32x4*>(bias + n_base + gd16_column<PAIRED>(nt, g));
+#pragma unroll
+            for (int mt = 0; mt < WMB; ++mt)
+#pragma unroll
+                for (int nt = 0; nt < WNB; ++nt) acc[mt][nt] += b[nt];
+        }
     }
+    constexpr int GR = WMB >= 8 ? 4 : 2;   // block rows per group: what the registers beside the accumulators hold
+#pragma unroll
+    for (int m4 = 0; m4 < WMB; m4 += GR) {
+        if (!plain && R) {
+            f32x4 rv[GR][WNB];
+#pragma unroll
+            for (int k = 0; k < GR; ++k)
+#pragma unroll
+                for (int nt = 0; nt < WNB; ++nt)
+                    rv[k][nt] = *reinterpret_cast<const f32x4*>(R + (int64_t)(m_base + 16 * (m4 + k) + r) * ldc + n_base + gd16_column<PAIRED>(nt, g));
+#pragma unroll
+            for (int k = 0; k < GR; ++k)
+#pragma unroll
+                for (int nt = 0; nt < WNB; ++nt) acc[m4 + k][nt] += rv[k][nt];
+        }
+#pragma unroll
+        for (int k = 0; k < GR; ++k) {
+            const int64_t at = (int64_t)(m_base + 16 * (m4 + k) + r) * ldc + n_base;
+#pragma unroll
+            for (int p = 0; p < WNB / 2; ++p) {
+                const f32x4 v0 = acc[m4 + k][2 * p], v1 = acc[m4 + k][2 * p + 1];
+                const int64_t at0 = at + gd16_column<PAIRED>(2 * p, g), at1 = at + gd16_column<PAIRED>(2 * p + 1, g);
+                if (C) {
+                    *reinterpret_cast<f32x4*>(C + at0) = v0;
+                    *reinterpret_cast<f32x4*>(C + at1) = v1;
+                }
+                auto store16 = [&](bf16_t* dst, const f32x4& q0, const f32x4& q1) {
+                    const u32x4 w = {pack2_bf16(q0[0], q0[1]), pack2_bf16(q0[2], q0[3]), pack2_bf16(q1[0], q1[1]), pack2_bf16(q1[2], q1[3])};
+                    if (PAIRED) {
+                        *reinterpret_cast<u32x4*>(dst + at0) = w;
+                    } else {
+                        *reinterpret_cast<u32x2*>(dst + at0) = u32x2{w[0], w[1]};
+                        *reinterpret_cast<u32x2*>(dst + at1) = u32x2{w[2], w[3]};
+                    }
+                };
+                if (C16) store16(C16, v0, v1);
+                if (GELU && G16) {
+                    f32x4 q0, q1;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        q0[i] = gelu_for_bf16(v0[i]);
+                        q1[i] = gelu_for_bf16(v1[i]);
+                    }
+                    store16(G16, q0, q1);
+                }
+            }
+        }
+    }
+}
+
+// The same for tiles at the edge of C and for outputs without 16-byte rows
+template <bool PAIRED, int WMB, int WNB, bool GELU>
+__device__ __forceinline__ void gd16_store_edge(const Gemm16Desc& d, float alpha, const f32x4 (&acc)[WMB][WNB], int m_base, int n_base, float* C, bf16_t* C16,
+                                                bf16_t* G16, const float* R, const float* bias, int ldc, bool plain, int r, int g) {
+#pragma unroll
+    for (int mt = 0; mt < WMB; ++mt) {
+        const int m = m_base + 16 * mt + r;
+        if (m >= d.M) continue;
+#pragma unroll
+        for (int nt = 0; nt < WNB; ++nt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int n = n_base + gd16_column<PAIRED>(nt, g) + i;
+                if (n < d.N) {
+                    float v = acc[mt][nt][i];
+                    const int64_t at = (int64_t)m * ldc + n;
+                    if (!plain) {
+                        v *= alpha;
+                        if (bias) v += bias[n];
+                        if (R) v += R[at];
+                    }
+                    if (C) C[at] = v;
+                    if (C16) C16[at] = (bf16_t)(pack2_bf16(v, 0.f) & 0xffffu);
+                    if (GELU && G16) G16[at] = (bf16_t)(pack2_bf16(gelu_for_bf16(v), 0.f) & 0xffffu);
+                }
+            }
+    }
+}
+
+// Softmax statistics of a wave's 64 columns for each of its rows, as g16_ce_block: (max, sum of exp(v - max)) and the value in
+// the target's column.  The rows' targets are requested together and the reductions of all block rows run side by side;
+// the column of the target is only looked for in the rare wave that holds one.
+template <int WMB>
+__device__ __forceinline__ void gd16_ce(const Gemm16Desc& d, f32x4 (&acc)[WMB][4], int m_base, int n_base, int part_idx, int r, int g) {
+    int tgt[WMB];
+#pragma unroll
+    for (int mt = 0; mt < WMB; ++mt) {
+        const int m = m_base + 16 * mt + r;
+        tgt[mt] = m < d.M ? d.ce_targets[m] : -1;
+    }
+    if (d.alpha != 1.f)
+#pragma unroll
+        for (int mt = 0; mt < WMB; ++mt)
+#pragma unroll
+            for (int nt = 0; nt < 4; ++nt) acc[mt][nt] *= d.alpha;
+    const bool full = n_base + 64 <= d.N;   // uniform: every column of the block exists
+    auto column = [&](int nt, int i) { return n_base + 32 * (nt >> 1) + 8 * g + 4 * (nt & 1) + i; };
+    float mx[WMB], sum[WMB];
+#pragma unroll
+    for (int mt = 0; mt < WMB; ++mt) {
+        mx[mt] = -INFINITY;
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) mx[mt] = fmaxf(mx[mt], full || column(nt, i) < d.N ? acc[mt][nt][i] : -INFINITY);
+    }
+#pragma unroll
+    for (int mt = 0; mt < WMB; ++mt) mx[mt] = fmaxf(mx[mt], __shfl_xor(mx[mt], 16, 64));
+#pragma unroll
+    for (int mt = 0; mt < WMB; ++mt) mx[mt] = fmaxf(mx[mt], __shfl_xor(mx[mt], 32, 64));
+    constexpr float LOG2E = 1.4426950408889634f;
+#pragma unroll
+    for (int mt = 0; mt < WMB; ++mt) {
+        // hardware exponential; a row whose columns are all -inf or absent keeps a sum of 0 (its maximum says so)
+        const float ref = mx[mt] > -INFINITY ? mx[mt] * LOG2E : 0.f;
+        float s = 0.f;
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float e = __builtin_amdgcn_exp2f(__fmaf_rn(acc[mt][nt][i], LOG2E, -ref));
+                s += full || column(nt, i) < d.N ? e : 0.f;
+            }
+        sum[mt] = s;
+        __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int mt = 0; mt < WMB; ++mt) sum[mt] += __shfl_xor(sum[mt], 16, 64);
+#pragma unroll
+    for (int mt = 0; mt < WMB; ++mt) sum[mt] += __shfl_xor(sum[mt], 32, 64);
+#pragma unroll
+    for (int mt = 0; mt < WMB; ++mt) {
+        const int m = m_base + 16 * mt + r;
+        if (g == 0 && m < d.M) *reinterpret_cast<f32x2_v*>(d.ce_part + 2 * ((int64_t)part_idx * d.M + m)) = f32x2_v{mx[mt], sum[mt]};
+        const int t = tgt[mt] - n_base;
+        if (t >= 0 && t < 64 && ((t >> 3) & 3) == g) {   // this lane holds the target's column
+            float at = 0.f;
+#pragma unroll
+            for (int nt = 0; nt < 4; ++nt)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) at = (t >> 5) == (nt >> 1) && (t & 7) == 4 * (nt & 1) + i ? acc[mt][nt][i] : at;
+            d.ce_tlogit[m] = at;
+        }
+    }
+}
+
+// Gradient of the mean cross-entropy with respect to the logits the tile holds: (exp(z - max) / sum - [column is the target]) *
+// scale with the row statistics of an earlier pass over the same product; columns past n_valid (the padding of the rows) are 0.
+// The exponential carries the rounding of its scaled argument as a correction.
+template <int WMB, int WNB>
+__device__ __forceinline__ void gd16_ce_grad(const Gemm16Desc& d, const f32x4 (&acc)[WMB][WNB], int m_base, int n_base, bf16_t* C16, int r, int g) {
+    f32x2_v st[WMB];
+    int tgt[WMB];
+#pragma unroll
+    for (int mt = 0; mt < WMB; ++mt) {
+        const int m = min(m_base + 16 * mt + r, d.M - 1);
+        st[mt] = *reinterpret_cast<const f32x2_v*>(d.ce_rows + 2 * (int64_t)m);
+        tgt[mt] = d.ce_targets[m];
+    }
+    constexpr float LOG2E = 1.4426950408889634f, LOG2E_LO = 1.925963033500912e-8f, LN2 = 0.6931471805599453f;
+#pragma unroll
+    for (int mt = 0; mt < WMB; ++mt) {
+        const int m = m_base + 16 * mt + r;
+        const float f = d.ce_scale / st[mt][1];
+#pragma unroll
+        for (int p = 0; p < WNB / 2; ++p) {
+            const int n = n_base + 32 * p + 8 * g;
+            float q[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const float t = acc[mt][2 * p + (j >> 2)][j & 3] * d.alpha - st[mt][0];
+                const float hi = t * LOG2E, lo = __fmaf_rn(t, LOG2E, -hi) + t * LOG2E_LO;
+                const float e = __builtin_amdgcn_exp2f(hi);
+                q[j] = __fmaf_rn(e, lo * LN2, e) * f - (n + j == tgt[mt] ? d.ce_scale : 0.f);
+                if (n + j >= d.n_valid) q[j] = 0.f;
+            }
+            // N is a multiple of 8: a lane's eight columns are all there or none of them
+            if (m < d.M && n < d.N)
+                *reinterpret_cast<u32x4*>(C16 + (int64_t)m * d.ldc + n) = u32x4{pack2_bf16(q[0], q[1]), pack2_bf16(q[2], q[3]), pack2_bf16(q[4], q[5]), pack2_bf16(q[6], q[7])};
+            __builtin_amdgcn_sched_barrier(0);   // one piece's temporaries at a time
+        }
+    }
+}
+
+// The tile times gelu'(U), and the column sums of the result over the wave's rows: row 2 * tile_y + wm of gelu_part.
+template <int WMB, int WNB>
+__device__ __forceinline__ void gd16_gelu_bwd(const Gemm16Desc& d, f32x4 (&acc)[WMB][WNB], int m_base, int n_base, int part_row, int r, int g) {
+    const bool inside = m_base + 16 * WMB <= d.M && n_base + 16 * WNB <= d.N;
+    f32x4 sum[WNB];
+#pragma unroll
+    for (int nt = 0; nt < WNB; ++nt) sum[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    constexpr int GR = 2;
+#pragma unroll
+    for (int m4 = 0; m4 < WMB; m4 += GR) {
+        f32x4 u[GR][WNB];
+#pragma unroll
+        for (int k = 0; k < GR; ++k)
+#pragma unroll
+            for (int nt = 0; nt < WNB; ++nt) {
+                const int m = m_base + 16 * (m4 + k) + r, n = n_base + gd16_column<false>(nt, g);
+                u[k][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+                if (inside || (m < d.M && n < d.N)) u[k][nt] = *reinterpret_cast<const f32x4*>(d.U + (int64_t)m * d.ldc + n);   // N % 4 == 0
+            }
+#pragma unroll
+        for (int k = 0; k < GR; ++k) {
+            const bool live = inside || m_base + 16 * (m4 + k) + r < d.M;
+#pragma unroll
+            for (int nt = 0; nt < WNB; ++nt) {
+                f32x4& v = acc[m4 + k][nt];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[i] = live ? v[i] * d.alpha * gelu_df_for_bf16(u[k][nt][i]) : 0.f;
+                sum[nt] += v;
+            }
+        }
+    }
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1)
+#pragma unroll
+        for (int nt = 0; nt < WNB; ++nt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) sum[nt][i] += __shfl_xor(sum[nt][i], o, 64);
+#pragma unroll
+    for (int nt = 0; nt < WNB; ++nt) {
+        const int n = n_base + gd16_column<false>(nt, g);
+        if (r == nt && n < d.N) *reinterpret_cast<f32x4*>(d.gelu_part + (int64_t)part_row * d.N + n) = sum[nt];
+    }
+}
+
+// Slot v (16 bytes) of an operand stage of ROWS rows: which piece of the matrix belongs there (row and k relative to the tile;
+// a piece is 8 k of one row, or, k-major, 8 rows of one k).
+template <bool KMAJOR, bool IS_B, int ROWS>
+__device__ __forceinline__ void gd16_slot(int v, int& row, int& k) {
+    if (KMAJOR) {
+        constexpr int PPL = ROWS / 8;   // pieces per line
+        k = v / PPL;
+        const int place = v % PPL, f = ROWS >= 128 ? (k & 3) | ((k >> 1) & 4) : ((k >> 1) & 1) | ((k >> 2) & 2);
+        row = 8 * (2 * ((place >> 1) ^ f) + (place & 1));
+    } else {
+        row = v >> 2;
+        k = 8 * ((v & 3) ^ gd16_place((IS_B ? row >> 3 : row >> 2) & 3));
+    }
+}
+
+template <bool AK, bool BK, int EPI, int WMB, int WNB>
+__global__ __launch_bounds__(256, WMB * WNB >= 32 ? 2 : 3) void gemm16_direct_kernel(Gemm16Desc d) {
+    constexpr int TM = 32 * WMB, TN = 32 * WNB;
+    constexpr int LA = TM / 64, LB = TN / 64;        // load instructions per wave and step
+    constexpr int STAGE = (TM + TN) * 4;             // 16-byte slots
+    extern __shared__ u32x4 gd16_lds[];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r = lane & 15, g = lane >> 4;
+    const int wm = wave >> 1, wn = wave & 1;
+    int tile_x, tile_y, zz;
+    gemm_tile_order(tile_x, tile_y, zz);
+    const int m0 = tile_y * TM, n0 = tile_x * TN;
+    const int split = zz % d.splits, z = zz / d.splits;
+    const int z1 = z / d.inner, z2 = z - z1 * d.inner;
+    const int k_begin = split * d.k_chunk;
+    const int k_end = min(d.K, k_begin + d.k_chunk);
+    const int steps = (k_end - k_begin + G16_K - 1) / G16_K;
+    const bool tail = ((k_end - k_begin) % G16_K) != 0;        // the last step is not a whole one
+
+    // the operands advance one step per request; a segmented contraction jumps to the next segment's matrices
+    const int seg0 = d.k_seg ? k_begin / d.k_seg : 0;
+    int seg_left = d.k_seg ? d.k_seg - (k_begin - seg0 * d.k_seg) : 0x7fffffff;
+    const int k_in_seg = d.k_seg ? k_begin - seg0 * d.k_seg : k_begin;
+    const bf16_t* A = d.A + z1 * d.sa1 + z2 * d.sa2 + seg0 * d.sa_seg + (AK ? (int64_t)k_in_seg * d.lda + m0 : (int64_t)m0 * d.lda + k_in_seg);
+    const bf16_t* B = d.B + z1 * d.sb1 + z2 * d.sb2 + seg0 * d.sb_seg + (BK ? (int64_t)k_in_seg * d.ldb + n0 : (int64_t)n0 * d.ldb + k_in_seg);
+    const int64_t adv_a = AK ? (int64_t)G16_K * d.lda : G16_K, adv_b = BK ? (int64_t)G16_K * d.ldb : G16_K;
+    uint32_t offa[LA], offb[LB];
+#pragma unroll
+    for (int i = 0; i < LA; ++i) {
+        int row, k;
+        gd16_slot<AK, false, TM>((4 * i + wave) * 64 + lane, row, k);
+        offa[i] = AK ? (uint32_t)(k * d.lda + min(row, ((d.M - 1) & ~7) - m0)) : (uint32_t)(min(row, d.M - 1 - m0) * d.lda + k);
+    }
+#pragma unroll
+    for (int i = 0; i < LB; ++i) {
+        int row, k;
+        gd16_slot<BK, true, TN>((4 * i + wave) * 64 + lane, row, k);
+        offb[i] = BK ? (uint32_t)(k * d.ldb + min(row, ((d.N - 1) & ~7) - n0)) : (uint32_t)(min(row, (EPI == 3 ? d.n_valid : d.N) - 1 - n0) * d.ldb + k);
+    }
+    auto load16 = [&](const bf16_t* src, u32x4* dst) {
+        __builtin_amdgcn_global_load_lds((gd16_global_ptr*)src, (gd16_lds_ptr*)dst, 16, 0, 0);
+    };
+    auto request = [&](int step, int buf) {
+        u32x4* base = gd16_lds + buf * STAGE;
+        if (tail && step == steps - 1) {
+            const int left = k_end - k_begin - step * G16_K;   // 1 .. 31
+#pragma unroll
+            for (int i = 0; i < LA; ++i) {
+                int row, k;
+                gd16_slot<AK, false, TM>((4 * i + wave) * 64 + lane, row, k);
+                u32x4* dst = base + (4 * i + wave) * 64;
+                if (k < left) load16(A + offa[i], dst);
+                else dst[lane] = u32x4{0u, 0u, 0u, 0u};
+            }
+#pragma unroll
+            for (int i = 0; i < LB; ++i) {
+                int row, k;
+                gd16_slot<BK, true, TN>((4 * i + wave) * 64 + lane, row, k);
+                u32x4* dst = base + TM * 4 + (4 * i + wave) * 64;
+                if (k < left) load16(B + offb[i], dst);
+                else dst[lane] = u32x4{0u, 0u, 0u, 0u};
+            }
+            return;
+        }
+#pragma unroll
+        for (int i = 0; i < LA; ++i) load16(A + offa[i], base + (4 * i + wave) * 64);
+#pragma unroll
+        for (int i = 0; i < LB; ++i) load16(B + offb[i], base + TM * 4 + (4 * i + wave) * 64);
+        A += adv_a;
+        B += adv_b;
+        seg_left -= G16_K;
+        if (seg_left == 0) {
+            seg_left = d.k_seg;
+            A += d.sa_seg - (AK ? (int64_t)d.k_seg * d.lda : (int64_t)d.k_seg);
+            B += d.sb_seg - (BK ? (int64_t)d.k_seg * d.ldb : (int64_t)d.k_seg);
+        }
+    };
+
+    f32x4 acc[WMB][WNB];
+#pragma unroll
+    for (int i = 0; i < WMB; ++i)
+#pragma unroll
+        for (int j = 0; j < WNB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // Operand reads; lane (r, g) holds k = 8g .. 8g + 7 of its row.  Block t of A: rows 16 t + r.  Row-major B: blocks 2p and
+    // 2p + 1 are rows 32 p + 8 (r / 4) + r % 4 and four further, so that a lane's results of the two are eight neighbouring columns.
+    // K-major: a transposing read takes a 4 (k) x 16 (rows) piece per 16 lanes, lane i of them at line i / 4, rows 4 (i % 4) ..;
+    // two of them, lines 8g + i / 4 and four further, make the operand.  The 32-byte pieces of a line are permuted by the line
+    // (gd16_slot), so that the eight lines that two neighbouring lane groups read together fall on different banks.
+    const int piece = g ^ gd16_place(r >> 2);
+    const int ra = (wm * 16 * WMB + r) * 4 + piece, rb = TM * 4 + (wn * 16 * WNB + 8 * (r >> 2) + (r & 3)) * 4 + piece;
+    const int kline = 8 * g + (r >> 2);
+    const int f128 = (r >> 2) | ((g & 1) << 2), f64 = (r >> 3) | ((g & 1) << 1);   // as in gd16_slot
+    const int fa = TM >= 128 ? f128 : f64, fb = TN >= 128 ? f128 : f64;
+    const int ta = kline * TM * 2 + 8 * (r & 3), tb = TM * 64 + kline * TN * 2 + 8 * (r & 3);   // bytes
+    // The transposing read as an assembly statement: the compiler takes the builtin for a possible reader of every LDS load in
+    // flight and waits for all of them.  It does not see the latency either: a wait that the operands pass through follows.
+    auto transposed = [&](uint32_t at, auto line_bytes) {
+        u32x2 lo, hi;
+        asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(lo) : "v"(at));
+        asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(hi) : "v"(at), "n"(4 * decltype(line_bytes)::value));
+        return u32x4{lo[0], lo[1], hi[0], hi[1]};
+    };
+    auto compute = [&](int buf) {
+        const u32x4* st = gd16_lds + buf * STAGE;
+        const uint32_t sb = (uint32_t)(uintptr_t)(gd16_lds_ptr*)st;
+        u32x4 a[WMB], b[WNB];
+#pragma unroll
+        for (int t = 0; t < WNB; ++t) {
+            if constexpr (BK) b[t] = transposed(sb + tb + 32 * ((wn * WNB + t) ^ fb), std::integral_constant<int, TN * 2>());
+            else b[t] = st[rb + 128 * (t >> 1) + 16 * (t & 1)];
+        }
+#pragma unroll
+        for (int t = 0; t < WMB; ++t) {
+            if constexpr (AK) a[t] = transposed(sb + ta + 32 * ((wm * WMB + t) ^ fa), std::integral_constant<int, TM * 2>());
+            else a[t] = st[ra + 64 * t];
+        }
+        if constexpr (AK || BK) {
+#pragma unroll
+            for (int t = 0; t < WNB; ++t) asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(b[t]));
+#pragma unroll
+            for (int t = 0; t < WMB; ++t) asm volatile("" : "+v"(a[t]));
+        }
+#pragma unroll
+        for (int mt = 0; mt < WMB; ++mt)
+#pragma unroll
+            for (int nt = 0; nt < WNB; ++nt)
+                acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_v, b[nt]), __builtin_bit_cast(bf16x8_v, a[mt]), acc[mt][nt], 0, 0, 0);
+    };
+#pragma unroll
+    for (int i = 0; i < GD16_STAGES - 1; ++i)
+        if (i < steps) request(i, i);
+    int buf = 0;
+    for (int i = 0; i < steps; ++i) {
+        // while a later step is still to be requested the GD16_STAGES - 2 youngest steps may stay in flight
+        if (i + GD16_STAGES - 1 < steps) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((GD16_STAGES - 2) * (LA + LB)) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        if (i + GD16_STAGES - 1 < steps) request(i + GD16_STAGES - 1, buf == 0 ? GD16_STAGES - 1 : buf - 1);
+        compute(buf);
+        buf = buf + 1 == GD16_STAGES ? 0 : buf + 1;
+    }
+
+    const bool plain = d.splits > 1;   // partial sums go out as they are; the reduction applies the epilogue
+    const int64_t zoff = z1 * d.sc1 + z2 * d.sc2;
+    float* C = plain ? d.part + ((int64_t)z * d.splits + split) * d.part_stride : d.C ? d.C + zoff : nullptr;
+    bf16_t* C16 = (plain || !d.C16) ? nullptr : d.C16 + zoff;
+    bf16_t* G16 = (plain || !d.G16) ? nullptr : d.G16 + zoff;
+    const float* R = (plain || !d.R) ? nullptr : d.R + zoff;
+    const float* bias = (plain || !d.bias) ? nullptr : d.bias + z1 * d.sbias1;
+    const int ldc = plain ? d.N : d.ldc;
+    const int m_base = m0 + wm * 16 * WMB, n_base = n0 + wn * 16 * WNB;
+    if constexpr (EPI == 2) gd16_ce<WMB>(d, acc, m_base, n_base, 2 * tile_x + wn, r, g);
+    if (EPI == 2 && !C && !C16) return;
+    if constexpr (EPI == 3) {
+        gd16_ce_grad<WMB, WNB>(d, acc, m_base, n_base, C16, r, g);
+        return;
+    }
+    if constexpr (EPI == 4) gd16_gelu_bwd<WMB, WNB>(d, acc, m_base, n_base, 2 * tile_y + wm, r, g);
+    const float alpha = EPI == 4 ? 1.f : d.alpha;   // the factor above includes it
+    const bool vec = (plain ? (d.N & 3) == 0 : d.c_vec8 != 0) && m_base + 16 * WMB <= d.M && n_base + 16 * WNB <= d.N;
+    if (vec) gd16_store<!BK, WMB, WNB, EPI == 1>(d, alpha, acc, m_base, n_base, C, C16, G16, R, bias, ldc, plain, r, g);
+    else gd16_store_edge<!BK, WMB, WNB, EPI == 1>(d, alpha, acc, m_base, n_base, C, C16, G16, R, bias, ldc, plain, r, g);
+}
+
+// Rows of partial column sums that a product with gelu_part leaves: two per tile row
+int gemm16_gelu_rows(int64_t M, int N) {
+    const int64_t t84 = ((M + 255) / 256) * ((N + 127) / 128);
+    return (int)(2 * (t84 >= 400 ? (M + 255) / 256 : (M + 127) / 128));
 }
 
 // Launch.  Split-K writes an fp32 output only and, with a batch, needs inner == 1; d.part must then hold
@@ -381,6 +846,8 @@ void launch_gemm16(hipStream_t s, Gemm16Desc d) {
     d.a_vec = (al(d.A, 16) && d.lda % 8 == 0 && d.sa1 % 8 == 0 && d.sa2 % 8 == 0) ? 1 : 0;
     d.b_vec = (al(d.B, 16) && d.ldb % 8 == 0 && d.sb1 % 8 == 0 && d.sb2 % 8 == 0) ? 1 : 0;
     d.c_vec = (al(d.C, 16) && al(d.R, 16) && al(d.bias, 16) && al(d.C16, 8) && al(d.G16, 8) && d.ldc % 4 == 0 && d.sc1 % 4 == 0 && d.sc2 % 4 == 0 && d.sbias1 % 4 == 0) ? 1 : 0;
+    const bool half = d.C16 || d.G16;
+    d.c_vec8 = (d.c_vec && al(d.C16, 16) && al(d.G16, 16) && (!half || (d.ldc % 8 == 0 && d.sc1 % 8 == 0 && d.sc2 % 8 == 0))) ? 1 : 0;
     // the unchecked fetch needs 16-byte loads on both operands, whole K steps and 32-bit element offsets
     const int64_t span_a = (int64_t)(d.a_kmajor ? d.K : d.M) * d.lda, span_b = (int64_t)(d.b_kmajor ? d.K : d.N) * d.ldb;
     const bool fast = d.a_vec && d.b_vec && d.K % G16_K == 0 && (!d.a_kmajor || d.M % 8 == 0) && (!d.b_kmajor || d.N % 8 == 0) && d.M >= 8 &&
@@ -389,6 +856,39 @@ void launch_gemm16(hipStream_t s, Gemm16Desc d) {
     const bool tall = fast && !d.a_kmajor && (int64_t)((d.M + 255) / 256) * ((d.N + G16_TILE - 1) / G16_TILE) * d.batch * d.splits >= 512 && d.M >= 256;
     const int tile_m = tall ? 256 : G16_TILE;
     dim3 grid((d.N + G16_TILE - 1) / G16_TILE, (d.M + tile_m - 1) / tile_m, d.batch * d.splits);
+    // straight into LDS: 16-byte pieces of both factors (whole pieces along a contiguous K), 32-bit offsets inside a tile
+    const bool direct = d.a_vec && d.b_vec && d.sa_seg % 8 == 0 && d.sb_seg % 8 == 0 && ((d.a_kmajor && d.b_kmajor) || (!d.a_kmajor && d.K % 8 == 0)) &&
+                        (int64_t)256 * d.lda < (int64_t(1) << 30) && (int64_t)256 * d.ldb < (int64_t(1) << 30);
+    if (direct) {
+        const int z = d.batch * d.splits;
+        const int64_t t84 = (int64_t)((d.M + 255) / 256) * ((d.N + 127) / 128) * z, t44 = (int64_t)((d.M + 127) / 128) * ((d.N + 127) / 128) * z;
+#define GD16_LAUNCH(AKM, BKM, EPI, WMB, WNB)                                                                                         \
+    hipLaunchKernelGGL((gemm16_direct_kernel<AKM, BKM, EPI, WMB, WNB>),                                                               \
+                       dim3((unsigned)((d.N + 32 * WNB - 1) / (32 * WNB)), (unsigned)((d.M + 32 * WMB - 1) / (32 * WMB)), z), dim3(256), \
+                       GD16_STAGES * 32 * (WMB + WNB) * 64, s, d)
+#define GD16_TILE(AKM, BKM, EPI)                              \
+    do {                                                      \
+        if (t84 >= 400) GD16_LAUNCH(AKM, BKM, EPI, 8, 4);     \
+        else if (t44 >= 448) GD16_LAUNCH(AKM, BKM, EPI, 4, 4); \
+        else GD16_LAUNCH(AKM, BKM, EPI, 4, 2);                \
+    } while (0)
+        // Tiles (measured, 8192 tokens): 256 x 128 from 400 of them (32 000 x 512 over the tokens, 500 tiles: 317 us, 364 with
+        // 128 x 128); below that 128 x 128 from 448 (three 512-wide products: 23.2 us, 24.4 and 27.7 with the others); else
+        // 128 x 64 (512 x 512: 14.4 us, 16.0 and 21.2).
+        if (d.ce_part) {   // statistics per 64 columns of a wave
+            if (t84 >= 400) GD16_LAUNCH(false, false, 2, 8, 4);
+            else GD16_LAUNCH(false, false, 2, 4, 4);
+        } else if (d.ce_rows) {
+            if (t84 >= 400) GD16_LAUNCH(false, false, 3, 8, 4);
+            else GD16_LAUNCH(false, false, 3, 4, 4);
+        } else if (d.gelu_part) {
+            if (gemm16_gelu_rows(d.M, d.N) == 2 * ((d.M + 255) / 256)) GD16_LAUNCH(false, true, 4, 8, 4);
+            else GD16_LAUNCH(false, true, 4, 4, 4);
+        } else if (d.G16 && !d.a_kmajor && !d.b_kmajor) GD16_TILE(false, false, 1);
+        else if (d.a_kmajor) GD16_TILE(true, true, 0);
+        else if (d.b_kmajor) GD16_TILE(false, true, 0);
+        else GD16_TILE(false, false, 0);
+    } else {
 #define G16_LAUNCH(AKM, BKM, EPI, TALL_OK)                                                                     \
     do {                                                                                                       \
         if (TALL_OK && tall) hipLaunchKernelGGL((gemm16_kernel<AKM, BKM, true, EPI, TALL_OK ? 8 : 4>), grid, dim3(256), 0, s, d); \
@@ -402,11 +902,7 @@ void launch_gemm16(hipStream_t s, Gemm16Desc d) {
     else if (d.b_kmajor) G16_LAUNCH(false, true, 0, true);
     else G16_LAUNCH(false, false, 0, true);
 #undef G16_LAUNCH
-    if (d.splits > 1) {
-        int64_t total = (int64_t)d.M * d.N;
-        int64_t blocks = (total + 255) / 256;
-        if (blocks > 4096) blocks = 4096;
-        hipLaunchKernelGGL(gemm16_split_reduce_kernel, dim3((unsigned)blocks, (unsigned)d.batch), dim3(256), 0, s, d.part, d.splits, d.M, d.N, d.alpha,
-                           d.bias, d.R, d.ldc, d.C, d.sc1);
     }
+    if (d.splits > 1)
+        launch_split_reduce(s, d.part, d.splits, d.M, d.N, d.batch, d.alpha, d.bias, d.sbias1, d.R, d.ldc, d.C, d.sc1, d.c_vec != 0);
 }

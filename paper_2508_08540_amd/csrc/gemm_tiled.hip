@@ -226,16 +226,8 @@ __global__ __launch_bounds__(256, 2) void gemm_direct_kernel(GemmDesc d) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = lane & 15, g = lane >> 4;
     const int wm = wave >> 1, wn = wave & 1;
-    // XCD-aware order over the whole grid: launch slot i runs on XCD i % 8 and takes the i / 8-th tile of that XCD's
-    // contiguous range (n fastest, then m, then split and batch)
-    int id = (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
-    {
-        const int total = gridDim.x * gridDim.y * gridDim.z, per = total >> 3, rem = total & 7, x = id & 7;
-        id = x * per + min(x, rem) + (id >> 3);
-    }
-    const int tile_x = id % gridDim.x;
-    id /= gridDim.x;
-    const int tile_y = id % gridDim.y, zz = id / gridDim.y;
+    int tile_x, tile_y, zz;
+    gemm_tile_order(tile_x, tile_y, zz);
     const int m0 = tile_y * TM, n0 = tile_x * TN;
     const int split = zz % d.splits, z = zz / d.splits;
     const int z1 = z / d.inner, z2 = z - z1 * d.inner;
@@ -448,6 +440,21 @@ __global__ __launch_bounds__(256) void gemm_split_reduce4_kernel(const f32x4* __
     }
 }
 
+// `aligned`: bias, R and out allow 16-byte accesses in every row
+void launch_split_reduce(hipStream_t s, const float* part, int splits, int M, int N, int batch, float alpha, const float* bias, int64_t sbias1,
+                         const float* R, int ldc, float* out, int64_t sc1, bool aligned) {
+    const bool vec = N % 4 == 0 && aligned;
+    int64_t blocks = ceil_div((int64_t)M * N / (vec ? 4 : 1), 256);
+    if (blocks > 4096) blocks = 4096;
+    if (blocks < 1) blocks = 1;
+    if (vec)
+        hipLaunchKernelGGL(gemm_split_reduce4_kernel, dim3((unsigned)blocks, batch), dim3(256), 0, s, reinterpret_cast<const f32x4*>(part), splits, M,
+                           N / 4, alpha, bias, R, ldc, out, sc1, sbias1);
+    else
+        hipLaunchKernelGGL(gemm_split_reduce_kernel, dim3((unsigned)blocks, batch), dim3(256), 0, s, part, splits, M, N, alpha, bias, R, ldc, out, sc1,
+                           sbias1);
+}
+
 size_t gemm_tiled_partial_floats(int M, int N, int splits) { return splits > 1 ? (size_t)M * N * splits : 0; }
 
 // Tile and split of a product on gemm_direct_kernel: the pair with the smallest estimate of
@@ -521,16 +528,6 @@ void launch_gemm_tiled(hipStream_t s, GemmDesc d) {
         else if (d.b_kmajor) hipLaunchKernelGGL((gemm_tiled_kernel<false, true>), grid, dim3(256), 0, s, d);
         else hipLaunchKernelGGL((gemm_tiled_kernel<false, false>), grid, dim3(256), 0, s, d);
     }
-    if (d.splits > 1) {
-        const bool vec = d.N % 4 == 0 && d.c_vec;
-        int64_t blocks = ceil_div((int64_t)d.M * d.N / (vec ? 4 : 1), 256);
-        if (blocks > 4096) blocks = 4096;
-        if (blocks < 1) blocks = 1;
-        if (vec)
-            hipLaunchKernelGGL(gemm_split_reduce4_kernel, dim3((unsigned)blocks, d.batch), dim3(256), 0, s, reinterpret_cast<const f32x4*>(d.part),
-                               d.splits, d.M, d.N / 4, d.alpha, d.bias, d.R, d.ldc, d.C, d.sc1, d.sbias1);
-        else
-            hipLaunchKernelGGL(gemm_split_reduce_kernel, dim3((unsigned)blocks, d.batch), dim3(256), 0, s, d.part, d.splits, d.M, d.N, d.alpha,
-                               d.bias, d.R, d.ldc, d.C, d.sc1, d.sbias1);
-    }
+    if (d.splits > 1)
+        launch_split_reduce(s, d.part, d.splits, d.M, d.N, d.batch, d.alpha, d.bias, d.sbias1, d.R, d.ldc, d.C, d.sc1, d.c_vec != 0);
 }

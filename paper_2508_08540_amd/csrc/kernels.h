@@ -280,6 +280,25 @@ struct WconvBn {
 int launch_wconv(hipStream_t s, int act, int taps, int B, int h_in, int h_out, int c_in, int c_out, int stride, int ups, const void* x,
                  const void* w, void* y, const void* add, fixsum_t* sums, double scale, const WconvBn* bn = nullptr);
 
+// Tile of C (and split / batch index zz) that a workgroup of a grid (n tiles, m tiles, splits * batch) takes.  Launch slot i runs
+// on XCD i % 8 and takes the i / 8-th tile of that XCD's contiguous share, so that neighbouring tiles meet in one L2.  Inside
+// a matrix the tiles come in bands of GEMM_BAND tile rows, m fastest: the 64 or so workgroups of an XCD then cover about
+// 8 x 8 tiles instead of a strip of one tile row, and the strip's factor is read from memory once per band instead of once
+// per tile row (8192^3 in bf16, 256 x 128 tiles: 4.5 TB/s of L2 misses with single rows).
+#define GEMM_BAND 8
+__device__ __forceinline__ void gemm_tile_order(int& tile_x, int& tile_y, int& zz) {
+    const int nx = gridDim.x, ny = gridDim.y, total = nx * ny * gridDim.z;
+    int id = (blockIdx.z * ny + blockIdx.y) * nx + blockIdx.x;
+    const int per = total >> 3, rem = total & 7, x = id & 7;
+    id = x * per + min(x, rem) + (id >> 3);
+    zz = id / (nx * ny);
+    id -= zz * nx * ny;
+    const int band = id / (GEMM_BAND * nx), first = band * GEMM_BAND, rows = min(GEMM_BAND, ny - first);
+    id -= first * nx;
+    tile_x = id / rows;
+    tile_y = first + (id - tile_x * rows);
+}
+
 // ---- gemm_tiled.hip -----------------------------------------------------------------------------------
 // C[m][n] = alpha * sum_k A(m,k) B(n,k) [+ bias[n]] [+ R[m][n]]; A(m,k) = a_kmajor ? A[k*lda + m] : A[m*lda + k], same for B.
 // Batched over z = z1 * inner + z2 (z1 < batch / inner): pointer offsets z1*s?1 + z2*s?2 (R uses C's).  splits > 1 splits
@@ -306,6 +325,9 @@ struct GemmDesc {
 };
 size_t gemm_tiled_partial_floats(int M, int N, int splits);
 void launch_gemm_tiled(hipStream_t s, GemmDesc d);
+// out = alpha * (sum of the partial results in split order) (+ bias) (+ R), for a batch of matrices
+void launch_split_reduce(hipStream_t s, const float* part, int splits, int M, int N, int batch, float alpha, const float* bias, int64_t sbias1,
+                         const float* R, int ldc, float* out, int64_t sc1, bool aligned);
 
 // true where the bf16 weight-gradient kernel (wgrad16.hip) takes the layer
 bool wgrad16_covers(int act, const ConvShape& cs);
@@ -325,16 +347,29 @@ struct Gemm16Desc {
     int batch, inner, splits;
     int64_t sa1, sa2, sb1, sb2, sc1, sc2;
     int64_t sbias1;   // floats between the bias vectors of consecutive z1 (unsplit products only)
+    int k_seg;        // > 0 (a multiple of 32, row-major factors): the contraction runs over K / k_seg pairs of matrices
+    int64_t sa_seg, sb_seg;
     float alpha;
     // optional softmax statistics of the rows of C (single matrix, no split): per row and per 64-column block the pair
     // (max, sum exp(C - max)) into ce_part[2 * ceil(N / 128)][M][2], and C[m][ce_targets[m]] into ce_tlogit[m]
     float* ce_part;
     const int32_t* ce_targets;
     float* ce_tlogit;
+    // optional gradient of the mean cross-entropy instead of the product itself (row-major factors, D % 8 == 0): C16 =
+    // (softmax - onehot(ce_targets)) * ce_scale from the rows' (max, sum) in ce_rows [M][2]; N is the padded row length,
+    // columns n_valid .. N - 1 are stored as zeros
+    const float* ce_rows;
+    float ce_scale;
+    int n_valid;
+    // optional factor gelu'(U[m][n]) on the product (row-major A, k-major B; U has C's layout, N % 4 == 0), with the column sums
+    // of the result in gelu_part [gemm16_gelu_rows(M, N)][N]
+    const float* U;
+    float* gelu_part;
     // ----
-    int k_chunk, a_vec, b_vec, c_vec;
+    int k_chunk, a_vec, b_vec, c_vec, c_vec8;
     int64_t part_stride;
 };
+int gemm16_gelu_rows(int64_t M, int N);
 void launch_gemm16(hipStream_t s, Gemm16Desc d);
 
 // ---- seq.hip ------------------------------------------------------------------------------------------

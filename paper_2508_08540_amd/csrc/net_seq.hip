@@ -45,6 +45,11 @@ struct LayerAct {
 
 struct SeqScratch {
     bool bf = false;
+    // bf16 mode with 16-byte rows everywhere (width and feed-forward width multiples of 8): the logits are never stored, their
+    // gradient comes from a second pass over the vocabulary projection (268 Gflop instead of a 1 GB round trip per 8192 tokens
+    // of a 32 000-word vocabulary), and the GELU derivative rides in the epilogue of the product before it
+    bool lean = false;
+    int ldv = 0;                    // row pitch of the logits' gradient
     int32_t *tok, *tgt;
     uint16_t* w16;                  // bf16 copy of the parameter vector (bf16 mode)
     std::vector<Mat> x;             // x[l] is the input of layer l, x[layers] the encoder output
@@ -70,7 +75,8 @@ int wgrad_splits(int M, int N, int64_t K, int batch = 1) {
     int64_t s = ceil_div(512, tiles);
     const int64_t max_s = K / 256 > 1 ? K / 256 : 1;
     if (s > max_s) s = max_s;
-    if (s > 64) s = 64;
+    // 512 x 512 outputs over 8192 tokens, products and reduction: 22 us with 8 or 12 parts, 28 with 16
+    if (s > 12) s = 12;
     return (int)s;
 }
 
@@ -82,7 +88,7 @@ int dgrad_splits(bool bf, int64_t M, int N, int K) {
     const int64_t tiles = ceil_div(M, 128) * ceil_div(N, 128);
     if (!bf) return tiles >= 512 || K < 512 ? 1 : K / 256 < 16 ? K / 256 : 16;
     if (K < DGRAD_SPLIT_MIN_K || tiles >= 512) return 1;
-    int64_t s = ceil_div(768, tiles);
+    int64_t s = ceil_div(1024, tiles);   // 512 tiles of 256 x 128: two workgroups per compute unit
     if (s > K / 1024) s = K / 1024;
     return (int)(s > 1 ? s : 1);
 }
@@ -109,9 +115,11 @@ SeqScratch carve(Carver& c, const bls_model* m, int B, bool train) {
     const int64_t T = (int64_t)B * L, PP = (int64_t)B * H * L * L;
     SeqScratch s{};
     const bool bf = s.bf = m->desc.act_dtype == BLS_ACT_BF16;
+    const bool lean = s.lean = bf && D % 8 == 0 && F % 8 == 0;
+    s.ldv = lean ? (V + 7) & ~7 : V;
     s.tok = c.take<int32_t>(T);
     s.tgt = c.take<int32_t>(T);
-    s.w16 = bf ? c.take<uint16_t>(m->num_params) : nullptr;
+    s.w16 = bf ? c.take<uint16_t>(m->num_params + 8 * D) : nullptr;   // eight more rows of the vocabulary projection, zeros: its padding
     const int sets = train ? layers : 1;
     s.x.resize(layers + 1);
     for (int l = 0; l <= layers; ++l) s.x[l] = (train || l < 2) ? take(c, bf, BOTH, T * D) : s.x[l - 2];
@@ -134,7 +142,7 @@ SeqScratch carve(Carver& c, const bls_model* m, int B, bool train) {
         a.st2 = c.take<float>(2 * T);
     }
     // bf16 mode: the vocabulary projection leaves row statistics behind and scoring never stores the logits
-    s.logits = (bf && !train) ? nullptr : c.take<float>(T * V);
+    s.logits = (bf && (!train || lean)) ? nullptr : c.take<float>(T * V);
     s.ce_parts = 2 * (int)ceil_div(V, 128);
     s.ce_part = bf ? c.take<float>(T * s.ce_parts * 2) : nullptr;
     s.ce_tlogit = bf ? c.take<float>(T) : nullptr;
@@ -149,7 +157,7 @@ SeqScratch carve(Carver& c, const bls_model* m, int B, bool train) {
         }
     s.part_main = train ? c.take<float>(part ? part : 1) : nullptr;
     if (!train) return s;
-    if (bf) s.dlogits.h = c.take<uint16_t>(T * V);
+    if (bf) s.dlogits.h = c.take<uint16_t>(T * s.ldv);
     else s.dlogits.f = s.logits;
     s.grad = c.take<float>(m->num_params);
     s.da = c.take<float>(T * D);
@@ -159,7 +167,7 @@ SeqScratch carve(Carver& c, const bls_model* m, int B, bool train) {
     for (int l = 0; l < layers; ++l) {
         s.db2[l] = take(c, bf, BOTH, T * D);
         s.db1[l] = take(c, bf, BOTH, T * D);
-        s.df[l] = take(c, bf, BOTH, T * F);
+        s.df[l] = take(c, bf, lean ? FACTOR_ONLY : BOTH, T * F);
         take3(c, bf, BOTH, T * D, s.dq[l], s.dk[l], s.dv[l]);
     }
     part = 0;
@@ -177,7 +185,7 @@ SeqScratch carve(Carver& c, const bls_model* m, int B, bool train) {
     need(V, D);
     s.part = c.take<float>(part ? part : 1);
     // partial column sums of one backward pass: per layer five D-wide and one F-wide bias gradient and two layer norms
-    const size_t per_layer = 3 * colsum_partial_floats(T, D) + colsum_partial_floats(T, F) + gelu_bwd_colsum_floats(T, F) + 2 * layernorm_bwd_partial_floats(T, D) + (size_t)12 * B * D;
+    const size_t per_layer = 3 * colsum_partial_floats(T, D) + colsum_partial_floats(T, F) + (lean ? (size_t)gemm16_gelu_rows(T, F) * F : gelu_bwd_colsum_floats(T, F)) + 2 * layernorm_bwd_partial_floats(T, D) + (size_t)12 * B * D;
     const size_t pos = colsum_partial_floats(B, L * D);
     s.cpart_floats = per_layer * layers > pos ? per_layer * layers : pos;
     s.cpart = c.take<float>(s.cpart_floats);
@@ -202,11 +210,16 @@ struct Product {
     bool a_kmajor = false, b_kmajor = false;
     int batch = 1, inner = 1, splits = 1;
     int64_t sa1 = 0, sa2 = 0, sb1 = 0, sb2 = 0, sc1 = 0, sc2 = 0, sbias1 = 0;
-    int k_seg = 0;                         // fp32 mode: the contraction runs over K / k_seg pairs of matrices
+    int k_seg = 0;                         // the contraction runs over K / k_seg pairs of matrices
     int64_t sa_seg = 0, sb_seg = 0;
     float alpha = 1.f;
     const int32_t* ce_targets = nullptr;   // bf16 mode only: leave softmax statistics of the rows behind
     float *ce_part = nullptr, *ce_tlogit = nullptr;
+    const float* ce_rows = nullptr;        // bf16 mode only: the gradient of the logits instead of the logits
+    float ce_scale = 0.f;
+    int n_valid = 0;
+    const float* U = nullptr;              // bf16 mode only: times gelu'(U), column sums into gelu_part
+    float* gelu_part = nullptr;
 };
 
 void multiply(bls_ctx* ctx, hipStream_t st, bool bf, const Product& p, int prof_class) {
@@ -222,6 +235,9 @@ void multiply(bls_ctx* ctx, hipStream_t st, bool bf, const Product& p, int prof_
         d.sbias1 = p.sbias1;
         d.alpha = p.alpha;
         d.ce_part = p.ce_part; d.ce_targets = p.ce_targets; d.ce_tlogit = p.ce_tlogit;
+        d.ce_rows = p.ce_rows; d.ce_scale = p.ce_scale; d.n_valid = p.n_valid;
+        d.U = p.U; d.gelu_part = p.gelu_part;
+        d.k_seg = p.k_seg; d.sa_seg = p.sa_seg; d.sb_seg = p.sb_seg;
         launch_gemm16(st, d);
     } else {
         GemmDesc d{};
@@ -273,7 +289,7 @@ struct Net {
         p.ldc = V;
         p.M = (int)T; p.N = V; p.K = D;
         if (s->bf) {
-            p.out.f = keep_logits ? s->logits : nullptr;
+            p.out.f = keep_logits && !s->lean ? s->logits : nullptr;
             p.ce_part = s->ce_part; p.ce_targets = targets; p.ce_tlogit = s->ce_tlogit;
             multiply(ctx, st, true, p, PROF_GEMM);
             PROF(ctx, PROF_HEAD, launch_ce_combine(st, s->ce_part, s->ce_parts, s->ce_tlogit, T, s->tok_loss, keep_logits ? s->ce_rows : nullptr));
@@ -282,14 +298,36 @@ struct Net {
             multiply(ctx, st, false, p, PROF_GEMM);
         }
     }
-    // dx[T][n_in] = dy[T][n_out] W (+ R)
-    void linear_dgrad(Mat dy, int64_t T, int n_out, int64_t w_off, int n_in, Mat dx, const float* R = nullptr) const {
+    // dlogits = (softmax(logits) - onehot(targets)) * scale from the statistics token_losses left, by the same product again
+    // (the same sums in the same order: the same logits)
+    void logits_gradient(Mat hf, const int32_t* targets, int64_t T, float scale) const {
+        Product p;
+        p.A = hf; p.lda = m->enc_D;
+        p.B = weight(m->enc_head); p.ldb = m->enc_D;
+        p.out = s->dlogits; p.ldc = s->ldv;
+        p.M = (int)T; p.N = s->ldv; p.K = m->enc_D;
+        p.ce_targets = targets; p.ce_rows = s->ce_rows; p.ce_scale = scale; p.n_valid = m->enc_V;
+        multiply(ctx, st, true, p, PROF_GEMM);
+    }
+    // du[T][F] = (dy[T][D] W) * gelu'(u) as bf16, and the partial column sums of du (gemm16_gelu_rows rows)
+    void gelu_dgrad(Mat dy, int64_t T, int n_out, int64_t w_off, int n_in, Mat du, const float* u, float* part) const {
         Product p;
         p.A = dy; p.lda = n_out;
         p.B = weight(w_off); p.ldb = n_in; p.b_kmajor = true;
+        p.out = Mat{nullptr, du.h}; p.ldc = n_in;
+        p.M = (int)T; p.N = n_in; p.K = n_out;
+        p.U = u; p.gelu_part = part;
+        multiply(ctx, st, true, p, PROF_GEMM);
+    }
+    // dx[T][n_in] = dy[T][n_out] W (+ R); rows of dy are `pitch` apart (0: n_out), zeros behind the n_out values, and W is
+    // followed by as many rows
+    void linear_dgrad(Mat dy, int64_t T, int n_out, int64_t w_off, int n_in, Mat dx, const float* R = nullptr, int pitch = 0) const {
+        Product p;
+        p.A = dy; p.lda = pitch ? pitch : n_out;
+        p.B = weight(w_off); p.ldb = n_in; p.b_kmajor = true;
         p.out = dx; p.ldc = n_in;
         p.R = R;
-        p.M = (int)T; p.N = n_in; p.K = n_out;
+        p.M = (int)T; p.N = n_in; p.K = p.lda;
         if (!dx.h) {   // partial sums are added into fp32 only
             p.splits = dgrad_splits(s->bf, T, n_in, n_out);
             p.part = s->part_main;
@@ -297,9 +335,9 @@ struct Net {
         multiply(ctx, st, s->bf, p, PROF_GEMM);
     }
     // dW[n_out][n_in] = dy^T x, contraction over the T tokens
-    void linear_wgrad(Mat dy, Mat x, int64_t T, int n_out, int n_in, int64_t w_off) const {
+    void linear_wgrad(Mat dy, Mat x, int64_t T, int n_out, int n_in, int64_t w_off, int pitch = 0) const {
         Product p;
-        p.A = dy; p.lda = n_out; p.a_kmajor = true;
+        p.A = dy; p.lda = pitch ? pitch : n_out; p.a_kmajor = true;
         p.B = x; p.ldb = n_in; p.b_kmajor = true;
         p.out.f = s->grad + w_off; p.ldc = n_in;
         p.M = n_out; p.N = n_in; p.K = (int)T;
@@ -347,22 +385,24 @@ struct Net {
         linear_wgrad(dk, x, T, D, D, e.wk);
         linear_wgrad(dv, x, T, D, D, e.wv);
     }
-    // dx = dq Wq + dk Wk + dv Wv + R: in fp32 mode one contraction over the three pairs
+    // dx = dq Wq + dk Wk + dv Wv + R: one contraction over the three pairs
     void qkv_dgrad(Mat dq, Mat dk, Mat dv, int64_t T, const EncLayer& e, Mat dx, const float* R) const {
         const int D = m->enc_D;
         const int64_t sw = e.wk - e.wq;
         // (segments need the 16-byte rows of the direct kernel)
-        if (!s->bf && e.wv - e.wk == sw && sw % 4 == 0 && dv.f - dk.f == dk.f - dq.f && D % 16 == 0 && (reinterpret_cast<uintptr_t>(params + e.wq) & 15) == 0) {
+        const int64_t sd = s->bf ? dk.h - dq.h : dk.f - dq.f;
+        const bool rows16 = s->bf ? D % 32 == 0 : D % 16 == 0 && (reinterpret_cast<uintptr_t>(params + e.wq) & 15) == 0;
+        if (e.wv - e.wk == sw && (s->bf ? dv.h - dk.h : dv.f - dk.f) == sd && rows16) {
             Product p;
-            p.A = dq; p.lda = D; p.sa_seg = dk.f - dq.f;
+            p.A = dq; p.lda = D; p.sa_seg = sd;
             p.B = weight(e.wq); p.ldb = D; p.b_kmajor = true; p.sb_seg = sw;
             p.k_seg = D;
             p.out = dx; p.ldc = D;
             p.R = R;
             p.M = (int)T; p.N = D; p.K = 3 * D;
-            p.splits = dgrad_splits(false, T, D, 3 * D);
+            p.splits = dgrad_splits(s->bf, T, D, 3 * D);
             p.part = s->part_main;
-            multiply(ctx, st, false, p, PROF_GEMM);
+            multiply(ctx, st, s->bf, p, PROF_GEMM);
             return;
         }
         linear_dgrad(dq, T, D, e.wq, D, dx, R);    // starting from the residual path
@@ -425,6 +465,9 @@ struct Net {
         if (!s->bf) return;
         const int64_t first = m->enc_layers[0].wq;
         PROF(ctx, PROF_UPDATE, launch_to_bf16(st, params + first, s->w16 + first, m->num_params - first));
+    }
+    void clear_weight_padding() const {   // once per call: nothing else writes there
+        if (s->bf) PROF(ctx, PROF_UPDATE, launch_fill_zero(st, reinterpret_cast<float*>(s->w16 + m->num_params), 4 * m->enc_D));
     }
 };
 
@@ -530,6 +573,7 @@ int seq_local_step(bls_ctx* ctx, const bls_model* m, float* params, float* momen
     const float att = 1.f / sqrtf((float)dh);
     const Mat da{s.da, nullptr};
 
+    net.clear_weight_padding();
     for (int64_t j = 0; j < tau; ++j) {
         net.refresh_weight_copies();
         {
@@ -539,7 +583,8 @@ int seq_local_step(bls_ctx* ctx, const bls_model* m, float* params, float* momen
         net.forward(s.tok, true);
         const Mat hf = s.x[layers];
         net.token_losses(hf, s.tgt, T, true);
-        if (s.bf) PROF(ctx, PROF_HEAD, launch_ce_grad(st, s.logits, s.tgt, s.ce_rows, T, V, gscale, s.dlogits.h));
+        if (s.lean) net.logits_gradient(hf, s.tgt, T, gscale);
+        else if (s.bf) PROF(ctx, PROF_HEAD, launch_ce_grad(st, s.logits, s.tgt, s.ce_rows, T, V, gscale, s.dlogits.h));
         else PROF(ctx, PROF_HEAD, launch_token_ce(st, s.logits, s.tgt, T, V, s.tok_loss, gscale, nullptr));
         PROF(ctx, PROF_HEAD, launch_sample_mean(st, s.tok_loss, B, L, step_losses_out ? step_losses_out + j * B : s.loss));
         // Weight gradients are off the critical path (only the update needs them): each product runs on the side stream
@@ -559,8 +604,8 @@ int seq_local_step(bls_ctx* ctx, const bls_model* m, float* params, float* momen
         int rc2;
         // head
         if ((rc2 = aside()) != BLS_OK) return rc2;
-        side.linear_wgrad(s.dlogits, hf, T, V, D, m->enc_head);
-        net.linear_dgrad(s.dlogits, T, V, m->enc_head, D, da);
+        side.linear_wgrad(s.dlogits, hf, T, V, D, m->enc_head, s.ldv);
+        net.linear_dgrad(s.dlogits, T, V, m->enc_head, D, da, nullptr, s.ldv);
         for (int l = layers - 1; l >= 0; --l) {
             const EncLayer& e = m->enc_layers[l];
             const LayerAct& a = s.act[l];
@@ -571,8 +616,13 @@ int seq_local_step(bls_ctx* ctx, const bls_model* m, float* params, float* momen
             // r2 = h1 + g W2^T + b2
             if ((rc2 = aside()) != BLS_OK) return rc2;
             side.linear_wgrad(db2, a.g, T, D, F, e.w2);
-            net.linear_dgrad(db2, T, D, e.w2, F, Mat{df.f, nullptr});
-            {
+            if (s.lean) {
+                const int rows = gemm16_gelu_rows(T, F);
+                float* part = reserve_sums((size_t)rows * F);
+                net.gelu_dgrad(db2, T, D, e.w2, F, df, a.u, part);   // du = (dr2 W2) * gelu'(u)
+                push_sums(part - s.cpart, rows, F, F, e.b1);
+            } else {
+                net.linear_dgrad(db2, T, D, e.w2, F, Mat{df.f, nullptr});
                 // du = dg * gelu'(u) with the partial sums of the bias gradient
                 float* part = reserve_sums(gelu_bwd_colsum_floats(T, F));
                 int rows = 0;
