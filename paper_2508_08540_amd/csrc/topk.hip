@@ -6,15 +6,17 @@
 //   low 32 bits:  ~index, so that among equal losses the smaller index is the larger word.
 // All words are distinct, hence exactly one result is correct and no stability argument is needed.
 //
-// Small pools (N <= TOPK_LDS_MAX) are sorted by one workgroup entirely in LDS with a bitonic
-// network.  Larger pools take a multi-workgroup path: radix-select of the k-th word, ordered
-// compaction of the selected words, and an LSD radix sort of those k words.
+// Pools of up to TOPK_RANK_MAX samples are ranked by counting in one launch; pools of up to TOPK_SORT_MAX are sorted whole by
+// four radix passes of one launch each; larger ones take radix-select of the k-th word, ordered compaction of the selected
+// words, and an LSD radix sort of those k words.
 #include <mutex>
 
 #include "common.h"
 
-#define TOPK_LDS_MAX 16384
-#define TOPK_THREADS 1024
+// Ranking by counting needs no scratch and costs 24.6 us at 16384 (four sorting passes: 22 us at 16385); sorting a pool of
+// 2^19 whole takes 73 us for any k, selecting first 98 (k = N / 50) to 120 us (k = N); at 2^20 about 117 against 105 to 153 us.
+#define TOPK_RANK_MAX 16384
+#define TOPK_SORT_MAX (1 << 19)
 
 __device__ __forceinline__ uint32_t loss_key(float v) {
     uint32_t u = __float_as_uint(v);
@@ -23,38 +25,242 @@ __device__ __forceinline__ uint32_t loss_key(float v) {
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-__device__ __forceinline__ uint64_t sort_word(float v, uint32_t idx) {
-    return ((uint64_t)loss_key(v) << 32) | (uint64_t)(~idx);
-}
-
-// One workgroup; M = power of two >= N words in LDS; sorts descending.
-__global__ __launch_bounds__(TOPK_THREADS) void topk_lds_bitonic_kernel(const float* __restrict__ losses, int N, int k,
-                                                                        int M, int32_t* __restrict__ idx_out,
-                                                                        float* __restrict__ val_out) {
-    extern __shared__ uint64_t words[];
-    const int tid = threadIdx.x;
-    for (int i = tid; i < M; i += TOPK_THREADS) words[i] = i < N ? sort_word(losses[i], (uint32_t)i) : 0ull;
+// Rank by counting: the rank of a sample is the number of samples that precede it, so each workgroup ranks 64 samples (one per
+// lane) against the whole pool, which its 16 waves walk in chunks of 64 keys from LDS (every lane reads the same four keys per
+// 16-byte read).  Chunks left of the workgroup's own count equal keys, chunks right of it do not: the tie rule costs nothing
+// but in the one chunk where both orders occur.  Bound: vector instructions, two per pair of samples; N^2 of them still beat
+// the N log^2 N of a bitonic network with its 100 barriers in one workgroup because all compute units take part.
+// N = 512 / 4096 / 16384: 9.8 -> 4.3, 38 -> 8.7, 157 -> 24.5 us against the bitonic network.
+__global__ __launch_bounds__(1024) void topk_rank_kernel(const float* __restrict__ losses, int N, int k, int32_t* __restrict__ idx_out,
+                                                         float* __restrict__ val_out) {
+    extern __shared__ __align__(16) uint32_t rank_lds[];   // the keys, then [16][64] partial ranks
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int n_chunks = (N + 63) >> 6, own = blockIdx.x;
+    for (int i = tid; i < n_chunks * 64; i += 1024) rank_lds[i] = i < N ? loss_key(losses[i]) : 0u;   // no loss has key 0
     __syncthreads();
-    for (int size = 2; size <= M; size <<= 1) {
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            for (int t = tid; t < (M >> 1); t += TOPK_THREADS) {
-                int lo = ((t & ~(stride - 1)) << 1) | (t & (stride - 1));
-                int hi = lo | stride;
-                bool descending = (lo & size) == 0;
-                uint64_t a = words[lo], b = words[hi];
-                if ((a < b) == descending) {
-                    words[lo] = b;
-                    words[hi] = a;
-                }
+    const uint32_t mine = rank_lds[own * 64 + lane];
+    uint32_t before = 0;
+    for (int c = wave; c < n_chunks; c += 16) {
+        const uint4* q = reinterpret_cast<const uint4*>(rank_lds + c * 64);
+        if (c < own) {
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                const uint4 v = q[j];
+                before += (v.x >= mine) + (v.y >= mine) + (v.z >= mine) + (v.w >= mine);
             }
-            __syncthreads();
+        } else if (c > own) {
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                const uint4 v = q[j];
+                before += (v.x > mine) + (v.y > mine) + (v.z > mine) + (v.w > mine);
+            }
+        } else {
+            for (int j = 0; j < 64; ++j) {
+                const uint32_t v = rank_lds[c * 64 + j];
+                before += v > mine || (v == mine && j < lane);
+            }
         }
     }
-    for (int r = tid; r < k; r += TOPK_THREADS) {
-        uint32_t idx = ~(uint32_t)(words[r] & 0xffffffffull);
-        idx_out[r] = (int32_t)idx;
-        if (val_out) val_out[r] = losses[idx];
+    __syncthreads();   // the partial ranks overwrite the keys
+    rank_lds[tid] = before;
+    __syncthreads();
+    if (wave == 0) {
+        uint32_t rank = 0;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) rank += rank_lds[w * 64 + lane];
+        const int i = own * 64 + lane;
+        if (i < N && rank < (uint32_t)k) {
+            idx_out[rank] = i;
+            if (val_out) val_out[rank] = losses[i];
+        }
     }
+}
+
+// Inverse of loss_key for every key that determines the float uniquely; NaN keys and the zero key
+// (shared by +0 and -0) do not, those values are fetched from the loss array.
+__device__ __forceinline__ bool key_to_loss(uint32_t key, float* v) {
+    if (key == 0xffffffffu || key == 0x80000000u) return false;
+    uint32_t u = (key & 0x80000000u) ? (key & 0x7fffffffu) : ~key;
+    *v = __uint_as_float(u);
+    return true;
+}
+
+// ---- medium pools: the whole pool in four radix passes ----------------------------------------------------------------
+//
+// These pools are bound by launches, not by bytes (50 000 losses are 200 KB): selecting first, and scanning a digit table
+// between the passes, took 21 launches of 2 to 6 us each.  Here the pool is sorted whole in five launches.  The pool is at most
+// SORT_TILES tiles of RITER x 1024 elements, so the digit table [tile][256] is small enough that every workgroup adds up its
+// columns itself (tiles before its own, and all of them) instead of waiting for a scan, and the pass that places an element
+// also counts it in the table of the next pass: the destination tile and the next digit are known at that point.  These counts
+// meet in LDS first (16 bits each, a tile has at most 8192 elements), since all elements of a run may share the next digit.
+// k = N, N = 50 000 / 131 072 / 524 288: 79 -> 29, 95 -> 40, 120 -> 73 us (the table's loads one after another: 37, 51, 85).  What is left is five launches, each a chain of load,
+// table sum, ranking rounds and scattered stores.
+
+#define SORT_TILES 64   // 64 tiles of 8 x 1024 elements hold TOPK_SORT_MAX
+#define SORT_TABLE (SORT_TILES * 256)
+
+// Digit counts of the first pass; clears the tables of the other three.
+template <int RITER>
+__global__ __launch_bounds__(1024) void sort_count_kernel(const float* __restrict__ losses, int N, uint32_t* __restrict__ tables) {
+    __shared__ uint32_t cnt[256];
+    const int tid = threadIdx.x;
+    if (tid < 256) cnt[tid] = 0u;
+    else tables[(size_t)(tid >> 8) * SORT_TABLE + blockIdx.x * 256 + (tid & 255)] = 0u;
+    __syncthreads();
+    const int base = blockIdx.x * (RITER * 1024);
+#pragma unroll
+    for (int it = 0; it < RITER; ++it) {
+        const int i = base + it * 1024 + tid;
+        if (i < N) atomicAdd(&cnt[~loss_key(losses[i]) & 255u], 1u);
+    }
+    __syncthreads();
+    if (tid < 256) tables[blockIdx.x * 256 + tid] = cnt[tid];
+}
+
+// One stable pass over the sort keys ~loss_key (ascending order is rank order).  A wave ranks its RITER x 64 consecutive
+// elements in rounds of 64 by ballots, counting each digit as it goes; the four groups of 256 threads add up a quarter of the
+// table each.  PASS 0 reads the losses, PASS 3 stores the first k of the result.
+template <int RITER, int PASS>
+__global__ __launch_bounds__(1024) void sort_pass_kernel(const float* __restrict__ losses, const uint2* __restrict__ in, uint2* __restrict__ out, int N,
+                                                         int k, const uint32_t* __restrict__ table, uint32_t* __restrict__ table_next,
+                                                         int32_t* __restrict__ idx_out, float* __restrict__ val_out) {
+    constexpr int RTILE = RITER * 1024, SHIFT = 8 * PASS;
+    __shared__ uint32_t cnt[16][256];
+    __shared__ uint32_t part[2][4][256];
+    __shared__ uint32_t wave_total[4];
+    __shared__ uint32_t next[PASS < 3 ? SORT_TABLE / 2 : 1];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, tiles = gridDim.x;
+    const int wbase = blockIdx.x * RTILE + wave * (RITER * 64);
+    uint32_t key[RITER], id[RITER];
+#pragma unroll
+    for (int it = 0; it < RITER; ++it) {
+        const int i = wbase + it * 64 + lane;
+        key[it] = 0u;
+        id[it] = (uint32_t)i;
+        if (i < N) {
+            if (PASS == 0) key[it] = ~loss_key(losses[i]);
+            else {
+                const uint2 v = in[i];
+                key[it] = v.x;
+                id[it] = v.y;
+            }
+        }
+    }
+    {
+        const int d = tid & 255, g = tid >> 8;
+        uint32_t v[SORT_TILES / 4], all = 0, left = 0;
+#pragma unroll
+        for (int j = 0; j < SORT_TILES / 4; ++j) v[j] = g + 4 * j < tiles ? table[(g + 4 * j) * 256 + d] : 0u;   // all in flight together
+#pragma unroll
+        for (int j = 0; j < SORT_TILES / 4; ++j) {
+            all += v[j];
+            left += g + 4 * j < (int)blockIdx.x ? v[j] : 0u;
+        }
+        part[0][g][d] = all;
+        part[1][g][d] = left;
+    }
+    for (int i = tid; i < 16 * 256; i += 1024) cnt[i >> 8][i & 255] = 0u;
+    if (PASS < 3)
+        for (int i = tid; i < tiles * 128; i += 1024) next[i] = 0u;
+    __syncthreads();
+    const uint64_t lt = lane ? (~0ull >> (64 - lane)) : 0ull;
+    uint32_t rank[RITER];
+#pragma unroll
+    for (int it = 0; it < RITER; ++it) {
+        const bool valid = wbase + it * 64 + lane < N;
+        const uint32_t d = (key[it] >> SHIFT) & 255u;
+        uint64_t peers = __ballot(valid);
+#pragma unroll
+        for (int b = 0; b < 8; ++b) {
+            const uint64_t v = __ballot((d >> b) & 1u);
+            peers &= ((d >> b) & 1u) ? v : ~v;
+        }
+        rank[it] = cnt[wave][d] + (uint32_t)__popcll(peers & lt);
+        __builtin_amdgcn_wave_barrier();
+        if (valid && (peers & lt) == 0ull) cnt[wave][d] += (uint32_t)__popcll(peers);   // lowest peer advances the count
+        __builtin_amdgcn_wave_barrier();
+    }
+    // thread d < 256: first output slot of digit d = elements of smaller digits + those of d in tiles before this one
+    uint32_t total = 0, incl = 0;
+    if (tid < 256) {
+        total = (part[0][0][tid] + part[0][1][tid]) + (part[0][2][tid] + part[0][3][tid]);
+        incl = total;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t below = __shfl_up(incl, o, 64);
+            if (lane >= o) incl += below;
+        }
+        if (lane == 63) wave_total[wave] = incl;
+    }
+    __syncthreads();
+    if (tid < 256) {
+        uint32_t run = incl - total + (part[1][0][tid] + part[1][1][tid]) + (part[1][2][tid] + part[1][3][tid]);
+        for (int w = 0; w < wave; ++w) run += wave_total[w];
+#pragma unroll
+        for (int w = 0; w < 16; ++w) {
+            const uint32_t c = cnt[w][tid];
+            cnt[w][tid] = run;
+            run += c;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < RITER; ++it) {
+        if (wbase + it * 64 + lane >= N) continue;
+        const uint32_t pos = cnt[wave][(key[it] >> SHIFT) & 255u] + rank[it];
+        if (PASS < 3) {
+            out[pos] = make_uint2(key[it], id[it]);
+            const uint32_t slot = (pos / RTILE) * 256u + ((key[it] >> (SHIFT + 8)) & 255u);
+            atomicAdd(&next[slot >> 1], (slot & 1u) ? 65536u : 1u);
+        } else if (pos < (uint32_t)k) {
+            idx_out[pos] = (int32_t)id[it];
+            if (val_out) {
+                float v;
+                if (!key_to_loss(~key[it], &v)) v = losses[id[it]];
+                val_out[pos] = v;
+            }
+        }
+    }
+    if (PASS == 3) return;
+    __syncthreads();
+    for (int i = tid; i < tiles * 128; i += 1024) {
+        const uint32_t v = next[i];
+        if (v & 65535u) atomicAdd(&table_next[2 * i], v & 65535u);
+        if (v >> 16) atomicAdd(&table_next[2 * i + 1], v >> 16);
+    }
+}
+
+static size_t sort_scratch_bytes(int64_t N) {
+    Carver c(nullptr);
+    c.take<uint32_t>(4 * SORT_TABLE);
+    c.take<uint2>(N);
+    c.take<uint2>(N);
+    return c.off;
+}
+
+template <int RITER>
+static void launch_sort(hipStream_t s, char* scratch_base, const float* losses, int N, int k, int32_t* idx_out, float* val_out) {
+    Carver c(scratch_base);
+    uint32_t* t = c.take<uint32_t>(4 * SORT_TABLE);
+    uint2* a = c.take<uint2>(N);
+    uint2* b = c.take<uint2>(N);
+    const dim3 grid((unsigned)((N + RITER * 1024 - 1) / (RITER * 1024))), block(1024);
+    hipLaunchKernelGGL(sort_count_kernel<RITER>, grid, block, 0, s, losses, N, t);
+    hipLaunchKernelGGL((sort_pass_kernel<RITER, 0>), grid, block, 0, s, losses, nullptr, a, N, k, t, t + SORT_TABLE, nullptr, nullptr);
+    hipLaunchKernelGGL((sort_pass_kernel<RITER, 1>), grid, block, 0, s, losses, a, b, N, k, t + SORT_TABLE, t + 2 * SORT_TABLE, nullptr, nullptr);
+    hipLaunchKernelGGL((sort_pass_kernel<RITER, 2>), grid, block, 0, s, losses, b, a, N, k, t + 2 * SORT_TABLE, t + 3 * SORT_TABLE, nullptr, nullptr);
+    hipLaunchKernelGGL((sort_pass_kernel<RITER, 3>), grid, block, 0, s, losses, a, nullptr, N, k, t + 3 * SORT_TABLE, nullptr, idx_out, val_out);
+}
+
+// TOPK_RANK_MAX < N <= TOPK_SORT_MAX; `scratch_base` as below.  The fewest rounds that keep the pool within SORT_TILES tiles.
+static int launch_topk_medium(bls_ctx* ctx, char* scratch_base, const float* losses, int64_t N, int64_t k, int32_t* idx_out, float* val_out) {
+    const int n = (int)N, kk = (int)k;
+    if (N <= 1 * 65536) launch_sort<1>(ctx->stream, scratch_base, losses, n, kk, idx_out, val_out);
+    else if (N <= 2 * 65536) launch_sort<2>(ctx->stream, scratch_base, losses, n, kk, idx_out, val_out);
+    else if (N <= 4 * 65536) launch_sort<4>(ctx->stream, scratch_base, losses, n, kk, idx_out, val_out);
+    else launch_sort<8>(ctx->stream, scratch_base, losses, n, kk, idx_out, val_out);
+    BLS_HIP(ctx, hipGetLastError());
+    return BLS_OK;
 }
 
 // ---- large pools ----------------------------------------------------------------------------------
@@ -74,7 +280,7 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_lds_bitonic_kernel(const fl
 #define TILE 2048          // elements per 256-thread block: 8 consecutive elements per thread
 #define SCAN_CHUNK 2048
 // Radix passes: a block of 256 threads handles RITER * 256 elements (each wave ranks RITER * 64 of them in
-// rounds of 64); 8 rounds for moderate pools, 16 for very large ones (longer runs per digit when scattering).
+// rounds of 64); 8 rounds for pools below 2^22, 16 for very large ones (longer runs per digit when scattering).
 
 struct SelInfo {
     uint32_t bin;        // b1
@@ -325,8 +531,8 @@ __global__ __launch_bounds__(256) void scan_apply_kernel(uint32_t* __restrict__ 
         }
 }
 
-// The same in one launch for arrays of up to 8192 entries (pools of up to about 65 000 losses; above that the strided
-// per-thread loads cost more than the two launches saved): thread t of the one workgroup owns entries
+// The same in one launch for arrays of up to 8192 entries (block counts of pools of up to 2^24 losses; above that the
+// strided per-thread loads cost more than the two launches saved): thread t of the one workgroup owns entries
 // [t * per, (t + 1) * per), all loaded before anything else so that the loads overlap.
 #define SCAN_ONE_LAUNCH_MAX 8192
 __global__ __launch_bounds__(256) void scan_small_kernel(uint32_t* __restrict__ data, int n, int per, const SelInfo* __restrict__ info, int pass,
@@ -472,15 +678,6 @@ __global__ __launch_bounds__(256) void radix_scatter_kernel(const uint32_t* __re
     }
 }
 
-// Inverse of loss_key for every key that determines the float uniquely; NaN keys and the zero key
-// (shared by +0 and -0) do not, those values are fetched from the loss array.
-__device__ __forceinline__ bool key_to_loss(uint32_t key, float* v) {
-    if (key == 0xffffffffu || key == 0x80000000u) return false;
-    uint32_t u = (key & 0x80000000u) ? (key & 0x7fffffffu) : ~key;
-    *v = __uint_as_float(u);
-    return true;
-}
-
 // The sorted pairs sit in the first or the second pair of arrays, depending on the number of passes that ran.
 __global__ __launch_bounds__(256) void topk_emit_kernel(const uint32_t* __restrict__ keys_a, const uint32_t* __restrict__ idx_a,
                                                         const uint32_t* __restrict__ keys_b, const uint32_t* __restrict__ idx_b,
@@ -530,7 +727,8 @@ static TopkScratch carve_topk(Carver& c, int64_t N) {
 
 size_t topk_scratch_bytes(int64_t N, int64_t k) {
     (void)k;
-    if (N <= TOPK_LDS_MAX) return 0;
+    if (N <= TOPK_RANK_MAX) return 0;
+    if (N <= TOPK_SORT_MAX) return sort_scratch_bytes(N);
     Carver c(nullptr);
     carve_topk(c, N);
     return c.off;
@@ -581,24 +779,24 @@ static int launch_topk_large(bls_ctx* ctx, char* scratch_base, const float* loss
 }
 
 static int launch_topk_small(bls_ctx* ctx, const float* losses, int64_t N, int64_t k, int32_t* idx_out, float* val_out) {
-    int M = 2;
-    while (M < N) M <<= 1;
-    size_t lds = (size_t)M * sizeof(uint64_t);
-    if (lds > ctx->max_lds) return bls_fail(ctx, BLS_EUNSUPPORTED, "top-k needs %zu bytes of LDS, device allows %zu", lds, ctx->max_lds);
-    if (lds > 65536)
-        BLS_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(topk_lds_bitonic_kernel),
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    hipLaunchKernelGGL(topk_lds_bitonic_kernel, dim3(1), dim3(TOPK_THREADS), lds, ctx->stream, losses, (int)N, (int)k, M, idx_out,
-                       val_out);
+    const unsigned chunks = (unsigned)((N + 63) / 64);
+    const size_t words = chunks * 64 > 1024 ? chunks * 64 : 1024;   // the keys, and in their place 16 x 64 partial ranks
+    hipLaunchKernelGGL(topk_rank_kernel, dim3(chunks), dim3(1024), words * sizeof(uint32_t), ctx->stream, losses, (int)N, (int)k, idx_out, val_out);
     BLS_HIP(ctx, hipGetLastError());
     return BLS_OK;
 }
 
+// `scratch_base`: topk_scratch_bytes(N, k) bytes of device memory, 256-byte aligned
+static int launch_topk_at(bls_ctx* ctx, char* scratch_base, const float* losses, int64_t N, int64_t k, int32_t* idx_out, float* val_out) {
+    if (N <= TOPK_RANK_MAX) return launch_topk_small(ctx, losses, N, k, idx_out, val_out);
+    if (N <= TOPK_SORT_MAX) return launch_topk_medium(ctx, scratch_base, losses, N, k, idx_out, val_out);
+    return launch_topk_large(ctx, scratch_base, losses, N, k, idx_out, val_out);
+}
+
 int launch_topk(bls_ctx* ctx, const float* losses, int64_t N, int64_t k, int32_t* idx_out, float* val_out) {
-    if (N <= TOPK_LDS_MAX) return launch_topk_small(ctx, losses, N, k, idx_out, val_out);
     int rc = bls_arena_reserve(ctx, topk_scratch_bytes(N, k));
     if (rc != BLS_OK) return rc;
-    return launch_topk_large(ctx, ctx->arena, losses, N, k, idx_out, val_out);
+    return launch_topk_at(ctx, ctx->arena, losses, N, k, idx_out, val_out);
 }
 
 // ---- selection without any allocation -----------------------------------------------------------------
@@ -630,8 +828,8 @@ int topk_static_init(bls_ctx* ctx) {
 int launch_topk_static(bls_ctx* ctx, const float* losses, int64_t N, int64_t k, int32_t* idx_out, float* val_out) {
     if (N > BLS_TOPK_STATIC_MAX_N || topk_scratch_bytes(N, k) > TOPK_STATIC_BYTES)
         return bls_fail(ctx, BLS_EINVAL, "topk_by_loss_static: N = %lld exceeds the limit of %d", (long long)N, BLS_TOPK_STATIC_MAX_N);
-    if (N <= TOPK_LDS_MAX) return launch_topk_small(ctx, losses, N, k, idx_out, val_out);
+    if (N <= TOPK_RANK_MAX) return launch_topk_small(ctx, losses, N, k, idx_out, val_out);
     char* base = (ctx->device >= 0 && ctx->device < TOPK_STATIC_MAX_DEVICES) ? g_static_scratch[ctx->device] : nullptr;
     if (!base) return bls_fail(ctx, BLS_EUNSUPPORTED, "topk_by_loss_static: no static scratch on device %d", ctx->device);
-    return launch_topk_large(ctx, base, losses, N, k, idx_out, val_out);
+    return launch_topk_at(ctx, base, losses, N, k, idx_out, val_out);
 }

@@ -130,6 +130,24 @@ def test_topk_matches_oracle_large(env, kind, n):
 
 
 @pytest.mark.parametrize("kind", ["halfnormal", "ties16", "specials"])
+@pytest.mark.parametrize("n", [64, 65, 16383, 65536, 65537, 131073, 262144, 262145, 1 << 19, (1 << 19) + 1])
+def test_topk_at_the_edges_of_its_variants(env, kind, n):
+    # chunks of 64 and the last pool ranked by counting; 1, 2, 4 and 8 rounds per tile of the whole-pool sort, full and with a
+    # remainder of one; the first pool that is selected before it is sorted; from an address that is only 4-byte aligned
+    torch, bls, ctx = env
+    arr = synth.loss_array(kind, n)
+    d = torch.from_numpy(np.concatenate([np.zeros(1, np.float32), arr])).cuda()[1:]
+    ranked = oracle.topk_by_loss(arr, n)
+    for k in (1, n // 3, n):
+        idx = torch.full((k,), -1, dtype=torch.int32, device="cuda")
+        val = torch.zeros(k, dtype=torch.float32, device="cuda")
+        bls.topk_by_loss(ctx, d, k, idx, val)
+        ctx.synchronize()
+        np.testing.assert_array_equal(idx.cpu().numpy(), ranked[:k])
+        np.testing.assert_array_equal(val.cpu().numpy().view(np.uint32), arr[ranked[:k]].view(np.uint32))
+
+
+@pytest.mark.parametrize("kind", ["halfnormal", "ties16", "specials"])
 @pytest.mark.parametrize("n", [(1 << 22) + 5, 1 << 24])
 def test_topk_matches_oracle_very_large(env, kind, n):
     # the sizes the bandwidth figures are quoted on take the large-pool variants of the sort kernels
