@@ -198,7 +198,7 @@ def main():
                 "vs_baseline": None, "dtype": "f32", "data": "synthetic",
                 "config": {"workload": args.workload, "pool": N, "k": k, "batch": B, "tau": tau, "P": P, "d": int(d)}, "finite": finite,
                 "phase_ms_per_step": phases,
-                "roofline": {"bound": "mfma", "kernel": "gemm16_kernel (fully connected layer: forward and weight gradient)",
+                "roofline": {"bound": "mfma", "kernel": "mlp_fc1_kernel + mlp_update_kernel (fully connected layer: forward, weight gradient and update)",
                              "achieved": round(achieved, 3), "peak": FP32_MFMA_PEAK_TFLOPS, "unit": "TFLOP/s",
                              "frac": round(achieved / FP32_MFMA_PEAK_TFLOPS, 5), "traffic": None, "avg_launch_us": round(1e3 * ms / cnt, 2),
                              "launches_per_step": cnt // args.steps,

@@ -62,11 +62,6 @@ void launch_gather_images_reps(hipStream_t s, const float* src, const int32_t* y
                                          c_src, c_dst, (T*)dst, y_dst, reps.stride));
 }
 
-void launch_gather_rows(hipStream_t s, const float* src, const int32_t* y_src, const int32_t* sel, int64_t k,
-                        int64_t start, int batch, int64_t row, float* dst, int32_t* y_dst) {
-    launch_gather_images(s, src, y_src, sel, k, start, 0, batch, 1, (int)row, (int)row, ACT_F32, dst, y_dst);
-}
-
 // SGD with momentum and coupled weight decay: g += wd*x; buf = mu*buf + g; x -= lr*buf.
 __global__ __launch_bounds__(256) void sgd_kernel(float* __restrict__ params, float* __restrict__ momentum,
                                                   const float* __restrict__ grad, int64_t d, float lr, float mu, float wd) {
@@ -85,18 +80,6 @@ void launch_sgd(hipStream_t s, float* params, float* momentum, const float* grad
     int64_t blocks = (d + 255) / 256;
     if (blocks > 2048) blocks = 2048;
     hipLaunchKernelGGL(sgd_kernel, dim3((unsigned)blocks), dim3(256), 0, s, params, momentum, grad, d, lr, mu, wd);
-}
-
-__global__ __launch_bounds__(256) void colsum_kernel(const float* __restrict__ in, int rows, int cols, float* __restrict__ out) {
-    int n = blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= cols) return;
-    float acc = 0.f;
-    for (int b = 0; b < rows; ++b) acc += in[(int64_t)b * cols + n];
-    out[n] = acc;
-}
-
-void launch_colsum(hipStream_t s, const float* in, int rows, int cols, float* out) {
-    hipLaunchKernelGGL(colsum_kernel, dim3((cols + 255) / 256), dim3(256), 0, s, in, rows, cols, out);
 }
 
 __global__ __launch_bounds__(256) void fill_zero_kernel(float* p, int64_t n, int64_t rstride) {

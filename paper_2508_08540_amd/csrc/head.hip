@@ -15,12 +15,15 @@ __device__ __forceinline__ float wave_sum(float v) {
 // features stay in registers; F % 4 == 0.  Four waves per sample (a single one leaves the compute unit nearly empty and
 // spends its time waiting for one load after another): wave w pools positions w, w + 4, ..., takes classes w, w + 4, ...
 // and, for the feature gradient, sums over those classes; the partial results meet in LDS and are added in wave order.
-template <int PQ, typename T>
+// MLP: the rows pooled are the partial sums of a fully connected layer, whose bias and ReLU are applied here, and the labels
+// are read through the batch's selection list (a launch each for sum, bias and ReLU, and for a copy of the labels, otherwise).
+template <int PQ, typename T, bool MLP>
 __global__ __launch_bounds__(256) void head_forward_kernel(const T* __restrict__ act, int positions, int F,
                                                                const float* __restrict__ W, const float* __restrict__ bias,
                                                                int C, const int32_t* __restrict__ y, float* __restrict__ loss,
                                                                float* __restrict__ feat, float* __restrict__ dlogits,
-                                                               float* __restrict__ dfeat, float grad_scale, int relu_mask, int64_t rstride) {
+                                                               float* __restrict__ dfeat, float grad_scale, int relu_mask, int64_t rstride,
+                                                               const float* __restrict__ pre_bias, BatchRows rows) {
     if (rstride) {   // one replica of several: every buffer sits blockIdx.z slots further
         const int64_t ro = (int64_t)blockIdx.z * rstride;
         act = rep_at(act, ro); W = rep_at(W, ro); bias = rep_at(bias, ro); y = rep_at(y, ro); loss = rep_at(loss, ro); feat = rep_at(feat, ro);
@@ -30,7 +33,7 @@ __global__ __launch_bounds__(256) void head_forward_kernel(const T* __restrict__
     __shared__ __attribute__((aligned(16))) float fs[256 * PQ];        // pooled features
     __shared__ float zs[HEAD_MAX_C];
     const int b = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const float inv_pos = 1.f / (float)positions;
+    const float inv_pos = MLP ? 1.f : 1.f / (float)positions;
     const T* a = act + (int64_t)b * positions * F;
 #pragma unroll
     for (int i = 0; i < PQ; ++i) {
@@ -48,8 +51,12 @@ __global__ __launch_bounds__(256) void head_forward_kernel(const T* __restrict__
     }
     __syncthreads();
     for (int c = 4 * threadIdx.x; c < F; c += 1024) {
-        const f32x4 v = ((*reinterpret_cast<const f32x4*>(&part[0][c]) + *reinterpret_cast<const f32x4*>(&part[1][c])) +
-                         (*reinterpret_cast<const f32x4*>(&part[2][c]) + *reinterpret_cast<const f32x4*>(&part[3][c]))) * inv_pos;
+        f32x4 v = ((*reinterpret_cast<const f32x4*>(&part[0][c]) + *reinterpret_cast<const f32x4*>(&part[1][c])) +
+                   (*reinterpret_cast<const f32x4*>(&part[2][c]) + *reinterpret_cast<const f32x4*>(&part[3][c]))) * inv_pos;
+        if (MLP) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[j] = relu_keep_nan(v[j] + pre_bias[c + j]);
+        }
         *reinterpret_cast<f32x4*>(&fs[c]) = v;
         if (feat) *reinterpret_cast<f32x4*>(feat + (int64_t)b * F + c) = v;
     }
@@ -86,7 +93,7 @@ __global__ __launch_bounds__(256) void head_forward_kernel(const T* __restrict__
 #pragma unroll
     for (int h = 0; h < 2; ++h) ex[h] = lane + 64 * h < C ? expf(z_mine[h] - m) : 0.f;
     const float sum = wave_sum(ex[0]) + wave_sum(ex[1]);
-    const int label = y[b];
+    const int label = MLP ? y[pool_row(rows, b)] : y[b];
     const float z_label = __shfl(label < 64 ? z_mine[0] : z_mine[1], label & 63, 64);
     if (threadIdx.x == 0) loss[b] = (m + logf(sum)) - z_label;
     if (!dlogits) return;
@@ -130,9 +137,21 @@ void launch_head_forward(hipStream_t s, int act_type, const void* act, int B, in
                          int C, const int32_t* y, float* loss, float* feat, float* dlogits, float* dfeat,
                          float grad_scale, bool relu_mask, Reps reps) {
 #define HEAD_LAUNCH(PQ)                                                                                                     \
-    ACT_DISPATCH(act_type, hipLaunchKernelGGL((head_forward_kernel<PQ, T>), dim3(B, 1, reps.n), dim3(256), 0, s, (const T*)act, positions, F, W, \
-                                              bias, C, y, loss, feat, dlogits, dfeat, grad_scale, relu_mask ? 1 : 0, reps.stride))
+    ACT_DISPATCH(act_type, hipLaunchKernelGGL((head_forward_kernel<PQ, T, false>), dim3(B, 1, reps.n), dim3(256), 0, s, (const T*)act, positions, F, W, \
+                                              bias, C, y, loss, feat, dlogits, dfeat, grad_scale, relu_mask ? 1 : 0, reps.stride, nullptr, BatchRows{}))
     const int quads = (F / 4 + 63) / 64;   // F is a multiple of 16, at most 1024
+    if (quads <= 1) HEAD_LAUNCH(1);
+    else if (quads <= 2) HEAD_LAUNCH(2);
+    else HEAD_LAUNCH(4);
+#undef HEAD_LAUNCH
+}
+
+void launch_head_mlp(hipStream_t s, const float* part, int B, int splits, int F, const float* pre_bias, const float* W, const float* bias, int C,
+                     const int32_t* y, const BatchRows& rows, float* loss, float* feat, float* dlogits, float* dfeat, float grad_scale) {
+#define HEAD_LAUNCH(PQ)                                                                                                            \
+    hipLaunchKernelGGL((head_forward_kernel<PQ, float, true>), dim3(B), dim3(256), 0, s, part, splits, F, W, bias, C, y, loss, feat, dlogits, dfeat, \
+                       grad_scale, 1, 0, pre_bias, rows)
+    const int quads = (F / 4 + 63) / 64;
     if (quads <= 1) HEAD_LAUNCH(1);
     else if (quads <= 2) HEAD_LAUNCH(2);
     else HEAD_LAUNCH(4);

@@ -5,6 +5,8 @@
 #include <hip/hip_ext.h>
 #include <stdint.h>
 
+#include "../../include/bls.h"
+
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // Storage type of activations in the launchers below (pointers to activations are void*).
@@ -103,10 +105,6 @@ struct KernelTiming {
 };
 
 // ---- elementwise.hip ----------------------------------------------------------------------------
-// dst[b][0..row) = src[idx[(start + b) % k]][0..row_src) zero-padded to `row` floats per `group`:
-// each source row is `row_src/group_src`... see gather_rows for the image variant.
-void launch_gather_rows(hipStream_t s, const float* src, const int32_t* y_src, const int32_t* sel, int64_t k,
-                        int64_t start, int batch, int64_t row, float* dst, int32_t* y_dst);
 // Images float [n][pixels][c_src] -> storage type `act` [batch][pixels][c_dst] with zero-filled extra channels; sel == nullptr copies
 // images first .. first+batch-1, otherwise image b is sel[(start + b) % k].
 void launch_gather_images(hipStream_t s, const float* src, const int32_t* y_src, const int32_t* sel, int64_t k,
@@ -117,17 +115,26 @@ void launch_gather_images_reps(hipStream_t s, const float* src, const int32_t* y
                                int pixels, int c_src, int c_dst, int act, void* dst, int32_t* y_dst, Reps reps);
 void launch_sgd(hipStream_t s, float* params, float* momentum, const float* grad, int64_t d, float lr, float mu,
                 float wd);
-// out[n] = sum_b in[b][n]
-void launch_colsum(hipStream_t s, const float* in, int rows, int cols, float* out);
 void launch_fill_zero(hipStream_t s, float* p, int64_t n, Reps reps = Reps{});
 
-// ---- gemm.hip ---------------------------------------------------------------------------------------
-// C[m][n] = sum_k A(m,k) * B(n,k); A(m,k) = a_kmajor ? A[k*lda+m] : A[m*lda+k], likewise B.
-// Split over `splits` K-ranges into part[splits][M][N], then reduced in split order into out with
-// optional bias[n] add, ReLU, and multiplication by (mask[m][n] > 0).
-size_t gemm_partial_floats(int M, int N, int splits);
-void launch_gemm(hipStream_t s, const float* A, int lda, bool a_kmajor, const float* B, int ldb, bool b_kmajor, int M,
-                 int N, int K, int splits, float* part, float* out, const float* bias, bool relu, const float* mask);
+// ---- mlp.hip ----------------------------------------------------------------------------------------
+// Rows of a batch in the pool: sample b is row sel[(start + b) % k], or row b without a selection list.
+struct BatchRows {
+    const int32_t* sel;
+    int64_t k, start;
+};
+__device__ __forceinline__ int64_t pool_row(const BatchRows& rows, int b) { return rows.sel ? (int64_t)rows.sel[(rows.start + b) % rows.k] : b; }
+// Positions of the tensors in the parameter vector
+struct MlpOffsets {
+    int64_t fc1_w, fc1_b, fc2_w, fc2_b;
+};
+#define MLP_SPLITS 8
+// part[b][z][h], z < MLP_SPLITS: partial sums of x W^T; hid is a multiple of 16
+void launch_mlp_fc1(hipStream_t s, const float* x, const BatchRows& rows, const float* W, int B, int hid, int K, float* part);
+// Gradients from h [B][hid], dlogits [B][C], dpre [B][hid] (gradient before the ReLU) and the batch, and the SGD step of every
+// parameter: g += wd*x; buf = mu*buf + g; x -= lr*buf.
+void launch_mlp_update(hipStream_t s, float* params, float* momentum, const MlpOffsets& off, const float* x, const BatchRows& rows, const float* h,
+                       const float* dlogits, const float* dpre, int B, int hid, int C, int K, const bls_sgd& opt);
 
 // ---- head.hip ---------------------------------------------------------------------------------------
 // One wave per sample: feature = mean over `positions` of act[b][p][F] (storage type act_type); logits = W feature + bias;
@@ -137,6 +144,10 @@ void launch_gemm(hipStream_t s, const float* A, int lda, bool a_kmajor, const fl
 void launch_head_forward(hipStream_t s, int act_type, const void* act, int B, int positions, int F, const float* W, const float* bias,
                          int C, const int32_t* y, float* loss, float* feat, float* dlogits, float* dfeat,
                          float grad_scale, bool relu_mask, Reps reps = Reps{});
+// The same behind a fully connected layer given by its partial sums: feature = relu(sum over z < splits of part[b][z][F] +
+// pre_bias), labels y[pool_row(rows, b)], gradient masked by feature > 0.
+void launch_head_mlp(hipStream_t s, const float* part, int B, int splits, int F, const float* pre_bias, const float* W, const float* bias, int C,
+                     const int32_t* y, const BatchRows& rows, float* loss, float* feat, float* dlogits, float* dfeat, float grad_scale);
 // dW[c][f] = sum_b dlogits[b][c] feat[b][f]; db[c] = sum_b dlogits[b][c]
 void launch_head_wgrad(hipStream_t s, const float* dlogits, const float* feat, int B, int C, int F, float* dW, float* db, Reps reps = Reps{});
 

@@ -1,0 +1,182 @@
+// The two-layer perceptron: its first layer forward, and the end of a training step (all gradients and the update).
+//
+// A step of 64 samples moves about 9 MB and computes 100 Mflop: every launch is latency, a chain of loads of about 1 us each.
+// The step therefore takes three launches (first layer, head, gradients + update).  The batch is never copied: rows of the pool
+// are read through the selection list.  The first layer's partial sums are added by the head (which pools `positions` rows
+// per sample anyway), and a gradient goes from the accumulators straight into the momentum and the parameter.
+// Pass of 4 steps of 64 with 128 hidden units and a pool of 256: 272 -> 97 us (of nine launches a step before).
+#include "kernels.h"
+
+// Four consecutive floats of a row of `cols`, from column c; past the end, or without 16-byte alignment, element by element.
+__device__ __forceinline__ f32x4 load_cols4(const float* __restrict__ row, int c, int cols, bool vec) {
+    if (vec && c + 3 < cols) return *reinterpret_cast<const f32x4*>(row + c);
+    f32x4 v;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = c + j < cols ? row[c + j] : 0.f;
+    return v;
+}
+
+// part[b][z][h] = sum over the z-th part of the inputs of x[row b][i] W[h][i].  A workgroup owns 16 samples x 16 hidden units and
+// one part; its four waves take a quarter of the part each and meet in LDS.  Lane l supplies row l % 16 of both factors and, in a
+// step of 16 inputs, inputs 4 (l / 16) .. + 3, so that both are 16-byte loads.  The loads of six steps are in flight together
+// (3072 inputs over 32 waves are six steps: one round trip to memory).
+__global__ __launch_bounds__(256) void mlp_fc1_kernel(const float* __restrict__ x, BatchRows rows, const float* __restrict__ W, int B, int hid, int K,
+                                                      int k_wave, float* __restrict__ part, int x_vec, int w_vec) {
+    constexpr int STEPS = 6;
+    __shared__ f32x4 red[4][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane & 15, g = lane >> 4;
+    const int m0 = blockIdx.x * 16, n0 = blockIdx.y * 16;
+    const int k_begin = (blockIdx.z * 4 + wave) * k_wave, k_end = min(K, k_begin + k_wave);
+    const int m = min(m0 + r, B - 1);   // rows past the batch repeat its last one and are not stored
+    const float* xr = x + pool_row(rows, m) * K;
+    const float* wr = W + (int64_t)(n0 + r) * K;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int k0 = k_begin; k0 < k_end; k0 += 16 * STEPS) {
+        f32x4 a[STEPS], b[STEPS];
+        if (x_vec && w_vec && k0 + 16 * STEPS <= k_end) {
+#pragma unroll
+            for (int u = 0; u < STEPS; ++u) {
+                a[u] = *reinterpret_cast<const f32x4*>(xr + k0 + 16 * u + 4 * g);
+                b[u] = *reinterpret_cast<const f32x4*>(wr + k0 + 16 * u + 4 * g);
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < STEPS; ++u) {
+                a[u] = load_cols4(xr, k0 + 16 * u + 4 * g, k_end, x_vec != 0);
+                b[u] = load_cols4(wr, k0 + 16 * u + 4 * g, k_end, w_vec != 0);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < STEPS; ++u)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][j], b[u][j], acc, 0, 0, 0);
+    }
+    red[wave][lane] = acc;
+    __syncthreads();
+    if (wave != 0) return;
+    const f32x4 sum = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
+    // lane holds samples m0 + 4 g + i, hidden unit n0 + r
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        if (m0 + 4 * g + i < B) part[((int64_t)(m0 + 4 * g + i) * gridDim.z + blockIdx.z) * hid + n0 + r] = sum[i];
+}
+
+void launch_mlp_fc1(hipStream_t s, const float* x, const BatchRows& rows, const float* W, int B, int hid, int K, float* part) {
+    const int k_wave = ((K + 4 * MLP_SPLITS - 1) / (4 * MLP_SPLITS) + 15) / 16 * 16;
+    const int x_vec = K % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0, w_vec = K % 4 == 0 && reinterpret_cast<uintptr_t>(W) % 16 == 0;
+    hipLaunchKernelGGL(mlp_fc1_kernel, dim3((B + 15) / 16, hid / 16, MLP_SPLITS), dim3(256), 0, s, x, rows, W, B, hid, K, k_wave, part, x_vec, w_vec);
+}
+
+__device__ __forceinline__ void sgd_one(float& p, float& m, float grad, const bls_sgd& o) {
+    const float buf = __fmaf_rn(o.momentum, m, __fmaf_rn(o.weight_decay, p, grad));
+    m = buf;
+    p = __fmaf_rn(-o.lr, buf, p);
+}
+
+// Gradients and update of every parameter, by workgroups of three kinds in one launch:
+//   the second layer: 64 weights of one class (and, from the first 64, its bias), four slices of the batch folded through LDS;
+//   the first layer's bias: 64 hidden units, likewise;
+//   the first layer's weights: 16 hidden units x 256 inputs, a wave 16 x 64: lane l supplies hidden unit l % 16 and inputs
+//   4 (l % 16) .. + 3 of samples 4 (l / 16) + j, one 16-byte load of x for four products, and owns four rows of four neighbouring
+//   weights, which it updates with 16-byte accesses.  Two steps (32 samples) of loads are in flight together.
+// The small kinds come first: they are the longer chains.
+__global__ __launch_bounds__(256) void mlp_update_kernel(float* __restrict__ params, float* __restrict__ momentum, MlpOffsets off,
+                                                         const float* __restrict__ x, BatchRows rows, const float* __restrict__ h,
+                                                         const float* __restrict__ dlogits, const float* __restrict__ dpre, int B, int hid, int C,
+                                                         int K, bls_sgd opt, int x_vec, int p_vec) {
+    __shared__ float red[4][64];
+    __shared__ int64_t at[256];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int f_blocks = (hid + 63) / 64;
+    int blk = blockIdx.x;
+    if (blk < (C + 1) * f_blocks) {
+        const int c = blk / f_blocks, f = (blk - c * f_blocks) * 64 + lane;
+        float acc = 0.f;
+        if (c < C) {
+            if (f < hid) {
+#pragma unroll 8
+                for (int b = wave; b < B; b += 4) acc = __fmaf_rn(dlogits[(int64_t)b * C + c], h[(int64_t)b * hid + f], acc);
+            }
+        } else if (f < hid) {
+#pragma unroll 8
+            for (int b = wave; b < B; b += 4) acc += dpre[(int64_t)b * hid + f];
+        }
+        red[wave][lane] = acc;
+        __syncthreads();
+        if (wave == 0 && f < hid) {
+            const int64_t o = c < C ? off.fc2_w + (int64_t)c * hid + f : off.fc1_b + f;
+            sgd_one(params[o], momentum[o], (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]), opt);
+        }
+        if (c < C && blk == c * f_blocks && wave == 1) {
+            float sum = 0.f;
+            for (int b = lane; b < B; b += 64) sum += dlogits[(int64_t)b * C + c];
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+            if (lane == 0) sgd_one(params[off.fc2_b + c], momentum[off.fc2_b + c], sum, opt);
+        }
+        return;
+    }
+    blk -= (C + 1) * f_blocks;
+    const int r = lane & 15, g = lane >> 4;
+    const int n_blocks = (K + 255) / 256;
+    const int m0 = (blk / n_blocks) * 16, n = (blk % n_blocks) * 256 + wave * 64 + 4 * r;
+    const int nn = n < K ? n : 0;   // a lane past the last input reads the first ones and stores nothing
+    f32x4 acc[4] = {};
+    for (int b0 = 0; b0 < B; b0 += 256) {
+        __syncthreads();
+        at[tid] = pool_row(rows, min(b0 + tid, B - 1));
+        __syncthreads();
+        const int b_end = min(B, b0 + 256);
+        for (int k0 = b0; k0 < b_end; k0 += 32) {
+            float a[8];
+            f32x4 v[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const int b = min(k0 + 16 * (j >> 2) + 4 * g + (j & 3), b_end - 1);
+                a[j] = dpre[(int64_t)b * hid + m0 + r];
+                const float* row = x + at[b - b0] * K;
+                if (x_vec) v[j] = *reinterpret_cast<const f32x4*>(row + nn);
+                else v[j] = load_cols4(row, nn, K, false);
+            }
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const bool ok = k0 + 16 * (j >> 2) + 4 * g + (j & 3) < b_end;   // samples past the batch: zero factors
+                const float aj = ok ? a[j] : 0.f;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) acc[q] = __builtin_amdgcn_mfma_f32_16x16x4f32(aj, ok ? v[j][q] : 0.f, acc[q], 0, 0, 0);
+            }
+        }
+    }
+    if (n >= K) return;
+    // lane holds hidden units m0 + 4 g + i, inputs n .. n + 3
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        float* p = params + off.fc1_w + (int64_t)(m0 + 4 * g + i) * K + n;
+        float* m = momentum + off.fc1_w + (int64_t)(m0 + 4 * g + i) * K + n;
+        if (p_vec) {
+            f32x4 pv = *reinterpret_cast<const f32x4*>(p), mv = *reinterpret_cast<const f32x4*>(m);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                float ps = pv[q], ms = mv[q];
+                sgd_one(ps, ms, acc[q][i], opt);
+                pv[q] = ps;
+                mv[q] = ms;
+            }
+            *reinterpret_cast<f32x4*>(p) = pv;
+            *reinterpret_cast<f32x4*>(m) = mv;
+        } else {
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (n + q < K) sgd_one(p[q], m[q], acc[q][i], opt);
+        }
+    }
+}
+
+void launch_mlp_update(hipStream_t s, float* params, float* momentum, const MlpOffsets& off, const float* x, const BatchRows& rows, const float* h,
+                       const float* dlogits, const float* dpre, int B, int hid, int C, int K, const bls_sgd& opt) {
+    const int x_vec = K % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0;
+    const int p_vec = K % 4 == 0 && (reinterpret_cast<uintptr_t>(params + off.fc1_w) | reinterpret_cast<uintptr_t>(momentum + off.fc1_w)) % 16 == 0;
+    const unsigned blocks = (unsigned)((C + 1) * ((hid + 63) / 64) + (hid / 16) * ((K + 255) / 256));
+    hipLaunchKernelGGL(mlp_update_kernel, dim3(blocks), dim3(256), 0, s, params, momentum, off, x, rows, h, dlogits, dpre, B, hid, C, K, opt, x_vec,
+                       p_vec);
+}

@@ -25,7 +25,6 @@ namespace {
 constexpr int PAD_C = 16;       // the stem's input is zero-padded to 16 channels so it runs on the same kernels
 constexpr int SCORE_CHUNK = 2048;
 constexpr int FUSED_BWD_MIN_C = 16;   // channel count from which the batch-norm backward rides in the input gradient's staging
-constexpr int MLP_SPLITS = 8;
 
 int64_t max64(int64_t a, int64_t b) { return a > b ? a : b; }
 
@@ -44,29 +43,20 @@ typedef uint8_t act_t;  // activations are addressed as bytes; the model's stora
 // ---- MLP ----------------------------------------------------------------------------------------
 
 struct MlpScratch {
-    float *xb, *h, *part, *loss, *dlogits, *dpre, *grad;
-    int32_t* yb;
+    float *part, *h, *loss, *dlogits, *dpre;
 };
 
 MlpScratch carve_mlp(Carver& c, const bls_model* m, int B, bool train) {
     MlpScratch s{};
     const int hid = m->desc.hidden;
-    s.h = c.take<float>((size_t)B * hid);
-    s.part = c.take<float>(max64(gemm_partial_floats(B, hid, MLP_SPLITS), train ? gemm_partial_floats(hid, m->d_in, 1) : 0));
+    s.part = c.take<float>((size_t)B * MLP_SPLITS * hid);
     s.loss = c.take<float>(B);
     if (train) {
-        s.xb = c.take<float>((size_t)B * m->d_in);
-        s.yb = c.take<int32_t>(B);
+        s.h = c.take<float>((size_t)B * hid);
         s.dlogits = c.take<float>((size_t)B * m->desc.classes);
         s.dpre = c.take<float>((size_t)B * hid);
-        s.grad = c.take<float>(m->num_params);
     }
     return s;
-}
-
-void mlp_hidden(bls_ctx* ctx, hipStream_t st, const bls_model* m, const float* params, const float* x, int B, const MlpScratch& s) {
-    PROF(ctx, PROF_GEMM, launch_gemm(st, x, m->d_in, false, params + m->fc1_w, m->d_in, false, B, m->desc.hidden, m->d_in, MLP_SPLITS, s.part,
-                s.h, params + m->fc1_b, true, nullptr));
 }
 
 // ---- residual network ---------------------------------------------------------------------------------
@@ -505,9 +495,10 @@ int net_score(bls_ctx* ctx, const bls_model* m, const float* params, const float
         MlpScratch s = carve_mlp(c, m, chunk, false);
         for (int64_t first = 0; first < N; first += chunk) {
             int B = (int)(N - first < chunk ? N - first : chunk);
-            mlp_hidden(ctx, st, m, params, x + first * m->d_in, B, s);
-            PROF(ctx, PROF_HEAD, launch_head_forward(st, ACT_F32, s.h, B, 1, m->desc.hidden, params + m->fc2_w, params + m->fc2_b, m->desc.classes,
-                                y + first, losses_out + first, nullptr, nullptr, nullptr, 0.f, false));
+            const BatchRows rows{nullptr, 0, 0};
+            PROF(ctx, PROF_GEMM, launch_mlp_fc1(st, x + first * m->d_in, rows, params + m->fc1_w, B, m->desc.hidden, m->d_in, s.part));
+            PROF(ctx, PROF_HEAD, launch_head_mlp(st, s.part, B, MLP_SPLITS, m->desc.hidden, params + m->fc1_b, params + m->fc2_w, params + m->fc2_b,
+                                m->desc.classes, y + first, rows, losses_out + first, nullptr, nullptr, nullptr, 0.f));
         }
     } else {
         ResScratch s = carve_resnet(c, m, chunk, false);
@@ -537,17 +528,14 @@ int net_local_step(bls_ctx* ctx, const bls_model* m, float* params, float* buffe
         const float inv_b = 1.f / (float)B;
         MlpScratch s = carve_mlp(c, m, B, true);
         const int hid = m->desc.hidden, C = m->desc.classes;
+        const MlpOffsets off{m->fc1_w, m->fc1_b, m->fc2_w, m->fc2_b};
         for (int64_t j = 0; j < tau; ++j) {
             float* loss = step_losses_out ? step_losses_out + j * B : s.loss;
-            PROF(ctx, PROF_GATHER, launch_gather_rows(st, x_pool, y_pool, sel, k, j * B, B, m->d_in, s.xb, s.yb));
-            mlp_hidden(ctx, st, m, params, s.xb, B, s);
-            PROF(ctx, PROF_HEAD, launch_head_forward(st, ACT_F32, s.h, B, 1, hid, params + m->fc2_w, params + m->fc2_b, C, s.yb, loss, nullptr, s.dlogits,
-                                s.dpre, inv_b, true));
-            PROF(ctx, PROF_HEAD, launch_head_wgrad(st, s.dlogits, s.h, B, C, hid, s.grad + m->fc2_w, s.grad + m->fc2_b));
-            PROF(ctx, PROF_GEMM, launch_gemm(st, s.dpre, hid, true, s.xb, m->d_in, true, hid, m->d_in, B, 1, s.part, s.grad + m->fc1_w, nullptr,
-                        false, nullptr));
-            PROF(ctx, PROF_UPDATE, launch_colsum(st, s.dpre, B, hid, s.grad + m->fc1_b));
-            PROF(ctx, PROF_UPDATE, launch_sgd(st, params, momentum, s.grad, m->num_params, opt.lr, opt.momentum, opt.weight_decay));
+            const BatchRows rows{sel, k, j * B};
+            PROF(ctx, PROF_GEMM, launch_mlp_fc1(st, x_pool, rows, params + m->fc1_w, B, hid, m->d_in, s.part));
+            PROF(ctx, PROF_HEAD, launch_head_mlp(st, s.part, B, MLP_SPLITS, hid, params + m->fc1_b, params + m->fc2_w, params + m->fc2_b, C, y_pool,
+                                rows, loss, s.h, s.dlogits, s.dpre, inv_b));
+            PROF(ctx, PROF_GEMM, launch_mlp_update(st, params, momentum, off, x_pool, rows, s.h, s.dlogits, s.dpre, B, hid, C, m->d_in, opt));
         }
     } else {
         ResScratch s = carve_resnet(c, m, B, true);

@@ -93,3 +93,33 @@ def test_noops_and_errors(h, data):
         h.local_step(p, {}, _zeros(p), x, y, np.arange(4), 0, 1, lr=0.1)
     with pytest.raises(h.bls.BlsError):
         h.local_step(p, {}, _zeros(p), x, y, np.arange(4), 2, 1, lr=float("nan"))
+
+
+@pytest.mark.parametrize("hw,channels,hidden,classes,batch", [
+    (5, 3, 16, 2, 1),        # 75 inputs: no 16-byte loads, fewer inputs than one step of all waves; one sample
+    (9, 3, 80, 64, 17),     # 243 inputs: one past a 16 x 16 tile of samples, hidden units past a block of 64, most classes
+    (16, 1, 272, 10, 33),    # 256 inputs: one workgroup of columns, filled; two feature quads per lane
+    (18, 1, 1024, 3, 16),    # 324 inputs: a second workgroup of columns, nearly empty; the largest hidden layer
+    (8, 2, 48, 7, 257),      # a second block of 256 samples in the weight gradient, with one sample
+])
+def test_gradients_and_update_at_the_edges_of_the_kernels(hw, channels, hidden, classes, batch):
+    import torch
+    import paper_2508_08540_amd as bls
+    ctx = bls.Context(0)
+    try:
+        h = Harness(torch, bls, ctx, bls.Model.mlp(hw, channels, hidden, classes), oracle.MLP())
+        x, y = synth.image_pool(3, 40, classes, hw=hw, channels=channels)
+        p = synth.mlp_init(3, hw * hw * channels, hidden, classes)
+        assert_losses_close(h.score(p, {}, x, y), oracle.score_losses(h.oracle_model, p, {}, x, y))
+        sel = np.arange(37, 3, -1, dtype=np.int32)      # shorter than the largest batch: it wraps inside one batch
+        mom0 = {k: 0.01 * synth.normal(5, i, v.size).reshape(v.shape) for i, (k, v) in enumerate(p.items())}
+        rp, _, rm, rl = oracle.local_step(h.oracle_model, p, {}, mom0, x, y, sel, batch, 1, 0.05, momentum=0.9, weight_decay=1e-2)
+        gp, _, gm, gl = h.local_step(p, {}, mom0, x, y, sel, batch, 1, lr=0.05, mu=0.9, wd=1e-2)
+        assert_losses_close(gl, rl)
+        # momentum = 0.9 * initial + gradient: sums of at most 257 products in fp32, as in the gradient test above
+        assert_tensors_close(gm, rm, 1e-4, "momentum")
+        # relative to the change itself, which the fp32 parameter quantises to 2^-24 of its size: |p| / |change| < 200 here
+        delta = lambda a: {k: a[k] - p[k].astype(np.float64) for k in p}
+        assert_tensors_close(delta(gp), delta(rp), 3e-4, "parameter change")
+    finally:
+        ctx.close()
