@@ -14,7 +14,7 @@
 #include "common.h"
 
 // Ranking by counting needs no scratch and costs 24.6 us at 16384 (four sorting passes: 22 us at 16385); sorting a pool of
-// 2^19 whole takes 73 us for any k, selecting first 98 (k = N / 50) to 120 us (k = N); at 2^20 about 117 against 105 to 153 us.
+// 2^19 whole takes 73 us for any k, selecting first 98 (k = N / 50) to 120 us (k = N); at 2^20 about 117 against 93 to 116 us.
 #define TOPK_RANK_MAX 16384
 #define TOPK_SORT_MAX (1 << 19)
 
@@ -269,7 +269,7 @@ static int launch_topk_medium(bls_ctx* ctx, char* scratch_base, const float* los
 //    holds it, a second histogram of the next 11 bits over the members of b1 gives the 22-bit prefix `thr`: the M
 //    elements with key >> 10 >= thr are selected (M >= k; the excess is at most the members of one 22-bit prefix).
 //    Histograms are aggregated per wave before they touch LDS (losses crowd into a few exponent bins).
-// 2. The selected elements are compacted, in index order, into (sort key, index) arrays; the sort key is hi - key
+// 2. The selected elements are compacted, in index order, into (sort key, index) pairs; the sort key is hi - key
 //    (hi bounds every key), so that ascending order is rank order and the keys only span the range that occurs.
 // 3. Stable LSD radix sort of the M pairs, 8 bits per pass, with as many passes as that range needs (the later passes
 //    exit at once).  Stability keeps equal losses in ascending index order, which is the tie rule.
@@ -316,12 +316,15 @@ __device__ __forceinline__ void load_keys4(const float* __restrict__ losses, int
 // LEVEL 1: bins of key >> 21 over all elements.  Losses crowd into a handful of exponent bins, so every bin has
 // SUB counters in LDS and a lane adds to counter lane % SUB: the lanes of a wave that meet in one bin spread over SUB
 // addresses.  LEVEL 2: bins of (key >> 10) & 2047 over the members of info->bin only (those bits are spread evenly).
+// 1024 threads per histogram: the loop waits for memory (256 threads, two to eight workgroups per unit: 25 + 29 us at 2^24
+// keys, now 15 + 19), while every further histogram costs a clear and a fold of 2048 bins.
+#define HIST_THREADS 1024
 template <int LEVEL, bool VEC>
-__global__ __launch_bounds__(256) void sel_hist_kernel(const float* __restrict__ losses, int64_t N, const SelInfo* __restrict__ info,
+__global__ __launch_bounds__(HIST_THREADS) void sel_hist_kernel(const float* __restrict__ losses, int64_t N, const SelInfo* __restrict__ info,
                                                        uint32_t* __restrict__ hist) {
     constexpr int SUB = LEVEL == 1 ? 8 : 1;
     __shared__ uint32_t h[SEL_BINS * SUB];
-    for (int i = threadIdx.x; i < SEL_BINS * SUB; i += 256) h[i] = 0u;
+    for (int i = threadIdx.x; i < SEL_BINS * SUB; i += HIST_THREADS) h[i] = 0u;
     __syncthreads();
     const uint32_t b1 = LEVEL == 2 ? info->bin : 0u;
     const uint32_t sub = threadIdx.x & (SUB - 1);
@@ -343,7 +346,7 @@ __global__ __launch_bounds__(256) void sel_hist_kernel(const float* __restrict__
             }
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < SEL_BINS; i += 256) {
+    for (int i = threadIdx.x; i < SEL_BINS; i += HIST_THREADS) {
         uint32_t c = 0;
 #pragma unroll
         for (int u = 0; u < SUB; ++u) c += h[i * SUB + u];
@@ -448,24 +451,25 @@ __global__ __launch_bounds__(256) void sel_count_kernel(const float* __restrict_
     if (threadIdx.x == 0) counts[blockIdx.x] = total;
 }
 
-// counts has been exclusive-scanned into offsets
+// counts has been exclusive-scanned into offsets.  The selected pairs of a tile are gathered in LDS and stored side by side: from
+// the threads' own eight elements every store would go to 64 places (16 M keys, 4 M
+// selected: 29 -> 19 us).
 template <bool VEC>
 __global__ __launch_bounds__(256) void sel_compact_kernel(const float* __restrict__ losses, int64_t N, const SelInfo* __restrict__ info,
-                                                          const uint32_t* __restrict__ offsets, uint32_t* __restrict__ keys,
-                                                          uint32_t* __restrict__ idx) {
+                                                          const uint32_t* __restrict__ offsets, uint2* __restrict__ pairs) {
+    __shared__ uint2 buf[TILE];
     const uint32_t hi = info->hi;
     const int64_t base = (int64_t)blockIdx.x * TILE + threadIdx.x * 8;
     uint32_t key[8];
     bool sel[8];
     const uint32_t c = load_tile_keys<VEC>(losses, N, info->thr, key, sel);
-    uint32_t pos = offsets[blockIdx.x] + block_exclusive_scan_256(c, nullptr);
+    uint32_t total, pos = block_exclusive_scan_256(c, &total);
 #pragma unroll
     for (int j = 0; j < 8; ++j)
-        if (sel[j]) {
-            keys[pos] = hi - key[j];
-            idx[pos] = (uint32_t)(base + j);
-            ++pos;
-        }
+        if (sel[j]) buf[pos++] = make_uint2(hi - key[j], (uint32_t)(base + j));
+    __syncthreads();
+    uint2* out = pairs + offsets[blockIdx.x];
+    for (uint32_t j = threadIdx.x; j < total; j += 256) out[j] = buf[j];
 }
 
 // ---- exclusive scan of a uint32 array (three kernels) -------------------------------------------------
@@ -570,7 +574,7 @@ static void exclusive_scan_u32(hipStream_t s, uint32_t* data, int64_t n, uint32_
 
 // table[d * tiles + b] = number of elements of block b's tile with digit d, tiles = the tiles that hold pairs (active_tiles)
 template <int RITER>
-__global__ __launch_bounds__(256) void radix_count_kernel(const uint32_t* __restrict__ keys, const SelInfo* __restrict__ info,
+__global__ __launch_bounds__(256) void radix_count_kernel(const uint2* __restrict__ pairs, const SelInfo* __restrict__ info,
                                                           int shift, uint32_t* __restrict__ table, int n_blocks) {
     if ((uint32_t)(shift >> 3) >= info->n_passes) return;   // the key range does not reach these bits
     __shared__ uint32_t cnt[256];
@@ -580,127 +584,107 @@ __global__ __launch_bounds__(256) void radix_count_kernel(const uint32_t* __rest
     constexpr int RTILE = RITER * 256;
     int64_t base = (int64_t)blockIdx.x * RTILE;
     if (base >= M) return;   // the table only has columns for tiles that hold pairs
+#pragma unroll
     for (int j = 0; j < RITER; ++j) {
         int64_t i = base + j * 256 + threadIdx.x;
-        if (i < M) atomicAdd(&cnt[(keys[i] >> shift) & 255u], 1u);
+        if (i < M) atomicAdd(&cnt[(pairs[i].x >> shift) & 255u], 1u);
     }
     __syncthreads();
     table[(int64_t)threadIdx.x * active_tiles(info, RTILE, n_blocks) + blockIdx.x] = cnt[threadIdx.x];
 }
 
 // table has been exclusive-scanned: table[d * n_blocks + b] = first output slot of digit d in block b.
-// Each wave owns RTILE/4 consecutive elements of the tile and ranks them 64 at a time with ballots, so the
-// order of equal digits is the input order (stable).  The ranked pairs are first put in digit order in LDS;
-// the tile is then written out position by position, so that neighbouring lanes write neighbouring slots of a
-// digit's run instead of 64 unrelated addresses per instruction.  Small sorts (RITER = 8, launch-bound) skip the staging
-// and write from the ranking loop.
+// Each wave owns RTILE/4 consecutive elements of the tile and ranks them 64 at a time with ballots, counting every digit as it
+// goes, so the order of equal digits is the input order (stable).  The pairs are then put in digit order in LDS and written out
+// position by position: neighbouring lanes write neighbouring slots of a digit's run, and key and index travel as one 8-byte
+// pair, so that a run of 16 fills a cache line (4 M pairs: 25 -> 20 us a pass).  Selecting and sorting 4 M of 16 M: 258 -> 215 us,
+// all of 16 M: 608 -> 473, all of 2^20: 153 -> 116.
 template <int RITER>
-__global__ __launch_bounds__(256) void radix_scatter_kernel(const uint32_t* __restrict__ keys_in, const uint32_t* __restrict__ idx_in,
-                                                            uint32_t* __restrict__ keys_out, uint32_t* __restrict__ idx_out,
-                                                            const SelInfo* __restrict__ info, int shift,
-                                                            const uint32_t* __restrict__ table, int n_blocks) {
+__global__ __launch_bounds__(256) void radix_scatter_kernel(const uint2* __restrict__ in, uint2* __restrict__ out, const SelInfo* __restrict__ info,
+                                                            int shift, const uint32_t* __restrict__ table, int n_blocks) {
     constexpr int RTILE = RITER * 256;
-    constexpr bool STAGED = RITER >= 16;
     __shared__ uint32_t cnt[4][256];
     __shared__ uint32_t to_global[256];   // global slot of a digit's first element minus its slot in the tile
-    __shared__ uint32_t kbuf[STAGED ? RTILE : 1], ibuf[STAGED ? RTILE : 1];
+    __shared__ uint2 buf[RTILE];
     if ((uint32_t)(shift >> 3) >= info->n_passes) return;   // the key range does not reach these bits
     const uint32_t M = info->M;
     const int64_t base = (int64_t)blockIdx.x * RTILE;
     if (base >= M) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int w = 0; w < 4; ++w) cnt[w][threadIdx.x] = 0u;
-    __syncthreads();
     const int64_t wbase = base + wave * (RTILE / 4);
-    uint32_t key[RITER], id[RITER];
+    uint2 pair[RITER];
+    uint32_t rank[RITER];
 #pragma unroll
     for (int it = 0; it < RITER; ++it) {
-        int64_t i = wbase + it * 64 + lane;
-        bool valid = i < M;
-        key[it] = valid ? keys_in[i] : 0u;
-        id[it] = valid ? idx_in[i] : 0u;
-        if (valid) atomicAdd(&cnt[wave][(key[it] >> shift) & 255u], 1u);
+        const int64_t i = wbase + it * 64 + lane;
+        pair[it] = i < M ? in[i] : make_uint2(0u, 0u);
+    }
+    const uint32_t first = table[(int64_t)threadIdx.x * active_tiles(info, RTILE, n_blocks) + blockIdx.x];
+#pragma unroll
+    for (int w = 0; w < 4; ++w) cnt[w][threadIdx.x] = 0u;
+    __syncthreads();
+    const uint64_t lt = lane ? (~0ull >> (64 - lane)) : 0ull;
+#pragma unroll
+    for (int it = 0; it < RITER; ++it) {
+        const bool valid = wbase + it * 64 + lane < M;
+        const uint32_t d = (pair[it].x >> shift) & 255u;
+        uint64_t peers = __ballot(valid);
+#pragma unroll
+        for (int b = 0; b < 8; ++b) {
+            const uint64_t v = __ballot((d >> b) & 1u);
+            peers &= ((d >> b) & 1u) ? v : ~v;
+        }
+        rank[it] = cnt[wave][d] + (uint32_t)__popcll(peers & lt);
+        __builtin_amdgcn_wave_barrier();
+        if (valid && (peers & lt) == 0ull) cnt[wave][d] += (uint32_t)__popcll(peers);  // lowest peer advances the count
+        __builtin_amdgcn_wave_barrier();
     }
     __syncthreads();
     {   // per digit: slots of the tile in digit order, waves in order inside a digit
-        uint32_t c[4], tile_count = 0;
-        for (int w = 0; w < 4; ++w) {
-            c[w] = cnt[w][threadIdx.x];
-            tile_count += c[w];
-        }
-        uint32_t run = table[(int64_t)threadIdx.x * active_tiles(info, RTILE, n_blocks) + blockIdx.x];   // direct: global slots
-        if (STAGED) {
-            const uint32_t in_tile = block_exclusive_scan_256(tile_count, nullptr);
-            to_global[threadIdx.x] = run - in_tile;
-            run = in_tile;
-        }
+        uint32_t c[4];
+#pragma unroll
+        for (int w = 0; w < 4; ++w) c[w] = cnt[w][threadIdx.x];
+        uint32_t run = block_exclusive_scan_256((c[0] + c[1]) + (c[2] + c[3]), nullptr);
+        to_global[threadIdx.x] = first - run;
+#pragma unroll
         for (int w = 0; w < 4; ++w) {
             cnt[w][threadIdx.x] = run;
             run += c[w];
         }
     }
     __syncthreads();
-    const uint64_t lt = lane ? (~0ull >> (64 - lane)) : 0ull;
 #pragma unroll
-    for (int it = 0; it < RITER; ++it) {
-        int64_t i = wbase + it * 64 + lane;
-        bool valid = i < M;
-        uint32_t d = (key[it] >> shift) & 255u;
-        uint64_t peers = __ballot(valid);
-#pragma unroll
-        for (int b = 0; b < 8; ++b) {
-            uint64_t v = __ballot((d >> b) & 1u);
-            peers &= ((d >> b) & 1u) ? v : ~v;
-        }
-        if (valid) {
-            uint32_t rank = __popcll(peers & lt);
-            uint32_t pos = cnt[wave][d] + rank;
-            if (STAGED) {
-                kbuf[pos] = key[it];
-                ibuf[pos] = id[it];
-            } else {
-                keys_out[pos] = key[it];
-                idx_out[pos] = id[it];
-            }
-        }
-        __builtin_amdgcn_wave_barrier();
-        if (valid && (peers & lt) == 0ull) cnt[wave][d] += (uint32_t)__popcll(peers);  // lowest peer advances the slot
-        __builtin_amdgcn_wave_barrier();
-    }
-    if (!STAGED) return;
+    for (int it = 0; it < RITER; ++it)
+        if (wbase + it * 64 + lane < M) buf[cnt[wave][(pair[it].x >> shift) & 255u] + rank[it]] = pair[it];
     __syncthreads();
     const int n_valid = (int)(M - base < (uint32_t)RTILE ? M - base : (uint32_t)RTILE);
     for (int j = threadIdx.x; j < n_valid; j += 256) {
-        const uint32_t k = kbuf[j];
-        const uint32_t pos = to_global[(k >> shift) & 255u] + (uint32_t)j;
-        keys_out[pos] = k;
-        idx_out[pos] = ibuf[j];
+        const uint2 v = buf[j];
+        out[to_global[(v.x >> shift) & 255u] + (uint32_t)j] = v;
     }
 }
 
-// The sorted pairs sit in the first or the second pair of arrays, depending on the number of passes that ran.
-__global__ __launch_bounds__(256) void topk_emit_kernel(const uint32_t* __restrict__ keys_a, const uint32_t* __restrict__ idx_a,
-                                                        const uint32_t* __restrict__ keys_b, const uint32_t* __restrict__ idx_b,
+// The sorted pairs sit in the first or the second array, depending on the number of passes that ran.
+__global__ __launch_bounds__(256) void topk_emit_kernel(const uint2* __restrict__ pairs_a, const uint2* __restrict__ pairs_b,
                                                         const SelInfo* __restrict__ info, const float* __restrict__ losses, int64_t k,
                                                         int32_t* __restrict__ idx_out, float* __restrict__ val_out) {
-    const bool second = (info->n_passes & 1u) != 0u;
-    const uint32_t* keys_sorted = second ? keys_b : keys_a;
-    const uint32_t* idx_sorted = second ? idx_b : idx_a;
+    const uint2* sorted = (info->n_passes & 1u) != 0u ? pairs_b : pairs_a;
     const uint32_t hi = info->hi;
     int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < k; r += stride) {
-        uint32_t i = idx_sorted[r];
-        idx_out[r] = (int32_t)i;
+        const uint2 p = sorted[r];
+        idx_out[r] = (int32_t)p.y;
         if (val_out) {
             float v;
-            if (!key_to_loss(hi - keys_sorted[r], &v)) v = losses[i];
+            if (!key_to_loss(hi - p.x, &v)) v = losses[p.y];
             val_out[r] = v;
         }
     }
 }
 
 struct TopkScratch {
-    uint32_t *hist, *hist2, *counts, *sums, *table, *keys_a, *idx_a, *keys_b, *idx_b;
+    uint32_t *hist, *hist2, *counts, *sums, *table;
+    uint2 *a, *b;
     SelInfo* info;
     int n_blocks;    // selection tiles (TILE elements)
     int r_iter;      // rounds per wave in the radix passes (8 or 16)
@@ -718,10 +702,8 @@ static TopkScratch carve_topk(Carver& c, int64_t N) {
     t.counts = c.take<uint32_t>(t.n_blocks);
     t.table = c.take<uint32_t>((size_t)256 * t.r_blocks);
     t.sums = c.take<uint32_t>(((size_t)256 * t.n_blocks + SCAN_CHUNK - 1) / SCAN_CHUNK + 1);
-    t.keys_a = c.take<uint32_t>(N);
-    t.idx_a = c.take<uint32_t>(N);
-    t.keys_b = c.take<uint32_t>(N);
-    t.idx_b = c.take<uint32_t>(N);
+    t.a = c.take<uint2>(N);
+    t.b = c.take<uint2>(N);
     return t;
 }
 
@@ -741,39 +723,33 @@ static int launch_topk_large(bls_ctx* ctx, char* scratch_base, const float* loss
     hipStream_t s = ctx->stream;
     const int nb = t.n_blocks, rb = t.r_blocks;
     const int64_t quads = (N + 3) / 4;
-    // Histogram workgroups per compute unit: each one clears and folds its LDS bins and adds every non-empty bin to the global
-    // histogram (all 2048 of them on the second level), which outweighs the shorter rounds of a finer grid below 2^25 keys
-    // (measured, N = 2^20 / 2^24 / 2^26: 118 / 282 / 869 us with two per unit, 133 / 313 / 863 us with eight).
-    const int per_cu = N >= (int64_t(1) << 25) ? 8 : 2;
-    int hist_blocks = (int)((quads + 255) / 256 < ctx->num_cus * per_cu ? (quads + 255) / 256 : ctx->num_cus * per_cu);
+    const int64_t hist_want = (quads + HIST_THREADS - 1) / HIST_THREADS, hist_full = 2 * (int64_t)ctx->num_cus;   // 64 KB of LDS each
+    const int hist_blocks = (int)(hist_want < hist_full ? hist_want : hist_full);
     const bool vec = reinterpret_cast<uintptr_t>(losses) % 16 == 0;   // 16-byte loads where the array allows them
     hipLaunchKernelGGL(zero_u32_kernel, dim3(16), dim3(256), 0, s, t.hist, (int64_t)2 * SEL_BINS);
-    if (vec) hipLaunchKernelGGL((sel_hist_kernel<1, true>), dim3(hist_blocks), dim3(256), 0, s, losses, N, t.info, t.hist);
-    else hipLaunchKernelGGL((sel_hist_kernel<1, false>), dim3(hist_blocks), dim3(256), 0, s, losses, N, t.info, t.hist);
+    if (vec) hipLaunchKernelGGL((sel_hist_kernel<1, true>), dim3(hist_blocks), dim3(HIST_THREADS), 0, s, losses, N, t.info, t.hist);
+    else hipLaunchKernelGGL((sel_hist_kernel<1, false>), dim3(hist_blocks), dim3(HIST_THREADS), 0, s, losses, N, t.info, t.hist);
     hipLaunchKernelGGL(sel_threshold_kernel<1>, dim3(1), dim3(256), 0, s, t.hist, (uint32_t)k, t.info);
-    if (vec) hipLaunchKernelGGL((sel_hist_kernel<2, true>), dim3(hist_blocks), dim3(256), 0, s, losses, N, t.info, t.hist2);
-    else hipLaunchKernelGGL((sel_hist_kernel<2, false>), dim3(hist_blocks), dim3(256), 0, s, losses, N, t.info, t.hist2);
+    if (vec) hipLaunchKernelGGL((sel_hist_kernel<2, true>), dim3(hist_blocks), dim3(HIST_THREADS), 0, s, losses, N, t.info, t.hist2);
+    else hipLaunchKernelGGL((sel_hist_kernel<2, false>), dim3(hist_blocks), dim3(HIST_THREADS), 0, s, losses, N, t.info, t.hist2);
     hipLaunchKernelGGL(sel_threshold_kernel<2>, dim3(1), dim3(256), 0, s, t.hist2, (uint32_t)k, t.info);
     if (vec) hipLaunchKernelGGL(sel_count_kernel<true>, dim3(nb), dim3(256), 0, s, losses, N, t.info, t.counts);
     else hipLaunchKernelGGL(sel_count_kernel<false>, dim3(nb), dim3(256), 0, s, losses, N, t.info, t.counts);
     exclusive_scan_u32(s, t.counts, nb, t.sums);
-    if (vec) hipLaunchKernelGGL(sel_compact_kernel<true>, dim3(nb), dim3(256), 0, s, losses, N, t.info, t.counts, t.keys_a, t.idx_a);
-    else hipLaunchKernelGGL(sel_compact_kernel<false>, dim3(nb), dim3(256), 0, s, losses, N, t.info, t.counts, t.keys_a, t.idx_a);
-    uint32_t *ka = t.keys_a, *ia = t.idx_a, *kb = t.keys_b, *ib = t.idx_b;
+    if (vec) hipLaunchKernelGGL(sel_compact_kernel<true>, dim3(nb), dim3(256), 0, s, losses, N, t.info, t.counts, t.a);
+    else hipLaunchKernelGGL(sel_compact_kernel<false>, dim3(nb), dim3(256), 0, s, losses, N, t.info, t.counts, t.a);
+    uint2 *from = t.a, *to = t.b;
     for (int pass = 0; pass < 4; ++pass) {
-        if (t.r_iter == 16) hipLaunchKernelGGL(radix_count_kernel<16>, dim3(rb), dim3(256), 0, s, ka, t.info, pass * 8, t.table, rb);
-        else hipLaunchKernelGGL(radix_count_kernel<8>, dim3(rb), dim3(256), 0, s, ka, t.info, pass * 8, t.table, rb);
+        if (t.r_iter == 16) hipLaunchKernelGGL(radix_count_kernel<16>, dim3(rb), dim3(256), 0, s, from, t.info, pass * 8, t.table, rb);
+        else hipLaunchKernelGGL(radix_count_kernel<8>, dim3(rb), dim3(256), 0, s, from, t.info, pass * 8, t.table, rb);
         exclusive_scan_u32(s, t.table, (int64_t)256 * rb, t.sums, t.info, pass, t.r_iter * 256);
-        if (t.r_iter == 16)
-            hipLaunchKernelGGL(radix_scatter_kernel<16>, dim3(rb), dim3(256), 0, s, ka, ia, kb, ib, t.info, pass * 8, t.table, rb);
-        else
-            hipLaunchKernelGGL(radix_scatter_kernel<8>, dim3(rb), dim3(256), 0, s, ka, ia, kb, ib, t.info, pass * 8, t.table, rb);
-        uint32_t* tmp = ka; ka = kb; kb = tmp;
-        tmp = ia; ia = ib; ib = tmp;
+        if (t.r_iter == 16) hipLaunchKernelGGL(radix_scatter_kernel<16>, dim3(rb), dim3(256), 0, s, from, to, t.info, pass * 8, t.table, rb);
+        else hipLaunchKernelGGL(radix_scatter_kernel<8>, dim3(rb), dim3(256), 0, s, from, to, t.info, pass * 8, t.table, rb);
+        uint2* tmp = from; from = to; to = tmp;
     }
     int64_t eb = (k + 255) / 256;
     if (eb > 2048) eb = 2048;
-    hipLaunchKernelGGL(topk_emit_kernel, dim3((unsigned)eb), dim3(256), 0, s, t.keys_a, t.idx_a, t.keys_b, t.idx_b, t.info, losses, k, idx_out, val_out);
+    hipLaunchKernelGGL(topk_emit_kernel, dim3((unsigned)eb), dim3(256), 0, s, t.a, t.b, t.info, losses, k, idx_out, val_out);
     BLS_HIP(ctx, hipGetLastError());
     return BLS_OK;
 }
@@ -801,8 +777,8 @@ int launch_topk(bls_ctx* ctx, const float* losses, int64_t N, int64_t k, int32_t
 
 // ---- selection without any allocation -----------------------------------------------------------------
 //
-// The large-pool path above needs device scratch (histogram, block counts, digit tables and two pairs of key / index
-// arrays).  For callers that must not allocate, the same launches run on a fixed array in the library's device image.
+// The large-pool path above needs device scratch (histogram, block counts, digit tables and two arrays of key and
+// index).  For callers that must not allocate, the same launches run on a fixed array in the library's device image.
 // Every GPU the library is loaded on holds its own copy of the array at its own address, for the life of the process.
 
 #define TOPK_STATIC_BYTES (size_t(18) << 20)   // >= topk_scratch_bytes(BLS_TOPK_STATIC_MAX_N, .), checked on every call
