@@ -25,14 +25,29 @@ __device__ __forceinline__ uint32_t loss_key(float v) {
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
+// One selection; two independent ones over pools of one size share their launches (blockIdx.y).
+struct SelJob {
+    const float* losses;
+    int k;
+    int32_t* idx_out;
+    float* val_out;
+    // whole-pool sort only
+    uint32_t* tables;
+    uint2 *a, *b;
+};
+struct SelJobs {
+    SelJob j[2];
+};
+
 // Rank by counting: the rank of a sample is the number of samples that precede it, so each workgroup ranks 64 samples (one per
 // lane) against the whole pool, which its 16 waves walk in chunks of 64 keys from LDS (every lane reads the same four keys per
 // 16-byte read).  Chunks left of the workgroup's own count equal keys, chunks right of it do not: the tie rule costs nothing
 // but in the one chunk where both orders occur.  Bound: vector instructions, two per pair of samples; N^2 of them still beat
 // the N log^2 N of a bitonic network with its 100 barriers in one workgroup because all compute units take part.
 // N = 512 / 4096 / 16384: 9.8 -> 4.3, 38 -> 8.7, 157 -> 24.5 us against the bitonic network.
-__global__ __launch_bounds__(1024) void topk_rank_kernel(const float* __restrict__ losses, int N, int k, int32_t* __restrict__ idx_out,
-                                                         float* __restrict__ val_out) {
+__global__ __launch_bounds__(1024) void topk_rank_kernel(SelJobs jobs, int N) {
+    const SelJob& job = jobs.j[blockIdx.y];
+    const float* __restrict__ losses = job.losses;
     extern __shared__ __align__(16) uint32_t rank_lds[];   // the keys, then [16][64] partial ranks
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n_chunks = (N + 63) >> 6, own = blockIdx.x;
@@ -69,9 +84,9 @@ __global__ __launch_bounds__(1024) void topk_rank_kernel(const float* __restrict
 #pragma unroll
         for (int w = 0; w < 16; ++w) rank += rank_lds[w * 64 + lane];
         const int i = own * 64 + lane;
-        if (i < N && rank < (uint32_t)k) {
-            idx_out[rank] = i;
-            if (val_out) val_out[rank] = losses[i];
+        if (i < N && rank < (uint32_t)job.k) {
+            job.idx_out[rank] = i;
+            if (job.val_out) job.val_out[rank] = losses[i];
         }
     }
 }
@@ -101,7 +116,9 @@ __device__ __forceinline__ bool key_to_loss(uint32_t key, float* v) {
 
 // Digit counts of the first pass; clears the tables of the other three.
 template <int RITER>
-__global__ __launch_bounds__(1024) void sort_count_kernel(const float* __restrict__ losses, int N, uint32_t* __restrict__ tables) {
+__global__ __launch_bounds__(1024) void sort_count_kernel(SelJobs jobs, int N) {
+    const float* __restrict__ losses = jobs.j[blockIdx.y].losses;
+    uint32_t* __restrict__ tables = jobs.j[blockIdx.y].tables;
     __shared__ uint32_t cnt[256];
     const int tid = threadIdx.x;
     if (tid < 256) cnt[tid] = 0u;
@@ -121,9 +138,13 @@ __global__ __launch_bounds__(1024) void sort_count_kernel(const float* __restric
 // elements in rounds of 64 by ballots, counting each digit as it goes; the four groups of 256 threads add up a quarter of the
 // table each.  PASS 0 reads the losses, PASS 3 stores the first k of the result.
 template <int RITER, int PASS>
-__global__ __launch_bounds__(1024) void sort_pass_kernel(const float* __restrict__ losses, const uint2* __restrict__ in, uint2* __restrict__ out, int N,
-                                                         int k, const uint32_t* __restrict__ table, uint32_t* __restrict__ table_next,
-                                                         int32_t* __restrict__ idx_out, float* __restrict__ val_out) {
+__global__ __launch_bounds__(1024) void sort_pass_kernel(SelJobs jobs, int N) {
+    const SelJob& job = jobs.j[blockIdx.y];
+    const float* __restrict__ losses = job.losses;
+    const uint2* __restrict__ in = PASS == 2 ? job.b : job.a;
+    uint2* __restrict__ out = PASS == 1 ? job.b : job.a;
+    const uint32_t* __restrict__ table = job.tables + PASS * SORT_TABLE;
+    uint32_t* __restrict__ table_next = job.tables + (PASS + 1) * SORT_TABLE;
     constexpr int RTILE = RITER * 1024, SHIFT = 8 * PASS;
     __shared__ uint32_t cnt[16][256];
     __shared__ uint32_t part[2][4][256];
@@ -212,12 +233,12 @@ __global__ __launch_bounds__(1024) void sort_pass_kernel(const float* __restrict
             out[pos] = make_uint2(key[it], id[it]);
             const uint32_t slot = (pos / RTILE) * 256u + ((key[it] >> (SHIFT + 8)) & 255u);
             atomicAdd(&next[slot >> 1], (slot & 1u) ? 65536u : 1u);
-        } else if (pos < (uint32_t)k) {
-            idx_out[pos] = (int32_t)id[it];
-            if (val_out) {
+        } else if (pos < (uint32_t)job.k) {
+            job.idx_out[pos] = (int32_t)id[it];
+            if (job.val_out) {
                 float v;
                 if (!key_to_loss(~key[it], &v)) v = losses[id[it]];
-                val_out[pos] = v;
+                job.val_out[pos] = v;
             }
         }
     }
@@ -230,35 +251,31 @@ __global__ __launch_bounds__(1024) void sort_pass_kernel(const float* __restrict
     }
 }
 
-static size_t sort_scratch_bytes(int64_t N) {
-    Carver c(nullptr);
-    c.take<uint32_t>(4 * SORT_TABLE);
-    c.take<uint2>(N);
-    c.take<uint2>(N);
-    return c.off;
+static void carve_sort(Carver& c, int64_t N, SelJob& job) {
+    job.tables = c.take<uint32_t>(4 * SORT_TABLE);
+    job.a = c.take<uint2>(N);
+    job.b = c.take<uint2>(N);
 }
 
 template <int RITER>
-static void launch_sort(hipStream_t s, char* scratch_base, const float* losses, int N, int k, int32_t* idx_out, float* val_out) {
-    Carver c(scratch_base);
-    uint32_t* t = c.take<uint32_t>(4 * SORT_TABLE);
-    uint2* a = c.take<uint2>(N);
-    uint2* b = c.take<uint2>(N);
-    const dim3 grid((unsigned)((N + RITER * 1024 - 1) / (RITER * 1024))), block(1024);
-    hipLaunchKernelGGL(sort_count_kernel<RITER>, grid, block, 0, s, losses, N, t);
-    hipLaunchKernelGGL((sort_pass_kernel<RITER, 0>), grid, block, 0, s, losses, nullptr, a, N, k, t, t + SORT_TABLE, nullptr, nullptr);
-    hipLaunchKernelGGL((sort_pass_kernel<RITER, 1>), grid, block, 0, s, losses, a, b, N, k, t + SORT_TABLE, t + 2 * SORT_TABLE, nullptr, nullptr);
-    hipLaunchKernelGGL((sort_pass_kernel<RITER, 2>), grid, block, 0, s, losses, b, a, N, k, t + 2 * SORT_TABLE, t + 3 * SORT_TABLE, nullptr, nullptr);
-    hipLaunchKernelGGL((sort_pass_kernel<RITER, 3>), grid, block, 0, s, losses, a, nullptr, N, k, t + 3 * SORT_TABLE, nullptr, idx_out, val_out);
+static void launch_sort(hipStream_t s, const SelJobs& jobs, int n_jobs, int N) {
+    const dim3 grid((unsigned)((N + RITER * 1024 - 1) / (RITER * 1024)), n_jobs), block(1024);
+    hipLaunchKernelGGL(sort_count_kernel<RITER>, grid, block, 0, s, jobs, N);
+    hipLaunchKernelGGL((sort_pass_kernel<RITER, 0>), grid, block, 0, s, jobs, N);
+    hipLaunchKernelGGL((sort_pass_kernel<RITER, 1>), grid, block, 0, s, jobs, N);
+    hipLaunchKernelGGL((sort_pass_kernel<RITER, 2>), grid, block, 0, s, jobs, N);
+    hipLaunchKernelGGL((sort_pass_kernel<RITER, 3>), grid, block, 0, s, jobs, N);
 }
 
-// TOPK_RANK_MAX < N <= TOPK_SORT_MAX; `scratch_base` as below.  The fewest rounds that keep the pool within SORT_TILES tiles.
-static int launch_topk_medium(bls_ctx* ctx, char* scratch_base, const float* losses, int64_t N, int64_t k, int32_t* idx_out, float* val_out) {
-    const int n = (int)N, kk = (int)k;
-    if (N <= 1 * 65536) launch_sort<1>(ctx->stream, scratch_base, losses, n, kk, idx_out, val_out);
-    else if (N <= 2 * 65536) launch_sort<2>(ctx->stream, scratch_base, losses, n, kk, idx_out, val_out);
-    else if (N <= 4 * 65536) launch_sort<4>(ctx->stream, scratch_base, losses, n, kk, idx_out, val_out);
-    else launch_sort<8>(ctx->stream, scratch_base, losses, n, kk, idx_out, val_out);
+// TOPK_RANK_MAX < N <= TOPK_SORT_MAX; `scratch_base` as below, n_jobs times.  The fewest rounds that keep the pool within
+// SORT_TILES tiles.
+static int launch_topk_medium(bls_ctx* ctx, char* scratch_base, SelJobs jobs, int n_jobs, int64_t N) {
+    Carver c(scratch_base);
+    for (int i = 0; i < n_jobs; ++i) carve_sort(c, N, jobs.j[i]);
+    if (N <= 1 * 65536) launch_sort<1>(ctx->stream, jobs, n_jobs, (int)N);
+    else if (N <= 2 * 65536) launch_sort<2>(ctx->stream, jobs, n_jobs, (int)N);
+    else if (N <= 4 * 65536) launch_sort<4>(ctx->stream, jobs, n_jobs, (int)N);
+    else launch_sort<8>(ctx->stream, jobs, n_jobs, (int)N);
     BLS_HIP(ctx, hipGetLastError());
     return BLS_OK;
 }
@@ -710,8 +727,12 @@ static TopkScratch carve_topk(Carver& c, int64_t N) {
 size_t topk_scratch_bytes(int64_t N, int64_t k) {
     (void)k;
     if (N <= TOPK_RANK_MAX) return 0;
-    if (N <= TOPK_SORT_MAX) return sort_scratch_bytes(N);
     Carver c(nullptr);
+    if (N <= TOPK_SORT_MAX) {
+        SelJob job;
+        carve_sort(c, N, job);
+        return c.off;
+    }
     carve_topk(c, N);
     return c.off;
 }
@@ -754,25 +775,43 @@ static int launch_topk_large(bls_ctx* ctx, char* scratch_base, const float* loss
     return BLS_OK;
 }
 
-static int launch_topk_small(bls_ctx* ctx, const float* losses, int64_t N, int64_t k, int32_t* idx_out, float* val_out) {
+static int launch_topk_small(bls_ctx* ctx, const SelJobs& jobs, int n_jobs, int64_t N) {
     const unsigned chunks = (unsigned)((N + 63) / 64);
     const size_t words = chunks * 64 > 1024 ? chunks * 64 : 1024;   // the keys, and in their place 16 x 64 partial ranks
-    hipLaunchKernelGGL(topk_rank_kernel, dim3(chunks), dim3(1024), words * sizeof(uint32_t), ctx->stream, losses, (int)N, (int)k, idx_out, val_out);
+    hipLaunchKernelGGL(topk_rank_kernel, dim3(chunks, n_jobs), dim3(1024), words * sizeof(uint32_t), ctx->stream, jobs, (int)N);
     BLS_HIP(ctx, hipGetLastError());
     return BLS_OK;
 }
 
 // `scratch_base`: topk_scratch_bytes(N, k) bytes of device memory, 256-byte aligned
 static int launch_topk_at(bls_ctx* ctx, char* scratch_base, const float* losses, int64_t N, int64_t k, int32_t* idx_out, float* val_out) {
-    if (N <= TOPK_RANK_MAX) return launch_topk_small(ctx, losses, N, k, idx_out, val_out);
-    if (N <= TOPK_SORT_MAX) return launch_topk_medium(ctx, scratch_base, losses, N, k, idx_out, val_out);
-    return launch_topk_large(ctx, scratch_base, losses, N, k, idx_out, val_out);
+    if (N > TOPK_SORT_MAX) return launch_topk_large(ctx, scratch_base, losses, N, k, idx_out, val_out);
+    SelJobs jobs{};
+    jobs.j[0] = {losses, (int)k, idx_out, val_out, nullptr, nullptr, nullptr};
+    if (N <= TOPK_RANK_MAX) return launch_topk_small(ctx, jobs, 1, N);
+    return launch_topk_medium(ctx, scratch_base, jobs, 1, N);
 }
 
 int launch_topk(bls_ctx* ctx, const float* losses, int64_t N, int64_t k, int32_t* idx_out, float* val_out) {
     int rc = bls_arena_reserve(ctx, topk_scratch_bytes(N, k));
     if (rc != BLS_OK) return rc;
     return launch_topk_at(ctx, ctx->arena, losses, N, k, idx_out, val_out);
+}
+
+size_t topk_pair_scratch_bytes(int64_t N) { return (N <= TOPK_SORT_MAX ? 2 : 1) * topk_scratch_bytes(N, N); }
+
+// Two launch-bound selections cost one when they run side by side; from TOPK_SORT_MAX on each fills the chip by itself.
+int launch_topk_pair(bls_ctx* ctx, const float* losses_a, int64_t k_a, int32_t* idx_a, const float* losses_b, int64_t k_b, int32_t* idx_b, int64_t N) {
+    int rc = bls_arena_reserve(ctx, topk_pair_scratch_bytes(N));
+    if (rc != BLS_OK) return rc;
+    if (N > TOPK_SORT_MAX) {
+        rc = launch_topk(ctx, losses_a, N, k_a, idx_a, nullptr);
+        return rc != BLS_OK ? rc : launch_topk(ctx, losses_b, N, k_b, idx_b, nullptr);
+    }
+    SelJobs jobs{};
+    jobs.j[0] = {losses_a, (int)k_a, idx_a, nullptr, nullptr, nullptr, nullptr};
+    jobs.j[1] = {losses_b, (int)k_b, idx_b, nullptr, nullptr, nullptr, nullptr};
+    return N <= TOPK_RANK_MAX ? launch_topk_small(ctx, jobs, 2, N) : launch_topk_medium(ctx, ctx->arena, jobs, 2, N);
 }
 
 // ---- selection without any allocation -----------------------------------------------------------------
@@ -804,7 +843,7 @@ int topk_static_init(bls_ctx* ctx) {
 int launch_topk_static(bls_ctx* ctx, const float* losses, int64_t N, int64_t k, int32_t* idx_out, float* val_out) {
     if (N > BLS_TOPK_STATIC_MAX_N || topk_scratch_bytes(N, k) > TOPK_STATIC_BYTES)
         return bls_fail(ctx, BLS_EINVAL, "topk_by_loss_static: N = %lld exceeds the limit of %d", (long long)N, BLS_TOPK_STATIC_MAX_N);
-    if (N <= TOPK_RANK_MAX) return launch_topk_small(ctx, losses, N, k, idx_out, val_out);
+    if (N <= TOPK_RANK_MAX) return launch_topk_at(ctx, nullptr, losses, N, k, idx_out, val_out);
     char* base = (ctx->device >= 0 && ctx->device < TOPK_STATIC_MAX_DEVICES) ? g_static_scratch[ctx->device] : nullptr;
     if (!base) return bls_fail(ctx, BLS_EUNSUPPORTED, "topk_by_loss_static: no static scratch on device %d", ctx->device);
     return launch_topk_at(ctx, base, losses, N, k, idx_out, val_out);

@@ -118,7 +118,7 @@ def _check_variant(env, losses, uf, us, tf, pf, ts, ps, lam, scheme, to):
                                        ("separated", "none"), ("unified", "none")])
 @pytest.mark.parametrize("N,tf,pf,ts,ps,lam", [
     (8, 3, 1, 1, 1, 0.5), (257, 32, 8, 1, 2, 0.25), (5000, 3, 7, 2, 5, 1.0), (5000, 3, 7, 2, 5, 0.001), (16385, 32, 8, 16, 2, 0.3),
-    (50000, 32, 8, 1, 2, 0.5), (40000, 2, 2, 0, 0, 0.5),
+    (50000, 32, 8, 1, 2, 0.5), (40000, 2, 2, 0, 0, 0.5), ((1 << 19) + 3, 32, 8, 4, 2, 0.5),
 ])
 def test_variants_match_the_oracle(env, scheme, to, N, tf, pf, ts, ps, lam):
     seed = synth.inputs.BASE_SEED + 3 * N
