@@ -14,7 +14,7 @@
 #include "common.h"
 
 // Ranking by counting needs no scratch and costs 24.6 us at 16384 (four sorting passes: 22 us at 16385); sorting a pool of
-// 2^19 whole takes 73 us for any k, selecting first 98 (k = N / 50) to 120 us (k = N); at 2^20 about 117 against 93 to 116 us.
+// 2^19 whole takes 73 us for any k, selecting first 98 (k = N / 50) to 120 us (k = N); at 2^20 about 117 against 86 to 105 us.
 #define TOPK_RANK_MAX 16384
 #define TOPK_SORT_MAX (1 << 19)
 
@@ -290,7 +290,7 @@ static int launch_topk_medium(bls_ctx* ctx, char* scratch_base, SelJobs jobs, in
 //    (hi bounds every key), so that ascending order is rank order and the keys only span the range that occurs.
 // 3. Stable LSD radix sort of the M pairs, 8 bits per pass, with as many passes as that range needs (the later passes
 //    exit at once).  Stability keeps equal losses in ascending index order, which is the tie rule.
-// 4. The first k pairs are the result.
+// 4. The first k pairs are the result: the last pass stores indices and losses instead of pairs.
 // Nothing is read back to the host: grids are sized for the worst case M == N and blocks past M exit.
 
 #define SEL_BINS 2048
@@ -410,7 +410,7 @@ __global__ __launch_bounds__(256) void sel_threshold_kernel(const uint32_t* __re
                 const uint32_t range = info->hi - (thr << 10);   // sort keys lie in [0, range]
                 info->thr = thr;
                 info->M = info->above + with;
-                info->n_passes = range == 0u ? 0u : (32u - (uint32_t)__clz(range) + 7u) / 8u;
+                info->n_passes = range < 256u ? 1u : (32u - (uint32_t)__clz(range) + 7u) / 8u;   // the last pass stores the result
             }
         }
         above = with;
@@ -489,7 +489,7 @@ __global__ __launch_bounds__(256) void sel_compact_kernel(const float* __restric
     for (uint32_t j = threadIdx.x; j < total; j += 256) out[j] = buf[j];
 }
 
-// ---- exclusive scan of a uint32 array (three kernels) -------------------------------------------------
+// ---- exclusive scan of a uint32 array (two or three kernels) -------------------------------------------------
 
 // The scans take an optional (info, pass): a radix pass the key range does not need is skipped by all its kernels.
 __device__ __forceinline__ bool pass_skipped(const SelInfo* info, int pass) { return info && (uint32_t)pass >= info->n_passes; }
@@ -533,8 +533,11 @@ __global__ __launch_bounds__(256) void scan_sums_kernel(uint32_t* __restrict__ s
     }
 }
 
+// With `raw` the chunk sums have not been scanned: a workgroup adds up those before its own, a few loads per thread in place of a
+// launch of one workgroup (up to SCAN_RAW_MAX chunks).
+#define SCAN_RAW_MAX 4096
 __global__ __launch_bounds__(256) void scan_apply_kernel(uint32_t* __restrict__ data, int64_t n, const uint32_t* __restrict__ sums,
-                                                         const SelInfo* __restrict__ info, int pass, int rtile) {
+                                                         const SelInfo* __restrict__ info, int pass, int rtile, int raw) {
     if (pass_skipped(info, pass)) return;
     n = scan_length(n, info, rtile);
     if ((int64_t)blockIdx.x * SCAN_CHUNK >= n) return;
@@ -544,7 +547,15 @@ __global__ __launch_bounds__(256) void scan_apply_kernel(uint32_t* __restrict__ 
         v[j] = base + j < n ? data[base + j] : 0u;
         c += v[j];
     }
-    uint32_t run = sums[blockIdx.x] + block_exclusive_scan_256(c, nullptr);
+    uint32_t before = 0;
+    if (raw) {
+        uint32_t mine = 0;
+        for (unsigned i = threadIdx.x; i < blockIdx.x; i += 256) mine += sums[i];
+        block_exclusive_scan_256(mine, &before);
+    } else {
+        before = sums[blockIdx.x];
+    }
+    uint32_t run = before + block_exclusive_scan_256(c, nullptr);
     for (int j = 0; j < 8; ++j)
         if (base + j < n) {
             data[base + j] = run;
@@ -583,8 +594,9 @@ static void exclusive_scan_u32(hipStream_t s, uint32_t* data, int64_t n, uint32_
     }
     int n_chunks = (int)((n + SCAN_CHUNK - 1) / SCAN_CHUNK);
     hipLaunchKernelGGL(scan_chunk_sums_kernel, dim3(n_chunks), dim3(256), 0, s, data, n, sums, info, pass, rtile);
-    hipLaunchKernelGGL(scan_sums_kernel, dim3(1), dim3(256), 0, s, sums, n_chunks, n, info, pass, rtile);
-    hipLaunchKernelGGL(scan_apply_kernel, dim3(n_chunks), dim3(256), 0, s, data, n, sums, info, pass, rtile);
+    const int raw = n_chunks <= SCAN_RAW_MAX;
+    if (!raw) hipLaunchKernelGGL(scan_sums_kernel, dim3(1), dim3(256), 0, s, sums, n_chunks, n, info, pass, rtile);
+    hipLaunchKernelGGL(scan_apply_kernel, dim3(n_chunks), dim3(256), 0, s, data, n, sums, info, pass, rtile, raw);
 }
 
 // ---- radix sort passes --------------------------------------------------------------------------------
@@ -614,11 +626,13 @@ __global__ __launch_bounds__(256) void radix_count_kernel(const uint2* __restric
 // Each wave owns RTILE/4 consecutive elements of the tile and ranks them 64 at a time with ballots, counting every digit as it
 // goes, so the order of equal digits is the input order (stable).  The pairs are then put in digit order in LDS and written out
 // position by position: neighbouring lanes write neighbouring slots of a digit's run, and key and index travel as one 8-byte
-// pair, so that a run of 16 fills a cache line (4 M pairs: 25 -> 20 us a pass).  Selecting and sorting 4 M of 16 M: 258 -> 215 us,
-// all of 16 M: 608 -> 473, all of 2^20: 153 -> 116.
+// pair, so that a run of 16 fills a cache line; the last pass that the key range needs stores the first k of the result (4 M pairs: 25 -> 20 us a pass).  Selecting and sorting 4 M of 16 M: 258 -> 215 us,
+// all of 16 M: 608 -> 473, all of 2^20: 153 -> 116; without a launch that unpacks the result and one per scan: 201, 435, 105.
 template <int RITER>
 __global__ __launch_bounds__(256) void radix_scatter_kernel(const uint2* __restrict__ in, uint2* __restrict__ out, const SelInfo* __restrict__ info,
-                                                            int shift, const uint32_t* __restrict__ table, int n_blocks) {
+                                                            int shift, const uint32_t* __restrict__ table, int n_blocks,
+                                                            const float* __restrict__ losses, int64_t k, int32_t* __restrict__ idx_out,
+                                                            float* __restrict__ val_out) {
     constexpr int RTILE = RITER * 256;
     __shared__ uint32_t cnt[4][256];
     __shared__ uint32_t to_global[256];   // global slot of a digit's first element minus its slot in the tile
@@ -675,26 +689,20 @@ __global__ __launch_bounds__(256) void radix_scatter_kernel(const uint2* __restr
         if (wbase + it * 64 + lane < M) buf[cnt[wave][(pair[it].x >> shift) & 255u] + rank[it]] = pair[it];
     __syncthreads();
     const int n_valid = (int)(M - base < (uint32_t)RTILE ? M - base : (uint32_t)RTILE);
+    const bool last = (uint32_t)(shift >> 3) + 1u == info->n_passes;
+    const uint32_t hi = info->hi;
     for (int j = threadIdx.x; j < n_valid; j += 256) {
         const uint2 v = buf[j];
-        out[to_global[(v.x >> shift) & 255u] + (uint32_t)j] = v;
-    }
-}
-
-// The sorted pairs sit in the first or the second array, depending on the number of passes that ran.
-__global__ __launch_bounds__(256) void topk_emit_kernel(const uint2* __restrict__ pairs_a, const uint2* __restrict__ pairs_b,
-                                                        const SelInfo* __restrict__ info, const float* __restrict__ losses, int64_t k,
-                                                        int32_t* __restrict__ idx_out, float* __restrict__ val_out) {
-    const uint2* sorted = (info->n_passes & 1u) != 0u ? pairs_b : pairs_a;
-    const uint32_t hi = info->hi;
-    int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < k; r += stride) {
-        const uint2 p = sorted[r];
-        idx_out[r] = (int32_t)p.y;
-        if (val_out) {
-            float v;
-            if (!key_to_loss(hi - p.x, &v)) v = losses[p.y];
-            val_out[r] = v;
+        const uint32_t pos = to_global[(v.x >> shift) & 255u] + (uint32_t)j;
+        if (!last) {
+            out[pos] = v;
+        } else if (pos < k) {
+            idx_out[pos] = (int32_t)v.y;
+            if (val_out) {
+                float loss;
+                if (!key_to_loss(hi - v.x, &loss)) loss = losses[v.y];
+                val_out[pos] = loss;
+            }
         }
     }
 }
@@ -764,13 +772,10 @@ static int launch_topk_large(bls_ctx* ctx, char* scratch_base, const float* loss
         if (t.r_iter == 16) hipLaunchKernelGGL(radix_count_kernel<16>, dim3(rb), dim3(256), 0, s, from, t.info, pass * 8, t.table, rb);
         else hipLaunchKernelGGL(radix_count_kernel<8>, dim3(rb), dim3(256), 0, s, from, t.info, pass * 8, t.table, rb);
         exclusive_scan_u32(s, t.table, (int64_t)256 * rb, t.sums, t.info, pass, t.r_iter * 256);
-        if (t.r_iter == 16) hipLaunchKernelGGL(radix_scatter_kernel<16>, dim3(rb), dim3(256), 0, s, from, to, t.info, pass * 8, t.table, rb);
-        else hipLaunchKernelGGL(radix_scatter_kernel<8>, dim3(rb), dim3(256), 0, s, from, to, t.info, pass * 8, t.table, rb);
+        if (t.r_iter == 16) hipLaunchKernelGGL(radix_scatter_kernel<16>, dim3(rb), dim3(256), 0, s, from, to, t.info, pass * 8, t.table, rb, losses, k, idx_out, val_out);
+        else hipLaunchKernelGGL(radix_scatter_kernel<8>, dim3(rb), dim3(256), 0, s, from, to, t.info, pass * 8, t.table, rb, losses, k, idx_out, val_out);
         uint2* tmp = from; from = to; to = tmp;
     }
-    int64_t eb = (k + 255) / 256;
-    if (eb > 2048) eb = 2048;
-    hipLaunchKernelGGL(topk_emit_kernel, dim3((unsigned)eb), dim3(256), 0, s, t.a, t.b, t.info, losses, k, idx_out, val_out);
     BLS_HIP(ctx, hipGetLastError());
     return BLS_OK;
 }
