@@ -49,6 +49,10 @@ SHAPES = [
     (50, 8, 16, 2, 32, 9, 9),        # nine layers, 72 tokens: more column sums per backward pass than one table launch takes
     (32000, 128, 512, 8, 2048, 2, 2),  # the measured widths (two of the six layers, two sequences): 500 softmax-statistics
                                        # pairs per row, the split contraction of the vocabulary input gradient, batched q/k/v
+    (264, 33, 128, 2, 264, 1, 4),      # 132 tokens and 264 columns: a few past the tiles of 64 and 128; contractions of 264 and 132
+                                       # that end inside a step of 16 or 32
+    (32008, 75, 64, 2, 72, 1, 4),      # 300 tokens x 32 008 words: more than 400 tiles of 256 x 128, ragged in both directions; a
+                                       # contraction of 32 008 that ends inside a step
 ]
 
 
