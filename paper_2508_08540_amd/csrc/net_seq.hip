@@ -466,8 +466,8 @@ struct Net {
         const int64_t first = m->enc_layers[0].wq;
         PROF(ctx, PROF_UPDATE, launch_to_bf16(st, params + first, s->w16 + first, m->num_params - first));
     }
-    void clear_weight_padding() const {   // once per call: nothing else writes there
-        if (s->bf) PROF(ctx, PROF_UPDATE, launch_fill_zero(st, reinterpret_cast<float*>(s->w16 + m->num_params), 4 * m->enc_D));
+    void clear_weight_padding() const {   // once per call: nothing else writes there (lean: every tensor is a multiple of 8 long)
+        if (s->lean) PROF(ctx, PROF_UPDATE, launch_fill_zero(st, reinterpret_cast<float*>(s->w16 + m->num_params), 4 * m->enc_D));
     }
 };
 
