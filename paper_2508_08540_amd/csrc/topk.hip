@@ -108,8 +108,8 @@ __device__ __forceinline__ bool key_to_loss(uint32_t key, float* v) {
 // columns itself (tiles before its own, and all of them) instead of waiting for a scan, and the pass that places an element
 // also counts it in the table of the next pass: the destination tile and the next digit are known at that point.  These counts
 // meet in LDS first (16 bits each, a tile has at most 8192 elements), since all elements of a run may share the next digit.
-// k = N, N = 50 000 / 131 072 / 524 288: 79 -> 29, 95 -> 40, 120 -> 73 us (the table's loads one after another: 37, 51, 85).  What is left is five launches, each a chain of load,
-// table sum, ranking rounds and scattered stores.
+// k = N, N = 50 000 / 131 072 / 524 288: 79 -> 29, 95 -> 40, 120 -> 73 us (with the table's loads one after another: 37, 51,
+// 85).  What is left is five launches, each a chain of load, table sum, ranking rounds and scattered stores.
 
 #define SORT_TILES 64   // 64 tiles of 8 x 1024 elements hold TOPK_SORT_MAX
 #define SORT_TABLE (SORT_TILES * 256)
@@ -469,8 +469,7 @@ __global__ __launch_bounds__(256) void sel_count_kernel(const float* __restrict_
 }
 
 // counts has been exclusive-scanned into offsets.  The selected pairs of a tile are gathered in LDS and stored side by side: from
-// the threads' own eight elements every store would go to 64 places (16 M keys, 4 M
-// selected: 29 -> 19 us).
+// the threads' own eight elements every store would go to 64 places (16 M keys, 4 M selected: 29 -> 19 us).
 template <bool VEC>
 __global__ __launch_bounds__(256) void sel_compact_kernel(const float* __restrict__ losses, int64_t N, const SelInfo* __restrict__ info,
                                                           const uint32_t* __restrict__ offsets, uint2* __restrict__ pairs) {
@@ -626,8 +625,9 @@ __global__ __launch_bounds__(256) void radix_count_kernel(const uint2* __restric
 // Each wave owns RTILE/4 consecutive elements of the tile and ranks them 64 at a time with ballots, counting every digit as it
 // goes, so the order of equal digits is the input order (stable).  The pairs are then put in digit order in LDS and written out
 // position by position: neighbouring lanes write neighbouring slots of a digit's run, and key and index travel as one 8-byte
-// pair, so that a run of 16 fills a cache line; the last pass that the key range needs stores the first k of the result (4 M pairs: 25 -> 20 us a pass).  Selecting and sorting 4 M of 16 M: 258 -> 215 us,
-// all of 16 M: 608 -> 473, all of 2^20: 153 -> 116; without a launch that unpacks the result and one per scan: 201, 435, 105.
+// pair, so that a run of 16 fills a cache line (a pass over 4 M pairs: 25 -> 20 us).  The last pass that the key range needs
+// stores the first k of the result.  With the pair layout the whole selection went from 258 to 215 us (4 M of 16 M), 608 to 473
+// (all of 16 M) and 153 to 116 (all of 2^20); without a launch that unpacks the result and one per scan it takes 201, 435, 105.
 template <int RITER>
 __global__ __launch_bounds__(256) void radix_scatter_kernel(const uint2* __restrict__ in, uint2* __restrict__ out, const SelInfo* __restrict__ info,
                                                             int shift, const uint32_t* __restrict__ table, int n_blocks,
