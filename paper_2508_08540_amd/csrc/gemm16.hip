@@ -12,6 +12,8 @@
 // with a row pitch of 96 bytes (measured: the 16-byte operand reads, 16 rows x 4 k groups per instruction, run at the full LDS
 // rate when the pitch is 32 bytes more than a multiple of 64, at half of it with an odd number of 16-byte units such as 80 or 144
 // bytes); the next two steps' global loads are in flight in registers while the matrix instructions run.
+#include <type_traits>
+
 #include "act.h"
 #include "kernels.h"
 
@@ -373,7 +375,7 @@ __global__ __launch_bounds__(256, AK ? 2 : 3) void gemm16_kernel(Gemm16Desc d) {
 // frees the buffer read a step ago.  Rows are 64 bytes; piece c (16 bytes) of a row sits at place c ^ gd16_place(row),
 // so that the 16-byte operand reads, 16 rows x 4 pieces, are free of bank conflicts.  Rows past the end are clamped to the last one (they only
 // feed outputs that are never stored), pieces past the end of K are zeroed in LDS in the last step.
-#define GD16_STAGES 3
+#define GD16_STAGES 3   // the last two steps' waits count on it
 typedef __attribute__((address_space(1))) const void gd16_global_ptr;
 typedef __attribute__((address_space(3))) void gd16_lds_ptr;
 
@@ -748,6 +750,16 @@ __global__ __launch_bounds__(256, gd16_waves(gd16_runs(AK, WMB), WMB * WNB)) voi
     auto load16 = [&](const bf16_t* src, u32x4* dst) {
         __builtin_amdgcn_global_load_lds((gd16_global_ptr*)src, (gd16_lds_ptr*)dst, 16, 0, 0);
     };
+    auto advance = [&]() {
+        A += adv_a;
+        B += adv_b;
+        seg_left -= G16_K;
+        if (seg_left == 0) {
+            seg_left = d.k_seg;
+            A += d.sa_seg - (AK ? (int64_t)d.k_seg * d.lda : (int64_t)d.k_seg);
+            B += d.sb_seg - (BK ? (int64_t)d.k_seg * d.ldb : (int64_t)d.k_seg);
+        }
+    };
     auto request = [&](int step, int buf) {
         u32x4* base = gd16_lds + buf * STAGE;
         if (tail && step == steps - 1) {
@@ -774,14 +786,7 @@ __global__ __launch_bounds__(256, gd16_waves(gd16_runs(AK, WMB), WMB * WNB)) voi
         for (int i = 0; i < LA; ++i) load16(A + offa[i], base + (4 * i + wave) * 64);
 #pragma unroll
         for (int i = 0; i < LB; ++i) load16(B + offb[i], base + TM * 4 + (4 * i + wave) * 64);
-        A += adv_a;
-        B += adv_b;
-        seg_left -= G16_K;
-        if (seg_left == 0) {
-            seg_left = d.k_seg;
-            A += d.sa_seg - (AK ? (int64_t)d.k_seg * d.lda : (int64_t)d.k_seg);
-            B += d.sb_seg - (BK ? (int64_t)d.k_seg * d.ldb : (int64_t)d.k_seg);
-        }
+        advance();
     };
 
     f32x4 acc[WMB][WNB];
@@ -801,16 +806,32 @@ __global__ __launch_bounds__(256, gd16_waves(gd16_runs(AK, WMB), WMB * WNB)) voi
     const int f128 = (r >> 2) | ((g & 1) << 2), f64 = (r >> 3) | ((g & 1) << 1);   // as in gd16_slot
     const int fa = TM >= 128 ? f128 : f64, fb = TN >= 128 ? f128 : f64;
     const int ta = kline * TM * 2 + 8 * (r & 3), tb = TM * 64 + kline * TN * 2 + 8 * (r & 3);   // bytes
-    auto compute = [&](int buf) {
+    // One step out of LDS buffer `buf`; with LOAD it also requests a whole step into buffer `to`.  The order is fixed (the compiler's own
+    // reads two blocks, waits for them, multiplies, and so on, and puts the loads in front): the operands of AHEAD block rows are
+    // read first, those of the others AHEAD blocks before their use, and the load instructions, which the address unit takes 16
+    // clocks each for, go out one by one between the matrix instructions.  Transposing reads come with their wait, so an AK step
+    // reads all of them; its 256-row tile keeps the loads in front (32 000 x 512 over 8192 tokens: 226 us, 251 with the loads between).
+    // 65 536 x 32 000 x 512 with statistics 2453 -> 2256 us, 8192 x 32 000 x 512 349 -> 307, 512 x 2048 over 8192 tokens 42 -> 38.
+    auto multiply = [&](int buf, auto load, int to) {
+        constexpr bool LOAD = decltype(load)::value, FRONT = AK && WMB >= 8;
+        constexpr int AHEAD = !AK && WMB >= 8 ? 3 : WMB;
         const u32x4* st = gd16_lds + buf * STAGE;
         const uint32_t sb = (uint32_t)(uintptr_t)(gd16_lds_ptr*)st;
+        u32x4* base = gd16_lds + to * STAGE;
+        auto piece = [&](int p) {
+            if (p < LA) load16(A + offa[p], base + (4 * p + wave) * 64);
+            else if (p < LA + LB) load16(B + offb[p - LA], base + TM * 4 + (4 * (p - LA) + wave) * 64);
+        };
         u32x4 a[WMB], b[WNB];
-        if constexpr (!AK)
+        if constexpr (LOAD && FRONT)
 #pragma unroll
-            for (int t = 0; t < WMB; ++t) a[t] = st[ra + 64 * t];
+            for (int p = 0; p < LA + LB; ++p) piece(p);
         if constexpr (!BK)
 #pragma unroll
             for (int t = 0; t < WNB; ++t) b[t] = st[rb + 128 * (t >> 1) + 16 * (t & 1)];
+        if constexpr (!AK)
+#pragma unroll
+            for (int t = 0; t < AHEAD; ++t) a[t] = st[ra + 64 * t];
         if constexpr (BK) {
             constexpr int NA = AK ? WMB : 0;
             uint32_t at[WNB + NA];
@@ -825,25 +846,21 @@ __global__ __launch_bounds__(256, gd16_waves(gd16_runs(AK, WMB), WMB * WNB)) voi
 #pragma unroll
             for (int t = 0; t < NA; ++t) a[t] = x[WNB + t];
         }
+        static_assert(LA + LB <= WMB, "a load per block row");
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int mt = 0; mt < WMB; ++mt)
+        for (int mt = 0; mt < WMB; ++mt) {
+            if (!AK && mt + AHEAD < WMB) a[mt + AHEAD] = st[ra + 64 * (mt + AHEAD)];
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int nt = 0; nt < WNB; ++nt)
                 acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_v, b[nt]), __builtin_bit_cast(bf16x8_v, a[mt]), acc[mt][nt], 0, 0, 0);
+            if constexpr (LOAD && !FRONT) piece(mt);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (LOAD) advance();
     };
-#pragma unroll
-    for (int i = 0; i < GD16_STAGES - 1; ++i)
-        if (i < steps) request(i, i);
-    int buf = 0;
-    for (int i = 0; i < steps; ++i) {
-        // while a later step is still to be requested the GD16_STAGES - 2 youngest steps may stay in flight
-        if (i + GD16_STAGES - 1 < steps) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((GD16_STAGES - 2) * (LA + LB)) : "memory");
-        else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-        if (i + GD16_STAGES - 1 < steps) request(i + GD16_STAGES - 1, buf == 0 ? GD16_STAGES - 1 : buf - 1);
-        compute(buf);
-        buf = buf + 1 == GD16_STAGES ? 0 : buf + 1;
+    auto end_of_run = [&](int i) {
         if constexpr (RUNS) {
             if ((i + 1) % G16_RUN == 0) {
 #pragma unroll
@@ -855,6 +872,30 @@ __global__ __launch_bounds__(256, gd16_waves(gd16_runs(AK, WMB), WMB * WNB)) voi
                     }
             }
         }
+    };
+#pragma unroll
+    for (int i = 0; i < GD16_STAGES - 1; ++i)
+        if (i < steps) request(i, i);
+    int buf = 0, i = 0;
+    // while whole steps are still to be requested; the GD16_STAGES - 2 youngest may stay in flight
+    for (const int steady = steps - (GD16_STAGES - 1) - (tail ? 1 : 0); i < steady; ++i) {
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((GD16_STAGES - 2) * (LA + LB)) : "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        multiply(buf, std::true_type{}, buf == 0 ? GD16_STAGES - 1 : buf - 1);
+        buf = buf + 1 == GD16_STAGES ? 0 : buf + 1;
+        end_of_run(i);
+    }
+    for (; i < steps; ++i) {
+        // a tail is requested by fewer instructions: no counting with it
+        if (!tail && i + 1 < steps) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(LA + LB) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        if (i + GD16_STAGES - 1 < steps) request(i + GD16_STAGES - 1, buf == 0 ? GD16_STAGES - 1 : buf - 1);
+        multiply(buf, std::false_type{}, 0);
+        buf = buf + 1 == GD16_STAGES ? 0 : buf + 1;
+        end_of_run(i);
     }
     if constexpr (RUNS)
 #pragma unroll
