@@ -154,6 +154,9 @@ __device__ __forceinline__ void g16_tile_of_block(int& tile_x, int& tile_y) {
     tile_x = id - tile_y * nx;
 }
 
+// element (m, n) of the bf16 outputs: panels of 32 columns c16_panel apart (row-major: 32 apart)
+__device__ __forceinline__ int64_t g16_at16(const Gemm16Desc& d, int m, int n) { return (n >> 5) * d.c16_panel + (int64_t)m * d.ldc16 + (n & 31); }
+
 // Stores a wave's 64 x 64 block; lane (r, g) holds acc[mt][nt][i] = C[m_base + 16 mt + r][n_base + 16 nt + 4 g + i].
 template <bool VEC, bool GELU>
 __device__ __forceinline__ void g16_store_block(const Gemm16Desc& d, const f32x4 (&acc)[4][4], int m_base, int n_base, float* C, bf16_t* C16,
@@ -174,12 +177,12 @@ __device__ __forceinline__ void g16_store_block(const Gemm16Desc& d, const f32x4
                     if (R) v += *reinterpret_cast<const f32x4*>(R + at);
                 }
                 if (C) *reinterpret_cast<f32x4*>(C + at) = v;
-                if (C16) *reinterpret_cast<u32x2*>(C16 + at) = u32x2{pack2_bf16(v[0], v[1]), pack2_bf16(v[2], v[3])};
+                if (C16) *reinterpret_cast<u32x2*>(C16 + g16_at16(d, m, n)) = u32x2{pack2_bf16(v[0], v[1]), pack2_bf16(v[2], v[3])};
                 if (GELU && G16) {
                     f32x4 q;
 #pragma unroll
                     for (int i = 0; i < 4; ++i) q[i] = gelu_for_bf16(v[i]);
-                    *reinterpret_cast<u32x2*>(G16 + at) = u32x2{pack2_bf16(q[0], q[1]), pack2_bf16(q[2], q[3])};
+                    *reinterpret_cast<u32x2*>(G16 + g16_at16(d, m, n)) = u32x2{pack2_bf16(q[0], q[1]), pack2_bf16(q[2], q[3])};
                 }
             } else {
 #pragma unroll
@@ -193,8 +196,8 @@ __device__ __forceinline__ void g16_store_block(const Gemm16Desc& d, const f32x4
                             if (R) v += R[at];
                         }
                         if (C) C[at] = v;
-                        if (C16) C16[at] = (bf16_t)(pack2_bf16(v, 0.f) & 0xffffu);
-                        if (GELU && G16) G16[at] = (bf16_t)(pack2_bf16(gelu_for_bf16(v), 0.f) & 0xffffu);
+                        if (C16) C16[g16_at16(d, m, n + i)] = (bf16_t)(pack2_bf16(v, 0.f) & 0xffffu);
+                        if (GELU && G16) G16[g16_at16(d, m, n + i)] = (bf16_t)(pack2_bf16(gelu_for_bf16(v), 0.f) & 0xffffu);
                     }
                 }
             }
@@ -354,8 +357,9 @@ __global__ __launch_bounds__(256, AK ? 2 : 3) void gemm16_kernel(Gemm16Desc d) {
     const bool plain = d.splits > 1;   // partial sums go out as they are; the reduction applies the epilogue
     const int64_t zoff = z1 * d.sc1 + z2 * d.sc2;
     float* C = plain ? d.part + ((int64_t)z * d.splits + split) * d.part_stride : d.C ? d.C + zoff : nullptr;
-    bf16_t* C16 = (plain || !d.C16) ? nullptr : d.C16 + zoff;
-    bf16_t* G16 = (plain || !d.G16) ? nullptr : d.G16 + zoff;
+    const int64_t zoff16 = z1 * d.sc1_16 + z2 * d.sc2_16;
+    bf16_t* C16 = (plain || !d.C16) ? nullptr : d.C16 + zoff16;
+    bf16_t* G16 = (plain || !d.G16) ? nullptr : d.G16 + zoff16;
     const float* R = (plain || !d.R) ? nullptr : d.R + zoff;
     const float* bias = (plain || !d.bias) ? nullptr : d.bias + z1 * d.sbias1;
     const int ldc = plain ? d.N : d.ldc;
@@ -435,13 +439,14 @@ __device__ __forceinline__ void gd16_store(const Gemm16Desc& d, float alpha, f32
                     *reinterpret_cast<f32x4*>(C + at0) = v0;
                     *reinterpret_cast<f32x4*>(C + at1) = v1;
                 }
+                const int64_t at16 = g16_at16(d, m_base + 16 * (m4 + k) + r, n_base + 32 * p) + (PAIRED ? 8 * g : 4 * g);
                 auto store16 = [&](bf16_t* dst, const f32x4& q0, const f32x4& q1) {
                     const u32x4 w = {pack2_bf16(q0[0], q0[1]), pack2_bf16(q0[2], q0[3]), pack2_bf16(q1[0], q1[1]), pack2_bf16(q1[2], q1[3])};
                     if (PAIRED) {
-                        *reinterpret_cast<u32x4*>(dst + at0) = w;
+                        *reinterpret_cast<u32x4*>(dst + at16) = w;
                     } else {
-                        *reinterpret_cast<u32x2*>(dst + at0) = u32x2{w[0], w[1]};
-                        *reinterpret_cast<u32x2*>(dst + at1) = u32x2{w[2], w[3]};
+                        *reinterpret_cast<u32x2*>(dst + at16) = u32x2{w[0], w[1]};
+                        *reinterpret_cast<u32x2*>(dst + at16 + 16) = u32x2{w[2], w[3]};
                     }
                 };
                 if (C16) store16(C16, v0, v1);
@@ -481,8 +486,8 @@ __device__ __forceinline__ void gd16_store_edge(const Gemm16Desc& d, float alpha
                         if (R) v += R[at];
                     }
                     if (C) C[at] = v;
-                    if (C16) C16[at] = (bf16_t)(pack2_bf16(v, 0.f) & 0xffffu);
-                    if (GELU && G16) G16[at] = (bf16_t)(pack2_bf16(gelu_for_bf16(v), 0.f) & 0xffffu);
+                    if (C16) C16[g16_at16(d, m, n)] = (bf16_t)(pack2_bf16(v, 0.f) & 0xffffu);
+                    if (GELU && G16) G16[g16_at16(d, m, n)] = (bf16_t)(pack2_bf16(gelu_for_bf16(v), 0.f) & 0xffffu);
                 }
             }
     }
@@ -591,7 +596,7 @@ __device__ __forceinline__ void gd16_ce_grad(const Gemm16Desc& d, const f32x4 (&
             }
             // N is a multiple of 8: a lane's eight columns are all there or none of them
             if (m < d.M && n < d.N)
-                *reinterpret_cast<u32x4*>(C16 + (int64_t)m * d.ldc + n) = u32x4{pack2_bf16(q[0], q[1]), pack2_bf16(q[2], q[3]), pack2_bf16(q[4], q[5]), pack2_bf16(q[6], q[7])};
+                *reinterpret_cast<u32x4*>(C16 + g16_at16(d, m, n)) = u32x4{pack2_bf16(q[0], q[1]), pack2_bf16(q[2], q[3]), pack2_bf16(q[4], q[5]), pack2_bf16(q[6], q[7])};
             __builtin_amdgcn_sched_barrier(0);   // one piece's temporaries at a time
         }
     }
@@ -731,21 +736,23 @@ __global__ __launch_bounds__(256, gd16_waves(gd16_runs(AK, WMB), WMB * WNB)) voi
     const int seg0 = d.k_seg ? k_begin / d.k_seg : 0;
     int seg_left = d.k_seg ? d.k_seg - (k_begin - seg0 * d.k_seg) : 0x7fffffff;
     const int k_in_seg = d.k_seg ? k_begin - seg0 * d.k_seg : k_begin;
-    const bf16_t* A = d.A + z1 * d.sa1 + z2 * d.sa2 + seg0 * d.sa_seg + (AK ? (int64_t)k_in_seg * d.lda + m0 : (int64_t)m0 * d.lda + k_in_seg);
-    const bf16_t* B = d.B + z1 * d.sb1 + z2 * d.sb2 + seg0 * d.sb_seg + (BK ? (int64_t)k_in_seg * d.ldb + n0 : (int64_t)n0 * d.ldb + k_in_seg);
-    const int64_t adv_a = AK ? (int64_t)G16_K * d.lda : G16_K, adv_b = BK ? (int64_t)G16_K * d.ldb : G16_K;
+    const bf16_t* A = d.A + z1 * d.sa1 + z2 * d.sa2 + seg0 * d.sa_seg + (AK ? (int64_t)k_in_seg * d.lda + (m0 >> 5) * d.a_panel : (int64_t)m0 * d.lda + (k_in_seg >> 5) * d.a_panel);
+    const bf16_t* B = d.B + z1 * d.sb1 + z2 * d.sb2 + seg0 * d.sb_seg + (BK ? (int64_t)k_in_seg * d.ldb + (n0 >> 5) * d.b_panel : (int64_t)n0 * d.ldb + (k_in_seg >> 5) * d.b_panel);
+    const int64_t adv_a = AK ? (int64_t)G16_K * d.lda : d.a_panel, adv_b = BK ? (int64_t)G16_K * d.ldb : d.b_panel;
     uint32_t offa[LA], offb[LB];
 #pragma unroll
     for (int i = 0; i < LA; ++i) {
         int row, k;
         gd16_slot<AK, false, TM>((4 * i + wave) * 64 + lane, row, k);
-        offa[i] = AK ? (uint32_t)(k * d.lda + min(row, ((d.M - 1) & ~7) - m0)) : (uint32_t)(min(row, d.M - 1 - m0) * d.lda + k);
+        if (AK) row = min(row, ((d.M - 1) & ~7) - m0);
+        offa[i] = AK ? (uint32_t)(k * d.lda + (row >> 5) * (int)d.a_panel + (row & 31)) : (uint32_t)(min(row, d.M - 1 - m0) * d.lda + k);
     }
 #pragma unroll
     for (int i = 0; i < LB; ++i) {
         int row, k;
         gd16_slot<BK, true, TN>((4 * i + wave) * 64 + lane, row, k);
-        offb[i] = BK ? (uint32_t)(k * d.ldb + min(row, ((d.N - 1) & ~7) - n0)) : (uint32_t)(min(row, (EPI == 3 ? d.n_valid : d.N) - 1 - n0) * d.ldb + k);
+        if (BK) row = min(row, ((d.N - 1) & ~7) - n0);
+        offb[i] = BK ? (uint32_t)(k * d.ldb + (row >> 5) * (int)d.b_panel + (row & 31)) : (uint32_t)(min(row, (EPI == 3 ? d.n_valid : d.N) - 1 - n0) * d.ldb + k);
     }
     auto load16 = [&](const bf16_t* src, u32x4* dst) {
         __builtin_amdgcn_global_load_lds((gd16_global_ptr*)src, (gd16_lds_ptr*)dst, 16, 0, 0);
@@ -756,8 +763,8 @@ __global__ __launch_bounds__(256, gd16_waves(gd16_runs(AK, WMB), WMB * WNB)) voi
         seg_left -= G16_K;
         if (seg_left == 0) {
             seg_left = d.k_seg;
-            A += d.sa_seg - (AK ? (int64_t)d.k_seg * d.lda : (int64_t)d.k_seg);
-            B += d.sb_seg - (BK ? (int64_t)d.k_seg * d.ldb : (int64_t)d.k_seg);
+            A += d.sa_seg - (AK ? (int64_t)d.k_seg * d.lda : (d.k_seg >> 5) * d.a_panel);
+            B += d.sb_seg - (BK ? (int64_t)d.k_seg * d.ldb : (d.k_seg >> 5) * d.b_panel);
         }
     };
     auto request = [&](int step, int buf) {
@@ -906,8 +913,9 @@ __global__ __launch_bounds__(256, gd16_waves(gd16_runs(AK, WMB), WMB * WNB)) voi
     const bool plain = d.splits > 1;   // partial sums go out as they are; the reduction applies the epilogue
     const int64_t zoff = z1 * d.sc1 + z2 * d.sc2;
     float* C = plain ? d.part + ((int64_t)z * d.splits + split) * d.part_stride : d.C ? d.C + zoff : nullptr;
-    bf16_t* C16 = (plain || !d.C16) ? nullptr : d.C16 + zoff;
-    bf16_t* G16 = (plain || !d.G16) ? nullptr : d.G16 + zoff;
+    const int64_t zoff16 = z1 * d.sc1_16 + z2 * d.sc2_16;
+    bf16_t* C16 = (plain || !d.C16) ? nullptr : d.C16 + zoff16;
+    bf16_t* G16 = (plain || !d.G16) ? nullptr : d.G16 + zoff16;
     const float* R = (plain || !d.R) ? nullptr : d.R + zoff;
     const float* bias = (plain || !d.bias) ? nullptr : d.bias + z1 * d.sbias1;
     const int ldc = plain ? d.N : d.ldc;
@@ -942,16 +950,28 @@ int launch_gemm16(hipStream_t s, Gemm16Desc d) {
     d.splits = (d.K + k_chunk - 1) / k_chunk;
     d.k_chunk = k_chunk;
     d.part_stride = (int64_t)d.M * d.N;
+    const bool panels = d.a_panel || d.b_panel;
+    // row-major: the 32 columns of a step or of a block are 32 elements further
+    if (d.a_panel == 0) d.a_panel = 32;
+    else d.lda = 32;
+    if (d.b_panel == 0) d.b_panel = 32;
+    else d.ldb = 32;
+    if (d.ldc16 == 0) {
+        d.ldc16 = d.ldc;
+        d.sc1_16 = d.sc1;
+        d.sc2_16 = d.sc2;
+    }
+    if (d.c16_panel == 0) d.c16_panel = 32;
     auto al = [](const void* p, int bytes) { return p == nullptr || (reinterpret_cast<uintptr_t>(p) & (bytes - 1)) == 0; };
     d.a_vec = (al(d.A, 16) && d.lda % 8 == 0 && d.sa1 % 8 == 0 && d.sa2 % 8 == 0) ? 1 : 0;
     d.b_vec = (al(d.B, 16) && d.ldb % 8 == 0 && d.sb1 % 8 == 0 && d.sb2 % 8 == 0) ? 1 : 0;
-    d.c_vec = (al(d.C, 16) && al(d.R, 16) && al(d.bias, 16) && al(d.C16, 8) && al(d.G16, 8) && d.ldc % 4 == 0 && d.sc1 % 4 == 0 && d.sc2 % 4 == 0 && d.sbias1 % 4 == 0) ? 1 : 0;
+    d.c_vec = (al(d.C, 16) && al(d.R, 16) && al(d.bias, 16) && al(d.C16, 8) && al(d.G16, 8) && d.ldc % 4 == 0 && d.ldc16 % 4 == 0 && d.c16_panel % 4 == 0 && d.sc1_16 % 4 == 0 && d.sc2_16 % 4 == 0 && d.sc1 % 4 == 0 && d.sc2 % 4 == 0 && d.sbias1 % 4 == 0) ? 1 : 0;
     const bool half = d.C16 || d.G16;
-    d.c_vec8 = (d.c_vec && al(d.C16, 16) && al(d.G16, 16) && (!half || (d.ldc % 8 == 0 && d.sc1 % 8 == 0 && d.sc2 % 8 == 0))) ? 1 : 0;
+    d.c_vec8 = (d.c_vec && al(d.C16, 16) && al(d.G16, 16) && (!half || (d.ldc16 % 8 == 0 && d.c16_panel % 8 == 0 && d.sc1_16 % 8 == 0 && d.sc2_16 % 8 == 0))) ? 1 : 0;
     // straight into LDS: 16-byte pieces of both factors (whole pieces along a contiguous K), 32-bit offsets inside a tile
     const bool direct = d.a_vec && d.b_vec && d.sa_seg % 8 == 0 && d.sb_seg % 8 == 0 && ((d.a_kmajor && d.b_kmajor) || (!d.a_kmajor && d.K % 8 == 0)) &&
-                        (int64_t)256 * d.lda < (int64_t(1) << 30) && (int64_t)256 * d.ldb < (int64_t(1) << 30);
-    if ((d.k_seg || d.ce_rows || d.gelu_part) && !direct) return BLS_EUNSUPPORTED;   // gemm16_kernel has none of the three
+                        (int64_t)256 * d.lda + 8 * d.a_panel < (int64_t(1) << 30) && (int64_t)256 * d.ldb + 8 * d.b_panel < (int64_t(1) << 30);
+    if ((d.k_seg || d.ce_rows || d.gelu_part || panels) && !direct) return BLS_EUNSUPPORTED;   // gemm16_kernel takes none of the four
     if (direct) {
         const int z = d.batch * d.splits;
         const int64_t t84 = (int64_t)((d.M + 255) / 256) * ((d.N + 127) / 128) * z, t44 = (int64_t)((d.M + 127) / 128) * ((d.N + 127) / 128) * z;

@@ -359,6 +359,12 @@ struct Gemm16Desc {
     int batch, inner, splits;
     int64_t sa1, sa2, sb1, sb2, sc1, sc2;
     int64_t sbias1;   // floats between the bias vectors of consecutive z1 (unsplit products only)
+    // Panel layout [width / 32][rows][32] of a bf16 matrix: elements between its panels (0: row-major).  The pitch lda / ldb is then
+    // 32, and factors need 16-byte bases and strides (the launcher refuses others).  The bf16 outputs C16 and G16 may have a layout of their own: ldc16 > 0 is
+    // their pitch, c16_panel (0: row-major) the distance of their panels, sc1_16 / sc2_16 their batch strides.
+    int64_t a_panel, b_panel, c16_panel;
+    int ldc16;
+    int64_t sc1_16, sc2_16;
     // k_seg, ce_rows and gelu_part need 16-byte rows (16-byte bases, pitches and strides of both factors, K % 8 == 0 where a
     // factor is row-major); the launcher refuses others
     int k_seg;        // > 0 (a multiple of 32): the contraction runs over K / k_seg pairs of matrices
@@ -396,8 +402,22 @@ struct FixRangeTable {
     int n;
     FixRange r[FIX_MAX_RANGES];
 };
-void launch_embed(hipStream_t s, const int32_t* tokens, int64_t T, int L, int D, const float* tok, const float* pos, float* h, uint16_t* h16);
+// `panel` of a bf16 output: elements between its 32-column panels [rows][32] (0: row-major)
+void launch_embed(hipStream_t s, const int32_t* tokens, int64_t T, int L, int D, const float* tok, const float* pos, float* h, uint16_t* h16,
+                  int64_t panel);
 void launch_to_bf16(hipStream_t s, const float* in, uint16_t* out, int64_t n);
+// Matrices of a vector (off; rows x cols, cols % 32 == 0) as bf16 panels [cols / 32][rows_pad][32] at the same offset of another one;
+// rows past the end are zeros.
+#define PANEL_TABLE_MAX 64
+struct PanelJob {
+    int64_t off;
+    int rows, rows_pad, cols;
+};
+struct PanelTable {
+    PanelJob j[PANEL_TABLE_MAX];
+    int n;
+};
+void launch_to_bf16_panels(hipStream_t s, const PanelTable& tab, const float* in, uint16_t* out);
 void launch_embed_grad(hipStream_t s, const int32_t* tokens, int64_t T, int D, const float* dh, fixsum_t* acc_tok);
 // Column sums in two halves, the second half of many of them in one launch: partial sums of row chunks land in one
 // buffer (part_off), the table kernel folds each job's rows in a fixed order into out[out_off ..].
@@ -413,25 +433,27 @@ struct ColsumTable {
 int launch_colsum_partial(hipStream_t s, const float* X, int64_t M, int N, float* part);
 void launch_colsum_table(hipStream_t s, const ColsumTable& tab, const float* part, float* out);
 int launch_layernorm_bwd_partial(hipStream_t s, const float* dy, const float* x, const float* stats, int64_t T, int D, const float* g, float* dx,
-                                 uint16_t* dx16, float* part);
+                                 uint16_t* dx16, int64_t panel, float* part);
 size_t colsum_partial_floats(int64_t M, int N);
 void launch_colsum_tokens(hipStream_t s, const float* X, int64_t M, int N, float* part, float* out);
 void launch_fix_finalize(hipStream_t s, const FixRangeTable& tab, fixsum_t* acc, float* grad);
-void launch_layernorm(hipStream_t s, const float* x, int64_t T, int D, const float* g, const float* b, float* y, uint16_t* y16, float* stats);
+void launch_layernorm(hipStream_t s, const float* x, int64_t T, int D, const float* g, const float* b, float* y, uint16_t* y16,
+                      int64_t panel, float* stats);
 size_t layernorm_bwd_partial_floats(int64_t T, int D);
 void launch_layernorm_bwd(hipStream_t s, const float* dy, const float* x, const float* stats, int64_t T, int D, const float* g, float* dx,
                           uint16_t* dx16, float* part, float* dgb);
 // Fused self-attention with bf16 factors for short sequences (L <= 128, L % 8 == 0, dh 32 or 64): ctx = softmax(alpha q k^T) v per
-// (sample, head); P / P16 (nullable) keep the probabilities as [B][H][L][L].  Returns false, having launched nothing, for
+// (sample, head), rows of ctx ldc apart and, with c_panel, in panels of 32 columns; P / P16 (nullable) keep the probabilities as [B][H][L][L].  Returns false, having launched nothing, for
 // anything else.
 bool launch_attention16(hipStream_t s, const uint16_t* q, const uint16_t* k, const uint16_t* v, int ld, int B, int H, int L, int dh, float alpha,
-                        uint16_t* ctx, int ldc, float* P, uint16_t* P16);
-// Its backward pass from dctx (bf16) and the fp32 probabilities: dq, dk, dv as fp32 and bf16, same shapes and limits.
+                        uint16_t* ctx, int ldc, int64_t c_panel, float* P, uint16_t* P16);
+// Its backward pass from dctx (bf16) and the fp32 probabilities: dq, dk, dv as fp32 and bf16, same shapes and limits; with g_panel the bf16
+// gradients are in panels of 32 columns.
 // colsum (optional) takes partial column sums for the bias gradients: three [4 B][H dh] arrays (dq, dk, dv in that order), row
 // 4 b + w = the sum over the rows of sample b that wave w of its workgroups owned.
 bool launch_attention16_bwd(hipStream_t s, const uint16_t* q, const uint16_t* k, const uint16_t* v, const uint16_t* dctx, const float* P, int ld, int B,
                             int H, int L, int dh, float alpha, float* dq, float* dk, float* dv, uint16_t* dq16, uint16_t* dk16, uint16_t* dv16,
-                            float* colsum);
+                            int64_t g_panel, float* colsum);
 void launch_softmax_rows(hipStream_t s, float* sc, uint16_t* p16, bool store_f32, int64_t rows, int n);
 void launch_softmax_bwd_rows(hipStream_t s, float* dp, const float* p, uint16_t* ds16, int64_t rows, int n, float scale);
 void launch_gelu_bwd(hipStream_t s, float* dg, const float* u, uint16_t* du16, int64_t n);

@@ -36,6 +36,7 @@ int score_chunk(const bls_model* m, int64_t N) {
 struct Mat {
     float* f = nullptr;
     uint16_t* h = nullptr;
+    int64_t panel = 0;   // h in panels of 32 columns, this many elements apart (0: row-major)
 };
 
 struct LayerAct {
@@ -50,6 +51,12 @@ struct SeqScratch {
     // gradient comes from a second pass over the vocabulary projection (268 Gflop instead of a 1 GB round trip per 8192 tokens
     // of a 32 000-word vocabulary), and the GELU derivative rides in the epilogue of the product before it
     bool lean = false;
+    // Lean with widths (also a head's) that are multiples of 32: bf16 factors of products are kept in panels of 32 columns,
+    // [width / 32][rows][32].  A step of a row-major factor (32 values of K for the rows of a tile) is then one stretch of
+    // memory and one of a k-major factor whole cache lines too, where a row-major matrix gives half a line per row and step.
+    // Loops alone, one row-major layout against panels: 65 536 x 32 000 x 512 1.84 -> 1.65 ms, 65 536 x 512 x 2048 134 -> 109 us.
+    // q, k, v and the gradient of the attention output, which attention reads a row at a time, stay row-major.
+    bool panels = false;
     int ldv = 0;                    // row pitch of the logits' gradient
     int32_t *tok, *tgt;
     uint16_t* w16;                  // bf16 copy of the parameter vector (bf16 mode)
@@ -119,13 +126,19 @@ SeqScratch carve(Carver& c, const bls_model* m, int B, bool train) {
     SeqScratch s{};
     const bool bf = s.bf = m->desc.act_dtype == BLS_ACT_BF16;
     const bool lean = s.lean = bf && D % 8 == 0 && F % 8 == 0;
-    s.ldv = lean ? (V + 7) & ~7 : V;
+    const bool panels = s.panels = lean && D % 32 == 0 && F % 32 == 0 && (D / H) % 32 == 0;
+    s.ldv = panels ? (V + 31) & ~31 : lean ? (V + 7) & ~7 : V;
+    auto take_factor = [&](Kind kind, int64_t width) {   // a [T][width] factor of products
+        Mat t = take(c, bf, kind, T * width);
+        t.panel = panels ? T * 32 : 0;
+        return t;
+    };
     s.tok = c.take<int32_t>(T);
     s.tgt = c.take<int32_t>(T);
-    s.w16 = bf ? c.take<uint16_t>(m->num_params + 8 * D) : nullptr;   // eight more rows of the vocabulary projection, zeros: its padding
+    s.w16 = bf ? c.take<uint16_t>(m->num_params + 32 * D) : nullptr;   // more rows of the vocabulary projection, zeros: its padding
     const int sets = train ? layers : 1;
     s.x.resize(layers + 1);
-    for (int l = 0; l <= layers; ++l) s.x[l] = (train || l < 2) ? take(c, bf, BOTH, T * D) : s.x[l - 2];
+    for (int l = 0; l <= layers; ++l) s.x[l] = (train || l < 2) ? take_factor(BOTH, D) : s.x[l - 2];
     s.act.resize(layers);
     for (int l = 0; l < layers; ++l) {
         if (l >= sets) {
@@ -135,12 +148,12 @@ SeqScratch carve(Carver& c, const bls_model* m, int B, bool train) {
         LayerAct& a = s.act[l];
         take3(c, bf, FACTOR_ONLY, T * D, a.q, a.k, a.v);
         a.p = take(c, bf, BOTH, PP);
-        a.ctx = take(c, bf, FACTOR_ONLY, T * D);
+        a.ctx = take_factor(FACTOR_ONLY, D);
         a.r1 = c.take<float>(T * D);
         a.st1 = c.take<float>(2 * T);
-        a.h1 = take(c, bf, BOTH, T * D);
+        a.h1 = take_factor(BOTH, D);
         a.u = c.take<float>(T * F);
-        a.g = take(c, bf, FACTOR_ONLY, T * F);
+        a.g = take_factor(FACTOR_ONLY, F);
         a.r2 = c.take<float>(T * D);
         a.st2 = c.take<float>(2 * T);
     }
@@ -160,7 +173,10 @@ SeqScratch carve(Carver& c, const bls_model* m, int B, bool train) {
         }
     s.part_main = train ? c.take<float>(part ? part : 1) : nullptr;
     if (!train) return s;
-    if (bf) s.dlogits.h = c.take<uint16_t>(T * s.ldv);
+    if (bf) {
+        s.dlogits.h = c.take<uint16_t>(T * s.ldv);
+        s.dlogits.panel = panels ? T * 32 : 0;
+    }
     else s.dlogits.f = s.logits;
     s.grad = c.take<float>(m->num_params);
     s.da = c.take<float>(T * D);
@@ -168,10 +184,11 @@ SeqScratch carve(Carver& c, const bls_model* m, int B, bool train) {
     s.ds = take(c, bf, BOTH, PP);
     s.db2.resize(layers); s.db1.resize(layers); s.df.resize(layers); s.dq.resize(layers); s.dk.resize(layers); s.dv.resize(layers);
     for (int l = 0; l < layers; ++l) {
-        s.db2[l] = take(c, bf, BOTH, T * D);
-        s.db1[l] = take(c, bf, BOTH, T * D);
-        s.df[l] = take(c, bf, lean ? FACTOR_ONLY : BOTH, T * F);
+        s.db2[l] = take_factor(BOTH, D);
+        s.db1[l] = take_factor(BOTH, D);
+        s.df[l] = take_factor(lean ? FACTOR_ONLY : BOTH, F);
         take3(c, bf, BOTH, T * D, s.dq[l], s.dk[l], s.dv[l]);
+        s.dq[l].panel = s.dk[l].panel = s.dv[l].panel = panels ? T * 32 : 0;
     }
     part = 0;
     auto need = [&](int M, int N) {
@@ -213,6 +230,7 @@ struct Product {
     bool a_kmajor = false, b_kmajor = false;
     int batch = 1, inner = 1, splits = 1;
     int64_t sa1 = 0, sa2 = 0, sb1 = 0, sb2 = 0, sc1 = 0, sc2 = 0, sbias1 = 0;
+    int64_t sc1_16 = 0, sc2_16 = 0;        // of a bf16 result in panels
     int k_seg = 0;                         // the contraction runs over K / k_seg pairs of matrices
     int64_t sa_seg = 0, sb_seg = 0;
     float alpha = 1.f;
@@ -242,6 +260,12 @@ void multiply(bls_ctx* ctx, hipStream_t st, SeqScratch* s, const Product& p, int
         d.ce_rows = p.ce_rows; d.ce_scale = p.ce_scale; d.n_valid = p.n_valid;
         d.U = p.U; d.gelu_part = p.gelu_part;
         d.k_seg = p.k_seg; d.sa_seg = p.sa_seg; d.sb_seg = p.sb_seg;
+        d.a_panel = p.A.panel; d.b_panel = p.B.panel;
+        const Mat& half = p.gelu.h ? p.gelu : p.out;   // no product stores both
+        if (half.h && half.panel) {
+            d.c16_panel = half.panel; d.ldc16 = 32;
+            d.sc1_16 = p.sc1_16; d.sc2_16 = p.sc2_16;
+        }
         rc = launch_gemm16(st, d);
     } else {
         GemmDesc d{};
@@ -267,13 +291,14 @@ struct Net {
     SeqScratch* s;
     int B;
 
-    Mat weight(int64_t off) const { return Mat{const_cast<float*>(params) + off, s->bf ? s->w16 + off : nullptr}; }
+    // weight matrix of n_out rows
+    Mat weight(int64_t off, int n_out) const { return Mat{const_cast<float*>(params) + off, s->bf ? s->w16 + off : nullptr, s->panels ? (int64_t)n_out * 32 : 0}; }
 
     // y[T][n_out] = x[T][n_in] W^T + b (+ R); gelu (optional) takes gelu(y)
     void linear(Mat x, int64_t T, int n_in, int64_t w_off, int64_t b_off, int n_out, Mat y, const float* R = nullptr, Mat gelu = Mat{}) const {
         Product p;
         p.A = x; p.lda = n_in;
-        p.B = weight(w_off); p.ldb = n_in;
+        p.B = weight(w_off, n_out); p.ldb = n_in;
         p.out = y; p.gelu = gelu; p.ldc = n_out;
         p.bias = b_off >= 0 ? params + b_off : nullptr;
         p.R = R;
@@ -290,7 +315,7 @@ struct Net {
         const int D = m->enc_D, V = m->enc_V;
         Product p;
         p.A = hf; p.lda = D;
-        p.B = weight(m->enc_head); p.ldb = D;
+        p.B = weight(m->enc_head, s->ldv); p.ldb = D;
         p.ldc = V;
         p.M = (int)T; p.N = V; p.K = D;
         if (s->bf) {
@@ -308,7 +333,7 @@ struct Net {
     void logits_gradient(Mat hf, const int32_t* targets, int64_t T, float scale) const {
         Product p;
         p.A = hf; p.lda = m->enc_D;
-        p.B = weight(m->enc_head); p.ldb = m->enc_D;
+        p.B = weight(m->enc_head, s->ldv); p.ldb = m->enc_D;
         p.out = s->dlogits; p.ldc = s->ldv;
         p.M = (int)T; p.N = s->ldv; p.K = m->enc_D;
         p.ce_targets = targets; p.ce_rows = s->ce_rows; p.ce_scale = scale; p.n_valid = m->enc_V;
@@ -318,8 +343,8 @@ struct Net {
     void gelu_dgrad(Mat dy, int64_t T, int n_out, int64_t w_off, int n_in, Mat du, const float* u, float* part) const {
         Product p;
         p.A = dy; p.lda = n_out;
-        p.B = weight(w_off); p.ldb = n_in; p.b_kmajor = true;
-        p.out = Mat{nullptr, du.h}; p.ldc = n_in;
+        p.B = weight(w_off, n_out); p.ldb = n_in; p.b_kmajor = true;
+        p.out = Mat{nullptr, du.h, du.panel}; p.ldc = n_in;
         p.M = (int)T; p.N = n_in; p.K = n_out;
         p.U = u; p.gelu_part = part;
         multiply(ctx, st, s, p, PROF_GEMM);
@@ -329,7 +354,7 @@ struct Net {
     void linear_dgrad(Mat dy, int64_t T, int n_out, int64_t w_off, int n_in, Mat dx, const float* R = nullptr, int pitch = 0) const {
         Product p;
         p.A = dy; p.lda = pitch ? pitch : n_out;
-        p.B = weight(w_off); p.ldb = n_in; p.b_kmajor = true;
+        p.B = weight(w_off, p.lda); p.ldb = n_in; p.b_kmajor = true;
         p.out = dx; p.ldc = n_in;
         p.R = R;
         p.M = (int)T; p.N = n_in; p.K = p.lda;
@@ -358,7 +383,7 @@ struct Net {
         if (e.wv - e.wk == sw && e.bk - e.bq == sw && e.bv - e.bk == sw && (s->bf ? a.v.h - a.k.h : a.v.f - a.k.f) == so) {
             Product p;
             p.A = x; p.lda = D;
-            p.B = weight(e.wq); p.ldb = D; p.sb1 = sw;
+            p.B = weight(e.wq, D); p.ldb = D; p.sb1 = sw;
             p.out = a.q; p.ldc = D; p.sc1 = so;
             p.bias = params + e.bq; p.sbias1 = sw;
             p.M = (int)T; p.N = D; p.K = D;
@@ -401,7 +426,7 @@ struct Net {
         if (e.wv - e.wk == sw && (s->bf ? dv.h - dk.h : dv.f - dk.f) == sd && rows16) {
             Product p;
             p.A = dq; p.lda = D; p.sa_seg = sd;
-            p.B = weight(e.wq); p.ldb = D; p.b_kmajor = true; p.sb_seg = sw;
+            p.B = weight(e.wq, D); p.ldb = D; p.b_kmajor = true; p.sb_seg = sw;
             p.k_seg = D;
             p.out = dx; p.ldc = D;
             p.R = R;
@@ -428,6 +453,7 @@ struct Net {
         p.A = a; p.a_kmajor = a_kmajor; strides(a_probs, p.lda, p.sa1, p.sa2);
         p.B = b; p.b_kmajor = b_kmajor; strides(b_probs, p.ldb, p.sb1, p.sb2);
         p.out = c; strides(c_probs, p.ldc, p.sc1, p.sc2);
+        p.sc1_16 = (int64_t)L * 32; p.sc2_16 = dh / 32 * c.panel;   // a head's slice is dh / 32 panels
         p.M = L; p.N = N; p.K = K;
         p.batch = B * H; p.inner = H;
         p.alpha = alpha;
@@ -438,7 +464,7 @@ struct Net {
     void forward(const int32_t* tok, bool keep) const {
         const int L = m->enc_L, D = m->enc_D, H = m->enc_H, F = m->enc_F, dh = D / H;
         const int64_t T = (int64_t)B * L;
-        PROF(ctx, PROF_GATHER, launch_embed(st, tok, T, L, D, params + m->enc_tok, params + m->enc_pos, s->x[0].f, s->x[0].h));
+        PROF(ctx, PROF_GATHER, launch_embed(st, tok, T, L, D, params + m->enc_tok, params + m->enc_pos, s->x[0].f, s->x[0].h, s->x[0].panel));
         for (size_t l = 0; l < m->enc_layers.size(); ++l) {
             const EncLayer& e = m->enc_layers[l];
             const LayerAct& a = s->act[l];
@@ -449,7 +475,7 @@ struct Net {
             if (s->bf) {
                 // short sequences: scores, softmax and weighted values of a (sample, head) in one workgroup
                 ProfScope prof_(ctx, PROF_GEMM);
-                fused = launch_attention16(st, a.q.h, a.k.h, a.v.h, D, B, H, L, dh, att, a.ctx.h, D, keep ? a.p.f : nullptr, keep ? a.p.h : nullptr);
+                fused = launch_attention16(st, a.q.h, a.k.h, a.v.h, D, B, H, L, dh, att, a.ctx.h, a.ctx.panel ? 32 : D, a.ctx.panel, keep ? a.p.f : nullptr, keep ? a.p.h : nullptr);
             }
             if (!fused) {
                 // scores into the fp32 probability buffer, softmax in place (kept in fp32 only where something reads it)
@@ -458,22 +484,42 @@ struct Net {
                 attention(a.p, true, false, a.v, false, true, a.ctx, false, dh, L, 1.f);
             }
             linear(a.ctx, T, D, e.wo, e.bo, D, Mat{a.r1, nullptr}, x.f);
-            PROF(ctx, PROF_NORM, launch_layernorm(st, a.r1, T, D, params + e.ln1_g, params + e.ln1_b, a.h1.f, a.h1.h, keep ? a.st1 : nullptr));
+            PROF(ctx, PROF_NORM, launch_layernorm(st, a.r1, T, D, params + e.ln1_g, params + e.ln1_b, a.h1.f, a.h1.h, a.h1.panel, keep ? a.st1 : nullptr));
             // u = h1 W1^T + b1 and g = gelu(u) from one epilogue; scoring does not keep u
             linear(a.h1, T, D, e.w1, e.b1, F, Mat{keep ? a.u : nullptr, nullptr}, nullptr, a.g);
             linear(a.g, T, F, e.w2, e.b2, D, Mat{a.r2, nullptr}, a.h1.f);
-            PROF(ctx, PROF_NORM, launch_layernorm(st, a.r2, T, D, params + e.ln2_g, params + e.ln2_b, s->x[l + 1].f, s->x[l + 1].h, keep ? a.st2 : nullptr));
+            PROF(ctx, PROF_NORM, launch_layernorm(st, a.r2, T, D, params + e.ln2_g, params + e.ln2_b, s->x[l + 1].f, s->x[l + 1].h, s->x[l + 1].panel, keep ? a.st2 : nullptr));
         }
     }
 
     // bf16 copies of everything after the embeddings (the embeddings are only ever looked up)
     void refresh_weight_copies() const {
         if (!s->bf) return;
+        if (s->panels) {
+            const int D = m->enc_D, F = m->enc_F;
+            PanelTable tab;
+            tab.n = 0;
+            auto put = [&](int64_t off, int rows, int rows_pad, int cols) {
+                tab.j[tab.n++] = PanelJob{off, rows, rows_pad, cols};
+                if (tab.n == PANEL_TABLE_MAX) {
+                    PROF(ctx, PROF_UPDATE, launch_to_bf16_panels(st, tab, params, s->w16));
+                    tab.n = 0;
+                }
+            };
+            put(m->enc_head, m->enc_V, s->ldv, D);
+            for (const EncLayer& e : m->enc_layers) {
+                for (int64_t w : {e.wq, e.wk, e.wv, e.wo}) put(w, D, D, D);
+                put(e.w1, F, F, D);
+                put(e.w2, D, D, F);
+            }
+            PROF(ctx, PROF_UPDATE, launch_to_bf16_panels(st, tab, params, s->w16));
+            return;
+        }
         const int64_t first = m->enc_layers[0].wq;
         PROF(ctx, PROF_UPDATE, launch_to_bf16(st, params + first, s->w16 + first, m->num_params - first));
     }
     void clear_weight_padding() const {   // once per call: nothing else writes there (lean: every tensor is a multiple of 8 long)
-        if (s->lean) PROF(ctx, PROF_UPDATE, launch_fill_zero(st, reinterpret_cast<float*>(s->w16 + m->num_params), 4 * m->enc_D));
+        if (s->lean && !s->panels) PROF(ctx, PROF_UPDATE, launch_fill_zero(st, reinterpret_cast<float*>(s->w16 + m->num_params), 4 * m->enc_D));
     }
 };
 
@@ -568,10 +614,10 @@ int seq_local_step(bls_ctx* ctx, const bls_model* m, float* params, float* momen
         push_sums(part - s.cpart, rows, N, N, out_off);
     };
     // layer norm backward; the column sums of its result are the gradient of the bias at bias_off
-    auto layernorm_bwd = [&](const float* dy, const float* xin, const float* stats, int64_t g_off, float* dx, uint16_t* dx16, int64_t bias_off) {
+    auto layernorm_bwd = [&](const float* dy, const float* xin, const float* stats, int64_t g_off, Mat dx, int64_t bias_off) {
         float* part = reserve_sums(layernorm_bwd_partial_floats(T, D));
         int rows = 0;
-        PROF(ctx, PROF_NORM, rows = launch_layernorm_bwd_partial(st, dy, xin, stats, T, D, params + g_off, dx, dx16, part));
+        PROF(ctx, PROF_NORM, rows = launch_layernorm_bwd_partial(st, dy, xin, stats, T, D, params + g_off, dx.f, dx.h, dx.panel, part));
         push_sums(part - s.cpart, rows, 2 * D, 3 * D, g_off);
         push_sums(part - s.cpart + 2 * D, rows, D, 3 * D, bias_off);
     };
@@ -618,7 +664,7 @@ int seq_local_step(bls_ctx* ctx, const bls_model* m, float* params, float* momen
             const Mat x = s.x[l];
             const Mat db2 = s.db2[l], db1 = s.db1[l], df = s.df[l], dq = s.dq[l], dk = s.dk[l], dv = s.dv[l];
             // h = LN2(r2): da holds dh, db2 receives dr2
-            layernorm_bwd(s.da, a.r2, a.st2, e.ln2_g, db2.f, db2.h, e.b2);
+            layernorm_bwd(s.da, a.r2, a.st2, e.ln2_g, db2, e.b2);
             // r2 = h1 + g W2^T + b2
             if ((rc2 = aside()) != BLS_OK) return rc2;
             side.linear_wgrad(db2, a.g, T, D, F, e.w2);
@@ -645,7 +691,7 @@ int seq_local_step(bls_ctx* ctx, const bls_model* m, float* params, float* momen
             side.linear_wgrad(df, a.h1, T, F, D, e.w1);
             net.linear_dgrad(df, T, F, e.w1, D, da, db2.f);   // da = dh1 (both uses of h1)
             // h1 = LN1(r1): db1 receives dr1
-            layernorm_bwd(s.da, a.r1, a.st1, e.ln1_g, db1.f, db1.h, e.bo);
+            layernorm_bwd(s.da, a.r1, a.st1, e.ln1_g, db1, e.bo);
             // r1 = x + ctx Wo^T + bo
             if ((rc2 = aside()) != BLS_OK) return rc2;
             side.linear_wgrad(db1, a.ctx, T, D, D, e.wo);
@@ -655,7 +701,7 @@ int seq_local_step(bls_ctx* ctx, const bls_model* m, float* params, float* momen
             if (s.bf) {
                 float* part = reserve_sums((size_t)3 * 4 * B * D);
                 ProfScope prof_(ctx, PROF_GEMM);
-                fused = launch_attention16_bwd(st, a.q.h, a.k.h, a.v.h, s.dc.h, a.p.f, D, B, H, L, dh, att, dq.f, dk.f, dv.f, dq.h, dk.h, dv.h, part);
+                fused = launch_attention16_bwd(st, a.q.h, a.k.h, a.v.h, s.dc.h, a.p.f, D, B, H, L, dh, att, dq.f, dk.f, dv.f, dq.h, dk.h, dv.h, dq.panel, part);
                 const int64_t offs[3] = {e.bq, e.bk, e.bv};
                 for (int i = 0; fused && i < 3; ++i) push_sums(part - s.cpart + (size_t)i * 4 * B * D, 4 * B, D, D, offs[i]);
             }

@@ -21,6 +21,7 @@ __device__ __forceinline__ float wmax(float v) {
 typedef __bf16 sq_bf16x2 __attribute__((ext_vector_type(2)));
 typedef float sq_f32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t sq_u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t sq_u32x4 __attribute__((ext_vector_type(4)));
 // two floats -> two bf16 (nearest even) in one word, the first in the low half
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector((sq_f32x2){lo, hi}, sq_bf16x2));
@@ -29,10 +30,12 @@ __device__ __forceinline__ uint16_t to_bf16(float v) { return (uint16_t)(pack_bf
 __device__ __forceinline__ void store_bf16x4(uint16_t* p, f32x4 v) {
     *reinterpret_cast<sq_u32x2*>(p) = sq_u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
 }
+// column c of row t of a [T][D] matrix, or of its 32-column panels `panel` elements apart
+__device__ __forceinline__ int64_t at16(int64_t t, int c, int D, int64_t panel) { return panel ? (c >> 5) * panel + t * 32 + (c & 31) : t * D + c; }
 
 // h[t][:] = tok_emb[token[t]][:] + pos_emb[t % L][:]; one wave per token, D % 4 == 0
 __global__ __launch_bounds__(256) void embed_kernel(const int32_t* __restrict__ tokens, int64_t T, int L, int D, const float* __restrict__ tok,
-                                                    const float* __restrict__ pos, float* __restrict__ h, uint16_t* __restrict__ h16) {
+                                                    const float* __restrict__ pos, float* __restrict__ h, uint16_t* __restrict__ h16, int64_t panel) {
     const int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (t >= T) return;
     const int lane = threadIdx.x & 63;
@@ -41,7 +44,7 @@ __global__ __launch_bounds__(256) void embed_kernel(const int32_t* __restrict__ 
     for (int c = 4 * lane; c < D; c += 256) {
         const f32x4 v = *reinterpret_cast<const f32x4*>(e + c) + *reinterpret_cast<const f32x4*>(p + c);
         *reinterpret_cast<f32x4*>(h + t * D + c) = v;
-        if (h16) store_bf16x4(h16 + t * D + c, v);
+        if (h16) store_bf16x4(h16 + at16(t, c, D, panel), v);
     }
 }
 
@@ -127,7 +130,7 @@ __global__ __launch_bounds__(256) void fix_finalize_kernel(FixRangeTable tab, fi
 // y = (x - mean) * invstd * g + b per row; stats[row] = (mean, invstd); one wave per row, D <= 1024, D % 4 == 0
 __global__ __launch_bounds__(256) void layernorm_kernel(const float* __restrict__ x, int64_t T, int D, const float* __restrict__ g,
                                                         const float* __restrict__ b, float* __restrict__ y, uint16_t* __restrict__ y16,
-                                                        float* __restrict__ stats) {
+                                                        int64_t panel, float* __restrict__ stats) {
     const int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (t >= T) return;
     const int lane = threadIdx.x & 63;
@@ -159,7 +162,7 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const float* __restrict_
 #pragma unroll
             for (int j = 0; j < 4; ++j) o[j] = (v[i][j] - mean) * inv * gg[j] + bb[j];
             *reinterpret_cast<f32x4*>(y + t * D + c) = o;
-            if (y16) store_bf16x4(y16 + t * D + c, o);
+            if (y16) store_bf16x4(y16 + at16(t, c, D, panel), o);
         }
     }
     if (stats && lane == 0) {
@@ -174,8 +177,8 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const float* __restrict_
 // (the gradient of a bias added just before the normalised tensor).
 __global__ __launch_bounds__(256) void layernorm_bwd_kernel(const float* __restrict__ dy, const float* __restrict__ x,
                                                             const float* __restrict__ stats, int64_t T, int D, const float* __restrict__ g,
-                                                            float* __restrict__ dx, uint16_t* __restrict__ dx16, float* __restrict__ part,
-                                                            int rows_per_wave, int sum_dx) {
+                                                            float* __restrict__ dx, uint16_t* __restrict__ dx16, int64_t panel,
+                                                            float* __restrict__ part, int rows_per_wave, int sum_dx) {
     __shared__ float red[4][3 * 1024];
     const int lane = threadIdx.x & 63;
     const int64_t w = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -218,7 +221,7 @@ __global__ __launch_bounds__(256) void layernorm_bwd_kernel(const float* __restr
                 for (int j = 0; j < 4; ++j) o[j] = inv * (dh[i][j] - m1 - xh[i][j] * m2);
                 sx[i] += o;
                 *reinterpret_cast<f32x4*>(dx + t * D + c) = o;
-                if (dx16) store_bf16x4(dx16 + t * D + c, o);
+                if (dx16) store_bf16x4(dx16 + at16(t, c, D, panel), o);
             }
         }
     }
@@ -490,16 +493,45 @@ __global__ __launch_bounds__(256) void to_bf16_kernel(const float* __restrict__ 
         store_bf16x4(out + 4 * i, *reinterpret_cast<const f32x4*>(in + 4 * i));
 }
 
+// The same into panels: a thread converts 8 columns of a row.  blockIdx.y is the matrix.
+__global__ __launch_bounds__(256) void to_bf16_panels_kernel(PanelTable tab, const float* __restrict__ in, uint16_t* __restrict__ out) {
+    const PanelJob j = tab.j[blockIdx.y];
+    const int per_row = j.cols >> 3;
+    const int64_t pieces = (int64_t)j.rows_pad * per_row, panel = (int64_t)j.rows_pad * 32;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < pieces; i += (int64_t)gridDim.x * 256) {
+        const int64_t row = i / per_row;
+        const int c = 8 * (int)(i - row * per_row);
+        f32x4 lo = {0.f, 0.f, 0.f, 0.f}, hi = lo;
+        if (row < j.rows) {
+            const float* src = in + j.off + row * j.cols + c;
+            lo = *reinterpret_cast<const f32x4*>(src);
+            hi = *reinterpret_cast<const f32x4*>(src + 4);
+        }
+        uint16_t* dst = out + j.off + (c >> 5) * panel + row * 32 + (c & 31);
+        *reinterpret_cast<sq_u32x4*>(dst) = sq_u32x4{pack_bf16x2(lo[0], lo[1]), pack_bf16x2(lo[2], lo[3]), pack_bf16x2(hi[0], hi[1]), pack_bf16x2(hi[2], hi[3])};
+    }
+}
+
 // ---- launchers ---------------------------------------------------------------------------------------
 static unsigned nblk(int64_t n, int per) { return (unsigned)((n + per - 1) / per); }
 
-void launch_embed(hipStream_t s, const int32_t* tokens, int64_t T, int L, int D, const float* tok, const float* pos, float* h, uint16_t* h16) {
-    hipLaunchKernelGGL(embed_kernel, dim3(nblk(T, 4)), dim3(256), 0, s, tokens, T, L, D, tok, pos, h, h16);
+void launch_embed(hipStream_t s, const int32_t* tokens, int64_t T, int L, int D, const float* tok, const float* pos, float* h, uint16_t* h16,
+                  int64_t panel) {
+    hipLaunchKernelGGL(embed_kernel, dim3(nblk(T, 4)), dim3(256), 0, s, tokens, T, L, D, tok, pos, h, h16, panel);
 }
 // n must be a multiple of 4 and both pointers 16- / 8-byte aligned
 void launch_to_bf16(hipStream_t s, const float* in, uint16_t* out, int64_t n) {
     unsigned b = nblk(n / 4, 256);
     hipLaunchKernelGGL(to_bf16_kernel, dim3(b > 8192 ? 8192 : b), dim3(256), 0, s, in, out, n / 4);
+}
+void launch_to_bf16_panels(hipStream_t s, const PanelTable& tab, const float* in, uint16_t* out) {
+    int64_t most = 0;
+    for (int i = 0; i < tab.n; ++i) {
+        const int64_t n = (int64_t)tab.j[i].rows_pad * (tab.j[i].cols / 8);
+        most = n > most ? n : most;
+    }
+    const unsigned b = nblk(most, 256);
+    if (tab.n > 0) hipLaunchKernelGGL(to_bf16_panels_kernel, dim3(b > 2048 ? 2048 : b, tab.n), dim3(256), 0, s, tab, in, out);
 }
 void launch_embed_grad(hipStream_t s, const int32_t* tokens, int64_t T, int D, const float* dh, fixsum_t* acc_tok) {
     double limit = 2305843009213693952.0;   // 2^61
@@ -534,8 +566,9 @@ void launch_fix_finalize(hipStream_t s, const FixRangeTable& tab, fixsum_t* acc,
     if (bx > 2048) bx = 2048;
     hipLaunchKernelGGL(fix_finalize_kernel, dim3(bx, tab.n), dim3(256), 0, s, tab, acc, grad);
 }
-void launch_layernorm(hipStream_t s, const float* x, int64_t T, int D, const float* g, const float* b, float* y, uint16_t* y16, float* stats) {
-    hipLaunchKernelGGL(layernorm_kernel, dim3(nblk(T, 4)), dim3(256), 0, s, x, T, D, g, b, y, y16, stats);
+void launch_layernorm(hipStream_t s, const float* x, int64_t T, int D, const float* g, const float* b, float* y, uint16_t* y16,
+                      int64_t panel, float* stats) {
+    hipLaunchKernelGGL(layernorm_kernel, dim3(nblk(T, 4)), dim3(256), 0, s, x, T, D, g, b, y, y16, panel, stats);
 }
 #define LN_BWD_ROWS_PER_WAVE 4
 size_t layernorm_bwd_partial_floats(int64_t T, int D) { return (size_t)nblk(T, 4 * LN_BWD_ROWS_PER_WAVE) * 3 * D; }
@@ -543,15 +576,15 @@ size_t layernorm_bwd_partial_floats(int64_t T, int D) { return (size_t)nblk(T, 4
 void launch_layernorm_bwd(hipStream_t s, const float* dy, const float* x, const float* stats, int64_t T, int D, const float* g, float* dx,
                           uint16_t* dx16, float* part, float* dgb) {
     const unsigned wgs = nblk(T, 4 * LN_BWD_ROWS_PER_WAVE);
-    hipLaunchKernelGGL(layernorm_bwd_kernel, dim3(wgs), dim3(256), 0, s, dy, x, stats, T, D, g, dx, dx16, part, LN_BWD_ROWS_PER_WAVE, 0);
+    hipLaunchKernelGGL(layernorm_bwd_kernel, dim3(wgs), dim3(256), 0, s, dy, x, stats, T, D, g, dx, dx16, (int64_t)0, part, LN_BWD_ROWS_PER_WAVE, 0);
     hipLaunchKernelGGL(colsum_rows_kernel, dim3(nblk(2 * D, 64)), dim3(256), 0, s, part, (int)wgs, 2 * D, dgb);
 }
 // Without the final sum: part takes one row of (scale, shift, column sum of dx) partials, 3 D floats, per workgroup;
 // returns the number of rows
 int launch_layernorm_bwd_partial(hipStream_t s, const float* dy, const float* x, const float* stats, int64_t T, int D, const float* g, float* dx,
-                                 uint16_t* dx16, float* part) {
+                                 uint16_t* dx16, int64_t panel, float* part) {
     const unsigned wgs = nblk(T, 4 * LN_BWD_ROWS_PER_WAVE);
-    hipLaunchKernelGGL(layernorm_bwd_kernel, dim3(wgs), dim3(256), 0, s, dy, x, stats, T, D, g, dx, dx16, part, LN_BWD_ROWS_PER_WAVE, 1);
+    hipLaunchKernelGGL(layernorm_bwd_kernel, dim3(wgs), dim3(256), 0, s, dy, x, stats, T, D, g, dx, dx16, panel, part, LN_BWD_ROWS_PER_WAVE, 1);
     return (int)wgs;
 }
 void launch_softmax_rows(hipStream_t s, float* sc, uint16_t* p16, bool store_f32, int64_t rows, int n) {
