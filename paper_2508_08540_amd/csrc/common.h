@@ -110,9 +110,24 @@ int launch_weighted_aggregate(bls_ctx* ctx, const float* const* replicas, const 
                               float* out, bool broadcast);
 size_t topk_scratch_bytes(int64_t N, int64_t k);
 int launch_topk(bls_ctx* ctx, const float* losses, int64_t N, int64_t k, int32_t* idx_out, float* val_out);
-// Two selections of indices from pools of one size, without values; idx_a and idx_b do not overlap.
-size_t topk_pair_scratch_bytes(int64_t N);
-int launch_topk_pair(bls_ctx* ctx, const float* losses_a, int64_t k_a, int32_t* idx_a, const float* losses_b, int64_t k_b, int32_t* idx_b, int64_t N);
+// Up to three independent selections of indices from pools of one size N <= TOPK_SORT_MAX, which share their launches.
+#define TOPK_SORT_MAX (1 << 19)
+struct SelJob {
+    const float* losses;
+    int k;
+    int32_t* idx_out;    // the k first in rank order
+    float* val_out;      // their values, or NULL
+    uint8_t* chosen;     // N flags, 1 for the k first and 0 for the others, or NULL
+    int lift;            // a loss of -inf counts as the lowest finite float
+    // filled by the launcher, whole-pool sort only
+    uint32_t* tables;
+    uint2 *a, *b;
+};
+struct SelJobs {
+    SelJob j[3];
+};
+size_t topk_jobs_scratch_bytes(int n_jobs, int64_t N);
+int launch_topk_jobs(bls_ctx* ctx, char* scratch_base, SelJobs jobs, int n_jobs, int64_t N);
 // The same on the library's fixed device array (no allocation); topk_static_init looks its address up for ctx's device.
 int topk_static_init(bls_ctx* ctx);
 int launch_topk_static(bls_ctx* ctx, const float* losses, int64_t N, int64_t k, int32_t* idx_out, float* val_out);

@@ -16,7 +16,6 @@
 // Ranking by counting needs no scratch and costs 24.6 us at 16384 (four sorting passes: 22 us at 16385); sorting a pool of
 // 2^19 whole takes 73 us for any k, selecting first 98 (k = N / 50) to 120 us (k = N); at 2^20 about 117 against 86 to 105 us.
 #define TOPK_RANK_MAX 16384
-#define TOPK_SORT_MAX (1 << 19)
 
 __device__ __forceinline__ uint32_t loss_key(float v) {
     uint32_t u = __float_as_uint(v);
@@ -25,19 +24,10 @@ __device__ __forceinline__ uint32_t loss_key(float v) {
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-// One selection; two independent ones over pools of one size share their launches (blockIdx.y).
-struct SelJob {
-    const float* losses;
-    int k;
-    int32_t* idx_out;
-    float* val_out;
-    // whole-pool sort only
-    uint32_t* tables;
-    uint2 *a, *b;
-};
-struct SelJobs {
-    SelJob j[2];
-};
+__device__ __forceinline__ uint32_t job_key(const SelJob& job, int i) {
+    const float v = job.losses[i];
+    return loss_key(job.lift && v == -INFINITY ? -3.402823466e38f : v);
+}
 
 // Rank by counting: the rank of a sample is the number of samples that precede it, so each workgroup ranks 64 samples (one per
 // lane) against the whole pool, which its 16 waves walk in chunks of 64 keys from LDS (every lane reads the same four keys per
@@ -51,7 +41,7 @@ __global__ __launch_bounds__(1024) void topk_rank_kernel(SelJobs jobs, int N) {
     extern __shared__ __align__(16) uint32_t rank_lds[];   // the keys, then [16][64] partial ranks
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n_chunks = (N + 63) >> 6, own = blockIdx.x;
-    for (int i = tid; i < n_chunks * 64; i += 1024) rank_lds[i] = i < N ? loss_key(losses[i]) : 0u;   // no loss has key 0
+    for (int i = tid; i < n_chunks * 64; i += 1024) rank_lds[i] = i < N ? job_key(job, i) : 0u;   // no loss has key 0
     __syncthreads();
     const uint32_t mine = rank_lds[own * 64 + lane];
     uint32_t before = 0;
@@ -84,6 +74,7 @@ __global__ __launch_bounds__(1024) void topk_rank_kernel(SelJobs jobs, int N) {
 #pragma unroll
         for (int w = 0; w < 16; ++w) rank += rank_lds[w * 64 + lane];
         const int i = own * 64 + lane;
+        if (job.chosen && i < N) job.chosen[i] = rank < (uint32_t)job.k;
         if (i < N && rank < (uint32_t)job.k) {
             job.idx_out[rank] = i;
             if (job.val_out) job.val_out[rank] = losses[i];
@@ -114,24 +105,31 @@ __device__ __forceinline__ bool key_to_loss(uint32_t key, float* v) {
 #define SORT_TILES 64   // 64 tiles of 8 x 1024 elements hold TOPK_SORT_MAX
 #define SORT_TABLE (SORT_TILES * 256)
 
+// Tile of a workgroup.  Workgroups are dealt to the eight XCDs in turn; an XCD takes consecutive tiles, so that the short runs its
+// tiles write per digit lie side by side: a cache line that several XCDs write leaves each one's L2 by itself.
+__device__ __forceinline__ int sort_tile() {
+    const int tiles = gridDim.x, r = blockIdx.x & 7, per = tiles >> 3, rem = tiles & 7;
+    return r * per + min(r, rem) + ((int)blockIdx.x >> 3);
+}
+
 // Digit counts of the first pass; clears the tables of the other three.
 template <int RITER>
 __global__ __launch_bounds__(1024) void sort_count_kernel(SelJobs jobs, int N) {
-    const float* __restrict__ losses = jobs.j[blockIdx.y].losses;
-    uint32_t* __restrict__ tables = jobs.j[blockIdx.y].tables;
+    const SelJob& job = jobs.j[blockIdx.y];
+    uint32_t* __restrict__ tables = job.tables;
     __shared__ uint32_t cnt[256];
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, tile = sort_tile();
     if (tid < 256) cnt[tid] = 0u;
-    else tables[(size_t)(tid >> 8) * SORT_TABLE + blockIdx.x * 256 + (tid & 255)] = 0u;
+    else tables[(size_t)(tid >> 8) * SORT_TABLE + tile * 256 + (tid & 255)] = 0u;
     __syncthreads();
-    const int base = blockIdx.x * (RITER * 1024);
+    const int base = tile * (RITER * 1024);
 #pragma unroll
     for (int it = 0; it < RITER; ++it) {
         const int i = base + it * 1024 + tid;
-        if (i < N) atomicAdd(&cnt[~loss_key(losses[i]) & 255u], 1u);
+        if (i < N) atomicAdd(&cnt[~job_key(job, i) & 255u], 1u);
     }
     __syncthreads();
-    if (tid < 256) tables[blockIdx.x * 256 + tid] = cnt[tid];
+    if (tid < 256) tables[tile * 256 + tid] = cnt[tid];
 }
 
 // One stable pass over the sort keys ~loss_key (ascending order is rank order).  A wave ranks its RITER x 64 consecutive
@@ -140,7 +138,6 @@ __global__ __launch_bounds__(1024) void sort_count_kernel(SelJobs jobs, int N) {
 template <int RITER, int PASS>
 __global__ __launch_bounds__(1024) void sort_pass_kernel(SelJobs jobs, int N) {
     const SelJob& job = jobs.j[blockIdx.y];
-    const float* __restrict__ losses = job.losses;
     const uint2* __restrict__ in = PASS == 2 ? job.b : job.a;
     uint2* __restrict__ out = PASS == 1 ? job.b : job.a;
     const uint32_t* __restrict__ table = job.tables + PASS * SORT_TABLE;
@@ -150,8 +147,8 @@ __global__ __launch_bounds__(1024) void sort_pass_kernel(SelJobs jobs, int N) {
     __shared__ uint32_t part[2][4][256];
     __shared__ uint32_t wave_total[4];
     __shared__ uint32_t next[PASS < 3 ? SORT_TABLE / 2 : 1];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, tiles = gridDim.x;
-    const int wbase = blockIdx.x * RTILE + wave * (RITER * 64);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, tiles = gridDim.x, tile = sort_tile();
+    const int wbase = tile * RTILE + wave * (RITER * 64);
     uint32_t key[RITER], id[RITER];
 #pragma unroll
     for (int it = 0; it < RITER; ++it) {
@@ -159,7 +156,7 @@ __global__ __launch_bounds__(1024) void sort_pass_kernel(SelJobs jobs, int N) {
         key[it] = 0u;
         id[it] = (uint32_t)i;
         if (i < N) {
-            if (PASS == 0) key[it] = ~loss_key(losses[i]);
+            if (PASS == 0) key[it] = ~job_key(job, i);
             else {
                 const uint2 v = in[i];
                 key[it] = v.x;
@@ -175,7 +172,7 @@ __global__ __launch_bounds__(1024) void sort_pass_kernel(SelJobs jobs, int N) {
 #pragma unroll
         for (int j = 0; j < SORT_TILES / 4; ++j) {
             all += v[j];
-            left += g + 4 * j < (int)blockIdx.x ? v[j] : 0u;
+            left += g + 4 * j < tile ? v[j] : 0u;
         }
         part[0][g][d] = all;
         part[1][g][d] = left;
@@ -233,11 +230,14 @@ __global__ __launch_bounds__(1024) void sort_pass_kernel(SelJobs jobs, int N) {
             out[pos] = make_uint2(key[it], id[it]);
             const uint32_t slot = (pos / RTILE) * 256u + ((key[it] >> (SHIFT + 8)) & 255u);
             atomicAdd(&next[slot >> 1], (slot & 1u) ? 65536u : 1u);
-        } else if (pos < (uint32_t)job.k) {
+            continue;
+        }
+        if (job.chosen) job.chosen[id[it]] = pos < (uint32_t)job.k;
+        if (pos < (uint32_t)job.k) {
             job.idx_out[pos] = (int32_t)id[it];
             if (job.val_out) {
                 float v;
-                if (!key_to_loss(~key[it], &v)) v = losses[id[it]];
+                if (!key_to_loss(~key[it], &v)) v = job.losses[id[it]];
                 job.val_out[pos] = v;
             }
         }
@@ -792,7 +792,7 @@ static int launch_topk_small(bls_ctx* ctx, const SelJobs& jobs, int n_jobs, int6
 static int launch_topk_at(bls_ctx* ctx, char* scratch_base, const float* losses, int64_t N, int64_t k, int32_t* idx_out, float* val_out) {
     if (N > TOPK_SORT_MAX) return launch_topk_large(ctx, scratch_base, losses, N, k, idx_out, val_out);
     SelJobs jobs{};
-    jobs.j[0] = {losses, (int)k, idx_out, val_out, nullptr, nullptr, nullptr};
+    jobs.j[0] = {losses, (int)k, idx_out, val_out};
     if (N <= TOPK_RANK_MAX) return launch_topk_small(ctx, jobs, 1, N);
     return launch_topk_medium(ctx, scratch_base, jobs, 1, N);
 }
@@ -803,20 +803,20 @@ int launch_topk(bls_ctx* ctx, const float* losses, int64_t N, int64_t k, int32_t
     return launch_topk_at(ctx, ctx->arena, losses, N, k, idx_out, val_out);
 }
 
-size_t topk_pair_scratch_bytes(int64_t N) { return (N <= TOPK_SORT_MAX ? 2 : 1) * topk_scratch_bytes(N, N); }
+// Several selections fill the chip by counting where one does not yet, and are sorted from smaller pools on: an epoch's three draws take
+// 14 us from 3000 samples and 33 from 8192 by counting, 30 to 32 from 8193 to 16384 by sorting.
+#define TOPK_JOBS_RANK_MAX 7168
 
-// Two launch-bound selections cost one when they run side by side; from TOPK_SORT_MAX on each fills the chip by itself.
-int launch_topk_pair(bls_ctx* ctx, const float* losses_a, int64_t k_a, int32_t* idx_a, const float* losses_b, int64_t k_b, int32_t* idx_b, int64_t N) {
-    int rc = bls_arena_reserve(ctx, topk_pair_scratch_bytes(N));
-    if (rc != BLS_OK) return rc;
-    if (N > TOPK_SORT_MAX) {
-        rc = launch_topk(ctx, losses_a, N, k_a, idx_a, nullptr);
-        return rc != BLS_OK ? rc : launch_topk(ctx, losses_b, N, k_b, idx_b, nullptr);
-    }
-    SelJobs jobs{};
-    jobs.j[0] = {losses_a, (int)k_a, idx_a, nullptr, nullptr, nullptr, nullptr};
-    jobs.j[1] = {losses_b, (int)k_b, idx_b, nullptr, nullptr, nullptr, nullptr};
-    return N <= TOPK_RANK_MAX ? launch_topk_small(ctx, jobs, 2, N) : launch_topk_medium(ctx, ctx->arena, jobs, 2, N);
+size_t topk_jobs_scratch_bytes(int n_jobs, int64_t N) {
+    if (N <= TOPK_JOBS_RANK_MAX) return 0;
+    Carver c(nullptr);
+    SelJob job;
+    for (int i = 0; i < n_jobs; ++i) carve_sort(c, N, job);
+    return c.off;
+}
+
+int launch_topk_jobs(bls_ctx* ctx, char* scratch_base, SelJobs jobs, int n_jobs, int64_t N) {
+    return N <= TOPK_JOBS_RANK_MAX ? launch_topk_small(ctx, jobs, n_jobs, N) : launch_topk_medium(ctx, scratch_base, jobs, n_jobs, N);
 }
 
 // ---- selection without any allocation -----------------------------------------------------------------

@@ -152,3 +152,29 @@ def test_variants_with_special_losses_tied_keys_and_bad_arguments(env):
     with pytest.raises(bls.BlsError):
         ctx.check(bls.binding.lib.sample_epoch_variant(ctx.handle, z.data_ptr(), z.data_ptr(), z.data_ptr(), 4, 1, 1, 1, 1, 0.5, 2, 0,
                                                        o.data_ptr(), o.data_ptr()))          # an unknown scheme is rejected
+
+
+@pytest.mark.parametrize("scheme", ["separated", "unified"])
+@pytest.mark.parametrize("N,lam", [(1023, 0.5), (1025, 1.0), (7168, 0.5), (7169, 0.3), (16384, 0.5), (65537, 0.5), (1 << 19, 0.4), ((1 << 19) + 1, 0.4)])
+def test_draws_around_the_sizes_where_the_path_changes(env, scheme, N, lam):
+    """One tile of the order more and less, ranking by counting and by sorting, pools ranked together and one after the other; keys of
+    minus infinity rank with the lowest float when others are left out."""
+    seed = synth.inputs.BASE_SEED + 5 * N
+    uf, us = _keys(seed, 31, N), _keys(seed, 32, N)
+    _check_variant(env, synth.loss_array("ties16", N, seed=seed), uf, us, 8, 3, 4, 2, lam, scheme, "fast")
+    uf[::7] = -np.inf
+    uf[3::11] = np.finfo(np.float32).min
+    lowest = np.where(np.isinf(uf), np.finfo(np.float32).min, uf)
+    torch, bls, ctx = env
+    nf, k, ns = bls.epoch_allocation(N, 8, 3, 4, 2, lam)
+    if k > 0:
+        losses = torch.from_numpy(synth.loss_array("halfnormal", N, seed=seed)).cuda()
+        got = []
+        for keys in (uf, lowest):
+            fast, slow = torch.full((nf,), -7, dtype=torch.int32, device="cuda"), torch.full((max(ns, 1),), -7, dtype=torch.int32, device="cuda")
+            bls.sample_epoch(ctx, losses, torch.from_numpy(keys).cuda(), torch.from_numpy(us).cuda(), 8, 3, 4, 2, lam, fast, slow, scheme=scheme,
+                             high_loss_to="fast")
+            ctx.synchronize()
+            got.append((fast.cpu().numpy(), slow.cpu().numpy()))
+        np.testing.assert_array_equal(got[0][0], got[1][0])
+        np.testing.assert_array_equal(got[0][1], got[1][1])
