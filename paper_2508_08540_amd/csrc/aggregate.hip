@@ -33,8 +33,15 @@ __device__ __forceinline__ f32x4 agg_column(const AggArgs& a, int P, int64_t v) 
     return acc;
 }
 
-__global__ __launch_bounds__(256) void agg_vec4_kernel(AggArgs a, int P, int64_t n_vec, float* out,
-                                                       int broadcast) {
+__device__ __forceinline__ void agg_element(const AggArgs& a, int P, int64_t j, float* out, int broadcast) {
+    float acc = __fmul_rn(a.w[0], a.src[0][j]);
+    for (int i = 1; i < P; ++i) acc = __fmaf_rn(a.w[i], a.src[i][j], acc);
+    out[j] = acc;
+    if (broadcast)
+        for (int i = 0; i < P; ++i) const_cast<float*>(a.src[i])[j] = acc;
+}
+
+__global__ __launch_bounds__(256) void agg_vec4_kernel(AggArgs a, int P, int64_t n_vec, int64_t d, float* out, int broadcast) {
     int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n_vec; v += stride) {
         f32x4 acc = agg_column(a, P, v);
@@ -42,19 +49,14 @@ __global__ __launch_bounds__(256) void agg_vec4_kernel(AggArgs a, int P, int64_t
         if (broadcast)
             for (int i = 0; i < P; ++i) reinterpret_cast<f32x4*>(const_cast<float*>(a.src[i]))[v] = acc;
     }
+    // the up to three elements behind the last whole column
+    if (blockIdx.x == 0 && threadIdx.x < d - 4 * n_vec) agg_element(a, P, 4 * n_vec + threadIdx.x, out, broadcast);
 }
 
-// Scalar path: the tail after the last full float4, or everything when a pointer is not 16-byte aligned.
-__global__ __launch_bounds__(256) void agg_scalar_kernel(AggArgs a, int P, int64_t begin, int64_t d,
-                                                         float* out, int broadcast) {
+// Everything, when a pointer is not 16-byte aligned or there is no whole column.
+__global__ __launch_bounds__(256) void agg_scalar_kernel(AggArgs a, int P, int64_t d, float* out, int broadcast) {
     int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t j = begin + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < d; j += stride) {
-        float acc = __fmul_rn(a.w[0], a.src[0][j]);
-        for (int i = 1; i < P; ++i) acc = __fmaf_rn(a.w[i], a.src[i][j], acc);
-        out[j] = acc;
-        if (broadcast)
-            for (int i = 0; i < P; ++i) const_cast<float*>(a.src[i])[j] = acc;
-    }
+    for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < d; j += stride) agg_element(a, P, j, out, broadcast);
 }
 
 int launch_weighted_aggregate(bls_ctx* ctx, const float* const* replicas, const float* weights, int P, int64_t d,
@@ -71,16 +73,13 @@ int launch_weighted_aggregate(bls_ctx* ctx, const float* const* replicas, const 
         int64_t blocks = ceil_div(n_vec, 256);
         int64_t cap = (int64_t)ctx->num_cus * 8;
         if (blocks > cap) blocks = cap;
-        hipLaunchKernelGGL(agg_vec4_kernel, dim3((unsigned)blocks), dim3(256), 0, ctx->stream, a, P, n_vec, out,
+        hipLaunchKernelGGL(agg_vec4_kernel, dim3((unsigned)blocks), dim3(256), 0, ctx->stream, a, P, n_vec, d, out,
                            broadcast ? 1 : 0);
-    }
-    int64_t begin = n_vec * 4;
-    if (begin < d) {
-        int64_t blocks = ceil_div(d - begin, 256);
+    } else if (d > 0) {
+        int64_t blocks = ceil_div(d, 256);
         int64_t cap = (int64_t)ctx->num_cus * 8;
         if (blocks > cap) blocks = cap;
-        hipLaunchKernelGGL(agg_scalar_kernel, dim3((unsigned)blocks), dim3(256), 0, ctx->stream, a, P, begin, d, out,
-                           broadcast ? 1 : 0);
+        hipLaunchKernelGGL(agg_scalar_kernel, dim3((unsigned)blocks), dim3(256), 0, ctx->stream, a, P, d, out, broadcast ? 1 : 0);
     }
     BLS_HIP(ctx, hipGetLastError());
     return BLS_OK;
