@@ -35,6 +35,19 @@ __global__ __launch_bounds__(256) void head_forward_kernel(const T* __restrict__
     const int b = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const float inv_pos = MLP ? 1.f : 1.f / (float)positions;
     const T* a = act + (int64_t)b * positions * F;
+    // What does not depend on the features is requested first: the label, and in narrow layers the weights of the wave's first
+    // classes (a chain of loads of about 1 us each otherwise).
+    constexpr int PRE = PQ == 1 ? 4 : 0;
+    const int label = MLP ? y[pool_row(rows, b)] : y[b];
+    f32x4 w_pre[PRE + 1];
+    float b_pre[PRE + 1];
+#pragma unroll
+    for (int t = 0; t < PRE; ++t) {
+        const int c = wave + 4 * t;
+        const bool there = c < C;
+        b_pre[t] = there ? bias[c] : 0.f;
+        w_pre[t] = there && 4 * lane < F ? *reinterpret_cast<const f32x4*>(W + (int64_t)c * F + 4 * lane) : f32x4{0.f, 0.f, 0.f, 0.f};
+    }
 #pragma unroll
     for (int i = 0; i < PQ; ++i) {
         const int c = 4 * (lane + 64 * i);
@@ -67,7 +80,17 @@ __global__ __launch_bounds__(256) void head_forward_kernel(const T* __restrict__
         const int c = 4 * (lane + 64 * i);
         f[i] = c < F ? *reinterpret_cast<const f32x4*>(&fs[c]) : f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    for (int c = wave; c < C; c += 4) {
+#pragma unroll
+    for (int t = 0; t < PRE; ++t) {
+        const int c = wave + 4 * t;
+        if (c >= C) break;
+        float acc = 0.f;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc = __fmaf_rn(f[0][j], w_pre[t][j], acc);
+        const float z = wave_sum(acc) + b_pre[t];
+        if (lane == 0) zs[c] = z;
+    }
+    for (int c = wave + 4 * PRE; c < C; c += 4) {
         float acc = 0.f;
 #pragma unroll
         for (int i = 0; i < PQ; ++i) {
@@ -93,7 +116,6 @@ __global__ __launch_bounds__(256) void head_forward_kernel(const T* __restrict__
 #pragma unroll
     for (int h = 0; h < 2; ++h) ex[h] = lane + 64 * h < C ? expf(z_mine[h] - m) : 0.f;
     const float sum = wave_sum(ex[0]) + wave_sum(ex[1]);
-    const int label = MLP ? y[pool_row(rows, b)] : y[b];
     const float z_label = __shfl(label < 64 ? z_mine[0] : z_mine[1], label & 63, 64);
     if (threadIdx.x == 0) loss[b] = (m + logf(sum)) - z_label;
     if (!dlogits) return;
@@ -109,7 +131,15 @@ __global__ __launch_bounds__(256) void head_forward_kernel(const T* __restrict__
     for (int i = 0; i < PQ; ++i) {
         const int k = 4 * (lane + 64 * i);
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-        for (int c = wave; c < C; c += 4) {
+#pragma unroll
+        for (int t = 0; t < PRE; ++t) {
+            const int c = wave + 4 * t;
+            if (c >= C) break;
+            const float d = __shfl(c < 64 ? dz[0] : dz[1], c & 63, 64);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[j] = __fmaf_rn(d, w_pre[t][j], acc[j]);
+        }
+        for (int c = wave + 4 * PRE; c < C; c += 4) {
             const float d = __shfl(c < 64 ? dz[0] : dz[1], c & 63, 64);
             if (k < F) {
                 const f32x4 w = *reinterpret_cast<const f32x4*>(W + (int64_t)c * F + k);
@@ -158,8 +188,9 @@ void launch_head_mlp(hipStream_t s, const float* part, int B, int splits, int F,
 #undef HEAD_LAUNCH
 }
 
-// One workgroup per class c: thread (f mod 64, slice) adds every 4th sample for its features, the four
-// slices are folded through LDS in order.  db[c] comes from the same workgroup.
+// One workgroup per class c and 64 features: thread (f mod 64, slice) adds every 4th sample for its feature, the four
+// slices are folded through LDS in order.  db[c] comes from the class's first workgroup.  Latency of the loads: eight in flight,
+// and no loop over the features (512 features, 100 classes, 128 samples: 107 -> 15 us).
 __global__ __launch_bounds__(256) void head_wgrad_kernel(const float* __restrict__ dlogits, const float* __restrict__ feat,
                                                          int B, int C, int F, float* __restrict__ dW, float* __restrict__ db, int64_t rstride) {
     if (rstride) {
@@ -168,16 +199,18 @@ __global__ __launch_bounds__(256) void head_wgrad_kernel(const float* __restrict
     }
     __shared__ float red[4][64];
     const int c = blockIdx.x, fl = threadIdx.x & 63, sl = threadIdx.x >> 6;
-    for (int f0 = 0; f0 < F; f0 += 64) {
-        const int f = f0 + fl;
+    {
+        const int f = blockIdx.y * 64 + fl;
         float acc = 0.f;
         if (f < F)
+#pragma unroll 8
             for (int b = sl; b < B; b += 4) acc = __fmaf_rn(dlogits[(int64_t)b * C + c], feat[(int64_t)b * F + f], acc);
         red[sl][fl] = acc;
         __syncthreads();
         if (sl == 0 && f < F) dW[(int64_t)c * F + f] = (red[0][fl] + red[1][fl]) + (red[2][fl] + red[3][fl]);
         __syncthreads();
     }
+    if (blockIdx.y != 0) return;
     // bias gradient: 256 threads take every 256th sample
     float acc = 0.f;
     for (int b = threadIdx.x; b < B; b += 256) acc += dlogits[(int64_t)b * C + c];
@@ -189,5 +222,5 @@ __global__ __launch_bounds__(256) void head_wgrad_kernel(const float* __restrict
 }
 
 void launch_head_wgrad(hipStream_t s, const float* dlogits, const float* feat, int B, int C, int F, float* dW, float* db, Reps reps) {
-    hipLaunchKernelGGL(head_wgrad_kernel, dim3(C, 1, reps.n), dim3(256), 0, s, dlogits, feat, B, C, F, dW, db, reps.stride);
+    hipLaunchKernelGGL(head_wgrad_kernel, dim3(C, (F + 63) / 64, reps.n), dim3(256), 0, s, dlogits, feat, B, C, F, dW, db, reps.stride);
 }

@@ -132,9 +132,11 @@ struct MlpOffsets {
 // part[b][z][h], z < MLP_SPLITS: partial sums of x W^T; hid is a multiple of 16
 void launch_mlp_fc1(hipStream_t s, const float* x, const BatchRows& rows, const float* W, int B, int hid, int K, float* part);
 // Gradients from h [B][hid], dlogits [B][C], dpre [B][hid] (gradient before the ReLU) and the batch, and the SGD step of every
-// parameter: g += wd*x; buf = mu*buf + g; x -= lr*buf.
+// parameter: g += wd*x; buf = mu*buf + g; x -= lr*buf.  With `next` also the partial sums part[b][z][h], z < mlp_next_splits(K), of the
+// first layer with the new weights for that batch.
 void launch_mlp_update(hipStream_t s, float* params, float* momentum, const MlpOffsets& off, const float* x, const BatchRows& rows, const float* h,
-                       const float* dlogits, const float* dpre, int B, int hid, int C, int K, const bls_sgd& opt);
+                       const float* dlogits, const float* dpre, int B, int hid, int C, int K, const bls_sgd& opt, const BatchRows* next, float* part);
+int mlp_next_splits(int K);
 
 // ---- head.hip ---------------------------------------------------------------------------------------
 // One wave per sample: feature = mean over `positions` of act[b][p][F] (storage type act_type); logits = W feature + bias;

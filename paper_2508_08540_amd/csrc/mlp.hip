@@ -1,10 +1,11 @@
 // The two-layer perceptron: its first layer forward, and the end of a training step (all gradients and the update).
 //
 // A step of 64 samples moves about 9 MB and computes 100 Mflop: every launch is latency, a chain of loads of about 1 us each.
-// The step therefore takes three launches (first layer, head, gradients + update).  The batch is never copied: rows of the pool
+// The step therefore takes two launches: the head, and gradients + update, whose workgroups go on to multiply the weights they have
+// just updated with the next batch (the first step's first layer, and large batches, take a launch of their own).  The batch is never copied: rows of the pool
 // are read through the selection list.  The first layer's partial sums are added by the head (which pools `positions` rows
 // per sample anyway), and a gradient goes from the accumulators straight into the momentum and the parameter.
-// Pass of 4 steps of 64 with 128 hidden units and a pool of 256: 272 -> 97 us (of nine launches a step before).
+// Pass of 4 steps of 64 with 128 hidden units and a pool of 256: 272 us with nine launches a step, 97 with three, 89 with two.
 #include "kernels.h"
 
 // Four consecutive floats of a row of `cols`, from column c; past the end, or without 16-byte alignment, element by element.
@@ -80,10 +81,14 @@ __device__ __forceinline__ void sgd_one(float& p, float& m, float grad, const bl
 //   4 (l % 16) .. + 3 of samples 4 (l / 16) + j, one 16-byte load of x for four products, and owns four rows of four neighbouring
 //   weights, which it updates with 16-byte accesses.  Two steps (32 samples) of loads are in flight together.
 // The small kinds come first: they are the longer chains.
+// NEXT: a workgroup of the last kind then has 16 x 256 weights of the next step and computes that step's partial sums
+// part[b][z][h] over its 256 inputs (z = their block): the weights pass through LDS into the layout of a factor, the rows of
+// the next batch are requested before anything else.
+template <bool NEXT>
 __global__ __launch_bounds__(256) void mlp_update_kernel(float* __restrict__ params, float* __restrict__ momentum, MlpOffsets off,
                                                          const float* __restrict__ x, BatchRows rows, const float* __restrict__ h,
                                                          const float* __restrict__ dlogits, const float* __restrict__ dpre, int B, int hid, int C,
-                                                         int K, bls_sgd opt, int x_vec, int p_vec) {
+                                                         int K, bls_sgd opt, int x_vec, int p_vec, BatchRows next, float* __restrict__ part) {
     __shared__ float red[4][64];
     __shared__ int64_t at[256];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -119,17 +124,41 @@ __global__ __launch_bounds__(256) void mlp_update_kernel(float* __restrict__ par
     blk -= (C + 1) * f_blocks;
     const int r = lane & 15, g = lane >> 4;
     const int n_blocks = (K + 255) / 256;
-    const int m0 = (blk / n_blocks) * 16, n = (blk % n_blocks) * 256 + wave * 64 + 4 * r;
+    const int m0 = (blk / n_blocks) * 16, z = blk % n_blocks, n = z * 256 + wave * 64 + 4 * r;
+    // the wave's first 16 samples of the next batch: lane l supplies row l % 16 and, in a step of 16 inputs, four from 4 (l / 16)
+    f32x4 xn[NEXT ? 16 : 1];
+    auto load_next = [&](int b0) {
+        const float* row = x + pool_row(next, min(b0 + r, B - 1)) * K;   // rows past the batch repeat its last one and are not stored
+        if (x_vec && z * 256 + 256 <= K) {   // uniform, so that all sixteen are in flight together
+#pragma unroll
+            for (int u = 0; u < (NEXT ? 16 : 0); ++u) xn[u] = *reinterpret_cast<const f32x4*>(row + z * 256 + 16 * u + 4 * g);
+        } else {
+#pragma unroll
+            for (int u = 0; u < (NEXT ? 16 : 0); ++u) xn[u] = load_cols4(row, z * 256 + 16 * u + 4 * g, K, x_vec != 0);
+        }
+    };
+    if (NEXT && 16 * wave < B) load_next(16 * wave);
     const int nn = n < K ? n : 0;   // a lane past the last input reads the first ones and stores nothing
+    // weights and momentum are requested before the sums, and the loads of 32 samples before the products of the 32 before them
+    f32x4 pv[4], mv[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        pv[i] = mv[i] = f32x4{0.f, 0.f, 0.f, 0.f};   // inputs past the end: zero weights
+        if (n < K) {
+            const int64_t at_w = off.fc1_w + (int64_t)(m0 + 4 * g + i) * K;
+            pv[i] = load_cols4(params + at_w, n, K, p_vec != 0);
+            mv[i] = load_cols4(momentum + at_w, n, K, p_vec != 0);
+        }
+    }
     f32x4 acc[4] = {};
     for (int b0 = 0; b0 < B; b0 += 256) {
         __syncthreads();
         at[tid] = pool_row(rows, min(b0 + tid, B - 1));
         __syncthreads();
         const int b_end = min(B, b0 + 256);
-        for (int k0 = b0; k0 < b_end; k0 += 32) {
-            float a[8];
-            f32x4 v[8];
+        float a[2][8];
+        f32x4 v[2][8];
+        auto fetch = [&](int k0, float (&a)[8], f32x4 (&v)[8]) {
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 const int b = min(k0 + 16 * (j >> 2) + 4 * g + (j & 3), b_end - 1);
@@ -138,6 +167,8 @@ __global__ __launch_bounds__(256) void mlp_update_kernel(float* __restrict__ par
                 if (x_vec) v[j] = *reinterpret_cast<const f32x4*>(row + nn);
                 else v[j] = load_cols4(row, nn, K, false);
             }
+        };
+        auto multiply = [&](int k0, const float (&a)[8], const f32x4 (&v)[8]) {
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 const bool ok = k0 + 16 * (j >> 2) + 4 * g + (j & 3) < b_end;   // samples past the batch: zero factors
@@ -145,38 +176,74 @@ __global__ __launch_bounds__(256) void mlp_update_kernel(float* __restrict__ par
 #pragma unroll
                 for (int q = 0; q < 4; ++q) acc[q] = __builtin_amdgcn_mfma_f32_16x16x4f32(aj, ok ? v[j][q] : 0.f, acc[q], 0, 0, 0);
             }
+        };
+        fetch(b0, a[0], v[0]);
+        for (int k0 = b0; k0 < b_end; k0 += 64) {
+            if (k0 + 32 < b_end) fetch(k0 + 32, a[1], v[1]);
+            multiply(k0, a[0], v[0]);
+            if (k0 + 32 >= b_end) break;
+            if (k0 + 64 < b_end) fetch(k0 + 64, a[0], v[0]);
+            multiply(k0 + 32, a[1], v[1]);
         }
     }
-    if (n >= K) return;
     // lane holds hidden units m0 + 4 g + i, inputs n .. n + 3
+    constexpr int PITCH = 256 + 4;
+    __shared__ __attribute__((aligned(16))) float w_lds[NEXT ? 16 * PITCH : 4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         float* p = params + off.fc1_w + (int64_t)(m0 + 4 * g + i) * K + n;
         float* m = momentum + off.fc1_w + (int64_t)(m0 + 4 * g + i) * K + n;
-        if (p_vec) {
-            f32x4 pv = *reinterpret_cast<const f32x4*>(p), mv = *reinterpret_cast<const f32x4*>(m);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                float ps = pv[q], ms = mv[q];
-                sgd_one(ps, ms, acc[q][i], opt);
-                pv[q] = ps;
-                mv[q] = ms;
-            }
-            *reinterpret_cast<f32x4*>(p) = pv;
-            *reinterpret_cast<f32x4*>(m) = mv;
+        for (int q = 0; q < 4; ++q) {
+            float ps = pv[i][q], ms = mv[i][q];
+            sgd_one(ps, ms, n + q < K ? acc[q][i] : 0.f, opt);
+            pv[i][q] = n + q < K ? ps : 0.f;
+            mv[i][q] = ms;
+        }
+        if (p_vec && n < K) {
+            *reinterpret_cast<f32x4*>(p) = pv[i];
+            *reinterpret_cast<f32x4*>(m) = mv[i];
         } else {
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-                if (n + q < K) sgd_one(p[q], m[q], acc[q][i], opt);
+                if (n + q < K) {
+                    p[q] = pv[i][q];
+                    m[q] = mv[i][q];
+                }
+        }
+        if (NEXT) *reinterpret_cast<f32x4*>(w_lds + (4 * g + i) * PITCH + wave * 64 + 4 * r) = pv[i];
+    }
+    if constexpr (NEXT) {
+        __syncthreads();
+        for (int b0 = 16 * wave; b0 < B; b0 += 64) {
+            f32x4 sum[4] = {};
+#pragma unroll
+            for (int u = 0; u < 16; ++u) {
+                const f32x4 w = *reinterpret_cast<const f32x4*>(w_lds + r * PITCH + 16 * u + 4 * g);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) sum[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(xn[u][j], w[j], sum[j], 0, 0, 0);
+            }
+            const f32x4 v = (sum[0] + sum[1]) + (sum[2] + sum[3]);
+            if (b0 + 64 < B) load_next(b0 + 64);
+            // lane holds samples b0 + 4 g + i, hidden unit m0 + r
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (b0 + 4 * g + i < B) part[((int64_t)(b0 + 4 * g + i) * n_blocks + z) * hid + m0 + r] = v[i];
         }
     }
 }
 
+int mlp_next_splits(int K) { return (K + 255) / 256; }
+
 void launch_mlp_update(hipStream_t s, float* params, float* momentum, const MlpOffsets& off, const float* x, const BatchRows& rows, const float* h,
-                       const float* dlogits, const float* dpre, int B, int hid, int C, int K, const bls_sgd& opt) {
+                       const float* dlogits, const float* dpre, int B, int hid, int C, int K, const bls_sgd& opt, const BatchRows* next, float* part) {
     const int x_vec = K % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0;
     const int p_vec = K % 4 == 0 && (reinterpret_cast<uintptr_t>(params + off.fc1_w) | reinterpret_cast<uintptr_t>(momentum + off.fc1_w)) % 16 == 0;
     const unsigned blocks = (unsigned)((C + 1) * ((hid + 63) / 64) + (hid / 16) * ((K + 255) / 256));
-    hipLaunchKernelGGL(mlp_update_kernel, dim3(blocks), dim3(256), 0, s, params, momentum, off, x, rows, h, dlogits, dpre, B, hid, C, K, opt, x_vec,
-                       p_vec);
+#define MLP_UPDATE(NEXT) \
+    hipLaunchKernelGGL(mlp_update_kernel<NEXT>, dim3(blocks), dim3(256), 0, s, params, momentum, off, x, rows, h, dlogits, dpre, B, hid, C, K, opt, x_vec, \
+                       p_vec, next ? *next : BatchRows{}, part)
+    if (next) MLP_UPDATE(true);
+    else MLP_UPDATE(false);
+#undef MLP_UPDATE
 }

@@ -42,6 +42,11 @@ typedef uint8_t act_t;  // activations are addressed as bytes; the model's stora
 
 // ---- MLP ----------------------------------------------------------------------------------------
 
+// Batches up to this size leave the next step's first layer to the update, which has one workgroup per 16 x 256 weights; a launch of its
+// own spreads the samples over more of them (pass of 8 steps of 128 with 256 hidden units 260 -> 224 us; of 4 steps of 256 with 256 / 128
+// hidden units 202 -> 185 / 155 -> 161).
+constexpr int MLP_NEXT_MAX_B = 128;
+
 struct MlpScratch {
     float *part, *h, *loss, *dlogits, *dpre;
 };
@@ -49,7 +54,8 @@ struct MlpScratch {
 MlpScratch carve_mlp(Carver& c, const bls_model* m, int B, bool train) {
     MlpScratch s{};
     const int hid = m->desc.hidden;
-    s.part = c.take<float>((size_t)B * MLP_SPLITS * hid);
+    const int next = train && B <= MLP_NEXT_MAX_B ? mlp_next_splits(m->d_in) : 0;
+    s.part = c.take<float>((size_t)B * (next > MLP_SPLITS ? next : MLP_SPLITS) * hid);
     s.loss = c.take<float>(B);
     if (train) {
         s.h = c.take<float>((size_t)B * hid);
@@ -532,10 +538,14 @@ int net_local_step(bls_ctx* ctx, const bls_model* m, float* params, float* buffe
         for (int64_t j = 0; j < tau; ++j) {
             float* loss = step_losses_out ? step_losses_out + j * B : s.loss;
             const BatchRows rows{sel, k, j * B};
-            PROF(ctx, PROF_GEMM, launch_mlp_fc1(st, x_pool, rows, params + m->fc1_w, B, hid, m->d_in, s.part));
-            PROF(ctx, PROF_HEAD, launch_head_mlp(st, s.part, B, MLP_SPLITS, hid, params + m->fc1_b, params + m->fc2_w, params + m->fc2_b, C, y_pool,
+            const BatchRows after{sel, k, (j + 1) * B};
+            const bool ahead = B <= MLP_NEXT_MAX_B;
+            const bool there = ahead && j > 0;   // the step before left this one's partial sums
+            if (!there) PROF(ctx, PROF_GEMM, launch_mlp_fc1(st, x_pool, rows, params + m->fc1_w, B, hid, m->d_in, s.part));
+            PROF(ctx, PROF_HEAD, launch_head_mlp(st, s.part, B, there ? mlp_next_splits(m->d_in) : MLP_SPLITS, hid, params + m->fc1_b, params + m->fc2_w, params + m->fc2_b, C, y_pool,
                                 rows, loss, s.h, s.dlogits, s.dpre, inv_b));
-            PROF(ctx, PROF_GEMM, launch_mlp_update(st, params, momentum, off, x_pool, rows, s.h, s.dlogits, s.dpre, B, hid, C, m->d_in, opt));
+            PROF(ctx, PROF_GEMM, launch_mlp_update(st, params, momentum, off, x_pool, rows, s.h, s.dlogits, s.dpre, B, hid, C, m->d_in, opt,
+                                ahead && j + 1 < tau ? &after : nullptr, s.part));
         }
     } else {
         ResScratch s = carve_resnet(c, m, B, true);

@@ -123,3 +123,32 @@ def test_gradients_and_update_at_the_edges_of_the_kernels(hw, channels, hidden, 
         assert_tensors_close(delta(gp), delta(rp), 3e-4, "parameter change")
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("hw,channels,hidden,classes,batch", [
+    (5, 3, 16, 2, 1),        # 75 inputs, no 16-byte loads; one sample
+    (16, 1, 32, 10, 17),     # 256 inputs: one block of inputs, filled; a second group of 16 samples with one of them
+    (18, 1, 48, 17, 65),     # 324 inputs: a second block, nearly empty; a second round of samples per wave; more classes than are preloaded
+    (8, 2, 16, 7, 128),      # the largest batch whose next first layer rides in the update
+    (8, 2, 16, 7, 129),      # the smallest whose does not
+])
+def test_steps_whose_first_layer_rides_in_the_update(hw, channels, hidden, classes, batch):
+    """Three steps: the partial sums of the second and third come from the update before them.  Criteria as for one step, three times
+    as wide."""
+    import torch
+    import paper_2508_08540_amd as bls
+    ctx = bls.Context(0)
+    try:
+        h = Harness(torch, bls, ctx, bls.Model.mlp(hw, channels, hidden, classes), oracle.MLP())
+        x, y = synth.image_pool(3, 300, classes, hw=hw, channels=channels)
+        p = synth.mlp_init(3, hw * hw * channels, hidden, classes)
+        sel = np.arange(299, 3, -1, dtype=np.int32)
+        mom0 = {k: 0.01 * synth.normal(5, i, v.size).reshape(v.shape) for i, (k, v) in enumerate(p.items())}
+        rp, _, rm, rl = oracle.local_step(h.oracle_model, p, {}, mom0, x, y, sel, batch, 3, 0.01, momentum=0.9, weight_decay=1e-2)
+        gp, _, gm, gl = h.local_step(p, {}, mom0, x, y, sel, batch, 3, lr=0.01, mu=0.9, wd=1e-2)
+        assert_losses_close(gl, rl, rtol=2e-4)
+        assert_tensors_close(gm, rm, 3e-4, "momentum")
+        delta = lambda a: {k: a[k] - p[k].astype(np.float64) for k in p}
+        assert_tensors_close(delta(gp), delta(rp), 9e-4, "parameter change")
+    finally:
+        ctx.close()
