@@ -26,7 +26,6 @@ int bls_arena_reserve(bls_ctx* ctx, size_t bytes) {
     if (bytes <= ctx->arena_bytes) return BLS_OK;
     BLS_HIP(ctx, hipStreamSynchronize(ctx->stream));
     if (ctx->aux) BLS_HIP(ctx, hipStreamSynchronize(ctx->aux));
-    if (ctx->aux2) BLS_HIP(ctx, hipStreamSynchronize(ctx->aux2));
     if (ctx->arena) BLS_HIP(ctx, hipFree(ctx->arena));
     ctx->arena = nullptr;
     ctx->arena_bytes = 0;
@@ -66,9 +65,8 @@ int bls_ctx_create(bls_ctx** out, int device, void* hip_stream) {
         ctx->max_lds = (size_t)optin;
     (void)hipGetLastError();
     if (hipStreamCreateWithFlags(&ctx->aux, hipStreamNonBlocking) != hipSuccess ||
-        hipEventCreateWithFlags(&ctx->join_event, hipEventDisableTiming) != hipSuccess ||
-        hipEventCreateWithFlags(&ctx->join_event2, hipEventDisableTiming) != hipSuccess ||
-        hipEventCreateWithFlags(&ctx->head_event, hipEventDisableTiming) != hipSuccess) {
+        hipEventCreateWithFlags(&ctx->join_event, STREAM_EVENT) != hipSuccess ||
+        hipEventCreateWithFlags(&ctx->head_event, STREAM_EVENT) != hipSuccess) {
         delete ctx;
         return BLS_EHIP;
     }
@@ -93,13 +91,8 @@ void bls_ctx_destroy(bls_ctx* ctx) {
         (void)hipStreamSynchronize(ctx->aux);
         (void)hipStreamDestroy(ctx->aux);
     }
-    if (ctx->aux2) {
-        (void)hipStreamSynchronize(ctx->aux2);
-        (void)hipStreamDestroy(ctx->aux2);
-    }
     for (hipEvent_t e : ctx->fork_events) (void)hipEventDestroy(e);
     if (ctx->join_event) (void)hipEventDestroy(ctx->join_event);
-    if (ctx->join_event2) (void)hipEventDestroy(ctx->join_event2);
     if (ctx->head_event) (void)hipEventDestroy(ctx->head_event);
     if (ctx->arena) (void)hipFree(ctx->arena);
     if (ctx->round_losses) (void)hipFree(ctx->round_losses);
@@ -129,7 +122,7 @@ int bls_ctx_set_lanes(bls_ctx* ctx, int lanes) {
         lane->owns_stream = true;
         ctx->lanes.push_back(lane);
     }
-    if (!ctx->round_start) BLS_HIP(ctx, hipEventCreateWithFlags(&ctx->round_start, hipEventDisableTiming));
+    if (!ctx->round_start) BLS_HIP(ctx, hipEventCreateWithFlags(&ctx->round_start, STREAM_EVENT));
     return BLS_OK;
 }
 
@@ -588,7 +581,7 @@ int communication_round(bls_ctx* ctx, const bls_model* model, float* global_para
     const int n_lanes = (int)ctx->lanes.size();
     while ((int)ctx->lane_events.size() < P) {
         hipEvent_t e;
-        BLS_HIP(ctx, hipEventCreateWithFlags(&e, hipEventDisableTiming));
+        BLS_HIP(ctx, hipEventCreateWithFlags(&e, STREAM_EVENT));
         ctx->lane_events.push_back(e);
     }
     const float* trained[64];

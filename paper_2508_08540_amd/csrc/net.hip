@@ -277,18 +277,32 @@ const act_t* resnet_forward(bls_ctx* ctx, hipStream_t st, const bls_model* m, co
 // stream before the update.
 // `early_from`: the caller updates the parameters of layers early_from .. L-1 (and everything behind the last layer) as soon
 // as their weight gradients are in, while those of the layers below still run; the events that mark the two moments are
-// fork_events[L] / [L + 1] (one per side stream) and the join events.
+// fork_events[L] and the join event.
 int resnet_backward(bls_ctx* ctx, hipStream_t st, const bls_model* m, const float* params, int B, ResScratch& s, int early_from) {
     const int L = (int)m->layers.size();
-    while ((int)ctx->fork_events.size() < L + 2) {
+    while ((int)ctx->fork_events.size() < L + 1) {
         hipEvent_t e;
-        BLS_HIP(ctx, hipEventCreateWithFlags(&e, hipEventDisableTiming));
+        BLS_HIP(ctx, hipEventCreateWithFlags(&e, STREAM_EVENT));
         ctx->fork_events.push_back(e);
     }
-    // the second side stream exists only where it is used: idle streams still take part in the mapping of streams to
-    // hardware queues and cost concurrent workers (lanes) 15 % of their throughput
-    const bool two_sides = s.act == ACT_BF16;
-    if (two_sides && !ctx->aux2) BLS_HIP(ctx, hipStreamCreateWithFlags(&ctx->aux2, hipStreamNonBlocking));
+    // Profiling puts events of its own on these launches; a stream that is being captured takes only events that are recorded.
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    BLS_HIP(ctx, hipStreamIsCapturing(st, &capture));
+    const bool may_stamp = !ctx->profiling && capture == hipStreamCaptureStatusNone;
+    // dy of layer l is there: its weight gradient goes to the side stream.  `stamped`: the launch that stores dy carries the event as
+    // its own completion signal; an event recorded behind it is a packet of its own on the critical path (bf16 step 549 -> 520 us).
+    auto weight_gradient = [&](int l, bool stamped) -> int {
+        if (!stamped) BLS_HIP(ctx, hipEventRecord(ctx->fork_events[l], st));
+        BLS_HIP(ctx, hipStreamWaitEvent(ctx->aux, ctx->fork_events[l], 0));
+        if (l == L - 1) {   // the head's weight gradient, ready since the forward pass, needs no fork of its own
+            ProfScope prof_(ctx, PROF_HEAD, ctx->aux);
+            launch_head_wgrad(ctx->aux, s.dlogits, s.feat, B, m->desc.classes, m->final_c, s.grad + m->fc_w, s.grad + m->fc_b, s.reps);
+        }
+        const ConvShape cs = shape_of(m->layers[l], B);
+        PROF_KERNEL(ctx, PROF_CONV_WGRAD, launch_conv_wgrad(ctx->aux, s.act, cs, l == 0 ? s.xpad : s.a[l - 1], s.dy[l], s.wacc + s.utab.e[l].acc_off, kt, s.reps));
+        if (l == early_from) BLS_HIP(ctx, hipEventRecord(ctx->fork_events[L], ctx->aux));   // the last weight gradient of the early part
+        return BLS_OK;
+    };
     const ConvBn& last = m->layers[L - 1];
     const void* dout = s.dfeat;
     int shared = last.h_out * last.h_out;
@@ -302,7 +316,6 @@ int resnet_backward(bls_ctx* ctx, hipStream_t st, const bls_model* m, const floa
         ConvShape cs = shape_of(cb, B);
         const int64_t pixels = (int64_t)B * cb.h_out * cb.h_out;
         const bool is_conv2 = l > 0 && (l % 2 == 0);
-        const act_t* x_in = l == 0 ? s.xpad : s.a[l - 1];
         if (l == L - 1) {
             // top layer: its upstream gradient comes from the head; lower layers get these sums from the
             // input-gradient kernel of the layer above
@@ -312,18 +325,6 @@ int resnet_backward(bls_ctx* ctx, hipStream_t st, const bls_model* m, const floa
         // Layers whose upstream gradient is a tensor (all but the top one): the input-gradient convolution computes dy itself
         // while staging (for a stride-2 layer at the even positions of the zero-inserted image), the element-wise kernel goes
         const bool fused_bwd = l > 0 && !shared && cb.c_out <= 64 && cb.c_out >= FUSED_BWD_MIN_C;
-        auto weight_gradient = [&]() -> int {
-            BLS_HIP(ctx, hipEventRecord(ctx->fork_events[l], st));
-            // With bf16 storage the main stream's kernels are shorter than the weight gradients (which multiply in fp32), the
-            // side stream is the long pole and neighbouring layers' weight gradients alternate between two streams; with
-            // fp32 storage a third queue only slows the critical path (measured: +1.7 % per pass).
-            hipStream_t side = (two_sides && (l & 1)) ? ctx->aux2 : ctx->aux;
-            BLS_HIP(ctx, hipStreamWaitEvent(side, ctx->fork_events[l], 0));
-            PROF_KERNEL(ctx, PROF_CONV_WGRAD, launch_conv_wgrad(side, s.act, cs, x_in, s.dy[l], s.wacc + s.utab.e[l].acc_off, kt, s.reps));
-            // the last weight gradient of the early part on this stream (two streams take the layers in turn)
-            if (l >= early_from && l < early_from + (two_sides ? 2 : 1)) BLS_HIP(ctx, hipEventRecord(ctx->fork_events[L + (side == ctx->aux ? 0 : 1)], side));
-            return BLS_OK;
-        };
         if (is_conv2 && !shared) block_g = dout;   // as stored by the launch of the layer above
         if (!fused_bwd) {
             // the head's gradient is one row per sample: the element-wise kernel leaves the gradient behind the ReLU as a tensor
@@ -331,10 +332,11 @@ int resnet_backward(bls_ctx* ctx, hipStream_t st, const bls_model* m, const floa
             PROF(ctx, PROF_NORM, launch_bn_bwd_apply(st, s.act, dout, shared, s.a[l], s.y[l], pixels, cb.c_out, s.mean[l], s.invstd[l], params + cb.gamma_off,
                                 s.sums + ((size_t)l * 2 + 1) * FIX_SET, s.grad + cb.gamma_off, s.grad + cb.beta_off, s.dy[l], g_out, nullptr, s.reps));
             if (g_out) block_g = g_out;
-            int rcw = weight_gradient();
+            int rcw = weight_gradient(l, false);
             if (rcw != BLS_OK) return rcw;
         }
         if (l == 0) break;
+        bool stamped = false;
         act_t* dx = nullptr;   // neither the tensor the fused staging reads nor the shortcut gradient still to be added
         for (act_t* cand : ring)
             if (cand != dout && cand != block_g) dx = cand;
@@ -357,10 +359,16 @@ int resnet_backward(bls_ctx* ctx, hipStream_t st, const bls_model* m, const floa
                 e.bw_inv_count = 1.f / (float)pixels;
                 e.bw_dy_out = s.dy[l];
             }
-            PROF_KERNEL(ctx, PROF_CONV_DGRAD, launch_conv_dgrad(st, s.act, cs, s.dy[l], s.wpack + s.dgrad_off[l], dx, &e, kt, s.reps));
+            stamped = fused_bwd && may_stamp;
+            if (stamped) {
+                const KernelTiming done{nullptr, ctx->fork_events[l]};
+                launch_conv_dgrad(st, s.act, cs, s.dy[l], s.wpack + s.dgrad_off[l], dx, &e, &done, s.reps);
+            } else {
+                PROF_KERNEL(ctx, PROF_CONV_DGRAD, launch_conv_dgrad(st, s.act, cs, s.dy[l], s.wpack + s.dgrad_off[l], dx, &e, kt, s.reps));
+            }
         }
         if (fused_bwd) {
-            int rcw = weight_gradient();   // dy[l] exists once the input gradient has run
+            int rcw = weight_gradient(l, stamped);   // dy[l] exists once the input gradient has run
             if (rcw != BLS_OK) return rcw;
         }
         if (!is_conv2) block_g = nullptr;   // added by this launch
@@ -368,7 +376,6 @@ int resnet_backward(bls_ctx* ctx, hipStream_t st, const bls_model* m, const floa
         shared = 0;
     }
     BLS_HIP(ctx, hipEventRecord(ctx->join_event, ctx->aux));
-    if (two_sides) BLS_HIP(ctx, hipEventRecord(ctx->join_event2, ctx->aux2));
     return BLS_OK;
 }
 
@@ -381,33 +388,23 @@ int resnet_train_step(bls_ctx* ctx, hipStream_t st, const bls_model* m, float* p
     const act_t* fin = resnet_forward(ctx, st, m, params, buffers, B, s, true, first);
     PROF(ctx, PROF_HEAD, launch_head_forward(st, s.act, fin, B, m->final_hw * m->final_hw, m->final_c, params + m->fc_w, params + m->fc_b, C, s.yb,
                         loss, s.feat, s.dlogits, s.dfeat, inv_b, false, s.reps));
-    // the head's weight gradient is only needed by the update: side stream, joined at the end of the backward pass
-    BLS_HIP(ctx, hipEventRecord(ctx->head_event, st));
-    BLS_HIP(ctx, hipStreamWaitEvent(ctx->aux, ctx->head_event, 0));
-    {
-        ProfScope prof_(ctx, PROF_HEAD, ctx->aux);
-        launch_head_wgrad(ctx->aux, s.dlogits, s.feat, B, C, m->final_c, s.grad + m->fc_w, s.grad + m->fc_b, s.reps);
-    }
     // The update comes in two launches: the layers from `early` up (nearly all parameters) as soon as their weight gradients
     // are in, behind which the side stream still works on the weight gradients of the first layers; those layers, and the
     // clearing of the batch-norm accumulators, after the join.
     const int L = (int)m->layers.size();
     const int early = L > 3 ? 3 : L;
-    const bool two_sides = s.act == ACT_BF16;
     int rc = resnet_backward(ctx, st, m, params, B, s, early);
     if (rc != BLS_OK) return rc;
     const int64_t split = early < L ? m->layers[early].w_off : m->layers[L - 1].beta_off + m->layers[L - 1].c_out;
     // gradients of the convolution weights are still in the accumulators: the update reads them there
     if (early < L) {
         BLS_HIP(ctx, hipStreamWaitEvent(st, ctx->fork_events[L], 0));
-        if (two_sides && early + 1 < L) BLS_HIP(ctx, hipStreamWaitEvent(st, ctx->fork_events[L + 1], 0));
     } else {
         BLS_HIP(ctx, hipStreamWaitEvent(st, ctx->join_event, 0));   // nothing below: the head's weight gradient is all there is to wait for
     }
     PROF(ctx, PROF_UPDATE, launch_update(st, s.act, params, momentum, s.grad, m->num_params, opt.lr, opt.momentum, opt.weight_decay,
                                          s.wacc, s.wpack, s.utab, nullptr, 0, s.reps, split, -1));
     BLS_HIP(ctx, hipStreamWaitEvent(st, ctx->join_event, 0));
-    if (two_sides) BLS_HIP(ctx, hipStreamWaitEvent(st, ctx->join_event2, 0));
     PROF(ctx, PROF_UPDATE, launch_update(st, s.act, params, momentum, s.grad, m->num_params, opt.lr, opt.momentum, opt.weight_decay,
                                          s.wacc, s.wpack, s.utab, s.sums, (int64_t)L * 2 * FIX_SET, s.reps, 0, split));
     return BLS_OK;

@@ -645,7 +645,7 @@ int seq_local_step(bls_ctx* ctx, const bls_model* m, float* params, float* momen
         auto aside = [&]() -> int {
             if (n_forks == ctx->fork_events.size()) {
                 hipEvent_t ev;
-                BLS_HIP(ctx, hipEventCreateWithFlags(&ev, hipEventDisableTiming));
+                BLS_HIP(ctx, hipEventCreateWithFlags(&ev, STREAM_EVENT));
                 ctx->fork_events.push_back(ev);
             }
             hipEvent_t ev = ctx->fork_events[n_forks++];

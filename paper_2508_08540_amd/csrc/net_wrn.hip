@@ -468,7 +468,7 @@ int backward(bls_ctx* ctx, hipStream_t st, const bls_model* m, const float* para
     auto wgrad_aside = [&](const ConvRef& cr, const act_t* x, const act_t* dy) -> int {
         if (n_forks == ctx->fork_events.size()) {
             hipEvent_t e;
-            BLS_HIP(ctx, hipEventCreateWithFlags(&e, hipEventDisableTiming));
+            BLS_HIP(ctx, hipEventCreateWithFlags(&e, STREAM_EVENT));
             ctx->fork_events.push_back(e);
         }
         hipEvent_t ev = ctx->fork_events[n_forks++];
