@@ -372,7 +372,7 @@ __global__ __launch_bounds__(256, AK ? 2 : 3) void gemm16_kernel(Gemm16Desc d) {
 
 // ---- tiles straight into LDS (gemm16_direct_kernel) --------------------------------------------------------------------------
 //
-// Workgroup = 32 WMB x 32 WNB tile of C, four waves as 2 x 2, each 16 WMB x 16 WNB.  K advances 32 at a time through
+// Workgroup = 32 WMB x 32 WNB tile of C, four waves as 2 x 2, each 16 WMB x 16 WNB.  K advances 32 KS at a time through
 // GD16_STAGES LDS buffers [row][32 k] that global_load_lds fills (16 bytes per lane, 1 KB of consecutive LDS per
 // instruction): no staging registers, no LDS store instructions, two steps of loads in flight.  One barrier per step: a wave
 // waits for its own loads of the step (counted, the younger step stays in flight), the barrier makes everybody's visible and
@@ -710,13 +710,14 @@ constexpr bool gd16_runs(bool a_kmajor, int wmb) { return a_kmajor && wmb < 8; }
 // waves per SIMD the registers have to allow, for 16 x 16 blocks per wave
 constexpr int gd16_waves(bool runs, int blocks) { return blocks >= (runs ? 16 : 32) ? 2 : 3; }
 
-template <bool AK, bool BK, int EPI, int WMB, int WNB>
+template <bool AK, bool BK, int EPI, int WMB, int WNB, int KS>
 __global__ __launch_bounds__(256, gd16_waves(gd16_runs(AK, WMB), WMB * WNB)) void gemm16_direct_kernel(Gemm16Desc d) {
     static_assert(!AK || BK, "a k-major A comes with a k-major B");
     constexpr bool RUNS = gd16_runs(AK, WMB);
     constexpr int TM = 32 * WMB, TN = 32 * WNB;
     constexpr int LA = TM / 64, LB = TN / 64;        // load instructions per wave and step
-    constexpr int STAGE = (TM + TN) * 4;             // 16-byte slots
+    constexpr int SUB = (TM + TN) * 4, STAGE = KS * SUB;   // 16-byte slots of 32 k, of a stage
+    constexpr int STEP_K = KS * G16_K;
     extern __shared__ u32x4 gd16_lds[];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -729,8 +730,8 @@ __global__ __launch_bounds__(256, gd16_waves(gd16_runs(AK, WMB), WMB * WNB)) voi
     const int z1 = z / d.inner, z2 = z - z1 * d.inner;
     const int k_begin = split * d.k_chunk;
     const int k_end = min(d.K, k_begin + d.k_chunk);
-    const int steps = (k_end - k_begin + G16_K - 1) / G16_K;
-    const bool tail = ((k_end - k_begin) % G16_K) != 0;        // the last step is not a whole one
+    const int steps = (k_end - k_begin + STEP_K - 1) / STEP_K;
+    const bool tail = ((k_end - k_begin) % STEP_K) != 0;        // the last step is not a whole one
 
     // the operands advance one step per request; a segmented contraction jumps to the next segment's matrices
     const int seg0 = d.k_seg ? k_begin / d.k_seg : 0;
@@ -758,9 +759,9 @@ __global__ __launch_bounds__(256, gd16_waves(gd16_runs(AK, WMB), WMB * WNB)) voi
         __builtin_amdgcn_global_load_lds((gd16_global_ptr*)src, (gd16_lds_ptr*)dst, 16, 0, 0);
     };
     auto advance = [&]() {
-        A += adv_a;
-        B += adv_b;
-        seg_left -= G16_K;
+        A += KS * adv_a;
+        B += KS * adv_b;
+        seg_left -= STEP_K;
         if (seg_left == 0) {
             seg_left = d.k_seg;
             A += d.sa_seg - (AK ? (int64_t)d.k_seg * d.lda : (d.k_seg >> 5) * d.a_panel);
@@ -768,31 +769,34 @@ __global__ __launch_bounds__(256, gd16_waves(gd16_runs(AK, WMB), WMB * WNB)) voi
         }
     };
     auto request = [&](int step, int buf) {
-        u32x4* base = gd16_lds + buf * STAGE;
-        if (tail && step == steps - 1) {
-            const int left = k_end - k_begin - step * G16_K;   // 1 .. 31
 #pragma unroll
-            for (int i = 0; i < LA; ++i) {
-                int row, k;
-                gd16_slot<AK, false, TM>((4 * i + wave) * 64 + lane, row, k);
-                u32x4* dst = base + (4 * i + wave) * 64;
-                if (k < left) load16(A + offa[i], dst);
-                else dst[lane] = u32x4{0u, 0u, 0u, 0u};
+        for (int sub = 0; sub < KS; ++sub) {
+            u32x4* base = gd16_lds + buf * STAGE + sub * SUB;
+            if (tail && step == steps - 1) {
+                const int left = k_end - k_begin - step * STEP_K - sub * G16_K;   // below 32; nothing of this part where it is not positive
+#pragma unroll
+                for (int i = 0; i < LA; ++i) {
+                    int row, k;
+                    gd16_slot<AK, false, TM>((4 * i + wave) * 64 + lane, row, k);
+                    u32x4* dst = base + (4 * i + wave) * 64;
+                    if (k < left) load16(A + sub * adv_a + offa[i], dst);
+                    else dst[lane] = u32x4{0u, 0u, 0u, 0u};
+                }
+#pragma unroll
+                for (int i = 0; i < LB; ++i) {
+                    int row, k;
+                    gd16_slot<BK, true, TN>((4 * i + wave) * 64 + lane, row, k);
+                    u32x4* dst = base + TM * 4 + (4 * i + wave) * 64;
+                    if (k < left) load16(B + sub * adv_b + offb[i], dst);
+                    else dst[lane] = u32x4{0u, 0u, 0u, 0u};
+                }
+                continue;
             }
 #pragma unroll
-            for (int i = 0; i < LB; ++i) {
-                int row, k;
-                gd16_slot<BK, true, TN>((4 * i + wave) * 64 + lane, row, k);
-                u32x4* dst = base + TM * 4 + (4 * i + wave) * 64;
-                if (k < left) load16(B + offb[i], dst);
-                else dst[lane] = u32x4{0u, 0u, 0u, 0u};
-            }
-            return;
+            for (int i = 0; i < LA; ++i) load16(A + sub * adv_a + offa[i], base + (4 * i + wave) * 64);
+#pragma unroll
+            for (int i = 0; i < LB; ++i) load16(B + sub * adv_b + offb[i], base + TM * 4 + (4 * i + wave) * 64);
         }
-#pragma unroll
-        for (int i = 0; i < LA; ++i) load16(A + offa[i], base + (4 * i + wave) * 64);
-#pragma unroll
-        for (int i = 0; i < LB; ++i) load16(B + offb[i], base + TM * 4 + (4 * i + wave) * 64);
         advance();
     };
 
@@ -822,54 +826,57 @@ __global__ __launch_bounds__(256, gd16_waves(gd16_runs(AK, WMB), WMB * WNB)) voi
     auto multiply = [&](int buf, auto load, int to) {
         constexpr bool LOAD = decltype(load)::value, FRONT = AK && WMB >= 8;
         constexpr int AHEAD = !AK && WMB >= 8 ? 3 : WMB;
-        const u32x4* st = gd16_lds + buf * STAGE;
-        const uint32_t sb = (uint32_t)(uintptr_t)(gd16_lds_ptr*)st;
-        u32x4* base = gd16_lds + to * STAGE;
-        auto piece = [&](int p) {
-            if (p < LA) load16(A + offa[p], base + (4 * p + wave) * 64);
-            else if (p < LA + LB) load16(B + offb[p - LA], base + TM * 4 + (4 * (p - LA) + wave) * 64);
-        };
-        u32x4 a[WMB], b[WNB];
-        if constexpr (LOAD && FRONT)
 #pragma unroll
-            for (int p = 0; p < LA + LB; ++p) piece(p);
-        if constexpr (!BK)
+        for (int sub = 0; sub < KS; ++sub) {
+            const u32x4* st = gd16_lds + buf * STAGE + sub * SUB;
+            const uint32_t sb = (uint32_t)(uintptr_t)(gd16_lds_ptr*)st;
+            u32x4* base = gd16_lds + to * STAGE + sub * SUB;
+            auto piece = [&](int p) {
+                if (p < LA) load16(A + sub * adv_a + offa[p], base + (4 * p + wave) * 64);
+                else if (p < LA + LB) load16(B + sub * adv_b + offb[p - LA], base + TM * 4 + (4 * (p - LA) + wave) * 64);
+            };
+            u32x4 a[WMB], b[WNB];
+            if constexpr (LOAD && FRONT)
 #pragma unroll
-            for (int t = 0; t < WNB; ++t) b[t] = st[rb + 128 * (t >> 1) + 16 * (t & 1)];
-        if constexpr (!AK)
+                for (int p = 0; p < LA + LB; ++p) piece(p);
+            if constexpr (!BK)
 #pragma unroll
-            for (int t = 0; t < AHEAD; ++t) a[t] = st[ra + 64 * t];
-        if constexpr (BK) {
-            constexpr int NA = AK ? WMB : 0;
-            uint32_t at[WNB + NA];
-            u32x4 x[WNB + NA];
+                for (int t = 0; t < WNB; ++t) b[t] = st[rb + 128 * (t >> 1) + 16 * (t & 1)];
+            if constexpr (!AK)
 #pragma unroll
-            for (int t = 0; t < WNB; ++t) at[t] = sb + tb + 32 * ((wn * WNB + t) ^ fb);
+                for (int t = 0; t < AHEAD; ++t) a[t] = st[ra + 64 * t];
+            if constexpr (BK) {
+                constexpr int NA = AK ? WMB : 0;
+                uint32_t at[WNB + NA];
+                u32x4 x[WNB + NA];
 #pragma unroll
-            for (int t = 0; t < NA; ++t) at[WNB + t] = sb + ta + 32 * ((wm * WMB + t) ^ fa);
-            gd16_transposed<TN, TM, WNB, NA>(at, x);
+                for (int t = 0; t < WNB; ++t) at[t] = sb + tb + 32 * ((wn * WNB + t) ^ fb);
 #pragma unroll
-            for (int t = 0; t < WNB; ++t) b[t] = x[t];
+                for (int t = 0; t < NA; ++t) at[WNB + t] = sb + ta + 32 * ((wm * WMB + t) ^ fa);
+                gd16_transposed<TN, TM, WNB, NA>(at, x);
 #pragma unroll
-            for (int t = 0; t < NA; ++t) a[t] = x[WNB + t];
-        }
-        static_assert(LA + LB <= WMB, "a load per block row");
-        __builtin_amdgcn_sched_barrier(0);
+                for (int t = 0; t < WNB; ++t) b[t] = x[t];
 #pragma unroll
-        for (int mt = 0; mt < WMB; ++mt) {
-            if (!AK && mt + AHEAD < WMB) a[mt + AHEAD] = st[ra + 64 * (mt + AHEAD)];
+                for (int t = 0; t < NA; ++t) a[t] = x[WNB + t];
+            }
+            static_assert(LA + LB <= WMB, "a load per block row");
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int nt = 0; nt < WNB; ++nt)
-                acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_v, b[nt]), __builtin_bit_cast(bf16x8_v, a[mt]), acc[mt][nt], 0, 0, 0);
-            if constexpr (LOAD && !FRONT) piece(mt);
-            __builtin_amdgcn_sched_barrier(0);
+            for (int mt = 0; mt < WMB; ++mt) {
+                if (!AK && mt + AHEAD < WMB) a[mt + AHEAD] = st[ra + 64 * (mt + AHEAD)];
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int nt = 0; nt < WNB; ++nt)
+                    acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_v, b[nt]), __builtin_bit_cast(bf16x8_v, a[mt]), acc[mt][nt], 0, 0, 0);
+                if constexpr (LOAD && !FRONT) piece(mt);
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
         if constexpr (LOAD) advance();
     };
     auto end_of_run = [&](int i) {
         if constexpr (RUNS) {
-            if ((i + 1) % G16_RUN == 0) {
+            if ((i + 1) % (G16_RUN / KS) == 0) {
 #pragma unroll
                 for (int mt = 0; mt < WMB; ++mt)
 #pragma unroll
@@ -886,7 +893,7 @@ __global__ __launch_bounds__(256, gd16_waves(gd16_runs(AK, WMB), WMB * WNB)) voi
     int buf = 0, i = 0;
     // while whole steps are still to be requested; the GD16_STAGES - 2 youngest may stay in flight
     for (const int steady = steps - (GD16_STAGES - 1) - (tail ? 1 : 0); i < steady; ++i) {
-        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((GD16_STAGES - 2) * (LA + LB)) : "memory");
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((GD16_STAGES - 2) * KS * (LA + LB)) : "memory");
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
         multiply(buf, std::true_type{}, buf == 0 ? GD16_STAGES - 1 : buf - 1);
@@ -895,7 +902,7 @@ __global__ __launch_bounds__(256, gd16_waves(gd16_runs(AK, WMB), WMB * WNB)) voi
     }
     for (; i < steps; ++i) {
         // a tail is requested by fewer instructions: no counting with it
-        if (!tail && i + 1 < steps) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(LA + LB) : "memory");
+        if (!tail && i + 1 < steps) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(KS * (LA + LB)) : "memory");
         else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
@@ -975,28 +982,33 @@ int launch_gemm16(hipStream_t s, Gemm16Desc d) {
     if (direct) {
         const int z = d.batch * d.splits;
         const int64_t t84 = (int64_t)((d.M + 255) / 256) * ((d.N + 127) / 128) * z, t44 = (int64_t)((d.M + 127) / 128) * ((d.N + 127) / 128) * z;
-#define GD16_LAUNCH(AKM, BKM, EPI, WMB, WNB)                                                                                         \
-    hipLaunchKernelGGL((gemm16_direct_kernel<AKM, BKM, EPI, WMB, WNB>),                                                               \
+        const int64_t t42 = (int64_t)((d.M + 127) / 128) * ((d.N + 63) / 64) * z;
+        const bool deep = t42 <= 512 && d.k_seg % (2 * G16_K) == 0 && (d.splits == 1 || k_chunk % (2 * G16_K) == 0);
+#define GD16_LAUNCH(AKM, BKM, EPI, WMB, WNB, KS)                                                                                     \
+    hipLaunchKernelGGL((gemm16_direct_kernel<AKM, BKM, EPI, WMB, WNB, KS>),                                                               \
                        dim3((unsigned)((d.N + 32 * WNB - 1) / (32 * WNB)), (unsigned)((d.M + 32 * WMB - 1) / (32 * WMB)), z), dim3(256), \
-                       GD16_STAGES * 32 * (WMB + WNB) * 64, s, d)
+                       GD16_STAGES * KS * 32 * (WMB + WNB) * 64, s, d)
 #define GD16_TILE(AKM, BKM, EPI)                              \
     do {                                                      \
-        if (t84 >= 400) GD16_LAUNCH(AKM, BKM, EPI, 8, 4);     \
-        else if (t44 >= 448) GD16_LAUNCH(AKM, BKM, EPI, 4, 4); \
-        else GD16_LAUNCH(AKM, BKM, EPI, 4, 2);                \
+        if (t84 >= 400) GD16_LAUNCH(AKM, BKM, EPI, 8, 4, 1);     \
+        else if (t44 >= 448) GD16_LAUNCH(AKM, BKM, EPI, 4, 4, 1); \
+        else if (deep) GD16_LAUNCH(AKM, BKM, EPI, 4, 2, 2);    \
+        else GD16_LAUNCH(AKM, BKM, EPI, 4, 2, 1);             \
     } while (0)
         // Tiles (measured, 8192 tokens): 256 x 128 from 400 of them (32 000 x 512 over the tokens, 500 tiles: 317 us, 364 with
         // 128 x 128); below that 128 x 128 from 448 (three 512-wide products: 23.2 us, 24.4 and 27.7 with the others); else
-        // 128 x 64 (512 x 512: 14.4 us, 16.0 and 21.2).
+        // 128 x 64 (512 x 512: 14.4 us, 16.0 and 21.2).  A step of 32 is only 8 matrix instructions of a wave of that tile: where its
+        // workgroups fit the chip two per compute unit (72 KB each), a step is 64 (512 x 512 over 8192 tokens in 8 parts 22.0 -> 19.6 us,
+        // 8192 x 512 x 512 15.5 -> 14.7; 576 workgroups, a second round, 35 -> 38).
         if (d.ce_part) {   // statistics per 64 columns of a wave
-            if (t84 >= 400) GD16_LAUNCH(false, false, 2, 8, 4);
-            else GD16_LAUNCH(false, false, 2, 4, 4);
+            if (t84 >= 400) GD16_LAUNCH(false, false, 2, 8, 4, 1);
+            else GD16_LAUNCH(false, false, 2, 4, 4, 1);
         } else if (d.ce_rows) {
-            if (t84 >= 400) GD16_LAUNCH(false, false, 3, 8, 4);
-            else GD16_LAUNCH(false, false, 3, 4, 4);
+            if (t84 >= 400) GD16_LAUNCH(false, false, 3, 8, 4, 1);
+            else GD16_LAUNCH(false, false, 3, 4, 4, 1);
         } else if (d.gelu_part) {
-            if (gemm16_gelu_rows(d.M, d.N) == 2 * ((d.M + 255) / 256)) GD16_LAUNCH(false, true, 4, 8, 4);
-            else GD16_LAUNCH(false, true, 4, 4, 4);
+            if (gemm16_gelu_rows(d.M, d.N) == 2 * ((d.M + 255) / 256)) GD16_LAUNCH(false, true, 4, 8, 4, 1);
+            else GD16_LAUNCH(false, true, 4, 4, 4, 1);
         } else if (d.G16 && !d.a_kmajor && !d.b_kmajor) GD16_TILE(false, false, 1);
         else if (d.a_kmajor) GD16_TILE(true, true, 0);
         else if (d.b_kmajor) GD16_TILE(false, true, 0);
