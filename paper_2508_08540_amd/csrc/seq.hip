@@ -171,75 +171,110 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const float* __restrict_
     }
 }
 
-// dx = inv * (dxh - mean(dxh) - xhat * mean(dxh * xhat)), dxh = dy * g.  A wave walks `rows_per_wave` rows and keeps
+// dx = inv * (dxh - mean(dxh) - xhat * mean(dxh * xhat)), dxh = dy * g.  A wave takes LN_BWD_ROWS_PER_WAVE rows and keeps
 // the column sums of dy * xhat and dy for its channels in registers; the four waves fold theirs through LDS and the
 // workgroup writes one row part[blockIdx.x][0 .. D) = sum dy * xhat, [D .. 2D) = sum dy and, with sum_dx, [2D .. 3D) = sum dx
-// (the gradient of a bias added just before the normalised tensor).
+// (the gradient of a bias added just before the normalised tensor).  NV = ceil(D / 256) vectors per lane.
+// Bound: HBM (59 MB for 8192 x 512 with a bf16 copy).  All rows of a wave are requested together and their reductions run side
+// by side: row after row the wave waited four times for memory and eight times for a chain of six shuffles (four steps of 64
+// sequences, where it shares the chip with weight gradients: 17.08 -> 16.82 ms).
+#define LN_BWD_ROWS_PER_WAVE 4
+template <int NV>
 __global__ __launch_bounds__(256) void layernorm_bwd_kernel(const float* __restrict__ dy, const float* __restrict__ x,
                                                             const float* __restrict__ stats, int64_t T, int D, const float* __restrict__ g,
                                                             float* __restrict__ dx, uint16_t* __restrict__ dx16, int64_t panel,
-                                                            float* __restrict__ part, int rows_per_wave, int sum_dx) {
-    __shared__ float red[4][3 * 1024];
-    const int lane = threadIdx.x & 63;
-    const int64_t w = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int64_t t0 = w * rows_per_wave, t1 = t0 + rows_per_wave < T ? t0 + rows_per_wave : T;
-    f32x4 sg[4], sb[4], sx[4], gg[4];
+                                                            float* __restrict__ part, int sum_dx) {
+    constexpr int ROWS = LN_BWD_ROWS_PER_WAVE;
+    // one array at a time, so that a workgroup fits beside two of the weight gradients' (72 KB each)
+    __shared__ __attribute__((aligned(16))) float red[4][256 * NV];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t t0 = ((int64_t)blockIdx.x * 4 + wave) * ROWS;
+    const int rows = (int)(T - t0 < ROWS ? T - t0 : ROWS);   // not positive: nothing left for this wave
+    f32x4 xh[ROWS][NV], dh[ROWS][NV], gg[NV];
+    float inv[ROWS], s1[ROWS], s2[ROWS];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        sg[i] = sb[i] = sx[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < NV; ++i) {
         const int c = 4 * (lane + 64 * i);
-        gg[i] = c < D ? *reinterpret_cast<const f32x4*>(g + c) : sg[i];
+        gg[i] = c < D ? *reinterpret_cast<const f32x4*>(g + c) : f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    for (int64_t t = t0; t < t1; ++t) {
-        const float mean = stats[2 * t], inv = stats[2 * t + 1];
-        f32x4 xh[4], dh[4];
-        float s1 = 0.f, s2 = 0.f;
+    float mean[ROWS];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+    for (int q = 0; q < ROWS; ++q) {
+        mean[q] = inv[q] = 0.f;
+        if (q < rows) {
+            mean[q] = stats[2 * (t0 + q)];
+            inv[q] = stats[2 * (t0 + q) + 1];
+        }
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
             const int c = 4 * (lane + 64 * i);
-            xh[i] = dh[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-            if (c < D) {
-                const f32x4 xv = *reinterpret_cast<const f32x4*>(x + t * D + c), dv = *reinterpret_cast<const f32x4*>(dy + t * D + c);
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    xh[i][j] = (xv[j] - mean) * inv;
-                    dh[i][j] = dv[j] * gg[i][j];
-                    s1 += dh[i][j];
-                    s2 += dh[i][j] * xh[i][j];
-                    sg[i][j] += dv[j] * xh[i][j];
-                    sb[i][j] += dv[j];
-                }
+            xh[q][i] = dh[q][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (q < rows && c < D) {
+                xh[q][i] = *reinterpret_cast<const f32x4*>(x + (t0 + q) * D + c);
+                dh[q][i] = *reinterpret_cast<const f32x4*>(dy + (t0 + q) * D + c);
             }
         }
-        const float m1 = wsum(s1) / (float)D, m2 = wsum(s2) / (float)D;
+    }
+    f32x4 sg[NV], sb[NV], sx[NV];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < NV; ++i) sg[i] = sb[i] = sx[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int q = 0; q < ROWS; ++q) {
+        s1[q] = s2[q] = 0.f;
+        if (q >= rows) continue;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            if (4 * (lane + 64 * i) >= D) continue;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float dv = dh[q][i][j];
+                xh[q][i][j] = (xh[q][i][j] - mean[q]) * inv[q];
+                dh[q][i][j] = dv * gg[i][j];
+                s1[q] += dh[q][i][j];
+                s2[q] += dh[q][i][j] * xh[q][i][j];
+                sg[i][j] += dv * xh[q][i][j];
+                sb[i][j] += dv;
+            }
+        }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+        for (int q = 0; q < ROWS; ++q) {
+            s1[q] += __shfl_xor(s1[q], o, 64);
+            s2[q] += __shfl_xor(s2[q], o, 64);
+        }
+#pragma unroll
+    for (int q = 0; q < ROWS; ++q) {
+        if (q >= rows) continue;
+        const float m1 = s1[q] / (float)D, m2 = s2[q] / (float)D;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
             const int c = 4 * (lane + 64 * i);
             if (c < D) {
                 f32x4 o;
 #pragma unroll
-                for (int j = 0; j < 4; ++j) o[j] = inv * (dh[i][j] - m1 - xh[i][j] * m2);
+                for (int j = 0; j < 4; ++j) o[j] = inv[q] * (dh[q][i][j] - m1 - xh[q][i][j] * m2);
                 sx[i] += o;
-                *reinterpret_cast<f32x4*>(dx + t * D + c) = o;
-                if (dx16) store_bf16x4(dx16 + at16(t, c, D, panel), o);
+                *reinterpret_cast<f32x4*>(dx + (t0 + q) * D + c) = o;
+                if (dx16) store_bf16x4(dx16 + at16(t0 + q, c, D, panel), o);
             }
         }
     }
-    const int wave = threadIdx.x >> 6;
+    const int arrays = sum_dx ? 3 : 2;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int c = 4 * (lane + 64 * i);
-        if (c < D)
+    for (int k = 0; k < 3; ++k) {
+        if (k == arrays) break;
+        if (k) __syncthreads();
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                red[wave][c + j] = sg[i][j];
-                red[wave][D + c + j] = sb[i][j];
-                red[wave][2 * D + c + j] = sx[i][j];
-            }
+        for (int i = 0; i < NV; ++i) {
+            const int c = 4 * (lane + 64 * i);
+            if (c < D) *reinterpret_cast<f32x4*>(&red[wave][c]) = k == 0 ? sg[i] : k == 1 ? sb[i] : sx[i];
+        }
+        __syncthreads();
+        float* out = part + ((int64_t)blockIdx.x * arrays + k) * D;
+        for (int c = threadIdx.x; c < D; c += 256) out[c] = (red[0][c] + red[1][c]) + (red[2][c] + red[3][c]);
     }
-    __syncthreads();
-    const int width = (sum_dx ? 3 : 2) * D;
-    for (int c = threadIdx.x; c < width; c += 256) part[(int64_t)blockIdx.x * width + c] = (red[0][c] + red[1][c]) + (red[2][c] + red[3][c]);
 }
 
 // row <- softmax(row), in place when store_f32 is set, and/or as bf16 into p16; one wave per row of length n <= 1024
@@ -570,13 +605,20 @@ void launch_layernorm(hipStream_t s, const float* x, int64_t T, int D, const flo
                       int64_t panel, float* stats) {
     hipLaunchKernelGGL(layernorm_kernel, dim3(nblk(T, 4)), dim3(256), 0, s, x, T, D, g, b, y, y16, panel, stats);
 }
-#define LN_BWD_ROWS_PER_WAVE 4
+static void layernorm_bwd_any(hipStream_t s, unsigned wgs, const float* dy, const float* x, const float* stats, int64_t T, int D, const float* g, float* dx,
+                              uint16_t* dx16, int64_t panel, float* part, int sum_dx) {
+#define LN_BWD(NV) hipLaunchKernelGGL(layernorm_bwd_kernel<NV>, dim3(wgs), dim3(256), 0, s, dy, x, stats, T, D, g, dx, dx16, panel, part, sum_dx)
+    if (D <= 256) LN_BWD(1);
+    else if (D <= 512) LN_BWD(2);
+    else LN_BWD(4);   // D <= 1024
+#undef LN_BWD
+}
 size_t layernorm_bwd_partial_floats(int64_t T, int D) { return (size_t)nblk(T, 4 * LN_BWD_ROWS_PER_WAVE) * 3 * D; }
 // dgb[0 .. D) = gradient of the scale, dgb[D .. 2D) = gradient of the shift; part holds layernorm_bwd_partial_floats(T, D)
 void launch_layernorm_bwd(hipStream_t s, const float* dy, const float* x, const float* stats, int64_t T, int D, const float* g, float* dx,
                           uint16_t* dx16, float* part, float* dgb) {
     const unsigned wgs = nblk(T, 4 * LN_BWD_ROWS_PER_WAVE);
-    hipLaunchKernelGGL(layernorm_bwd_kernel, dim3(wgs), dim3(256), 0, s, dy, x, stats, T, D, g, dx, dx16, (int64_t)0, part, LN_BWD_ROWS_PER_WAVE, 0);
+    layernorm_bwd_any(s, wgs, dy, x, stats, T, D, g, dx, dx16, 0, part, 0);
     hipLaunchKernelGGL(colsum_rows_kernel, dim3(nblk(2 * D, 64)), dim3(256), 0, s, part, (int)wgs, 2 * D, dgb);
 }
 // Without the final sum: part takes one row of (scale, shift, column sum of dx) partials, 3 D floats, per workgroup;
@@ -584,7 +626,7 @@ void launch_layernorm_bwd(hipStream_t s, const float* dy, const float* x, const 
 int launch_layernorm_bwd_partial(hipStream_t s, const float* dy, const float* x, const float* stats, int64_t T, int D, const float* g, float* dx,
                                  uint16_t* dx16, int64_t panel, float* part) {
     const unsigned wgs = nblk(T, 4 * LN_BWD_ROWS_PER_WAVE);
-    hipLaunchKernelGGL(layernorm_bwd_kernel, dim3(wgs), dim3(256), 0, s, dy, x, stats, T, D, g, dx, dx16, panel, part, LN_BWD_ROWS_PER_WAVE, 1);
+    layernorm_bwd_any(s, wgs, dy, x, stats, T, D, g, dx, dx16, panel, part, 1);
     return (int)wgs;
 }
 void launch_softmax_rows(hipStream_t s, float* sc, uint16_t* p16, bool store_f32, int64_t rows, int n) {
