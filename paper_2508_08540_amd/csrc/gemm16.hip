@@ -495,7 +495,10 @@ __device__ __forceinline__ void gd16_store_edge(const Gemm16Desc& d, float alpha
 
 // Softmax statistics of a wave's 64 columns for each of its rows, as g16_ce_block: (max, sum of exp(v - max)) and the value in
 // the target's column.  The rows' targets are requested together and the reductions of all block rows run side by side;
-// the column of the target is only looked for in the rare wave that holds one.
+// the column of the target is only looked for in the rare wave that holds one.  Overwrites the block: the exponentials take the
+// place of the values, so that those of all rows are independent instructions (one temporary at a time, each waited for, and a mask
+// per value were a third of the 7 us that the statistics of a tile take beside another's K loop; 65 536 x 32 000 x 512
+// 2144 -> 1974 us, 8192 tokens 306 -> 273).
 template <int WMB>
 __device__ __forceinline__ void gd16_ce(const Gemm16Desc& d, f32x4 (&acc)[WMB][4], int m_base, int n_base, int part_idx, int r, int g) {
     int tgt[WMB];
@@ -504,13 +507,15 @@ __device__ __forceinline__ void gd16_ce(const Gemm16Desc& d, f32x4 (&acc)[WMB][4
         const int m = m_base + 16 * mt + r;
         tgt[mt] = m < d.M ? d.ce_targets[m] : -1;
     }
-    if (d.alpha != 1.f)
+    if (n_base + 64 > d.N) {   // uniform: columns that do not exist count as -inf
 #pragma unroll
-        for (int mt = 0; mt < WMB; ++mt)
+        for (int nt = 0; nt < 4; ++nt)
 #pragma unroll
-            for (int nt = 0; nt < 4; ++nt) acc[mt][nt] *= d.alpha;
-    const bool full = n_base + 64 <= d.N;   // uniform: every column of the block exists
-    auto column = [&](int nt, int i) { return n_base + 32 * (nt >> 1) + 8 * g + 4 * (nt & 1) + i; };
+            for (int i = 0; i < 4; ++i)
+                if (n_base + 32 * (nt >> 1) + 8 * g + 4 * (nt & 1) + i >= d.N)
+#pragma unroll
+                    for (int mt = 0; mt < WMB; ++mt) acc[mt][nt][i] = -INFINITY;
+    }
     float mx[WMB], sum[WMB];
 #pragma unroll
     for (int mt = 0; mt < WMB; ++mt) {
@@ -518,38 +523,15 @@ __device__ __forceinline__ void gd16_ce(const Gemm16Desc& d, f32x4 (&acc)[WMB][4
 #pragma unroll
         for (int nt = 0; nt < 4; ++nt)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) mx[mt] = fmaxf(mx[mt], full || column(nt, i) < d.N ? acc[mt][nt][i] : -INFINITY);
+            for (int i = 0; i < 4; ++i) mx[mt] = fmaxf(mx[mt], acc[mt][nt][i]);
     }
 #pragma unroll
     for (int mt = 0; mt < WMB; ++mt) mx[mt] = fmaxf(mx[mt], __shfl_xor(mx[mt], 16, 64));
 #pragma unroll
     for (int mt = 0; mt < WMB; ++mt) mx[mt] = fmaxf(mx[mt], __shfl_xor(mx[mt], 32, 64));
-    constexpr float LOG2E = 1.4426950408889634f;
-#pragma unroll
-    for (int mt = 0; mt < WMB; ++mt) {
-        // Hardware exponential; a row whose columns are all -inf or absent keeps a sum of 0 (its maximum says so).  The maximum is
-        // taken off first: scaled and taken off in one step, its rounding would be a common factor of all terms (rms error of the
-        // logarithm of the sum at maxima around 7 / 30: 7e-8 / 7e-8, in one step 2e-7 / 8e-7).
-        const float ref = mx[mt] > -INFINITY ? mx[mt] : 0.f;
-        float s = 0.f;
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float e = __builtin_amdgcn_exp2f((acc[mt][nt][i] - ref) * LOG2E);
-                s += full || column(nt, i) < d.N ? e : 0.f;
-            }
-        sum[mt] = s;
-        __builtin_amdgcn_sched_barrier(0);
-    }
-#pragma unroll
-    for (int mt = 0; mt < WMB; ++mt) sum[mt] += __shfl_xor(sum[mt], 16, 64);
-#pragma unroll
-    for (int mt = 0; mt < WMB; ++mt) sum[mt] += __shfl_xor(sum[mt], 32, 64);
 #pragma unroll
     for (int mt = 0; mt < WMB; ++mt) {
         const int m = m_base + 16 * mt + r;
-        if (g == 0 && m < d.M) *reinterpret_cast<f32x2_v*>(d.ce_part + 2 * ((int64_t)part_idx * d.M + m)) = f32x2_v{mx[mt], sum[mt]};
         const int t = tgt[mt] - n_base;
         if (t >= 0 && t < 64 && ((t >> 3) & 3) == g) {   // this lane holds the target's column
             float at = 0.f;
@@ -559,6 +541,34 @@ __device__ __forceinline__ void gd16_ce(const Gemm16Desc& d, f32x4 (&acc)[WMB][4
                 for (int i = 0; i < 4; ++i) at = (t >> 5) == (nt >> 1) && (t & 7) == 4 * (nt & 1) + i ? acc[mt][nt][i] : at;
             d.ce_tlogit[m] = at;
         }
+    }
+    constexpr float LOG2E = 1.4426950408889634f;
+    // Hardware exponential; a row whose columns are all -inf or absent keeps a sum of 0 (its maximum says so).  The maximum is
+    // taken off first: scaled and taken off in one step, its rounding would be a common factor of all terms (rms error of the
+    // logarithm of the sum at maxima around 7 / 30: 7e-8 / 7e-8, in one step 2e-7 / 8e-7).
+#pragma unroll
+    for (int mt = 0; mt < WMB; ++mt) {
+        const float ref = mx[mt] > -INFINITY ? mx[mt] : 0.f;
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[mt][nt][i] = __builtin_amdgcn_exp2f((acc[mt][nt][i] - ref) * LOG2E);
+        sum[mt] = 0.f;
+    }
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int mt = 0; mt < WMB; ++mt) sum[mt] += acc[mt][nt][i];
+#pragma unroll
+    for (int mt = 0; mt < WMB; ++mt) sum[mt] += __shfl_xor(sum[mt], 16, 64);
+#pragma unroll
+    for (int mt = 0; mt < WMB; ++mt) sum[mt] += __shfl_xor(sum[mt], 32, 64);
+#pragma unroll
+    for (int mt = 0; mt < WMB; ++mt) {
+        const int m = m_base + 16 * mt + r;
+        if (g == 0 && m < d.M) *reinterpret_cast<f32x2_v*>(d.ce_part + 2 * ((int64_t)part_idx * d.M + m)) = f32x2_v{mx[mt], sum[mt]};
     }
 }
 
@@ -927,17 +937,25 @@ __global__ __launch_bounds__(256, gd16_waves(gd16_runs(AK, WMB), WMB * WNB)) voi
     const float* bias = (plain || !d.bias) ? nullptr : d.bias + z1 * d.sbias1;
     const int ldc = plain ? d.N : d.ldc;
     const int m_base = m0 + wm * 16 * WMB, n_base = n0 + wn * 16 * WNB;
-    if constexpr (EPI == 2) gd16_ce<WMB>(d, acc, m_base, n_base, 2 * tile_x + wn, r, g);
-    if (EPI == 2 && !C && !C16) return;
+    if constexpr (EPI == 2) {
+        if (d.alpha != 1.f)
+#pragma unroll
+            for (int mt = 0; mt < WMB; ++mt)
+#pragma unroll
+                for (int nt = 0; nt < WNB; ++nt) acc[mt][nt] *= d.alpha;
+    }
     if constexpr (EPI == 3) {
         gd16_ce_grad<WMB, WNB>(d, acc, m_base, n_base, C16, r, g);
         return;
     }
     if constexpr (EPI == 4) gd16_gelu_bwd<WMB, WNB>(d, acc, m_base, n_base, 2 * tile_y + wm, r, g);
-    const float alpha = EPI == 4 ? 1.f : d.alpha;   // the factor above includes it
+    const float alpha = EPI == 2 || EPI == 4 ? 1.f : d.alpha;   // above
     const bool vec = (plain ? (d.N & 3) == 0 : d.c_vec8 != 0) && m_base + 16 * WMB <= d.M && n_base + 16 * WNB <= d.N;
-    if (vec) gd16_store<!BK, WMB, WNB, EPI == 1>(d, alpha, acc, m_base, n_base, C, C16, G16, R, bias, ldc, plain, r, g);
-    else gd16_store_edge<!BK, WMB, WNB, EPI == 1>(d, alpha, acc, m_base, n_base, C, C16, G16, R, bias, ldc, plain, r, g);
+    if (EPI != 2 || C || C16) {
+        if (vec) gd16_store<!BK, WMB, WNB, EPI == 1>(d, alpha, acc, m_base, n_base, C, C16, G16, R, bias, ldc, plain, r, g);
+        else gd16_store_edge<!BK, WMB, WNB, EPI == 1>(d, alpha, acc, m_base, n_base, C, C16, G16, R, bias, ldc, plain, r, g);
+    }
+    if constexpr (EPI == 2) gd16_ce<WMB>(d, acc, m_base, n_base, 2 * tile_x + wn, r, g);   // leaves nothing of the block
 }
 
 // Rows of partial column sums that a product with gelu_part leaves: two per tile row
