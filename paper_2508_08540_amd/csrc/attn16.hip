@@ -169,7 +169,8 @@ __global__ __launch_bounds__(256) void attention16_kernel(const bf16_t* __restri
 // ---- backward -----------------------------------------------------------------------------------------------------------
 // Gradients of one (sample, head) from dctx (bf16) and the probabilities the forward pass kept (fp32):
 //   dv = bf16(P)^T dctx,   dP = dctx v^T,   dS = alpha * P * (dP - rowsum(dP * P)),   dq = bf16(dS) k,   dk = bf16(dS)^T q,
-// each product with bf16 factors and fp32 sums; dq, dk, dv go out as fp32 and as bf16 ([tokens][ld] slices like q, k, v).
+// each product with bf16 factors and fp32 sums; dq, dk, dv go out as fp32 and as bf16 ([tokens][ld] slices like q, k, v,
+// the bf16 ones in panels of 32 columns where the products that read them want those).
 // Same wave and lane layout as the forward kernel.  dP and dS live in registers; bf16(P) and bf16(dS) pass through
 // LDS once row-major or transposed, as the product that reads them needs, in the space the dctx and v tiles occupied;
 // the [L][dh] factor of each product is transposed on its way into a second LDS region (its global loads are issued

@@ -1,6 +1,6 @@
 // GEMM on the bf16 matrix cores with both operands stored in bf16:
 //   C[m][n] = alpha * sum_k A(m,k) B(n,k) [+ bias[n]] [+ R[m][n]],  fp32 sums.
-// A(m,k) is A[m*lda + k] or, with a_kmajor, A[k*lda + m]; likewise B(n,k); batch index z = z1 * inner + z2 as in the
+// A(m,k) is A[m*lda + k] or, with a_kmajor, A[k*lda + m]; likewise B(n,k); or either in panels of 32 columns (Gemm16Desc); batch index z = z1 * inner + z2 as in the
 // fp32 products.  The result goes out as fp32 (C), as bf16 rounded to nearest even (C16), as bf16 gelu(C) (G16), or any
 // combination; bias and R are fp32.  With splits > 1 the K range is cut into fp32 partials that launch_split_reduce adds in
 // split order.  The B tile is the first operand of v_mfma_f32_16x16x32_bf16, so that lane (r, g) holds C[m = r][n = 4g .. 4g+3] of

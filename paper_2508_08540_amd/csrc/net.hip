@@ -45,7 +45,10 @@ typedef uint8_t act_t;  // activations are addressed as bytes; the model's stora
 // Batches up to this size leave the next step's first layer to the update, which has one workgroup per 16 x 256 weights; a launch of its
 // own spreads the samples over more of them (pass of 8 steps of 128 with 256 hidden units 260 -> 224 us; of 4 steps of 256 with 256 / 128
 // hidden units 202 -> 185 / 155 -> 161).
-constexpr int MLP_NEXT_MAX_B = 128;
+// Every 256 inputs leave a partial sum per hidden unit and sample that the head adds up (12 for 3072 inputs, 8 by the launch of its
+// own whatever their number): not for much larger inputs.
+constexpr int MLP_NEXT_MAX_B = 128, MLP_NEXT_MAX_SPLITS = 16;
+bool mlp_next_rides(const bls_model* m, int B) { return B <= MLP_NEXT_MAX_B && mlp_next_splits(m->d_in) <= MLP_NEXT_MAX_SPLITS; }
 
 struct MlpScratch {
     float *part, *h, *loss, *dlogits, *dpre;
@@ -54,7 +57,7 @@ struct MlpScratch {
 MlpScratch carve_mlp(Carver& c, const bls_model* m, int B, bool train) {
     MlpScratch s{};
     const int hid = m->desc.hidden;
-    const int next = train && B <= MLP_NEXT_MAX_B ? mlp_next_splits(m->d_in) : 0;
+    const int next = train && mlp_next_rides(m, B) ? mlp_next_splits(m->d_in) : 0;
     s.part = c.take<float>((size_t)B * (next > MLP_SPLITS ? next : MLP_SPLITS) * hid);
     s.loss = c.take<float>(B);
     if (train) {
@@ -536,7 +539,7 @@ int net_local_step(bls_ctx* ctx, const bls_model* m, float* params, float* buffe
             float* loss = step_losses_out ? step_losses_out + j * B : s.loss;
             const BatchRows rows{sel, k, j * B};
             const BatchRows after{sel, k, (j + 1) * B};
-            const bool ahead = B <= MLP_NEXT_MAX_B;
+            const bool ahead = mlp_next_rides(m, B);
             const bool there = ahead && j > 0;   // the step before left this one's partial sums
             if (!there) PROF(ctx, PROF_GEMM, launch_mlp_fc1(st, x_pool, rows, params + m->fc1_w, B, hid, m->d_in, s.part));
             PROF(ctx, PROF_HEAD, launch_head_mlp(st, s.part, B, there ? mlp_next_splits(m->d_in) : MLP_SPLITS, hid, params + m->fc1_b, params + m->fc2_w, params + m->fc2_b, C, y_pool,

@@ -8,6 +8,8 @@
 // residual sums, layer norm, softmax, GELU derivative, bias and layer-norm gradients, the loss, the parameters and
 // their update - reads and writes fp32.  Tensors that are only ever factors (q, k, v, the attention output, GELU
 // output, the gradients of the attention output, of the scores and of the logits) exist in bf16 alone.
+#include <algorithm>
+
 #include "kernels.h"
 #include "net.h"
 
@@ -126,7 +128,9 @@ SeqScratch carve(Carver& c, const bls_model* m, int B, bool train) {
     SeqScratch s{};
     const bool bf = s.bf = m->desc.act_dtype == BLS_ACT_BF16;
     const bool lean = s.lean = bf && D % 8 == 0 && F % 8 == 0;
-    const bool panels = s.panels = lean && D % 32 == 0 && F % 32 == 0 && (D / H) % 32 == 0;
+    // offsets inside a k-major tile reach over eight panels and are 32-bit
+    const int64_t longest = std::max({T, (int64_t)V + 31, (int64_t)F, (int64_t)D});
+    const bool panels = s.panels = lean && D % 32 == 0 && F % 32 == 0 && (D / H) % 32 == 0 && longest * 32 * 8 < (int64_t(1) << 29);
     s.ldv = panels ? (V + 31) & ~31 : lean ? (V + 7) & ~7 : V;
     auto take_factor = [&](Kind kind, int64_t width) {   // a [T][width] factor of products
         Mat t = take(c, bf, kind, T * width);

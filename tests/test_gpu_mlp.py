@@ -131,6 +131,8 @@ def test_gradients_and_update_at_the_edges_of_the_kernels(hw, channels, hidden, 
     (18, 1, 48, 17, 65),     # 324 inputs: a second block, nearly empty; a second round of samples per wave; more classes than are preloaded
     (8, 2, 16, 7, 128),      # the largest batch whose next first layer rides in the update
     (8, 2, 16, 7, 129),      # the smallest whose does not
+    (64, 1, 16, 3, 4),       # 4096 inputs, the most whose partial sums the head still adds up
+    (37, 3, 16, 3, 4),       # 4107 inputs
 ])
 def test_steps_whose_first_layer_rides_in_the_update(hw, channels, hidden, classes, batch):
     """Three steps: the partial sums of the second and third come from the update before them.  Criteria as for one step, three times
