@@ -290,8 +290,12 @@ int resnet_backward(bls_ctx* ctx, hipStream_t st, const bls_model* m, const floa
     }
     // Profiling puts events of its own on these launches; a stream that is being captured takes only events that are recorded.
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    BLS_HIP(ctx, hipStreamIsCapturing(st, &capture));
-    const bool may_stamp = !ctx->profiling && capture == hipStreamCaptureStatusNone;
+    bool may_stamp = !ctx->profiling;
+    if (hipStreamIsCapturing(st, &capture) != hipSuccess) {   // the legacy stream while another one is being captured
+        (void)hipGetLastError();
+        may_stamp = false;
+    }
+    may_stamp = may_stamp && capture == hipStreamCaptureStatusNone;
     // dy of layer l is there: its weight gradient goes to the side stream.  `stamped`: the launch that stores dy carries the event as
     // its own completion signal; an event recorded behind it is a packet of its own on the critical path (bf16 step 549 -> 520 us).
     auto weight_gradient = [&](int l, bool stamped) -> int {
