@@ -41,9 +41,6 @@ __device__ __forceinline__ void agg_element(const AggArgs& a, int P, int64_t j, 
         for (int i = 0; i < P; ++i) const_cast<float*>(a.src[i])[j] = acc;
 }
 
-// TAIL: the up to three elements behind the last whole column ride along (an instantiation of its own: the code behind the loop costs it
-// 1 %, 81.5 -> 82.4 us on ten replicas of 11 M).
-template <bool TAIL>
 __global__ __launch_bounds__(256) void agg_vec4_kernel(AggArgs a, int P, int64_t n_vec, int64_t d, float* out, int broadcast) {
     int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n_vec; v += stride) {
@@ -52,7 +49,8 @@ __global__ __launch_bounds__(256) void agg_vec4_kernel(AggArgs a, int P, int64_t
         if (broadcast)
             for (int i = 0; i < P; ++i) reinterpret_cast<f32x4*>(const_cast<float*>(a.src[i]))[v] = acc;
     }
-    if (TAIL && blockIdx.x == 0 && threadIdx.x < d - 4 * n_vec) agg_element(a, P, 4 * n_vec + threadIdx.x, out, broadcast);
+    // the up to three elements behind the last whole column ride along
+    if (blockIdx.x == 0 && threadIdx.x < d - 4 * n_vec) agg_element(a, P, 4 * n_vec + threadIdx.x, out, broadcast);
 }
 
 // Everything, when a pointer is not 16-byte aligned or there is no whole column.
@@ -75,8 +73,7 @@ int launch_weighted_aggregate(bls_ctx* ctx, const float* const* replicas, const 
         int64_t blocks = ceil_div(n_vec, 256);
         int64_t cap = (int64_t)ctx->num_cus * 8;
         if (blocks > cap) blocks = cap;
-        auto kern = d % 4 ? agg_vec4_kernel<true> : agg_vec4_kernel<false>;
-        hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), 0, ctx->stream, a, P, n_vec, d, out, broadcast ? 1 : 0);
+        hipLaunchKernelGGL(agg_vec4_kernel, dim3((unsigned)blocks), dim3(256), 0, ctx->stream, a, P, n_vec, d, out, broadcast ? 1 : 0);
     } else if (d > 0) {
         int64_t blocks = ceil_div(d, 256);
         int64_t cap = (int64_t)ctx->num_cus * 8;
