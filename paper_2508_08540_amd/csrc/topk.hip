@@ -803,12 +803,14 @@ int launch_topk(bls_ctx* ctx, const float* losses, int64_t N, int64_t k, int32_t
     return launch_topk_at(ctx, ctx->arena, losses, N, k, idx_out, val_out);
 }
 
-// Several selections fill the chip by counting where one does not yet, and are sorted from smaller pools on: an epoch's three draws take
-// 14 us from 3000 samples and 33 from 8192 by counting, 30 to 32 from 8193 to 16384 by sorting.
-#define TOPK_JOBS_RANK_MAX 7168
+// Counting beats sorting as long as its workgroups (64 samples of a selection each) run side by side; further selections share
+// the chip, while those that are sorted hardly notice each other.  An epoch's draws, by counting / by sorting: one draw of 15 000
+// samples 24.2 / 25.0 us, of 15 500 25.3 / 25.0; two of 8192 (a workgroup for each of 256 compute units) 15.9 / 24.3, of 9500
+// 30.3 / 26.7; three of 7000 29.7 / 30.4, of 8192 33 / 30.5.
+static int64_t jobs_rank_max(int n_jobs) { return n_jobs == 1 ? 15360 : n_jobs == 2 ? 8192 : 7168; }
 
 size_t topk_jobs_scratch_bytes(int n_jobs, int64_t N) {
-    if (N <= TOPK_JOBS_RANK_MAX) return 0;
+    if (N <= jobs_rank_max(n_jobs)) return 0;
     Carver c(nullptr);
     SelJob job;
     for (int i = 0; i < n_jobs; ++i) carve_sort(c, N, job);
@@ -816,7 +818,7 @@ size_t topk_jobs_scratch_bytes(int n_jobs, int64_t N) {
 }
 
 int launch_topk_jobs(bls_ctx* ctx, char* scratch_base, SelJobs jobs, int n_jobs, int64_t N) {
-    return N <= TOPK_JOBS_RANK_MAX ? launch_topk_small(ctx, jobs, n_jobs, N) : launch_topk_medium(ctx, scratch_base, jobs, n_jobs, N);
+    return N <= jobs_rank_max(n_jobs) ? launch_topk_small(ctx, jobs, n_jobs, N) : launch_topk_medium(ctx, scratch_base, jobs, n_jobs, N);
 }
 
 // ---- selection without any allocation -----------------------------------------------------------------

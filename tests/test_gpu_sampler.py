@@ -96,7 +96,7 @@ def test_errors(env):
 
 # ---- the appendix's sampling variants ---------------------------------------------------------------------------------
 
-def _check_variant(env, losses, uf, us, tf, pf, ts, ps, lam, scheme, to):
+def _check_variant(env, losses, uf, us, tf, pf, ts, ps, lam, scheme, to, oracle_uf=None, oracle_us=None):
     torch, bls, ctx = env
     N = losses.shape[0]
     nf, _, ns = bls.epoch_allocation(N, tf, pf, ts, ps, lam)
@@ -105,7 +105,8 @@ def _check_variant(env, losses, uf, us, tf, pf, ts, ps, lam, scheme, to):
     slow = torch.full((max(ns, 1),), -7, dtype=torch.int32, device="cuda")
     bls.sample_epoch(ctx, dev(losses), dev(uf), dev(us), tf, pf, ts, ps, lam, fast, slow, scheme=scheme, high_loss_to=to)
     ctx.synchronize()
-    ref = oracle.sample_epoch(losses, uf, us, tf, pf, ts, ps, lam, scheme=scheme, high_loss_to=to)
+    ref = oracle.sample_epoch(losses, uf if oracle_uf is None else oracle_uf, us if oracle_us is None else oracle_us, tf, pf, ts, ps, lam,
+                              scheme=scheme, high_loss_to=to)
     assert (nf, ns) == (ref["n_fast"], ref["n_slow"])
     for got, group, n, P in ((fast.cpu().numpy()[:nf], ref["fast"], nf, pf), (slow.cpu().numpy()[:ns], ref["slow"], ns, ps)):
         for p in range(P if n else 0):
@@ -155,26 +156,28 @@ def test_variants_with_special_losses_tied_keys_and_bad_arguments(env):
 
 
 @pytest.mark.parametrize("scheme", ["separated", "unified"])
-@pytest.mark.parametrize("N,lam", [(1023, 0.5), (1025, 1.0), (7168, 0.5), (7169, 0.3), (16384, 0.5), (65537, 0.5), (1 << 19, 0.4), ((1 << 19) + 1, 0.4)])
-def test_draws_around_the_sizes_where_the_path_changes(env, scheme, N, lam):
-    """One tile of the order more and less, ranking by counting and by sorting, pools ranked together and one after the other; keys of
-    minus infinity rank with the lowest float when others are left out."""
+@pytest.mark.parametrize("to", ["fast", "slow", "none"])
+@pytest.mark.parametrize("N,lam,ts", [
+    (1023, 0.5, 4), (1025, 1.0, 4),                       # one tile of the order more and less
+    (7168, 0.5, 4), (7169, 0.3, 4),                       # three draws ranked by counting; by sorting
+    (8192, 1.0, 4), (8193, 1.0, 4),                       # two draws
+    (15360, 1.0, 0), (15361, 1.0, 0), (16384, 0.5, 0),    # one draw, or two; no slow samples
+    (65537, 0.5, 4),
+    (1 << 19, 0.4, 4), ((1 << 19) + 1, 0.4, 4),           # ranked together; one selection after the other
+])
+def test_draws_around_the_sizes_where_the_path_changes(env, scheme, to, N, lam, ts):
+    """Against the oracle, with finite keys and with some of minus infinity: those rank with the lowest float in a draw that leaves out
+    samples that are taken already, and below it in a draw from all."""
     seed = synth.inputs.BASE_SEED + 5 * N
     uf, us = _keys(seed, 31, N), _keys(seed, 32, N)
-    _check_variant(env, synth.loss_array("ties16", N, seed=seed), uf, us, 8, 3, 4, 2, lam, scheme, "fast")
-    uf[::7] = -np.inf
-    uf[3::11] = np.finfo(np.float32).min
-    lowest = np.where(np.isinf(uf), np.finfo(np.float32).min, uf)
-    torch, bls, ctx = env
-    nf, k, ns = bls.epoch_allocation(N, 8, 3, 4, 2, lam)
-    if k > 0:
-        losses = torch.from_numpy(synth.loss_array("halfnormal", N, seed=seed)).cuda()
-        got = []
-        for keys in (uf, lowest):
-            fast, slow = torch.full((nf,), -7, dtype=torch.int32, device="cuda"), torch.full((max(ns, 1),), -7, dtype=torch.int32, device="cuda")
-            bls.sample_epoch(ctx, losses, torch.from_numpy(keys).cuda(), torch.from_numpy(us).cuda(), 8, 3, 4, 2, lam, fast, slow, scheme=scheme,
-                             high_loss_to="fast")
-            ctx.synchronize()
-            got.append((fast.cpu().numpy(), slow.cpu().numpy()))
-        np.testing.assert_array_equal(got[0][0], got[1][0])
-        np.testing.assert_array_equal(got[0][1], got[1][1])
+    _check_variant(env, synth.loss_array("ties16", N, seed=seed), uf, us, 8, 3, ts, 2, lam, scheme, to)
+    for u in (uf, us):
+        u[::7] = -np.inf
+        u[3::11] = np.finfo(np.float32).min
+    lifted = lambda u: np.where(np.isinf(u), np.finfo(np.float32).min, u)
+    nf, k, ns = oracle.sampling.allocation(N, 8, 3, ts, 2, lam)
+    first = "slow" if to == "slow" else "fast"
+    k = {"fast": k, "slow": int(lam * ns), "none": 0}[to]
+    leaves_out = {first: k > 0, "slow" if first == "fast" else "fast": scheme == "unified" and (ns if first == "slow" else nf) > 0}
+    _check_variant(env, synth.loss_array("halfnormal", N, seed=seed), uf, us, 8, 3, ts, 2, lam, scheme, to,
+                   lifted(uf) if leaves_out["fast"] else uf, lifted(us) if leaves_out["slow"] else us)
