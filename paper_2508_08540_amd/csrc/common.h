@@ -120,7 +120,7 @@ struct SelJob {
     int32_t* idx_out;    // the k first in rank order
     float* val_out;      // their values, or NULL
     uint8_t* chosen;     // N flags, 1 for the k first and 0 for the others, or NULL
-    int lift;            // a loss of -inf counts as the lowest finite float
+    float floor;         // losses below it count as it: -inf (none do), or the lowest finite float
     // filled by the launcher, whole-pool sort only
     uint32_t* tables;
     uint2 *a, *b;

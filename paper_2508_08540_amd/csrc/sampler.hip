@@ -157,12 +157,14 @@ static int sample_epoch_together(bls_ctx* ctx, const float* losses, const float*
     int32_t *ranked = reinterpret_cast<int32_t*>(part[1]), *order = reinterpret_cast<int32_t*>(part[2]), *ranked_other = reinterpret_cast<int32_t*>(part[3]);
     uint8_t* chosen = reinterpret_cast<uint8_t*>(part[4]);
     uint32_t* counts = reinterpret_cast<uint32_t*>(part[5]);
+    // keys are finite by contract; where others are left out, one of -inf ranks with the lowest float
+    constexpr float NONE = -INFINITY, LOWEST = -3.402823466e38f;
     SelJobs jobs{};
     int n = 0;
-    if (k > 0) jobs.j[n++] = SelJob{losses, (int)k, ranked, nullptr, after_loss || other_after ? chosen : nullptr, 0};
-    if (after_loss) jobs.j[n++] = SelJob{u_biased, (int)N, order, nullptr, nullptr, 1};
-    else if (rest) jobs.j[n++] = SelJob{u_biased, (int)n_biased, ranked, nullptr, other_after ? chosen : nullptr, 0};
-    if (n_other > 0) jobs.j[n++] = other_after ? SelJob{u_other, (int)N, ranked_other, nullptr, nullptr, 1} : SelJob{u_other, (int)n_other, ranked_other, nullptr, nullptr, 0};
+    if (k > 0) jobs.j[n++] = SelJob{losses, (int)k, ranked, nullptr, after_loss || other_after ? chosen : nullptr, NONE};
+    if (after_loss) jobs.j[n++] = SelJob{u_biased, (int)N, order, nullptr, nullptr, LOWEST};
+    else if (rest) jobs.j[n++] = SelJob{u_biased, (int)n_biased, ranked, nullptr, other_after ? chosen : nullptr, NONE};
+    if (n_other > 0) jobs.j[n++] = other_after ? SelJob{u_other, (int)N, ranked_other, nullptr, nullptr, LOWEST} : SelJob{u_other, (int)n_other, ranked_other, nullptr, nullptr, NONE};
     if (n == 0) return BLS_OK;
     rc = launch_topk_jobs(ctx, part[0], jobs, n, N);
     if (rc != BLS_OK) return rc;

@@ -26,7 +26,7 @@ __device__ __forceinline__ uint32_t loss_key(float v) {
 
 __device__ __forceinline__ uint32_t job_key(const SelJob& job, int i) {
     const float v = job.losses[i];
-    return loss_key(job.lift && v == -INFINITY ? -3.402823466e38f : v);
+    return loss_key(v < job.floor ? job.floor : v);   // a NaN stays one
 }
 
 // Rank by counting: the rank of a sample is the number of samples that precede it, so each workgroup ranks 64 samples (one per
@@ -119,15 +119,17 @@ __global__ __launch_bounds__(1024) void sort_count_kernel(SelJobs jobs, int N) {
     uint32_t* __restrict__ tables = job.tables;
     __shared__ uint32_t cnt[256];
     const int tid = threadIdx.x, tile = sort_tile();
+    const int base = tile * (RITER * 1024);
+    // requested before anything else, past the end the last one again: no branch that would wait for its load
+    uint32_t key[RITER];
+#pragma unroll
+    for (int it = 0; it < RITER; ++it) key[it] = ~job_key(job, min(base + it * 1024 + tid, N - 1));
     if (tid < 256) cnt[tid] = 0u;
     else tables[(size_t)(tid >> 8) * SORT_TABLE + tile * 256 + (tid & 255)] = 0u;
     __syncthreads();
-    const int base = tile * (RITER * 1024);
 #pragma unroll
-    for (int it = 0; it < RITER; ++it) {
-        const int i = base + it * 1024 + tid;
-        if (i < N) atomicAdd(&cnt[~job_key(job, i) & 255u], 1u);
-    }
+    for (int it = 0; it < RITER; ++it)
+        if (base + it * 1024 + tid < N) atomicAdd(&cnt[key[it] & 255u], 1u);
     __syncthreads();
     if (tid < 256) tables[tile * 256 + tid] = cnt[tid];
 }
@@ -152,16 +154,15 @@ __global__ __launch_bounds__(1024) void sort_pass_kernel(SelJobs jobs, int N) {
     uint32_t key[RITER], id[RITER];
 #pragma unroll
     for (int it = 0; it < RITER; ++it) {
-        const int i = wbase + it * 64 + lane;
-        key[it] = 0u;
-        id[it] = (uint32_t)i;
-        if (i < N) {
-            if (PASS == 0) key[it] = ~job_key(job, i);
-            else {
-                const uint2 v = in[i];
-                key[it] = v.x;
-                id[it] = v.y;
-            }
+        // past the end the last one again, which is not ranked: no branch that would wait for its load before the table's
+        const int i = wbase + it * 64 + lane, at = min(i, N - 1);
+        if (PASS == 0) {
+            key[it] = ~job_key(job, at);
+            id[it] = (uint32_t)i;
+        } else {
+            const uint2 v = in[at];
+            key[it] = v.x;
+            id[it] = v.y;
         }
     }
     {
@@ -792,7 +793,7 @@ static int launch_topk_small(bls_ctx* ctx, const SelJobs& jobs, int n_jobs, int6
 static int launch_topk_at(bls_ctx* ctx, char* scratch_base, const float* losses, int64_t N, int64_t k, int32_t* idx_out, float* val_out) {
     if (N > TOPK_SORT_MAX) return launch_topk_large(ctx, scratch_base, losses, N, k, idx_out, val_out);
     SelJobs jobs{};
-    jobs.j[0] = {losses, (int)k, idx_out, val_out};
+    jobs.j[0] = SelJob{losses, (int)k, idx_out, val_out, nullptr, -INFINITY};
     if (N <= TOPK_RANK_MAX) return launch_topk_small(ctx, jobs, 1, N);
     return launch_topk_medium(ctx, scratch_base, jobs, 1, N);
 }
