@@ -52,7 +52,14 @@ __global__ __launch_bounds__(256) void head_forward_kernel(const T* __restrict__
     for (int i = 0; i < PQ; ++i) {
         const int c = 4 * (lane + 64 * i);
         f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;
-        if (c < F) {
+        if (MLP) {   // at most 16 rows: the four of a wave in flight together
+            f32x4 q[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                q[t] = c < F && wave + 4 * t < positions ? Act<T>::load4(a + (int64_t)(wave + 4 * t) * F + c) : s0;
+            s0 = q[0] + q[2];
+            s1 = q[1] + q[3];
+        } else if (c < F) {
             int p = wave;
             for (; p + 4 < positions; p += 8) {
                 s0 += Act<T>::load4(a + (int64_t)p * F + c);

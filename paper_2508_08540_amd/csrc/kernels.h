@@ -129,14 +129,18 @@ struct MlpOffsets {
     int64_t fc1_w, fc1_b, fc2_w, fc2_b;
 };
 #define MLP_SPLITS 8
-// part[b][z][h], z < MLP_SPLITS: partial sums of x W^T; hid is a multiple of 16
-void launch_mlp_fc1(hipStream_t s, const float* x, const BatchRows& rows, const float* W, int B, int hid, int K, float* part);
+// A step whose first layer rides in the update before it sums MLP_PART inputs at a time (an update's workgroup has that many columns of the
+// new weights); so does the launch for the first step of such a call, with the same products in the same order: a call of
+// several steps gives the bits of as many calls of one step.
+#define MLP_PART 256
+inline int mlp_splits(int K, bool rides) { return rides ? (K + MLP_PART - 1) / MLP_PART : MLP_SPLITS; }
+// part[b][z][h], z < mlp_splits(K, rides): partial sums of x W^T; hid is a multiple of 16
+void launch_mlp_fc1(hipStream_t s, const float* x, const BatchRows& rows, const float* W, int B, int hid, int K, float* part, bool rides);
 // Gradients from h [B][hid], dlogits [B][C], dpre [B][hid] (gradient before the ReLU) and the batch, and the SGD step of every
-// parameter: g += wd*x; buf = mu*buf + g; x -= lr*buf.  With `next` also the partial sums part[b][z][h], z < mlp_next_splits(K), of the
+// parameter: g += wd*x; buf = mu*buf + g; x -= lr*buf.  With `next` also the partial sums of the
 // first layer with the new weights for that batch.
 void launch_mlp_update(hipStream_t s, float* params, float* momentum, const MlpOffsets& off, const float* x, const BatchRows& rows, const float* h,
                        const float* dlogits, const float* dpre, int B, int hid, int C, int K, const bls_sgd& opt, const BatchRows* next, float* part);
-int mlp_next_splits(int K);
 
 // ---- head.hip ---------------------------------------------------------------------------------------
 // One wave per sample: feature = mean over `positions` of act[b][p][F] (storage type act_type); logits = W feature + bias;

@@ -19,11 +19,11 @@ __device__ __forceinline__ f32x4 load_cols4(const float* __restrict__ row, int c
 
 // part[b][z][h] = sum over the z-th part of the inputs of x[row b][i] W[h][i].  A workgroup owns 16 samples x 16 hidden units and
 // one part; its four waves take a quarter of the part each and meet in LDS.  Lane l supplies row l % 16 of both factors and, in a
-// step of 16 inputs, inputs 4 (l / 16) .. + 3, so that both are 16-byte loads.  The loads of six steps are in flight together
-// (3072 inputs over 32 waves are six steps: one round trip to memory).
+// step of 16 inputs, inputs 4 (l / 16) .. + 3, so that both are 16-byte loads.  The loads of STEPS steps are in flight together
+// (3072 inputs over 32 waves are six steps, a part of 256 over its four waves four: one round trip to memory).
+template <int STEPS>
 __global__ __launch_bounds__(256) void mlp_fc1_kernel(const float* __restrict__ x, BatchRows rows, const float* __restrict__ W, int B, int hid, int K,
                                                       int k_wave, float* __restrict__ part, int x_vec, int w_vec) {
-    constexpr int STEPS = 6;
     __shared__ f32x4 red[4][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane & 15, g = lane >> 4;
     const int m0 = blockIdx.x * 16, n0 = blockIdx.y * 16;
@@ -62,10 +62,12 @@ __global__ __launch_bounds__(256) void mlp_fc1_kernel(const float* __restrict__ 
         if (m0 + 4 * g + i < B) part[((int64_t)(m0 + 4 * g + i) * gridDim.z + blockIdx.z) * hid + n0 + r] = sum[i];
 }
 
-void launch_mlp_fc1(hipStream_t s, const float* x, const BatchRows& rows, const float* W, int B, int hid, int K, float* part) {
-    const int k_wave = ((K + 4 * MLP_SPLITS - 1) / (4 * MLP_SPLITS) + 15) / 16 * 16;
+void launch_mlp_fc1(hipStream_t s, const float* x, const BatchRows& rows, const float* W, int B, int hid, int K, float* part, bool rides) {
     const int x_vec = K % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0, w_vec = K % 4 == 0 && reinterpret_cast<uintptr_t>(W) % 16 == 0;
-    hipLaunchKernelGGL(mlp_fc1_kernel, dim3((B + 15) / 16, hid / 16, MLP_SPLITS), dim3(256), 0, s, x, rows, W, B, hid, K, k_wave, part, x_vec, w_vec);
+    const dim3 grid((B + 15) / 16, hid / 16, mlp_splits(K, rides));
+    const int k_wave = rides ? MLP_PART / 4 : ((K + 4 * MLP_SPLITS - 1) / (4 * MLP_SPLITS) + 15) / 16 * 16;
+    if (rides) hipLaunchKernelGGL(mlp_fc1_kernel<4>, grid, dim3(256), 0, s, x, rows, W, B, hid, K, k_wave, part, x_vec, w_vec);
+    else hipLaunchKernelGGL(mlp_fc1_kernel<6>, grid, dim3(256), 0, s, x, rows, W, B, hid, K, k_wave, part, x_vec, w_vec);
 }
 
 __device__ __forceinline__ void sgd_one(float& p, float& m, float grad, const bls_sgd& o) {
@@ -83,7 +85,8 @@ __device__ __forceinline__ void sgd_one(float& p, float& m, float grad, const bl
 // The small kinds come first: they are the longer chains.
 // NEXT: a workgroup of the last kind then has 16 x 256 weights of the next step and computes that step's partial sums
 // part[b][z][h] over its 256 inputs (z = their block): the weights pass through LDS into the layout of a factor, the rows of
-// the next batch are requested before anything else.
+// the next batch are requested before anything else.  Sums as in mlp_fc1_kernel: a chain per quarter of the
+// part, added in pairs, so that the bits do not depend on which of the two a step's sums come from.
 template <bool NEXT>
 __global__ __launch_bounds__(256) void mlp_update_kernel(float* __restrict__ params, float* __restrict__ momentum, MlpOffsets off,
                                                          const float* __restrict__ x, BatchRows rows, const float* __restrict__ h,
@@ -123,7 +126,7 @@ __global__ __launch_bounds__(256) void mlp_update_kernel(float* __restrict__ par
     }
     blk -= (C + 1) * f_blocks;
     const int r = lane & 15, g = lane >> 4;
-    const int n_blocks = (K + 255) / 256;
+    const int n_blocks = (K + MLP_PART - 1) / MLP_PART;
     const int m0 = (blk / n_blocks) * 16, z = blk % n_blocks, n = z * 256 + wave * 64 + 4 * r;
     // the wave's first 16 samples of the next batch: lane l supplies row l % 16 and, in a step of 16 inputs, four from 4 (l / 16)
     f32x4 xn[NEXT ? 16 : 1];
@@ -218,10 +221,14 @@ __global__ __launch_bounds__(256) void mlp_update_kernel(float* __restrict__ par
         for (int b0 = 16 * wave; b0 < B; b0 += 64) {
             f32x4 sum[4] = {};
 #pragma unroll
-            for (int u = 0; u < 16; ++u) {
-                const f32x4 w = *reinterpret_cast<const f32x4*>(w_lds + r * PITCH + 16 * u + 4 * g);
+            for (int u = 0; u < 4; ++u) {
+                f32x4 w[4];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) sum[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(xn[u][j], w[j], sum[j], 0, 0, 0);
+                for (int q = 0; q < 4; ++q) w[q] = *reinterpret_cast<const f32x4*>(w_lds + r * PITCH + 64 * q + 16 * u + 4 * g);
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) sum[q] = __builtin_amdgcn_mfma_f32_16x16x4f32(xn[4 * q + u][j], w[q][j], sum[q], 0, 0, 0);
             }
             const f32x4 v = (sum[0] + sum[1]) + (sum[2] + sum[3]);
             if (b0 + 64 < B) load_next(b0 + 64);
@@ -232,8 +239,6 @@ __global__ __launch_bounds__(256) void mlp_update_kernel(float* __restrict__ par
         }
     }
 }
-
-int mlp_next_splits(int K) { return (K + 255) / 256; }
 
 void launch_mlp_update(hipStream_t s, float* params, float* momentum, const MlpOffsets& off, const float* x, const BatchRows& rows, const float* h,
                        const float* dlogits, const float* dpre, int B, int hid, int C, int K, const bls_sgd& opt, const BatchRows* next, float* part) {

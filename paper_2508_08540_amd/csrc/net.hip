@@ -47,8 +47,7 @@ typedef uint8_t act_t;  // activations are addressed as bytes; the model's stora
 // hidden units 202 -> 185 / 155 -> 161).
 // Every 256 inputs leave a partial sum per hidden unit and sample that the head adds up (12 for 3072 inputs, 8 by the launch of its
 // own whatever their number): not for much larger inputs.
-constexpr int MLP_NEXT_MAX_B = 128, MLP_NEXT_MAX_SPLITS = 16;
-bool mlp_next_rides(const bls_model* m, int B) { return B <= MLP_NEXT_MAX_B && mlp_next_splits(m->d_in) <= MLP_NEXT_MAX_SPLITS; }
+bool mlp_next_rides(const bls_model* m, int B) { return B <= 128 && m->d_in <= 16 * MLP_PART; }
 
 struct MlpScratch {
     float *part, *h, *loss, *dlogits, *dpre;
@@ -57,8 +56,7 @@ struct MlpScratch {
 MlpScratch carve_mlp(Carver& c, const bls_model* m, int B, bool train) {
     MlpScratch s{};
     const int hid = m->desc.hidden;
-    const int next = train && mlp_next_rides(m, B) ? mlp_next_splits(m->d_in) : 0;
-    s.part = c.take<float>((size_t)B * (next > MLP_SPLITS ? next : MLP_SPLITS) * hid);
+    s.part = c.take<float>((size_t)B * mlp_splits(m->d_in, train && mlp_next_rides(m, B)) * hid);
     s.loss = c.take<float>(B);
     if (train) {
         s.h = c.take<float>((size_t)B * hid);
@@ -506,7 +504,7 @@ int net_score(bls_ctx* ctx, const bls_model* m, const float* params, const float
         for (int64_t first = 0; first < N; first += chunk) {
             int B = (int)(N - first < chunk ? N - first : chunk);
             const BatchRows rows{nullptr, 0, 0};
-            PROF(ctx, PROF_GEMM, launch_mlp_fc1(st, x + first * m->d_in, rows, params + m->fc1_w, B, m->desc.hidden, m->d_in, s.part));
+            PROF(ctx, PROF_GEMM, launch_mlp_fc1(st, x + first * m->d_in, rows, params + m->fc1_w, B, m->desc.hidden, m->d_in, s.part, false));
             PROF(ctx, PROF_HEAD, launch_head_mlp(st, s.part, B, MLP_SPLITS, m->desc.hidden, params + m->fc1_b, params + m->fc2_w, params + m->fc2_b,
                                 m->desc.classes, y + first, rows, losses_out + first, nullptr, nullptr, nullptr, 0.f));
         }
@@ -543,10 +541,9 @@ int net_local_step(bls_ctx* ctx, const bls_model* m, float* params, float* buffe
             float* loss = step_losses_out ? step_losses_out + j * B : s.loss;
             const BatchRows rows{sel, k, j * B};
             const BatchRows after{sel, k, (j + 1) * B};
-            const bool ahead = mlp_next_rides(m, B);
-            const bool there = ahead && j > 0;   // the step before left this one's partial sums
-            if (!there) PROF(ctx, PROF_GEMM, launch_mlp_fc1(st, x_pool, rows, params + m->fc1_w, B, hid, m->d_in, s.part));
-            PROF(ctx, PROF_HEAD, launch_head_mlp(st, s.part, B, there ? mlp_next_splits(m->d_in) : MLP_SPLITS, hid, params + m->fc1_b, params + m->fc2_w, params + m->fc2_b, C, y_pool,
+            const bool ahead = mlp_next_rides(m, B);   // a step leaves the next one's partial sums
+            if (!ahead || j == 0) PROF(ctx, PROF_GEMM, launch_mlp_fc1(st, x_pool, rows, params + m->fc1_w, B, hid, m->d_in, s.part, ahead));
+            PROF(ctx, PROF_HEAD, launch_head_mlp(st, s.part, B, mlp_splits(m->d_in, ahead), hid, params + m->fc1_b, params + m->fc2_w, params + m->fc2_b, C, y_pool,
                                 rows, loss, s.h, s.dlogits, s.dpre, inv_b));
             PROF(ctx, PROF_GEMM, launch_mlp_update(st, params, momentum, off, x_pool, rows, s.h, s.dlogits, s.dpre, B, hid, C, m->d_in, opt,
                                 ahead && j + 1 < tau ? &after : nullptr, s.part));

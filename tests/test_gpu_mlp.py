@@ -154,3 +154,39 @@ def test_steps_whose_first_layer_rides_in_the_update(hw, channels, hidden, class
         assert_tensors_close(delta(gp), delta(rp), 9e-4, "parameter change")
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("hw,channels,hidden,classes,batch,shift", [
+    (5, 3, 16, 2, 1, 0),        # 75 inputs: one part of 256, its last two quarters empty
+    (18, 1, 48, 17, 64, 0),     # a second part with one quarter and a remainder; the largest batch of a narrow layer that rides
+    (18, 1, 48, 17, 65, 1),     # the smallest that does not; no 16-byte loads
+    (18, 1, 96, 17, 65, 1),     # one that does
+    (32, 3, 128, 10, 64, 0),    # the measured network
+    (16, 1, 96, 10, 128, 0),    # the largest batch whose next first layer rides in the update
+    (16, 1, 96, 10, 129, 0),    # the smallest whose does not
+    (64, 1, 16, 3, 4, 0),       # 4096 inputs, the most in parts of 256
+    (37, 3, 16, 3, 4, 0),       # 4107 inputs
+])
+def test_one_call_of_three_steps_is_three_calls_of_one(hw, channels, hidden, classes, batch, shift):
+    """The partial sums of the first layer are the same whether the update of the step before left them or a launch of its own: same
+    weights, momentum and losses, bit for bit."""
+    import torch
+    import paper_2508_08540_amd as bls
+    ctx = bls.Context(0)
+    try:
+        h = Harness(torch, bls, ctx, bls.Model.mlp(hw, channels, hidden, classes), oracle.MLP())
+        h.shift = shift
+        x, y = synth.image_pool(4, 3 * batch + 5, classes, hw=hw, channels=channels)
+        p = synth.mlp_init(4, hw * hw * channels, hidden, classes)
+        mom = {k: 0.01 * synth.normal(6, i, v.size).reshape(v.shape) for i, (k, v) in enumerate(p.items())}
+        sel = np.arange(x.shape[0] - 1, -1, -1, dtype=np.int32)
+        together = h.local_step(p, {}, mom, x, y, sel, batch, 3, lr=0.01, mu=0.9, wd=1e-2)
+        q, m = p, mom
+        for j in range(3):
+            q, _, m, losses = h.local_step(q, {}, m, x, y, sel[j * batch:(j + 1) * batch], batch, 1, lr=0.01, mu=0.9, wd=1e-2)
+            np.testing.assert_array_equal(losses[0], together[3][j])
+        for k in p:
+            np.testing.assert_array_equal(q[k], together[0][k])
+            np.testing.assert_array_equal(m[k], together[2][k])
+    finally:
+        ctx.close()
