@@ -42,12 +42,14 @@ typedef uint8_t act_t;  // activations are addressed as bytes; the model's stora
 
 // ---- MLP ----------------------------------------------------------------------------------------
 
-// Batches up to this size leave the next step's first layer to the update, which has one workgroup per 16 x 256 weights; a launch of its
-// own spreads the samples over more of them (pass of 8 steps of 128 with 256 hidden units 260 -> 224 us; of 4 steps of 256 with 256 / 128
-// hidden units 202 -> 185 / 155 -> 161).
+// Steps that leave the next one's first layer to their update, whose workgroups (one per 16 x 256 weights) take 64 samples after the
+// other; a launch of its own spreads them over more workgroups.  8 steps with a launch of its own / without: 64 samples and 16 / 64 / 112
+// hidden units 124 / 123, 131 / 126, 134 / 129 us; 65 samples and 64 / 96 / 112 / 256 units 142 / 146, 148 / 149, 162 / 150, 187 / 159;
+// 128 samples and 64 / 112 / 256 units 154 / 170, 171 / 173, 208 / 185.  At 256 samples 256 units gain (202 / 185, 4 steps) and 128
+// lose (155 / 161).
 // Every 256 inputs leave a partial sum per hidden unit and sample that the head adds up (12 for 3072 inputs, 8 by the launch of its
 // own whatever their number): not for much larger inputs.
-bool mlp_next_rides(const bls_model* m, int B) { return B <= 128 && m->d_in <= 16 * MLP_PART; }
+bool mlp_next_rides(const bls_model* m, int B) { return (B <= 64 || (B <= 128 && m->desc.hidden >= 112)) && m->d_in <= 16 * MLP_PART; }
 
 struct MlpScratch {
     float *part, *h, *loss, *dlogits, *dpre;
