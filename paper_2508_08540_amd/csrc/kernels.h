@@ -140,7 +140,7 @@ void launch_mlp_fc1(hipStream_t s, const float* x, const BatchRows& rows, const 
 // parameter: g += wd*x; buf = mu*buf + g; x -= lr*buf.  With `next` also the partial sums of the
 // first layer with the new weights for that batch.
 void launch_mlp_update(hipStream_t s, float* params, float* momentum, const MlpOffsets& off, const float* x, const BatchRows& rows, const float* h,
-                       const float* dlogits, const float* dpre, int B, int hid, int C, int K, const bls_sgd& opt, const BatchRows* next, float* part);
+                       const float* dlogits, const float* dpre, int B, int hid, int C, int K, const bls_sgd& opt, bool rides, const BatchRows* next, float* part);
 
 // ---- head.hip ---------------------------------------------------------------------------------------
 // One wave per sample: feature = mean over `positions` of act[b][p][F] (storage type act_type); logits = W feature + bias;

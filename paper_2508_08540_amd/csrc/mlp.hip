@@ -76,6 +76,15 @@ __device__ __forceinline__ void sgd_one(float& p, float& m, float grad, const bl
     p = __fmaf_rn(-o.lr, buf, p);
 }
 
+// Four weights of a row that starts at `at`, from input n, and their momentum; zeros past the end
+__device__ __forceinline__ void mlp_load_weights(f32x4& pv, f32x4& mv, const float* params, const float* momentum, int64_t at, int n, int K, int p_vec) {
+    pv = mv = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (n < K) {
+        pv = load_cols4(params + at, n, K, p_vec != 0);
+        mv = load_cols4(momentum + at, n, K, p_vec != 0);
+    }
+}
+
 // Gradients and update of every parameter, by workgroups of three kinds in one launch:
 //   the second layer: 64 weights of one class (and, from the first 64, its bias), four slices of the batch folded through LDS;
 //   the first layer's bias: 64 hidden units, likewise;
@@ -87,7 +96,11 @@ __device__ __forceinline__ void sgd_one(float& p, float& m, float grad, const bl
 // part[b][z][h] over its 256 inputs (z = their block): the weights pass through LDS into the layout of a factor, the rows of
 // the next batch are requested before anything else.  Sums as in mlp_fc1_kernel: a chain per quarter of the
 // part, added in pairs, so that the bits do not depend on which of the two a step's sums come from.
-template <bool NEXT>
+// AHEAD: weights and momentum are requested before the sums, and the loads of 32 samples before the products of the 32 before them.
+// Not for large batches and narrow layers: of the former several workgroups share a compute unit, and their number hides more than
+// the registers of those requests (8 steps of 200 samples with 1024 hidden units 621 us, 636 with them; 512 units and 256 samples
+// 434 / 439), the latter gain nothing (128 units and 200 samples 229.5 / 229.9).
+template <bool NEXT, bool AHEAD>
 __global__ __launch_bounds__(256) void mlp_update_kernel(float* __restrict__ params, float* __restrict__ momentum, MlpOffsets off,
                                                          const float* __restrict__ x, BatchRows rows, const float* __restrict__ h,
                                                          const float* __restrict__ dlogits, const float* __restrict__ dpre, int B, int hid, int C,
@@ -142,16 +155,10 @@ __global__ __launch_bounds__(256) void mlp_update_kernel(float* __restrict__ par
     };
     if (NEXT && 16 * wave < B) load_next(16 * wave);
     const int nn = n < K ? n : 0;   // a lane past the last input reads the first ones and stores nothing
-    // weights and momentum are requested before the sums, and the loads of 32 samples before the products of the 32 before them
     f32x4 pv[4], mv[4];
+    if constexpr (AHEAD) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        pv[i] = mv[i] = f32x4{0.f, 0.f, 0.f, 0.f};   // inputs past the end: zero weights
-        if (n < K) {
-            const int64_t at_w = off.fc1_w + (int64_t)(m0 + 4 * g + i) * K;
-            pv[i] = load_cols4(params + at_w, n, K, p_vec != 0);
-            mv[i] = load_cols4(momentum + at_w, n, K, p_vec != 0);
-        }
+        for (int i = 0; i < 4; ++i) mlp_load_weights(pv[i], mv[i], params, momentum, off.fc1_w + (int64_t)(m0 + 4 * g + i) * K, n, K, p_vec);
     }
     f32x4 acc[4] = {};
     for (int b0 = 0; b0 < B; b0 += 256) {
@@ -159,8 +166,8 @@ __global__ __launch_bounds__(256) void mlp_update_kernel(float* __restrict__ par
         at[tid] = pool_row(rows, min(b0 + tid, B - 1));
         __syncthreads();
         const int b_end = min(B, b0 + 256);
-        float a[2][8];
-        f32x4 v[2][8];
+        float a[AHEAD ? 2 : 1][8];
+        f32x4 v[AHEAD ? 2 : 1][8];
         auto fetch = [&](int k0, float (&a)[8], f32x4 (&v)[8]) {
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
@@ -180,14 +187,25 @@ __global__ __launch_bounds__(256) void mlp_update_kernel(float* __restrict__ par
                 for (int q = 0; q < 4; ++q) acc[q] = __builtin_amdgcn_mfma_f32_16x16x4f32(aj, ok ? v[j][q] : 0.f, acc[q], 0, 0, 0);
             }
         };
-        fetch(b0, a[0], v[0]);
-        for (int k0 = b0; k0 < b_end; k0 += 64) {
-            if (k0 + 32 < b_end) fetch(k0 + 32, a[1], v[1]);
-            multiply(k0, a[0], v[0]);
-            if (k0 + 32 >= b_end) break;
-            if (k0 + 64 < b_end) fetch(k0 + 64, a[0], v[0]);
-            multiply(k0 + 32, a[1], v[1]);
+        if constexpr (AHEAD) {
+            fetch(b0, a[0], v[0]);
+            for (int k0 = b0; k0 < b_end; k0 += 64) {
+                if (k0 + 32 < b_end) fetch(k0 + 32, a[1], v[1]);
+                multiply(k0, a[0], v[0]);
+                if (k0 + 32 >= b_end) break;
+                if (k0 + 64 < b_end) fetch(k0 + 64, a[0], v[0]);
+                multiply(k0 + 32, a[1], v[1]);
+            }
+        } else {
+            for (int k0 = b0; k0 < b_end; k0 += 32) {
+                fetch(k0, a[0], v[0]);
+                multiply(k0, a[0], v[0]);
+            }
         }
+    }
+    if constexpr (!AHEAD) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) mlp_load_weights(pv[i], mv[i], params, momentum, off.fc1_w + (int64_t)(m0 + 4 * g + i) * K, n, K, p_vec);
     }
     // lane holds hidden units m0 + 4 g + i, inputs n .. n + 3
     constexpr int PITCH = 256 + 4;
@@ -241,14 +259,15 @@ __global__ __launch_bounds__(256) void mlp_update_kernel(float* __restrict__ par
 }
 
 void launch_mlp_update(hipStream_t s, float* params, float* momentum, const MlpOffsets& off, const float* x, const BatchRows& rows, const float* h,
-                       const float* dlogits, const float* dpre, int B, int hid, int C, int K, const bls_sgd& opt, const BatchRows* next, float* part) {
+                       const float* dlogits, const float* dpre, int B, int hid, int C, int K, const bls_sgd& opt, bool rides, const BatchRows* next, float* part) {
     const int x_vec = K % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0;
     const int p_vec = K % 4 == 0 && (reinterpret_cast<uintptr_t>(params + off.fc1_w) | reinterpret_cast<uintptr_t>(momentum + off.fc1_w)) % 16 == 0;
     const unsigned blocks = (unsigned)((C + 1) * ((hid + 63) / 64) + (hid / 16) * ((K + 255) / 256));
-#define MLP_UPDATE(NEXT) \
-    hipLaunchKernelGGL(mlp_update_kernel<NEXT>, dim3(blocks), dim3(256), 0, s, params, momentum, off, x, rows, h, dlogits, dpre, B, hid, C, K, opt, x_vec, \
+#define MLP_UPDATE(NEXT, AHEAD) \
+    hipLaunchKernelGGL((mlp_update_kernel<NEXT, AHEAD>), dim3(blocks), dim3(256), 0, s, params, momentum, off, x, rows, h, dlogits, dpre, B, hid, C, K, opt, x_vec, \
                        p_vec, next ? *next : BatchRows{}, part)
-    if (next) MLP_UPDATE(true);
-    else MLP_UPDATE(false);
+    if (next) MLP_UPDATE(true, true);
+    else if (rides) MLP_UPDATE(false, true);
+    else MLP_UPDATE(false, false);
 #undef MLP_UPDATE
 }

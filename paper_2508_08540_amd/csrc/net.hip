@@ -547,7 +547,7 @@ int net_local_step(bls_ctx* ctx, const bls_model* m, float* params, float* buffe
             if (!ahead || j == 0) PROF(ctx, PROF_GEMM, launch_mlp_fc1(st, x_pool, rows, params + m->fc1_w, B, hid, m->d_in, s.part, ahead));
             PROF(ctx, PROF_HEAD, launch_head_mlp(st, s.part, B, mlp_splits(m->d_in, ahead), hid, params + m->fc1_b, params + m->fc2_w, params + m->fc2_b, C, y_pool,
                                 rows, loss, s.h, s.dlogits, s.dpre, inv_b));
-            PROF(ctx, PROF_GEMM, launch_mlp_update(st, params, momentum, off, x_pool, rows, s.h, s.dlogits, s.dpre, B, hid, C, m->d_in, opt,
+            PROF(ctx, PROF_GEMM, launch_mlp_update(st, params, momentum, off, x_pool, rows, s.h, s.dlogits, s.dpre, B, hid, C, m->d_in, opt, ahead,
                                 ahead && j + 1 < tau ? &after : nullptr, s.part));
         }
     } else {
