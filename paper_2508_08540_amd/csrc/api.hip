@@ -26,6 +26,7 @@ int bls_arena_reserve(bls_ctx* ctx, size_t bytes) {
     if (bytes <= ctx->arena_bytes) return BLS_OK;
     BLS_HIP(ctx, hipStreamSynchronize(ctx->stream));
     if (ctx->aux) BLS_HIP(ctx, hipStreamSynchronize(ctx->aux));
+    if (ctx->aux2) BLS_HIP(ctx, hipStreamSynchronize(ctx->aux2));
     if (ctx->arena) BLS_HIP(ctx, hipFree(ctx->arena));
     ctx->arena = nullptr;
     ctx->arena_bytes = 0;
@@ -90,6 +91,10 @@ void bls_ctx_destroy(bls_ctx* ctx) {
     if (ctx->aux) {
         (void)hipStreamSynchronize(ctx->aux);
         (void)hipStreamDestroy(ctx->aux);
+    }
+    if (ctx->aux2) {
+        (void)hipStreamSynchronize(ctx->aux2);
+        (void)hipStreamDestroy(ctx->aux2);
     }
     for (hipEvent_t e : ctx->fork_events) (void)hipEventDestroy(e);
     if (ctx->join_event) (void)hipEventDestroy(ctx->join_event);

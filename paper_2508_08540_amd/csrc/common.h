@@ -27,6 +27,7 @@ struct bls_ctx {
     int device = 0;
     hipStream_t stream = nullptr;
     hipStream_t aux = nullptr;             // library-owned side stream for work off the critical path
+    hipStream_t aux2 = nullptr;            // a second one, created on first use (idle streams cost concurrent workers): weight gradients of bf16 rounds
     std::vector<hipEvent_t> fork_events;   // main -> aux dependencies, one per use inside a call
     hipEvent_t join_event = nullptr;       // aux -> main
     hipEvent_t head_event = nullptr;       // main -> aux: the classifier head's gradients are written

@@ -275,19 +275,27 @@ const act_t* resnet_forward(bls_ctx* ctx, hipStream_t st, const bls_model* m, co
     return cur;
 }
 
+// Weight gradients of neighbouring layers alternate between two side streams where several workers train in bf16 inside the same kernels:
+// the main stream's launches are shorter than the weight gradients there, and what is left of those at the end of a step is
+// waited for.  Rounds of 10 workers, batch 16, one / three blocks a stage, one side stream / two: 2.90 / 2.50, 5.71 / 5.41 ms; batch
+// 128 9.51 / 9.39, 21.56 / 21.59.  A single worker pays for every fork twice and gains nothing (see weight_gradient), fp32 neither.
+bool two_sides(const ResScratch& s) { return s.act == ACT_BF16 && s.reps.n > 1; }
+
 // The weight gradients are off the critical path (only the update needs them), so they run on the
 // context's side stream, each after the event that marks its dy as ready; the caller joins the side
 // stream before the update.
 // `early_from`: the caller updates the parameters of layers early_from .. L-1 (and everything behind the last layer) as soon
 // as their weight gradients are in, while those of the layers below still run; the events that mark the two moments are
-// fork_events[L] and the join event.
+// fork_events[L] and the join event, and fork_events[L + 1] and [L + 2] on the second side stream.
 int resnet_backward(bls_ctx* ctx, hipStream_t st, const bls_model* m, const float* params, int B, ResScratch& s, int early_from) {
     const int L = (int)m->layers.size();
-    while ((int)ctx->fork_events.size() < L + 1) {
+    while ((int)ctx->fork_events.size() < L + 3) {
         hipEvent_t e;
         BLS_HIP(ctx, hipEventCreateWithFlags(&e, STREAM_EVENT));
         ctx->fork_events.push_back(e);
     }
+    const bool two = two_sides(s);
+    if (two && !ctx->aux2) BLS_HIP(ctx, hipStreamCreateWithFlags(&ctx->aux2, hipStreamNonBlocking));
     // Profiling puts events of its own on these launches; a stream that is being captured takes only events that are recorded.
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     bool may_stamp = !ctx->profiling;
@@ -300,14 +308,16 @@ int resnet_backward(bls_ctx* ctx, hipStream_t st, const bls_model* m, const floa
     // its own completion signal; an event recorded behind it is a packet of its own on the critical path (bf16 step 549 -> 520 us).
     auto weight_gradient = [&](int l, bool stamped) -> int {
         if (!stamped) BLS_HIP(ctx, hipEventRecord(ctx->fork_events[l], st));
-        BLS_HIP(ctx, hipStreamWaitEvent(ctx->aux, ctx->fork_events[l], 0));
+        hipStream_t side = two && (L - 1 - l) % 2 ? ctx->aux2 : ctx->aux;
+        BLS_HIP(ctx, hipStreamWaitEvent(side, ctx->fork_events[l], 0));
         if (l == L - 1) {   // the head's weight gradient, ready since the forward pass, needs no fork of its own
             ProfScope prof_(ctx, PROF_HEAD, ctx->aux);
             launch_head_wgrad(ctx->aux, s.dlogits, s.feat, B, m->desc.classes, m->final_c, s.grad + m->fc_w, s.grad + m->fc_b, s.reps);
         }
         const ConvShape cs = shape_of(m->layers[l], B);
-        PROF_KERNEL(ctx, PROF_CONV_WGRAD, launch_conv_wgrad(ctx->aux, s.act, cs, l == 0 ? s.xpad : s.a[l - 1], s.dy[l], s.wacc + s.utab.e[l].acc_off, kt, s.reps));
-        if (l == early_from) BLS_HIP(ctx, hipEventRecord(ctx->fork_events[L], ctx->aux));   // the last weight gradient of the early part
+        PROF_KERNEL(ctx, PROF_CONV_WGRAD, launch_conv_wgrad(side, s.act, cs, l == 0 ? s.xpad : s.a[l - 1], s.dy[l], s.wacc + s.utab.e[l].acc_off, kt, s.reps));
+        if (l == early_from) BLS_HIP(ctx, hipEventRecord(ctx->fork_events[L], side));   // the last weight gradient of the early part
+        if (two && l == early_from + 1) BLS_HIP(ctx, hipEventRecord(ctx->fork_events[L + 1], side));   // the last one of the other stream
         return BLS_OK;
     };
     const ConvBn& last = m->layers[L - 1];
@@ -383,6 +393,7 @@ int resnet_backward(bls_ctx* ctx, hipStream_t st, const bls_model* m, const floa
         shared = 0;
     }
     BLS_HIP(ctx, hipEventRecord(ctx->join_event, ctx->aux));
+    if (two) BLS_HIP(ctx, hipEventRecord(ctx->fork_events[L + 2], ctx->aux2));
     return BLS_OK;
 }
 
@@ -406,12 +417,14 @@ int resnet_train_step(bls_ctx* ctx, hipStream_t st, const bls_model* m, float* p
     // gradients of the convolution weights are still in the accumulators: the update reads them there
     if (early < L) {
         BLS_HIP(ctx, hipStreamWaitEvent(st, ctx->fork_events[L], 0));
+        if (two_sides(s) && early + 1 < L) BLS_HIP(ctx, hipStreamWaitEvent(st, ctx->fork_events[L + 1], 0));
     } else {
         BLS_HIP(ctx, hipStreamWaitEvent(st, ctx->join_event, 0));   // nothing below: the head's weight gradient is all there is to wait for
     }
     PROF(ctx, PROF_UPDATE, launch_update(st, s.act, params, momentum, s.grad, m->num_params, opt.lr, opt.momentum, opt.weight_decay,
                                          s.wacc, s.wpack, s.utab, nullptr, 0, s.reps, split, -1));
     BLS_HIP(ctx, hipStreamWaitEvent(st, ctx->join_event, 0));
+    if (two_sides(s)) BLS_HIP(ctx, hipStreamWaitEvent(st, ctx->fork_events[L + 2], 0));
     PROF(ctx, PROF_UPDATE, launch_update(st, s.act, params, momentum, s.grad, m->num_params, opt.lr, opt.momentum, opt.weight_decay,
                                          s.wacc, s.wpack, s.utab, s.sums, (int64_t)L * 2 * FIX_SET, s.reps, 0, split));
     return BLS_OK;
