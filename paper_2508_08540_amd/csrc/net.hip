@@ -308,7 +308,7 @@ int resnet_backward(bls_ctx* ctx, hipStream_t st, const bls_model* m, const floa
     // its own completion signal; an event recorded behind it is a packet of its own on the critical path (bf16 step 549 -> 520 us).
     auto weight_gradient = [&](int l, bool stamped) -> int {
         if (!stamped) BLS_HIP(ctx, hipEventRecord(ctx->fork_events[l], st));
-        hipStream_t side = two && (L - 1 - l) % 2 ? ctx->aux2 : ctx->aux;
+        hipStream_t side = two && l % 2 ? ctx->aux2 : ctx->aux;   // the stem's on the one that gathers the batches
         BLS_HIP(ctx, hipStreamWaitEvent(side, ctx->fork_events[l], 0));
         if (l == L - 1) {   // the head's weight gradient, ready since the forward pass, needs no fork of its own
             ProfScope prof_(ctx, PROF_HEAD, ctx->aux);
