@@ -30,7 +30,7 @@ struct bls_ctx {
     hipStream_t aux2 = nullptr;            // a second one, created on first use (idle streams cost concurrent workers): weight gradients of bf16 rounds
     std::vector<hipEvent_t> fork_events;   // main -> aux dependencies, one per use inside a call
     hipEvent_t join_event = nullptr;       // aux -> main
-    hipEvent_t head_event = nullptr;       // main -> aux: the classifier head's gradients are written
+    hipEvent_t head_event = nullptr;       // main -> aux: the work before this call's first step is enqueued (residual networks)
     float* round_losses = nullptr;   // per-sample losses of the workers' local steps (communication_round), grown on demand
     size_t round_losses_count = 0;
     std::vector<bls_ctx*> lanes;     // library-owned contexts (own stream, side stream and scratch) for concurrent workers

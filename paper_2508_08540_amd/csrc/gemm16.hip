@@ -730,7 +730,9 @@ __device__ __forceinline__ void gd16_transposed(const uint32_t (&at)[NX + NY], u
 // of so many tiles that they are never split.  Over 8192 tokens the gradients of a 512-wide layer are 5.3e-8 to 6.1e-8 off the
 // sum in 64 bits (relative 2-norm), in one running sum per part 7.5e-8 to 1.3e-7; four steps of the 6-layer encoder: 18.2 -> 18.45 ms.
 constexpr bool gd16_runs(bool a_kmajor, int wmb) { return a_kmajor && wmb < 8; }
-// waves per SIMD the registers have to allow, for 16 x 16 blocks per wave
+// waves per SIMD the registers have to allow, for 16 x 16 blocks per wave.  Of the 256 x 128 tiles those with the softmax statistics and
+// with the GELU derivative do not fit the 256 of two waves: 25 and 22 registers go to memory and back once in their epilogues,
+// none in the K loop (about 100 bytes a lane and tile, against 512 of results and 1 to 2 KB of operands).
 constexpr int gd16_waves(bool runs, int blocks) { return blocks >= (runs ? 16 : 32) ? 2 : 3; }
 
 template <bool AK, bool BK, int EPI, int WMB, int WNB, int KS>
@@ -796,7 +798,7 @@ __global__ __launch_bounds__(256, gd16_waves(gd16_runs(AK, WMB), WMB * WNB)) voi
         for (int sub = 0; sub < KS; ++sub) {
             u32x4* base = gd16_lds + buf * STAGE + sub * SUB;
             if (tail && step == steps - 1) {
-                const int left = k_end - k_begin - step * STEP_K - sub * G16_K;   // below 32; nothing of this part where it is not positive
+                const int left = k_end - k_begin - step * STEP_K - sub * G16_K;   // below STEP_K - 32 sub; nothing of this part where it is not positive
 #pragma unroll
                 for (int i = 0; i < LA; ++i) {
                     int row, k;
@@ -845,7 +847,7 @@ __global__ __launch_bounds__(256, gd16_waves(gd16_runs(AK, WMB), WMB * WNB)) voi
     // read first, those of the others AHEAD blocks before their use, and the load instructions, which the address unit takes 16
     // clocks each for, go out one by one between the matrix instructions.  Transposing reads come with their wait, so an AK step
     // reads all of them; its 256-row tile keeps the loads in front (32 000 x 512 over 8192 tokens: 226 us, 251 with the loads between).
-    // 65 536 x 32 000 x 512 with statistics 2453 -> 2256 us, 8192 x 32 000 x 512 349 -> 307, 512 x 2048 over 8192 tokens 42 -> 38.
+    // 65 536 x 32 000 x 512 with statistics 2453 -> 2290 us, 8192 x 32 000 x 512 349 -> 307, 512 x 2048 over 8192 tokens 42 -> 38.
     auto multiply = [&](int buf, auto load, int to) {
         constexpr bool LOAD = decltype(load)::value, FRONT = AK && WMB >= 8;
         constexpr int AHEAD = !AK && WMB >= 8 ? 3 : WMB;

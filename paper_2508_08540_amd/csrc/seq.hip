@@ -127,7 +127,9 @@ __global__ __launch_bounds__(256) void fix_finalize_kernel(FixRangeTable tab, fi
     }
 }
 
-// y = (x - mean) * invstd * g + b per row; stats[row] = (mean, invstd); one wave per row, D <= 1024, D % 4 == 0
+// y = (x - mean) * invstd * g + b per row; stats[row] = (mean, invstd); one wave per row, D <= 1024, D % 4 == 0.  With panels a wave's bf16
+// store is half a cache line in each of D / 32 panels, here as in embed_kernel and the weight copies: 23.9 -> 25.8, 23.6 -> 26.4 and
+// 39 -> 45 us, which the products that read them gain many times over.
 __global__ __launch_bounds__(256) void layernorm_kernel(const float* __restrict__ x, int64_t T, int D, const float* __restrict__ g,
                                                         const float* __restrict__ b, float* __restrict__ y, uint16_t* __restrict__ y16,
                                                         int64_t panel, float* __restrict__ stats) {
@@ -177,7 +179,7 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const float* __restrict_
 // (the gradient of a bias added just before the normalised tensor).  NV = ceil(D / 256) vectors per lane.
 // Bound: HBM (59 MB for 8192 x 512 with a bf16 copy).  All rows of a wave are requested together and their reductions run side
 // by side: row after row the wave waited four times for memory and eight times for a chain of six shuffles (four steps of 64
-// sequences, where it shares the chip with weight gradients: 17.08 -> 16.82 ms).
+// sequences, where it shares the chip with weight gradients: 16.72 -> 16.44 ms; the launch itself takes no less time).
 #define LN_BWD_ROWS_PER_WAVE 4
 template <int NV>
 __global__ __launch_bounds__(256) void layernorm_bwd_kernel(const float* __restrict__ dy, const float* __restrict__ x,
