@@ -325,6 +325,7 @@ __device__ __forceinline__ void gemm_tile_order(int& tile_x, int& tile_y, int& z
 // strides of both factors), the launcher refuses others.  Fields below the line are filled by the launcher.
 struct GemmDesc {
     const float *A, *B;
+    const uint16_t* Bs;   // launch_gemm_split: the packed second factor, in place of B (sb1 counts its elements)
     float* C;
     const float *bias, *R;
     float* part;
@@ -343,6 +344,25 @@ struct GemmDesc {
 };
 size_t gemm_tiled_partial_floats(int M, int N, int splits);
 int launch_gemm_tiled(hipStream_t s, GemmDesc d);   // BLS_EUNSUPPORTED: nothing was launched
+// ---- gemm_split.hip -----------------------------------------------------------------------------------
+// The same product with B as a pack of three bf16 per value (Bs): a batch without inner index, A on 16-byte rows, k_seg (a multiple
+// of 16) for A alone, whose segments follow one another in the pack.  BLS_EUNSUPPORTED where gemm_split_takes says no.
+bool gemm_split_takes(const float* A, int lda, int64_t sa1, int64_t sa_seg, bool a_kmajor, int K, int k_seg);
+int launch_gemm_split(hipStream_t s, GemmDesc d);
+// Packs of `n` matrices of one source: job j is B(n,k) = src[j.src + n * j.ld + k], or [j.src + k * j.ld + n] with kmajor, to dst + j.dst
+// (a multiple of 8).
+#define SPLIT_PACK_MAX 40
+struct SplitPackJob {
+    int64_t src, dst;
+    int rows, K, ld;
+    int blocks;   // filled by the launcher
+};
+struct SplitPackTable {
+    SplitPackJob j[SPLIT_PACK_MAX];
+    int n;
+};
+size_t split_pack_elems(int64_t rows, int64_t K);
+void launch_split_pack(hipStream_t s, SplitPackTable tab, bool kmajor, const float* src, uint16_t* dst);
 // out = alpha * (sum of the partial results in split order) (+ bias) (+ R), for a batch of matrices
 void launch_split_reduce(hipStream_t s, const float* part, int splits, int M, int N, int batch, float alpha, const float* bias, int64_t sbias1,
                          const float* R, int ldc, float* out, int64_t sc1, bool aligned);

@@ -2,7 +2,8 @@
 // scores, attention-weighted values, their gradients and the weight gradients) is one launch of a tiled MFMA GEMM;
 // the kernels of seq.hip do the rest.  Activations are [tokens][width], heads are column slices of width D/H.
 //
-// Two modes.  fp32: every tensor is fp32 and the products run on the fp32 matrix instruction.  bf16 factors: every
+// Two modes.  fp32: every tensor is fp32 and the products run on the fp32 matrix instruction, those of the linear layers of larger
+// training batches on the bf16 one with every factor split into three (gemm_split.hip).  bf16 factors: every
 // tensor that is a factor of some product also (or only) exists as a bf16 copy, written by the kernel that produces
 // it, and the products read those copies (bf16 matrix instruction, fp32 sums); everything that is not a product -
 // residual sums, layer norm, softmax, GELU derivative, bias and layer-norm gradients, the loss, the parameters and
@@ -46,6 +47,13 @@ struct LayerAct {
     float *r1, *st1, *u, *r2, *st2;
 };
 
+// Packs of a weight matrix W[rows][cols] at `off` of the parameters: over cols (the projection) and over rows (its input gradient).
+struct SplitWeight {
+    int64_t off;
+    int rows, cols;
+    size_t f, t;
+};
+
 struct SeqScratch {
     int rc = BLS_OK;                // of the first product that could not be launched
     bool bf = false;
@@ -77,6 +85,9 @@ struct SeqScratch {
     size_t cpart_floats;
     fixsum_t* acc;
     int64_t acc_count;
+    // fp32 mode, training: the factors that gemm_split.hip reads as packs (empty: no packs)
+    std::vector<SplitWeight> packs;
+    uint16_t *pack_f, *pack_t, *pack_x;   // weights as second factor of a projection, of its input gradient; of the product at hand on the side stream
 };
 
 // Splits of the token contraction of a weight gradient so that about one workgroup per compute unit is in flight: the products
@@ -103,6 +114,15 @@ int dgrad_splits(bool bf, int64_t M, int N, int K) {
     int64_t s = ceil_div(1024, tiles);   // 512 tiles of 256 x 128: two workgroups per compute unit
     if (s > K / 1024) s = K / 1024;
     return (int)(s > 1 ? s : 1);
+}
+
+// Training in fp32 takes the linear layers' products to gemm_split.hip from this many tokens a batch on: the packs of the weights
+// cost the same (0.6 GB of traffic at 35 million parameters) whatever the batch.  Two steps of the 6-layer encoder, fp32 products
+// against split ones: 256 tokens 4.41 / 4.61 ms, 400 tokens 5.15 / 5.00, three layers with 600 tokens 2.68 / 2.48, 1600 tokens
+// 7.77 / 6.34, 3100 tokens 15.93 / 11.59.  (Scoring keeps the fp32 products: a score is the same bits in a pool of any size.)
+#define SPLIT_MIN_TOKENS 512
+bool uses_packs(const bls_model* m, int64_t T) {
+    return m->desc.act_dtype != BLS_ACT_BF16 && T >= SPLIT_MIN_TOKENS && m->enc_D % 16 == 0 && m->enc_F % 4 == 0;
 }
 
 enum Kind { F32_ONLY, BOTH, FACTOR_ONLY };   // FACTOR_ONLY: fp32 in fp32 mode, bf16 alone in bf16 mode
@@ -215,6 +235,23 @@ SeqScratch carve(Carver& c, const bls_model* m, int B, bool train) {
     s.cpart = c.take<float>(s.cpart_floats);
     s.acc_count = (int64_t)V * D;   // fixed-point accumulators of the token-embedding gradient
     s.acc = c.take<fixsum_t>(s.acc_count);
+    if (uses_packs(m, T)) {
+        size_t f = 0, t = 0;
+        auto pack = [&](int64_t off, int rows, int cols) {
+            s.packs.push_back(SplitWeight{off, rows, cols, f, t});
+            f += split_pack_elems(rows, cols);
+            t += split_pack_elems(cols, rows);
+        };
+        for (const EncLayer& e : m->enc_layers) {
+            for (int64_t w : {e.wq, e.wk, e.wv, e.wo}) pack(w, D, D);
+            pack(e.w1, F, D);
+            pack(e.w2, D, F);
+        }
+        pack(m->enc_head, V, D);
+        s.pack_f = c.take<uint16_t>(f);
+        s.pack_t = c.take<uint16_t>(t);
+        s.pack_x = c.take<uint16_t>(split_pack_elems(std::max(D, F), T));
+    }
     return s;
 }
 
@@ -243,9 +280,13 @@ struct Product {
     const float* ce_rows = nullptr;        // bf16 mode only: the gradient of the logits instead of the logits
     float ce_scale = 0.f;
     int n_valid = 0;
+    const uint16_t* Bs = nullptr;          // fp32 mode: B as a pack, sbs1 elements between those of a batch; where it cannot be taken, B
+    int64_t sbs1 = 0;
     const float* U = nullptr;              // bf16 mode only: times gelu'(U), column sums into gelu_part
     float* gelu_part = nullptr;
 };
+
+bool split_takes(const Product& p) { return gemm_split_takes(p.A.f, p.lda, p.sa1, p.sa_seg, p.a_kmajor, p.K, p.k_seg); }
 
 void multiply(bls_ctx* ctx, hipStream_t st, SeqScratch* s, const Product& p, int prof_class) {
     ProfScope prof(ctx, prof_class, st);
@@ -282,7 +323,13 @@ void multiply(bls_ctx* ctx, hipStream_t st, SeqScratch* s, const Product& p, int
         d.sbias1 = p.sbias1;
         d.k_seg = p.k_seg; d.sa_seg = p.sa_seg; d.sb_seg = p.sb_seg;
         d.alpha = p.alpha;
-        rc = launch_gemm_tiled(st, d);
+        if (p.Bs && split_takes(p)) {
+            d.Bs = p.Bs;
+            d.sb1 = p.sbs1;
+            rc = launch_gemm_split(st, d);
+        } else {
+            rc = launch_gemm_tiled(st, d);
+        }
     }
     if (rc != BLS_OK && s->rc == BLS_OK) s->rc = bls_fail(ctx, rc, "a %d x %d x %d product needs 16-byte rows", p.M, p.N, p.K);
 }
@@ -298,11 +345,42 @@ struct Net {
     // weight matrix of n_out rows
     Mat weight(int64_t off, int n_out) const { return Mat{const_cast<float*>(params) + off, s->bf ? s->w16 + off : nullptr, s->panels ? (int64_t)n_out * 32 : 0}; }
 
+    // pack of the weights at `off`, over its columns or (t) its rows; NULL where there are none
+    const uint16_t* pack(int64_t off, bool t) const {
+        for (const SplitWeight& w : s->packs)
+            if (w.off == off) return t ? s->pack_t + w.t : s->pack_f + w.f;
+        return nullptr;
+    }
+    void refresh_packs() const {
+        for (bool t : {false, true}) {
+            SplitPackTable tab;
+            tab.n = 0;
+            for (const SplitWeight& w : s->packs) {
+                tab.j[tab.n++] = SplitPackJob{w.off, (int64_t)(t ? w.t : w.f), t ? w.cols : w.rows, t ? w.rows : w.cols, w.cols, 0};
+                if (tab.n == SPLIT_PACK_MAX || &w == &s->packs.back()) {
+                    PROF(ctx, PROF_UPDATE, launch_split_pack(st, tab, t, params, t ? s->pack_t : s->pack_f));
+                    tab.n = 0;
+                }
+            }
+        }
+    }
+    // the second factor x[T][n_in] of a weight gradient as a pack over the tokens, in the side stream's buffer
+    const uint16_t* pack_tokens(Mat x, int64_t T, int n_in) const {
+        if (s->packs.empty()) return nullptr;
+        SplitPackTable tab;
+        tab.n = 1;
+        tab.j[0] = SplitPackJob{0, 0, n_in, (int)T, n_in, 0};
+        ProfScope prof(ctx, PROF_CONV_WGRAD, st);
+        launch_split_pack(st, tab, true, x.f, s->pack_x);
+        return s->pack_x;
+    }
+
     // y[T][n_out] = x[T][n_in] W^T + b (+ R); gelu (optional) takes gelu(y)
     void linear(Mat x, int64_t T, int n_in, int64_t w_off, int64_t b_off, int n_out, Mat y, const float* R = nullptr, Mat gelu = Mat{}) const {
         Product p;
         p.A = x; p.lda = n_in;
         p.B = weight(w_off, n_out); p.ldb = n_in;
+        p.Bs = pack(w_off, false);
         p.out = y; p.gelu = gelu; p.ldc = n_out;
         p.bias = b_off >= 0 ? params + b_off : nullptr;
         p.R = R;
@@ -320,6 +398,7 @@ struct Net {
         Product p;
         p.A = hf; p.lda = D;
         p.B = weight(m->enc_head, s->ldv); p.ldb = D;
+        p.Bs = pack(m->enc_head, false);
         p.ldc = V;
         p.M = (int)T; p.N = V; p.K = D;
         if (s->bf) {
@@ -359,6 +438,7 @@ struct Net {
         Product p;
         p.A = dy; p.lda = pitch ? pitch : n_out;
         p.B = weight(w_off, p.lda); p.ldb = n_in; p.b_kmajor = true;
+        p.Bs = pack(w_off, true);
         p.out = dx; p.ldc = n_in;
         p.R = R;
         p.M = (int)T; p.N = n_in; p.K = p.lda;
@@ -377,6 +457,7 @@ struct Net {
         p.M = n_out; p.N = n_in; p.K = (int)T;
         p.splits = wgrad_splits(n_out, n_in, T);
         p.part = s->part;
+        if (split_takes(p)) p.Bs = pack_tokens(x, T, n_in);
         multiply(ctx, st, s, p, PROF_CONV_WGRAD);
     }
     // q, k, v = x Wq^T + bq, ... as one batch of three products where the three weights (and biases, and outputs) are
@@ -388,6 +469,7 @@ struct Net {
             Product p;
             p.A = x; p.lda = D;
             p.B = weight(e.wq, D); p.ldb = D; p.sb1 = sw;
+            p.Bs = pack(e.wq, false); p.sbs1 = (int64_t)split_pack_elems(D, D);
             p.out = a.q; p.ldc = D; p.sc1 = so;
             p.bias = params + e.bq; p.sbias1 = sw;
             p.M = (int)T; p.N = D; p.K = D;
@@ -412,6 +494,7 @@ struct Net {
             p.batch = 3;
             p.splits = wgrad_splits(D, D, T, 3);
             p.part = s->part;
+            if (split_takes(p)) p.Bs = pack_tokens(x, T, D);
             multiply(ctx, st, s, p, PROF_CONV_WGRAD);
             return;
         }
@@ -431,6 +514,7 @@ struct Net {
             Product p;
             p.A = dq; p.lda = D; p.sa_seg = sd;
             p.B = weight(e.wq, D); p.ldb = D; p.b_kmajor = true; p.sb_seg = sw;
+            p.Bs = pack(e.wq, true);   // the three weights' packs follow one another, D rows (whole steps) each
             p.k_seg = D;
             p.out = dx; p.ldc = D;
             p.R = R;
@@ -632,6 +716,7 @@ int seq_local_step(bls_ctx* ctx, const bls_model* m, float* params, float* momen
     net.clear_weight_padding();
     for (int64_t j = 0; j < tau; ++j) {
         net.refresh_weight_copies();
+        net.refresh_packs();
         {
             ProfScope prof(ctx, PROF_GATHER);
             hipLaunchKernelGGL(gather_sequences_kernel, dim3(B), dim3(256), 0, st, x_pool, y_pool, sel, k, j * B, L, s.tok, s.tgt);

@@ -338,7 +338,10 @@ __global__ __launch_bounds__(256) void softmax_short_rows_kernel(float* __restri
     if (p16) store_bf16x4(p16 + rrow * n + 4 * sub, v);
 }
 
-// ds = p * (dp - sum_j dp_j p_j) * scale, in place on dp, or as bf16 into ds16 when that is given
+// ds = p * (dp - sum_j dp_j p_j) * scale, in place on dp, or as bf16 into ds16 when that is given.  The rounding of the sum is
+// common to a row, so the row of ds would not add up to zero, which the key bias sees alone; what is left of the row sum is
+// taken off once more (noise of a key bias whose gradient is zero, of the query
+// bias' gradient: up to 7e-6 before, 6e-7 with it).
 __global__ __launch_bounds__(256) void softmax_bwd_rows_kernel(float* __restrict__ dp, const float* __restrict__ p, uint16_t* __restrict__ ds16,
                                                                int64_t rows, int n, float scale) {
     const int64_t rrow = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -354,10 +357,17 @@ __global__ __launch_bounds__(256) void softmax_bwd_rows_kernel(float* __restrict
         dot += a[i] * d[i];
     }
     dot = wsum(dot);
+    float rest = 0.f;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        d[i] -= dot;
+        rest += a[i] * d[i];
+    }
+    rest = wsum(rest);
 #pragma unroll
     for (int i = 0; i < 16; ++i)
         if (lane + 64 * i < n) {
-            const float q = a[i] * (d[i] - dot) * scale;
+            const float q = a[i] * (d[i] - rest) * scale;
             if (ds16) ds16[rrow * n + lane + 64 * i] = to_bf16(q);
             else dp[rrow * n + lane + 64 * i] = q;
         }
