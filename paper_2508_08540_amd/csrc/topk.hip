@@ -6,16 +6,17 @@
 //   low 32 bits:  ~index, so that among equal losses the smaller index is the larger word.
 // All words are distinct, hence exactly one result is correct and no stability argument is needed.
 //
-// Pools of up to TOPK_RANK_MAX samples are ranked by counting in one launch; pools of up to TOPK_SORT_MAX are sorted whole by
-// four radix passes of one launch each; larger ones take radix-select of the k-th word, ordered compaction of the selected
-// words, and an LSD radix sort of those k words.
+// Pools of up to TOPK_RANK_MAX samples are ranked by counting in one launch; pools of up to TOPK_WHOLE_MAX are sorted whole by
+// four radix passes of one launch each; larger ones take radix-select of the k-th word and an LSD radix sort of the words selected.
 #include <mutex>
 
 #include "common.h"
 
-// Ranking by counting needs no scratch and costs 24.6 us at 16384 (four sorting passes: 22 us at 16385); sorting a pool of
-// 2^19 whole takes 73 us for any k, selecting first 98 (k = N / 50) to 120 us (k = N); at 2^20 about 117 against 86 to 105 us.
+// Ranking by counting needs no scratch and costs 24.6 us at 16384 (four sorting passes: 22 us at 16385).  Sorting whole / selecting
+// first, k = N / 50 and k = N: 200 000 samples 45 / 48 and 54 us, 262 144 (the last that four rounds of a tile hold) 51 / 48 and 55,
+// 400 000 64 / 49 and 58.  (Several selections in one go, TOPK_SORT_MAX, are another matter: they share the sort's launches.)
 #define TOPK_RANK_MAX 16384
+#define TOPK_WHOLE_MAX (1 << 18)
 
 __device__ __forceinline__ uint32_t loss_key(float v) {
     uint32_t u = __float_as_uint(v);
@@ -268,7 +269,7 @@ static void launch_sort(hipStream_t s, const SelJobs& jobs, int n_jobs, int N) {
     hipLaunchKernelGGL((sort_pass_kernel<RITER, 3>), grid, block, 0, s, jobs, N);
 }
 
-// TOPK_RANK_MAX < N <= TOPK_SORT_MAX; `scratch_base` as below, n_jobs times.  The fewest rounds that keep the pool within
+// N <= TOPK_SORT_MAX; `scratch_base` as below, n_jobs times.  The fewest rounds that keep the pool within
 // SORT_TILES tiles.
 static int launch_topk_medium(bls_ctx* ctx, char* scratch_base, SelJobs jobs, int n_jobs, int64_t N) {
     Carver c(scratch_base);
@@ -283,30 +284,39 @@ static int launch_topk_medium(bls_ctx* ctx, char* scratch_base, SelJobs jobs, in
 
 // ---- large pools ----------------------------------------------------------------------------------
 //
-// 1. Two-level radix select of the k-th largest key: a 2048-bin histogram of the top 11 key bits gives the bin b1 that
-//    holds it, a second histogram of the next 11 bits over the members of b1 gives the 22-bit prefix `thr`: the M
-//    elements with key >> 10 >= thr are selected (M >= k; the excess is at most the members of one 22-bit prefix).
-//    Histograms are aggregated per wave before they touch LDS (losses crowd into a few exponent bins).
-// 2. The selected elements are compacted, in index order, into (sort key, index) pairs; the sort key is hi - key
-//    (hi bounds every key), so that ascending order is rank order and the keys only span the range that occurs.
-// 3. Stable LSD radix sort of the M pairs, 8 bits per pass, with as many passes as that range needs (the later passes
-//    exit at once).  Stability keeps equal losses in ascending index order, which is the tie rule.
-// 4. The first k pairs are the result: the last pass stores indices and losses instead of pairs.
+// 1. Select: a histogram of the top 15 key bits gives the bin that holds the k-th largest key.  Where that bin holds more than
+//    N / 32 elements too many (they would all be sorted), a second histogram of the next 11 bits over its members gives a 26-bit
+//    prefix.  The M elements with key >= thr are selected (M >= k).
+// 2. Stable LSD radix sort of the M elements, 8 bits per pass, with as many passes as the range of their keys needs (the later
+//    ones exit at once).  The sort key is hi - key (hi bounds every key), so that ascending order is rank order and the keys
+//    only span the range that occurs.  The first pass reads the losses themselves and leaves (sort key, index) pairs; stability
+//    keeps equal losses in ascending index order, which is the tie rule.
+// 3. The first k pairs are the result: the last pass stores indices and losses instead of pairs.
 // Nothing is read back to the host: grids are sized for the worst case M == N and blocks past M exit.
+//
+// A pass is two launches: digit counts of every tile, with sums over groups of SEL_GROUP tiles, and the scatter, whose
+// workgroups add up the groups and the tiles of their own group before them, all requested at once (62 + 32 rows of 256 at 16 M
+// keys; in batches of eight the first pass took 56 us, now 50; sums over 16 groups as well made its atomics meet and the
+// counts 13.6 -> 18.6 us).  The launches that scanned
+// the table in between, two of 3 to 4 us and as many gaps a pass, are gone.  A compaction of
+// the selected pairs before the sort (count, scan, gather: 41 us for 16 M keys) is gone too: the first pass skips what is not selected.
+// 4 M of 16 M half-normal losses: 24 launches and 201 us before, 13 and 157; all of 16 M 436 -> 330; 84 000 of 4.2 M 119 -> 77; all of
+// 600 000 96 -> 64.
 
-#define SEL_BINS 2048
-#define TILE 2048          // elements per 256-thread block: 8 consecutive elements per thread
-#define SCAN_CHUNK 2048
-// Radix passes: a block of 256 threads handles RITER * 256 elements (each wave ranks RITER * 64 of them in
-// rounds of 64); 8 rounds for pools below 2^22, 16 for very large ones (longer runs per digit when scattering).
+#define SEL_BINS 32768       // level 1
+#define SEL_SHIFT 17
+#define SEL_BINS2 2048       // level 2
+#define SEL_SHIFT2 6
+#define SEL_GROUP 32         // tiles of a group of digit counts
+#define SEL_EXCESS 32        // level 2 runs where more than N / SEL_EXCESS elements too many would be selected
 
 struct SelInfo {
-    uint32_t bin;        // b1
-    uint32_t above;      // elements in bins above b1
-    uint32_t thr;        // selected: key >> 10 >= thr
+    uint32_t thr;        // selected: key >= thr
     uint32_t M;          // number of selected elements
     uint32_t hi;         // no key is larger; sort key = hi - key
-    uint32_t n_passes;   // 8-bit passes that cover hi - (thr << 10)
+    uint32_t n_passes;   // 8-bit passes that cover hi - thr
+    uint32_t above;      // elements in bins above that of thr (level 1)
+    uint32_t refine;     // level 2 runs
 };
 
 __global__ __launch_bounds__(256) void zero_u32_kernel(uint32_t* p, int64_t n) {
@@ -331,355 +341,303 @@ __device__ __forceinline__ void load_keys4(const float* __restrict__ losses, int
     }
 }
 
-// LEVEL 1: bins of key >> 21 over all elements.  Losses crowd into a handful of exponent bins, so every bin has
-// SUB counters in LDS and a lane adds to counter lane % SUB: the lanes of a wave that meet in one bin spread over SUB
-// addresses.  LEVEL 2: bins of (key >> 10) & 2047 over the members of info->bin only (those bits are spread evenly).
-// 1024 threads per histogram: the loop waits for memory (256 threads, two to eight workgroups per unit: 25 + 29 us at 2^24
-// keys, now 15 + 19), while every further histogram costs a clear and a fold of 2048 bins.
+// LEVEL 1: bins of the top 15 bits over all elements, 128 KB of LDS.  (Losses crowd into a few octaves, but an octave has 64 of
+// these bins: the lanes of a wave mostly add to different words.)  LEVEL 2: bins of the next 11 bits over the members of one.
+// One workgroup of 1024 threads per compute unit: the loop waits for memory, while every further histogram costs a clear and a
+// fold of its bins.
 #define HIST_THREADS 1024
 template <int LEVEL, bool VEC>
 __global__ __launch_bounds__(HIST_THREADS) void sel_hist_kernel(const float* __restrict__ losses, int64_t N, const SelInfo* __restrict__ info,
                                                        uint32_t* __restrict__ hist) {
-    constexpr int SUB = LEVEL == 1 ? 8 : 1;
-    __shared__ uint32_t h[SEL_BINS * SUB];
-    for (int i = threadIdx.x; i < SEL_BINS * SUB; i += HIST_THREADS) h[i] = 0u;
+    constexpr int BINS = LEVEL == 1 ? SEL_BINS : SEL_BINS2, DEPTH = 4;
+    extern __shared__ __align__(16) uint32_t sel_lds[];
+    if (LEVEL == 2 && !info->refine) return;
+    const uint32_t b1 = LEVEL == 2 ? info->thr >> SEL_SHIFT : 0u;
+    for (int i = threadIdx.x; i < BINS / 4; i += HIST_THREADS) reinterpret_cast<uint4*>(sel_lds)[i] = make_uint4(0u, 0u, 0u, 0u);
     __syncthreads();
-    const uint32_t b1 = LEVEL == 2 ? info->bin : 0u;
-    const uint32_t sub = threadIdx.x & (SUB - 1);
     const int64_t quads = (N + 3) >> 2, stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < quads; q += 2 * stride) {
-        uint32_t key[2][4];
-        bool ok[2][4] = {{false, false, false, false}, {false, false, false, false}};
-        load_keys4<VEC>(losses, N, q, key[0], ok[0]);
-        if (q + stride < quads) load_keys4<VEC>(losses, N, q + stride, key[1], ok[1]);
+    for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < quads; q += DEPTH * stride) {
+        uint32_t key[DEPTH][4];
+        bool ok[DEPTH][4];
 #pragma unroll
-        for (int u = 0; u < 2; ++u)
+        for (int u = 0; u < DEPTH; ++u) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) ok[u][j] = false;
+            if (q + u * stride < quads) load_keys4<VEC>(losses, N, q + u * stride, key[u], ok[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < DEPTH; ++u)
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                if (LEVEL == 1) {
-                    if (ok[u][j]) atomicAdd(&h[(key[u][j] >> 21) * SUB + sub], 1u);
-                } else {
-                    if (ok[u][j] && (key[u][j] >> 21) == b1) atomicAdd(&h[(key[u][j] >> 10) & (SEL_BINS - 1)], 1u);
-                }
+                if (!ok[u][j]) continue;
+                if (LEVEL == 1) atomicAdd(&sel_lds[key[u][j] >> SEL_SHIFT], 1u);
+                else if ((key[u][j] >> SEL_SHIFT) == b1) atomicAdd(&sel_lds[(key[u][j] >> SEL_SHIFT2) & (SEL_BINS2 - 1)], 1u);
             }
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < SEL_BINS; i += HIST_THREADS) {
-        uint32_t c = 0;
-#pragma unroll
-        for (int u = 0; u < SUB; ++u) c += h[i * SUB + u];
+    for (int i = threadIdx.x; i < BINS; i += HIST_THREADS) {
+        const uint32_t c = sel_lds[i];
         if (c) atomicAdd(&hist[i], c);
     }
 }
 
-// One block: suffix counts over the bins; the bin sought is the largest one whose suffix count reaches `want`.
-// LEVEL 1: want = k; stores bin, above and hi.  LEVEL 2: want = k - above over the sub-bins of b1; stores thr, M, n_passes.
+// One block: suffix counts over the bins; the bin sought is the largest one whose suffix count reaches `want`.  LEVEL 1: want = k;
+// stores what follows from its bins, and whether they are too coarse.  LEVEL 2: want = k - above over the sub-bins of that bin.
 template <int LEVEL>
-__global__ __launch_bounds__(256) void sel_threshold_kernel(const uint32_t* __restrict__ hist, uint32_t k, SelInfo* __restrict__ info) {
-    __shared__ uint32_t part[256];
-    __shared__ uint32_t top_bin;
-    const uint32_t want = LEVEL == 1 ? k : k - info->above;
-    uint32_t mine[8], tot = 0;
+__global__ __launch_bounds__(1024) void sel_threshold_kernel(const uint32_t* __restrict__ hist, uint32_t k, int64_t N, SelInfo* __restrict__ info) {
+    constexpr int PER = (LEVEL == 1 ? SEL_BINS : SEL_BINS2) / 1024;   // bins per thread
+    __shared__ uint32_t wave_total[16], top_bin;
+    extern __shared__ __align__(16) uint32_t sel_lds[];   // level 1: the bins, a word left out after every 32
+    if (LEVEL == 2 && !info->refine) return;
+    const uint32_t want = LEVEL == 1 ? k : k - info->above, first = LEVEL == 2 ? info->thr : 0u, hi_before = LEVEL == 2 ? info->hi : 0u,
+                   above_before = LEVEL == 2 ? info->above : 0u;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint32_t mine[PER], tot = 0;
     if (threadIdx.x == 0) top_bin = 0u;
-    for (int j = 0; j < 8; ++j) {
-        mine[j] = hist[threadIdx.x * 8 + j];
-        tot += mine[j];
+    if constexpr (LEVEL == 1) {
+        uint4 v[PER / 4];
+#pragma unroll
+        for (int j = 0; j < PER / 4; ++j) v[j] = reinterpret_cast<const uint4*>(hist)[j * 1024 + threadIdx.x];
+#pragma unroll
+        for (int j = 0; j < PER / 4; ++j) {
+            const int b = 4 * (j * 1024 + threadIdx.x), at = b + (b >> 5);
+            sel_lds[at] = v[j].x; sel_lds[at + 1] = v[j].y; sel_lds[at + 2] = v[j].z; sel_lds[at + 3] = v[j].w;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < PER; ++j) mine[j] = sel_lds[threadIdx.x * (PER + 1) + j];
+    } else {
+#pragma unroll
+        for (int j = 0; j < PER; ++j) mine[j] = hist[threadIdx.x * PER + j];
     }
-    part[threadIdx.x] = tot;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) tot += mine[j];
+    uint32_t incl = tot;   // of this thread and the higher ones
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t v = __shfl_down(incl, o, 64);
+        if (lane + o < 64) incl += v;
+    }
+    if (lane == 0) wave_total[wave] = incl;
     __syncthreads();
-    if (LEVEL == 1)
-        for (int j = 0; j < 8; ++j)
-            if (mine[j]) atomicMax(&top_bin, threadIdx.x * 8 + j);
-    // inclusive suffix sum over threads (thread t: bins 8t .. 8t+7)
-    for (int o = 1; o < 256; o <<= 1) {
-        uint32_t add = (threadIdx.x + o < 256) ? part[threadIdx.x + o] : 0u;
-        __syncthreads();
-        part[threadIdx.x] += add;
+    if (LEVEL == 1) {
+        int top = -1;
+#pragma unroll
+        for (int j = 0; j < PER; ++j)
+            if (mine[j]) top = j;
+        if (top >= 0) atomicMax(&top_bin, (uint32_t)(threadIdx.x * PER + top));
         __syncthreads();
     }
-    uint32_t above = part[threadIdx.x] - tot;  // elements in bins of higher threads
-    for (int j = 7; j >= 0; --j) {
-        uint32_t with = above + mine[j];
+    uint32_t above = incl - tot;
+    for (int w = wave + 1; w < 16; ++w) above += wave_total[w];
+#pragma unroll
+    for (int j = PER - 1; j >= 0; --j) {
+        const uint32_t with = above + mine[j];
         if (above < want && with >= want) {
-            const uint32_t b = threadIdx.x * 8 + j;
+            const uint32_t b = threadIdx.x * PER + j;
+            const uint32_t thr = LEVEL == 1 ? b << SEL_SHIFT : first | (b << SEL_SHIFT2);
+            const uint32_t hi = LEVEL == 1 ? ((top_bin + 1u) << SEL_SHIFT) - 1u : hi_before;   // the last bin: 2^32 - 1
+            const uint32_t range = hi - thr;   // sort keys lie in [0, range]
+            info->thr = thr;
+            info->hi = hi;
+            info->M = above_before + with;
+            info->n_passes = range < 256u ? 1u : (32u - (uint32_t)__clz(range) + 7u) / 8u;   // the last pass stores the result
             if (LEVEL == 1) {
-                info->bin = b;
                 info->above = above;
-                info->hi = top_bin == SEL_BINS - 1 ? 0xffffffffu : ((top_bin + 1u) << 21) - 1u;
-            } else {
-                const uint32_t thr = (info->bin << 11) | b;
-                const uint32_t range = info->hi - (thr << 10);   // sort keys lie in [0, range]
-                info->thr = thr;
-                info->M = info->above + with;
-                info->n_passes = range < 256u ? 1u : (32u - (uint32_t)__clz(range) + 7u) / 8u;   // the last pass stores the result
+                info->refine = (int64_t)(with - want) > N / SEL_EXCESS ? 1u : 0u;
             }
         }
         above = with;
     }
 }
 
-__device__ __forceinline__ uint32_t block_exclusive_scan_256(uint32_t v, uint32_t* total) {
-    // inclusive scan inside each wave by shuffles, then the four wave totals through LDS
-    __shared__ uint32_t wave_total[4];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint32_t incl = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t below = __shfl_up(incl, o, 64);
-        if (lane >= o) incl += below;
-    }
-    if (lane == 63) wave_total[wave] = incl;
-    __syncthreads();
-    uint32_t before = 0;
-    for (int w = 0; w < wave; ++w) before += wave_total[w];
-    const uint32_t all = (wave_total[0] + wave_total[1]) + (wave_total[2] + wave_total[3]);
-    __syncthreads();   // wave_total may be written again by the next call
-    if (total) *total = all;
-    return before + incl - v;
-}
-
-// The 8 consecutive elements of a thread (two quads)
-template <bool VEC>
-__device__ __forceinline__ uint32_t load_tile_keys(const float* __restrict__ losses, int64_t N, uint32_t thr, uint32_t (&key)[8], bool (&sel)[8]) {
-    const int64_t q0 = ((int64_t)blockIdx.x * TILE + threadIdx.x * 8) >> 2;
-    uint32_t c = 0;
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        uint32_t kq[4];
-        bool ok[4];
-        load_keys4<VEC>(losses, N, q0 + h, kq, ok);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            key[4 * h + j] = kq[j];
-            sel[4 * h + j] = ok[j] && (kq[j] >> 10) >= thr;
-            c += sel[4 * h + j] ? 1u : 0u;
-        }
-    }
-    return c;
-}
-
-template <bool VEC>
-__global__ __launch_bounds__(256) void sel_count_kernel(const float* __restrict__ losses, int64_t N, const SelInfo* __restrict__ info,
-                                                        uint32_t* __restrict__ counts) {
-    uint32_t key[8];
-    bool sel[8];
-    const uint32_t c = load_tile_keys<VEC>(losses, N, info->thr, key, sel);
-    uint32_t total;
-    block_exclusive_scan_256(c, &total);
-    if (threadIdx.x == 0) counts[blockIdx.x] = total;
-}
-
-// counts has been exclusive-scanned into offsets.  The selected pairs of a tile are gathered in LDS and stored side by side: from
-// the threads' own eight elements every store would go to 64 places (16 M keys, 4 M selected: 29 -> 19 us).
-template <bool VEC>
-__global__ __launch_bounds__(256) void sel_compact_kernel(const float* __restrict__ losses, int64_t N, const SelInfo* __restrict__ info,
-                                                          const uint32_t* __restrict__ offsets, uint2* __restrict__ pairs) {
-    __shared__ uint2 buf[TILE];
-    const uint32_t hi = info->hi;
-    const int64_t base = (int64_t)blockIdx.x * TILE + threadIdx.x * 8;
-    uint32_t key[8];
-    bool sel[8];
-    const uint32_t c = load_tile_keys<VEC>(losses, N, info->thr, key, sel);
-    uint32_t total, pos = block_exclusive_scan_256(c, &total);
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-        if (sel[j]) buf[pos++] = make_uint2(hi - key[j], (uint32_t)(base + j));
-    __syncthreads();
-    uint2* out = pairs + offsets[blockIdx.x];
-    for (uint32_t j = threadIdx.x; j < total; j += 256) out[j] = buf[j];
-}
-
-// ---- exclusive scan of a uint32 array (two or three kernels) -------------------------------------------------
-
-// The scans take an optional (info, pass): a radix pass the key range does not need is skipped by all its kernels.
-__device__ __forceinline__ bool pass_skipped(const SelInfo* info, int pass) { return info && (uint32_t)pass >= info->n_passes; }
-// Radix tiles that hold selected pairs (the grids and tables are sized for M == N on the host) and the length of a
-// pass's digit table, 256 entries per such tile; with rtile == 0 the scan takes the length it was given.
-__device__ __forceinline__ int active_tiles(const SelInfo* info, int rtile, int n_blocks) {
-    const int64_t a = ((int64_t)info->M + rtile - 1) / rtile;
-    return a < n_blocks ? (int)a : n_blocks;
-}
-__device__ __forceinline__ int64_t scan_length(int64_t n, const SelInfo* info, int rtile) {
-    if (!info || rtile == 0) return n;
-    const int64_t m = 256 * (((int64_t)info->M + rtile - 1) / rtile);
-    return m < n ? m : n;
-}
-
-__global__ __launch_bounds__(256) void scan_chunk_sums_kernel(const uint32_t* __restrict__ data, int64_t n, uint32_t* __restrict__ sums,
-                                                              const SelInfo* __restrict__ info, int pass, int rtile) {
-    if (pass_skipped(info, pass)) return;
-    n = scan_length(n, info, rtile);
-    if ((int64_t)blockIdx.x * SCAN_CHUNK >= n) return;
-    int64_t base = (int64_t)blockIdx.x * SCAN_CHUNK + threadIdx.x * 8;
-    uint32_t c = 0;
-    for (int j = 0; j < 8; ++j)
-        if (base + j < n) c += data[base + j];
-    uint32_t total;
-    block_exclusive_scan_256(c, &total);
-    if (threadIdx.x == 0) sums[blockIdx.x] = total;
-}
-
-__global__ __launch_bounds__(256) void scan_sums_kernel(uint32_t* __restrict__ sums, int n_chunks, int64_t n, const SelInfo* __restrict__ info, int pass,
-                                                        int rtile) {
-    if (pass_skipped(info, pass)) return;
-    n_chunks = (int)((scan_length(n, info, rtile) + SCAN_CHUNK - 1) / SCAN_CHUNK);
-    uint32_t carry = 0;
-    for (int b0 = 0; b0 < n_chunks; b0 += 256) {
-        int i = b0 + threadIdx.x;
-        uint32_t v = i < n_chunks ? sums[i] : 0u, total;
-        uint32_t ex = block_exclusive_scan_256(v, &total);
-        if (i < n_chunks) sums[i] = carry + ex;
-        carry += total;
-    }
-}
-
-// With `raw` the chunk sums have not been scanned: a workgroup adds up those before its own, a few loads per thread in place of a
-// launch of one workgroup (up to SCAN_RAW_MAX chunks).
-#define SCAN_RAW_MAX 4096
-__global__ __launch_bounds__(256) void scan_apply_kernel(uint32_t* __restrict__ data, int64_t n, const uint32_t* __restrict__ sums,
-                                                         const SelInfo* __restrict__ info, int pass, int rtile, int raw) {
-    if (pass_skipped(info, pass)) return;
-    n = scan_length(n, info, rtile);
-    if ((int64_t)blockIdx.x * SCAN_CHUNK >= n) return;
-    int64_t base = (int64_t)blockIdx.x * SCAN_CHUNK + threadIdx.x * 8;
-    uint32_t v[8], c = 0;
-    for (int j = 0; j < 8; ++j) {
-        v[j] = base + j < n ? data[base + j] : 0u;
-        c += v[j];
-    }
-    uint32_t before = 0;
-    if (raw) {
-        uint32_t mine = 0;
-        for (unsigned i = threadIdx.x; i < blockIdx.x; i += 256) mine += sums[i];
-        block_exclusive_scan_256(mine, &before);
-    } else {
-        before = sums[blockIdx.x];
-    }
-    uint32_t run = before + block_exclusive_scan_256(c, nullptr);
-    for (int j = 0; j < 8; ++j)
-        if (base + j < n) {
-            data[base + j] = run;
-            run += v[j];
-        }
-}
-
-// The same in one launch for arrays of up to 8192 entries (block counts of pools of up to 2^24 losses; above that the
-// strided per-thread loads cost more than the two launches saved): thread t of the one workgroup owns entries
-// [t * per, (t + 1) * per), all loaded before anything else so that the loads overlap.
-#define SCAN_ONE_LAUNCH_MAX 8192
-__global__ __launch_bounds__(256) void scan_small_kernel(uint32_t* __restrict__ data, int n, int per, const SelInfo* __restrict__ info, int pass,
-                                                         int rtile) {
-    if (pass_skipped(info, pass)) return;
-    n = (int)scan_length(n, info, rtile);
-    uint32_t v[32];
-    const int base = threadIdx.x * per;
-#pragma unroll
-    for (int j = 0; j < 32; ++j) v[j] = (j < per && base + j < n) ? data[base + j] : 0u;
-    uint32_t c = 0;
-#pragma unroll
-    for (int j = 0; j < 32; ++j) c += v[j];
-    uint32_t run = block_exclusive_scan_256(c, nullptr);
-#pragma unroll
-    for (int j = 0; j < 32; ++j)
-        if (j < per && base + j < n) {
-            data[base + j] = run;
-            run += v[j];
-        }
-}
-
-static void exclusive_scan_u32(hipStream_t s, uint32_t* data, int64_t n, uint32_t* sums, const SelInfo* info = nullptr, int pass = 0, int rtile = 0) {
-    if (n <= SCAN_ONE_LAUNCH_MAX) {
-        hipLaunchKernelGGL(scan_small_kernel, dim3(1), dim3(256), 0, s, data, (int)n, (int)((n + 255) / 256), info, pass, rtile);
-        return;
-    }
-    int n_chunks = (int)((n + SCAN_CHUNK - 1) / SCAN_CHUNK);
-    hipLaunchKernelGGL(scan_chunk_sums_kernel, dim3(n_chunks), dim3(256), 0, s, data, n, sums, info, pass, rtile);
-    const int raw = n_chunks <= SCAN_RAW_MAX;
-    if (!raw) hipLaunchKernelGGL(scan_sums_kernel, dim3(1), dim3(256), 0, s, sums, n_chunks, n, info, pass, rtile);
-    hipLaunchKernelGGL(scan_apply_kernel, dim3(n_chunks), dim3(256), 0, s, data, n, sums, info, pass, rtile, raw);
-}
-
 // ---- radix sort passes --------------------------------------------------------------------------------
 
-// table[d * tiles + b] = number of elements of block b's tile with digit d, tiles = the tiles that hold pairs (active_tiles)
-template <int RITER>
-__global__ __launch_bounds__(256) void radix_count_kernel(const uint2* __restrict__ pairs, const SelInfo* __restrict__ info,
-                                                          int shift, uint32_t* __restrict__ table, int n_blocks) {
-    if ((uint32_t)(shift >> 3) >= info->n_passes) return;   // the key range does not reach these bits
-    __shared__ uint32_t cnt[256];
-    cnt[threadIdx.x] = 0u;
-    __syncthreads();
-    const uint32_t M = info->M;
-    constexpr int RTILE = RITER * 256;
-    int64_t base = (int64_t)blockIdx.x * RTILE;
-    if (base >= M) return;   // the table only has columns for tiles that hold pairs
-#pragma unroll
-    for (int j = 0; j < RITER; ++j) {
-        int64_t i = base + j * 256 + threadIdx.x;
-        if (i < M) atomicAdd(&cnt[(pairs[i].x >> shift) & 255u], 1u);
-    }
-    __syncthreads();
-    table[(int64_t)threadIdx.x * active_tiles(info, RTILE, n_blocks) + blockIdx.x] = cnt[threadIdx.x];
+// Pools below 2^22: tiles of 8 rounds of 256 threads; larger ones 16 rounds of 512 (longer runs per digit when scattering,
+// fewer rows to add up).
+template <int THREADS, int RITER>
+struct RadixShape {
+    static constexpr int TILE = THREADS * RITER, WAVES = THREADS / 64;
+};
+
+// Element i of a pass as it is stored (past the end another one), the pair it sorts by, and whether it takes part.  FIRST: losses.
+template <bool FIRST>
+__device__ __forceinline__ uint2 radix_load(const uint2* __restrict__ pairs, const float* __restrict__ losses, int64_t N, uint32_t M, int64_t i) {
+    if (FIRST) return make_uint2(__float_as_uint(losses[i < N ? i : N - 1]), 0u);
+    return pairs[i < (int64_t)M ? i : 0];
+}
+template <bool FIRST>
+__device__ __forceinline__ bool radix_take(uint2& pair, int64_t N, uint32_t M, uint32_t thr, uint32_t hi, int64_t i) {
+    if (!FIRST) return i < (int64_t)M;
+    const uint32_t key = loss_key(__uint_as_float(pair.x));
+    pair = make_uint2(hi - key, (uint32_t)i);
+    return i < N && key >= thr;
 }
 
-// table has been exclusive-scanned: table[d * n_blocks + b] = first output slot of digit d in block b.
-// Each wave owns RTILE/4 consecutive elements of the tile and ranks them 64 at a time with ballots, counting every digit as it
+// table[tile][d] = number of elements of the tile with digit d, group[tile / SEL_GROUP][d] = their sums (cleared beforehand)
+template <int THREADS, int RITER, bool FIRST>
+__global__ __launch_bounds__(THREADS) void radix_count_kernel(const uint2* __restrict__ pairs, const float* __restrict__ losses, int64_t N,
+                                                              const SelInfo* __restrict__ info, int shift, uint32_t* __restrict__ table,
+                                                              uint32_t* __restrict__ group) {
+    if ((uint32_t)(shift >> 3) >= info->n_passes) return;   // the key range does not reach these bits
+    __shared__ uint32_t cnt[256];
+    const uint32_t M = info->M, thr = info->thr, hi = info->hi;
+    const int64_t base = (int64_t)blockIdx.x * RadixShape<THREADS, RITER>::TILE;
+    if (!FIRST && base >= M) return;
+    uint2 pair[RITER];
+    bool ok[RITER];
+#pragma unroll
+    for (int j = 0; j < RITER; ++j) pair[j] = radix_load<FIRST>(pairs, losses, N, M, base + j * THREADS + threadIdx.x);
+    if (threadIdx.x < 256) cnt[threadIdx.x] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < RITER; ++j) ok[j] = radix_take<FIRST>(pair[j], N, M, thr, hi, base + j * THREADS + threadIdx.x);
+#pragma unroll
+    for (int j = 0; j < RITER; ++j)
+        if (ok[j]) atomicAdd(&cnt[(pair[j].x >> shift) & 255u], 1u);
+    __syncthreads();
+    if (threadIdx.x < 256) {
+        const uint32_t c = cnt[threadIdx.x];
+        table[(int64_t)blockIdx.x * 256 + threadIdx.x] = c;
+        if (c) atomicAdd(&group[(int64_t)(blockIdx.x / SEL_GROUP) * 256 + threadIdx.x], c);
+    }
+}
+
+// Each wave owns RITER * 64 consecutive elements of the tile and ranks them 64 at a time with ballots, counting every digit as it
 // goes, so the order of equal digits is the input order (stable).  The pairs are then put in digit order in LDS and written out
 // position by position: neighbouring lanes write neighbouring slots of a digit's run, and key and index travel as one 8-byte
 // pair, so that a run of 16 fills a cache line (a pass over 4 M pairs: 25 -> 20 us).  The last pass that the key range needs
-// stores the first k of the result.  With the pair layout the whole selection went from 258 to 215 us (4 M of 16 M), 608 to 473
-// (all of 16 M) and 153 to 116 (all of 2^20); without a launch that unpacks the result and one per scan it takes 201, 435, 105.
-template <int RITER>
-__global__ __launch_bounds__(256) void radix_scatter_kernel(const uint2* __restrict__ in, uint2* __restrict__ out, const SelInfo* __restrict__ info,
-                                                            int shift, const uint32_t* __restrict__ table, int n_blocks,
-                                                            const float* __restrict__ losses, int64_t k, int32_t* __restrict__ idx_out,
-                                                            float* __restrict__ val_out) {
-    constexpr int RTILE = RITER * 256;
-    __shared__ uint32_t cnt[4][256];
+// stores the first k of the result.
+template <int THREADS, int RITER, bool FIRST>
+__global__ __launch_bounds__(THREADS, 4) void radix_scatter_kernel(const uint2* __restrict__ in, uint2* __restrict__ out, int64_t N,
+                                                                const SelInfo* __restrict__ info, int shift, const uint32_t* __restrict__ table,
+                                                                const uint32_t* __restrict__ group, const float* __restrict__ losses, int64_t k,
+                                                                int32_t* __restrict__ idx_out, float* __restrict__ val_out) {
+    constexpr int TILE = RadixShape<THREADS, RITER>::TILE, WAVES = RadixShape<THREADS, RITER>::WAVES;
+    __shared__ uint32_t cnt[WAVES][256];
     __shared__ uint32_t to_global[256];   // global slot of a digit's first element minus its slot in the tile
-    __shared__ uint2 buf[RTILE];
+    __shared__ uint32_t part[2][WAVES / 4][256];
+    __shared__ uint32_t wave_total[2][4];
+    __shared__ uint2 buf[TILE];
     if ((uint32_t)(shift >> 3) >= info->n_passes) return;   // the key range does not reach these bits
-    const uint32_t M = info->M;
-    const int64_t base = (int64_t)blockIdx.x * RTILE;
-    if (base >= M) return;
+    const uint32_t M = info->M, thr = info->thr, hi = info->hi;
+    const bool last = (uint32_t)(shift >> 3) + 1u == info->n_passes;
+    const int64_t base = (int64_t)blockIdx.x * TILE;
+    if (!FIRST && base >= M) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t wbase = base + wave * (RTILE / 4);
+    const int64_t wbase = base + wave * (RITER * 64);
     uint2 pair[RITER];
     uint32_t rank[RITER];
+    bool ok[RITER];
 #pragma unroll
-    for (int it = 0; it < RITER; ++it) {
-        const int64_t i = wbase + it * 64 + lane;
-        pair[it] = i < M ? in[i] : make_uint2(0u, 0u);
-    }
-    const uint32_t first = table[(int64_t)threadIdx.x * active_tiles(info, RTILE, n_blocks) + blockIdx.x];
+    for (int it = 0; it < RITER; ++it) pair[it] = radix_load<FIRST>(in, losses, N, M, wbase + it * 64 + lane);
+    {   // a digit's elements in all tiles, and in those before this one
+        constexpr int SLICES = WAVES / 4;
+        const int d = threadIdx.x & 255, g0 = threadIdx.x >> 8, tile = blockIdx.x;
+        const int64_t elements = FIRST ? N : (int64_t)M;
+        const int groups = (int)((elements + (int64_t)TILE * SEL_GROUP - 1) / ((int64_t)TILE * SEL_GROUP)), own = tile / SEL_GROUP;
+        uint32_t v[SEL_GROUP / SLICES], all = 0, left = 0;
 #pragma unroll
-    for (int w = 0; w < 4; ++w) cnt[w][threadIdx.x] = 0u;
-    __syncthreads();
-    const uint64_t lt = lane ? (~0ull >> (64 - lane)) : 0ull;
-#pragma unroll
-    for (int it = 0; it < RITER; ++it) {
-        const bool valid = wbase + it * 64 + lane < M;
-        const uint32_t d = (pair[it].x >> shift) & 255u;
-        uint64_t peers = __ballot(valid);
-#pragma unroll
-        for (int b = 0; b < 8; ++b) {
-            const uint64_t v = __ballot((d >> b) & 1u);
-            peers &= ((d >> b) & 1u) ? v : ~v;
+        for (int j = 0; j < SEL_GROUP / SLICES; ++j) {
+            const int t = own * SEL_GROUP + g0 + SLICES * j;
+            v[j] = t < tile ? table[(int64_t)t * 256 + d] : 0u;
         }
-        rank[it] = cnt[wave][d] + (uint32_t)__popcll(peers & lt);
+        for (int q = g0; q < groups; q += 16 * SLICES) {
+            uint32_t w[16];
+#pragma unroll
+            for (int j = 0; j < 16; ++j) w[j] = q + SLICES * j < groups ? group[(int64_t)(q + SLICES * j) * 256 + d] : 0u;
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                all += w[j];
+                left += q + SLICES * j < own ? w[j] : 0u;
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < SEL_GROUP / SLICES; ++j) left += v[j];
+        part[0][g0][d] = all;
+        part[1][g0][d] = left;
+    }
+    for (int i = threadIdx.x; i < WAVES * 256; i += THREADS) cnt[i >> 8][i & 255] = 0u;
+#pragma unroll
+    for (int it = 0; it < RITER; ++it) ok[it] = radix_take<FIRST>(pair[it], N, M, thr, hi, wbase + it * 64 + lane);   // waits for the loads
+    const uint64_t lt = lane ? (~0ull >> (64 - lane)) : 0ull;
+    int rounds = RITER;
+    if constexpr (FIRST) {
+        // the selected elements of the wave side by side, in order: rounds that rank nothing are skipped
+        uint2* own = buf + wave * (RITER * 64);
+        int n = 0;
+#pragma unroll
+        for (int it = 0; it < RITER; ++it) {
+            const uint64_t sel = __ballot(ok[it]);
+            if (ok[it]) own[n + __popcll(sel & lt)] = pair[it];
+            n += __popcll(sel);
+        }
         __builtin_amdgcn_wave_barrier();
-        if (valid && (peers & lt) == 0ull) cnt[wave][d] += (uint32_t)__popcll(peers);  // lowest peer advances the count
-        __builtin_amdgcn_wave_barrier();
+        rounds = (n + 63) >> 6;
+#pragma unroll
+        for (int it = 0; it < RITER; ++it) {
+            ok[it] = it * 64 + lane < n;
+            pair[it] = own[it * 64 + lane];   // past the n-th: not used
+        }
     }
     __syncthreads();
-    {   // per digit: slots of the tile in digit order, waves in order inside a digit
-        uint32_t c[4];
 #pragma unroll
-        for (int w = 0; w < 4; ++w) c[w] = cnt[w][threadIdx.x];
-        uint32_t run = block_exclusive_scan_256((c[0] + c[1]) + (c[2] + c[3]), nullptr);
+    for (int it = 0; it < RITER; ++it) {
+        rank[it] = 0;
+        if (!FIRST || it < rounds) {
+            const bool valid = ok[it];
+            const uint32_t d = (pair[it].x >> shift) & 255u;
+            uint64_t peers = __ballot(valid);
+#pragma unroll
+            for (int b = 0; b < 8; ++b) {
+                const uint64_t v = __ballot((d >> b) & 1u);
+                peers &= ((d >> b) & 1u) ? v : ~v;
+            }
+            rank[it] = cnt[wave][d] + (uint32_t)__popcll(peers & lt);
+            __builtin_amdgcn_wave_barrier();
+            if (valid && (peers & lt) == 0ull) cnt[wave][d] += (uint32_t)__popcll(peers);  // lowest peer advances the count
+            __builtin_amdgcn_wave_barrier();
+        }
+    }
+    __syncthreads();
+    // thread d < 256: slots of the tile in digit order, waves in order inside a digit, and the digit's first global slot
+    uint32_t c[WAVES], mine = 0, total = 0, in_mine = 0, in_total = 0;
+    if (threadIdx.x < 256) {
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) {
+            c[w] = cnt[w][threadIdx.x];
+            mine += c[w];
+        }
+#pragma unroll
+        for (int g = 0; g < WAVES / 4; ++g) total += part[0][g][threadIdx.x];
+        in_mine = mine;
+        in_total = total;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t a = __shfl_up(in_mine, o, 64), b = __shfl_up(in_total, o, 64);
+            if (lane >= o) {
+                in_mine += a;
+                in_total += b;
+            }
+        }
+        if (lane == 63) {
+            wave_total[0][wave] = in_mine;
+            wave_total[1][wave] = in_total;
+        }
+    }
+    __syncthreads();
+    int n_valid = (int)((wave_total[0][0] + wave_total[0][1]) + (wave_total[0][2] + wave_total[0][3]));
+    if (threadIdx.x < 256) {
+        uint32_t run = in_mine - mine, first = in_total - total;
+        for (int w = 0; w < wave; ++w) {
+            run += wave_total[0][w];
+            first += wave_total[1][w];
+        }
+#pragma unroll
+        for (int g = 0; g < WAVES / 4; ++g) first += part[1][g][threadIdx.x];
         to_global[threadIdx.x] = first - run;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) {
+        for (int w = 0; w < WAVES; ++w) {
             cnt[w][threadIdx.x] = run;
             run += c[w];
         }
@@ -687,12 +645,9 @@ __global__ __launch_bounds__(256) void radix_scatter_kernel(const uint2* __restr
     __syncthreads();
 #pragma unroll
     for (int it = 0; it < RITER; ++it)
-        if (wbase + it * 64 + lane < M) buf[cnt[wave][(pair[it].x >> shift) & 255u] + rank[it]] = pair[it];
+        if (ok[it]) buf[cnt[wave][(pair[it].x >> shift) & 255u] + rank[it]] = pair[it];
     __syncthreads();
-    const int n_valid = (int)(M - base < (uint32_t)RTILE ? M - base : (uint32_t)RTILE);
-    const bool last = (uint32_t)(shift >> 3) + 1u == info->n_passes;
-    const uint32_t hi = info->hi;
-    for (int j = threadIdx.x; j < n_valid; j += 256) {
+    for (int j = threadIdx.x; j < n_valid; j += THREADS) {
         const uint2 v = buf[j];
         const uint32_t pos = to_global[(v.x >> shift) & 255u] + (uint32_t)j;
         if (!last) {
@@ -709,35 +664,54 @@ __global__ __launch_bounds__(256) void radix_scatter_kernel(const uint2* __restr
 }
 
 struct TopkScratch {
-    uint32_t *hist, *hist2, *counts, *sums, *table;
+    uint32_t *hist, *hist2, *sums, *table;   // the first three are cleared together; sums: of groups, per pass
     uint2 *a, *b;
     SelInfo* info;
-    int n_blocks;    // selection tiles (TILE elements)
-    int r_iter;      // rounds per wave in the radix passes (8 or 16)
-    int r_blocks;    // radix tiles (r_iter * 256 elements)
+    int64_t cleared;
+    bool big;        // tiles of 16 x 512 elements instead of 8 x 256
+    int tiles, groups;
 };
 
 static TopkScratch carve_topk(Carver& c, int64_t N) {
     TopkScratch t;
-    t.n_blocks = (int)((N + TILE - 1) / TILE);
-    t.r_iter = N >= (int64_t(1) << 22) ? 16 : 8;
-    t.r_blocks = (int)((N + t.r_iter * 256 - 1) / (t.r_iter * 256));
-    t.hist = c.take<uint32_t>(2 * SEL_BINS);   // both levels, cleared together
+    t.big = N >= (int64_t(1) << 22);
+    t.tiles = (int)ceil_div(N, t.big ? RadixShape<512, 16>::TILE : RadixShape<256, 8>::TILE);
+    t.groups = (int)ceil_div(t.tiles, SEL_GROUP);
+    t.cleared = SEL_BINS + SEL_BINS2 + (int64_t)4 * t.groups * 256;
+    t.hist = c.take<uint32_t>(t.cleared);
     t.hist2 = t.hist + SEL_BINS;
+    t.sums = t.hist2 + SEL_BINS2;
     t.info = c.take<SelInfo>(1);
-    t.counts = c.take<uint32_t>(t.n_blocks);
-    t.table = c.take<uint32_t>((size_t)256 * t.r_blocks);
-    t.sums = c.take<uint32_t>(((size_t)256 * t.n_blocks + SCAN_CHUNK - 1) / SCAN_CHUNK + 1);
+    t.table = c.take<uint32_t>((size_t)256 * t.tiles);
     t.a = c.take<uint2>(N);
     t.b = c.take<uint2>(N);
     return t;
+}
+
+template <int THREADS, int RITER>
+static void launch_radix(hipStream_t s, const TopkScratch& t, const float* losses, int64_t N, int64_t k, int32_t* idx_out, float* val_out) {
+    const dim3 grid(t.tiles), threads(THREADS);
+    uint2 *from = t.b, *to = t.a;
+    for (int pass = 0; pass < 4; ++pass) {
+        uint32_t* group = t.sums + (int64_t)pass * t.groups * 256;
+#define RADIX_PASS(FIRST)                                                                                                                       \
+    do {                                                                                                                                        \
+        hipLaunchKernelGGL((radix_count_kernel<THREADS, RITER, FIRST>), grid, threads, 0, s, from, losses, N, t.info, pass * 8, t.table, group); \
+        hipLaunchKernelGGL((radix_scatter_kernel<THREADS, RITER, FIRST>), grid, threads, 0, s, from, to, N, t.info, pass * 8, t.table, group,   \
+                           losses, k, idx_out, val_out);                                                                                        \
+    } while (0)
+        if (pass == 0) RADIX_PASS(true);
+        else RADIX_PASS(false);
+#undef RADIX_PASS
+        uint2* tmp = from; from = to; to = tmp;
+    }
 }
 
 size_t topk_scratch_bytes(int64_t N, int64_t k) {
     (void)k;
     if (N <= TOPK_RANK_MAX) return 0;
     Carver c(nullptr);
-    if (N <= TOPK_SORT_MAX) {
+    if (N <= TOPK_WHOLE_MAX) {
         SelJob job;
         carve_sort(c, N, job);
         return c.off;
@@ -751,32 +725,21 @@ static int launch_topk_large(bls_ctx* ctx, char* scratch_base, const float* loss
     Carver c(scratch_base);
     TopkScratch t = carve_topk(c, N);
     hipStream_t s = ctx->stream;
-    const int nb = t.n_blocks, rb = t.r_blocks;
-    const int64_t quads = (N + 3) / 4;
-    const int64_t hist_want = (quads + HIST_THREADS - 1) / HIST_THREADS, hist_full = 2 * (int64_t)ctx->num_cus;   // 64 KB of LDS each
-    const int hist_blocks = (int)(hist_want < hist_full ? hist_want : hist_full);
+    const int64_t hist_want = ceil_div(ceil_div(N, 4), HIST_THREADS);
+    const int hist_blocks = (int)(hist_want < ctx->num_cus ? hist_want : ctx->num_cus);
     const bool vec = reinterpret_cast<uintptr_t>(losses) % 16 == 0;   // 16-byte loads where the array allows them
-    hipLaunchKernelGGL(zero_u32_kernel, dim3(16), dim3(256), 0, s, t.hist, (int64_t)2 * SEL_BINS);
-    if (vec) hipLaunchKernelGGL((sel_hist_kernel<1, true>), dim3(hist_blocks), dim3(HIST_THREADS), 0, s, losses, N, t.info, t.hist);
-    else hipLaunchKernelGGL((sel_hist_kernel<1, false>), dim3(hist_blocks), dim3(HIST_THREADS), 0, s, losses, N, t.info, t.hist);
-    hipLaunchKernelGGL(sel_threshold_kernel<1>, dim3(1), dim3(256), 0, s, t.hist, (uint32_t)k, t.info);
-    if (vec) hipLaunchKernelGGL((sel_hist_kernel<2, true>), dim3(hist_blocks), dim3(HIST_THREADS), 0, s, losses, N, t.info, t.hist2);
-    else hipLaunchKernelGGL((sel_hist_kernel<2, false>), dim3(hist_blocks), dim3(HIST_THREADS), 0, s, losses, N, t.info, t.hist2);
-    hipLaunchKernelGGL(sel_threshold_kernel<2>, dim3(1), dim3(256), 0, s, t.hist2, (uint32_t)k, t.info);
-    if (vec) hipLaunchKernelGGL(sel_count_kernel<true>, dim3(nb), dim3(256), 0, s, losses, N, t.info, t.counts);
-    else hipLaunchKernelGGL(sel_count_kernel<false>, dim3(nb), dim3(256), 0, s, losses, N, t.info, t.counts);
-    exclusive_scan_u32(s, t.counts, nb, t.sums);
-    if (vec) hipLaunchKernelGGL(sel_compact_kernel<true>, dim3(nb), dim3(256), 0, s, losses, N, t.info, t.counts, t.a);
-    else hipLaunchKernelGGL(sel_compact_kernel<false>, dim3(nb), dim3(256), 0, s, losses, N, t.info, t.counts, t.a);
-    uint2 *from = t.a, *to = t.b;
-    for (int pass = 0; pass < 4; ++pass) {
-        if (t.r_iter == 16) hipLaunchKernelGGL(radix_count_kernel<16>, dim3(rb), dim3(256), 0, s, from, t.info, pass * 8, t.table, rb);
-        else hipLaunchKernelGGL(radix_count_kernel<8>, dim3(rb), dim3(256), 0, s, from, t.info, pass * 8, t.table, rb);
-        exclusive_scan_u32(s, t.table, (int64_t)256 * rb, t.sums, t.info, pass, t.r_iter * 256);
-        if (t.r_iter == 16) hipLaunchKernelGGL(radix_scatter_kernel<16>, dim3(rb), dim3(256), 0, s, from, to, t.info, pass * 8, t.table, rb, losses, k, idx_out, val_out);
-        else hipLaunchKernelGGL(radix_scatter_kernel<8>, dim3(rb), dim3(256), 0, s, from, to, t.info, pass * 8, t.table, rb, losses, k, idx_out, val_out);
-        uint2* tmp = from; from = to; to = tmp;
-    }
+    hipLaunchKernelGGL(zero_u32_kernel, dim3(256), dim3(256), 0, s, t.hist, t.cleared);
+#define SEL_HIST(LEVEL, VEC, HIST) \
+    hipLaunchKernelGGL((sel_hist_kernel<LEVEL, VEC>), dim3(hist_blocks), dim3(HIST_THREADS), 4 * (LEVEL == 1 ? SEL_BINS : SEL_BINS2), s, losses, N, t.info, HIST)
+    if (vec) SEL_HIST(1, true, t.hist);
+    else SEL_HIST(1, false, t.hist);
+    hipLaunchKernelGGL(sel_threshold_kernel<1>, dim3(1), dim3(1024), 4 * (SEL_BINS + SEL_BINS / 32), s, t.hist, (uint32_t)k, N, t.info);
+    if (vec) SEL_HIST(2, true, t.hist2);
+    else SEL_HIST(2, false, t.hist2);
+#undef SEL_HIST
+    hipLaunchKernelGGL(sel_threshold_kernel<2>, dim3(1), dim3(1024), 0, s, t.hist2, (uint32_t)k, N, t.info);
+    if (t.big) launch_radix<512, 16>(s, t, losses, N, k, idx_out, val_out);
+    else launch_radix<256, 8>(s, t, losses, N, k, idx_out, val_out);
     BLS_HIP(ctx, hipGetLastError());
     return BLS_OK;
 }
@@ -791,7 +754,7 @@ static int launch_topk_small(bls_ctx* ctx, const SelJobs& jobs, int n_jobs, int6
 
 // `scratch_base`: topk_scratch_bytes(N, k) bytes of device memory, 256-byte aligned
 static int launch_topk_at(bls_ctx* ctx, char* scratch_base, const float* losses, int64_t N, int64_t k, int32_t* idx_out, float* val_out) {
-    if (N > TOPK_SORT_MAX) return launch_topk_large(ctx, scratch_base, losses, N, k, idx_out, val_out);
+    if (N > TOPK_WHOLE_MAX) return launch_topk_large(ctx, scratch_base, losses, N, k, idx_out, val_out);
     SelJobs jobs{};
     jobs.j[0] = SelJob{losses, (int)k, idx_out, val_out, nullptr, -INFINITY};
     if (N <= TOPK_RANK_MAX) return launch_topk_small(ctx, jobs, 1, N);

@@ -165,6 +165,32 @@ def test_topk_matches_oracle_very_large(env, kind, n):
         del idx, val
 
 
+@pytest.mark.parametrize("n", [262145, 32 * 2048 * 8 + 1, (1 << 22) - 1, (1 << 22) + 32 * 8192 - 5])
+@pytest.mark.parametrize("kind", ["narrow", "split", "sorted"])
+def test_topk_selects_through_coarse_and_fine_bins(env, kind, n):
+    """Pools that are selected before they are sorted, with the last tile and the last group of tiles not full.  narrow: all losses in one
+    or two of the first histogram's bins, so that the second one runs; split: its bin holds just under and just over the excess that
+    is sorted along; sorted: whole tiles selected and whole tiles not."""
+    torch, bls, ctx = env
+    rng = np.random.default_rng(n)
+    if kind == "narrow":
+        arr = (2.3025851 + 1e-4 * rng.standard_normal(n)).astype(np.float32)
+    else:
+        arr = np.abs(rng.standard_normal(n)).astype(np.float32) + np.float32(2.3)
+    if kind == "sorted":
+        arr = np.sort(arr)
+    if kind == "split":   # n / 32 + 100 losses in a bin of their own, far above the others
+        m = n // 32 + 100
+        arr[rng.permutation(n)[:m]] = np.float32(64.0) + np.arange(m, dtype=np.float32) * np.float32(2.0 ** -21 * 16)
+    ranked = oracle.topk_by_loss(arr, n)
+    d = torch.from_numpy(arr).cuda()
+    for k in (1, 99, 101, n // 3, n - 1):
+        idx = torch.full((k,), -1, dtype=torch.int32, device="cuda")
+        bls.topk_by_loss(ctx, d, k, idx, None)
+        ctx.synchronize()
+        np.testing.assert_array_equal(idx.cpu().numpy(), ranked[:k])
+
+
 def test_topk_of_scores_then_smaller_pool(env):
     # scratch is reused between calls of different sizes
     torch, bls, ctx = env
