@@ -295,10 +295,10 @@ static int launch_topk_medium(bls_ctx* ctx, char* scratch_base, SelJobs jobs, in
 // Nothing is read back to the host: grids are sized for the worst case M == N and blocks past M exit.
 //
 // A pass is two launches: digit counts of every tile, with sums over groups of SEL_GROUP tiles, and the scatter, whose
-// workgroups add up the groups and the tiles of their own group before them, all requested at once (62 + 32 rows of 256 at 16 M
-// keys; in batches of eight the first pass took 56 us, now 50; sums over 16 groups as well made its atomics meet and the
-// counts 13.6 -> 18.6 us).  The launches that scanned
-// the table in between, two of 3 to 4 us and as many gaps a pass, are gone.  A compaction of
+// workgroups add up the groups and the tiles of their own group before them (62 + 32 rows of 256 at 16 M keys), sixteen rows of each
+// half of the threads requested at a time: in batches of eight the first pass took 56 us, now 50, and 74 with all at once, whose 156
+// registers leave one workgroup per compute unit.  (Sums over 16 groups as well made its atomics meet: counts 13.6 -> 18.6 us.)
+// The launches that scanned the table in between, two of 3 to 4 us and as many gaps a pass, are gone.  A compaction of
 // the selected pairs before the sort (count, scan, gather: 41 us for 16 M keys) is gone too: the first pass skips what is not selected.
 // 4 M of 16 M half-normal losses: 24 launches and 201 us before, 13 and 157; all of 16 M 436 -> 330; 84 000 of 4.2 M 119 -> 77; all of
 // 600 000 96 -> 64.
