@@ -11,9 +11,10 @@
 // (A k-major) fold the first accumulator every GT_RUN steps: 3100 tokens 1.1e-7, fp32 instructions in the same runs 2.9e-7.
 // Values below 2^-110 lose the bits of l and m that bf16 cannot hold (2^-133).
 //
-// Infinities, NaN and values that round to a bf16 infinity: h + m + l is NaN or infinity minus infinity there, so a NaN in the
-// result is the sign; the workgroup then does its contraction again with the fp32 instruction (whose results are those of fp32
-// arithmetic: an infinite factor gives an infinite result).
+// Infinities, NaN and values that round to a bf16 infinity: h + m + l is NaN or infinity minus infinity there, and h h may be beyond
+// the largest float where the product is not (h is up to 2^-8 above its factor), so a result that is not finite is the sign; the
+// workgroup then does its contraction again with the fp32 instruction (whose results are those of fp32 arithmetic: an infinite factor
+// gives an infinite result).
 //
 // What bounds it is the vector unit beside the matrix pipe: splitting takes 5.5 vector instructions a value, and a SIMD that runs
 // 8 of them per matrix instruction (two waves, interleaved as well as it goes) reaches 70 % of its matrix rate, with 4 it reaches all
@@ -367,7 +368,7 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(GemmDesc d) {
     };
     contract(std::false_type{});
     // lane (r, g) holds acc[mt][nt][4q + i] = C[.. + r][.. + 8q + 4g + i] of every 32 x 32 block
-    bool nan = false;
+    bool again = false;
 #pragma unroll
     for (int mt = 0; mt < WMB; ++mt)
 #pragma unroll
@@ -376,8 +377,8 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(GemmDesc d) {
             for (int q = 0; q < 4; ++q)
                 if (m0 + (wm * WMB + mt) * 32 + r < d.M && n0 + (wn * WNB + nt) * 32 + 8 * q + 4 * g < d.N)
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) nan |= acc[mt][nt][4 * q + i] != acc[mt][nt][4 * q + i];
-    if (__syncthreads_or(nan)) contract(std::true_type{});
+                    for (int i = 0; i < 4; ++i) again |= !(fabsf(acc[mt][nt][4 * q + i]) < INFINITY);
+    if (__syncthreads_or(again)) contract(std::true_type{});
 
     const bool plain = d.splits > 1;   // partial sums go out as they are; the reduction applies the epilogue
     float* C = plain ? d.part + ((int64_t)z * d.splits + split) * d.part_stride : d.C ? d.C + z * d.sc1 : nullptr;
