@@ -298,7 +298,9 @@ static int launch_topk_medium(bls_ctx* ctx, char* scratch_base, SelJobs jobs, in
 // workgroups add up the groups and the tiles of their own group before them (62 + 32 rows of 256 at 16 M keys), sixteen rows of each
 // half of the threads requested at a time: in batches of eight the first pass took 56 us, now 50, and 74 with all at once, whose 156
 // registers leave one workgroup per compute unit.  (Sums over 16 groups as well made its atomics meet: counts 13.6 -> 18.6 us.)
-// The launches that scanned the table in between, two of 3 to 4 us and as many gaps a pass, are gone.  A compaction of
+// The launches that scanned the table in between, two of 3 to 4 us and as many gaps a pass, are gone up to 2^24 samples; beyond, where adding
+// up the groups would grow with the square of the pool, one launch scans their sums (SEL_GROUPS_MAX; 2 % and all of 2^25 half-normal
+// losses 185 -> 163 and 928 -> 831 us, 2 % of 2^28 2.85 -> 1.01 ms, of 2^30 35.9 -> 3.9).  A compaction of
 // the selected pairs before the sort (count, scan, gather: 41 us for 16 M keys) is gone too: the first pass skips what is not selected.
 // 4 M of 16 M half-normal losses: 24 launches and 201 us before, 13 and 157; all of 16 M 436 -> 330; 84 000 of 4.2 M 119 -> 77; all of
 // 600 000 96 -> 64.
@@ -308,6 +310,7 @@ static int launch_topk_medium(bls_ctx* ctx, char* scratch_base, SelJobs jobs, in
 #define SEL_BINS2 2048       // level 2
 #define SEL_SHIFT2 6
 #define SEL_GROUP 32         // tiles of a group of digit counts
+#define SEL_GROUPS_MAX 64    // up to this many groups a scatter adds them up itself; more are scanned by a launch between
 #define SEL_EXCESS 32        // level 2 runs where more than N / SEL_EXCESS elements too many would be selected
 
 struct SelInfo {
@@ -454,10 +457,12 @@ __global__ __launch_bounds__(1024) void sel_threshold_kernel(const uint32_t* __r
 // ---- radix sort passes --------------------------------------------------------------------------------
 
 // Pools below 2^22: tiles of 8 rounds of 256 threads; larger ones 16 rounds of 512 (longer runs per digit when scattering,
-// fewer rows to add up).
+// fewer rows to add up), whose groups may be scanned.  The smaller tiles make up at most SEL_GROUPS_MAX groups.
 template <int THREADS, int RITER>
 struct RadixShape {
     static constexpr int TILE = THREADS * RITER, WAVES = THREADS / 64;
+    static constexpr bool SCANS = THREADS == 512;
+    static __host__ __device__ int groups(int64_t elements) { return (int)((elements + (int64_t)TILE * SEL_GROUP - 1) / ((int64_t)TILE * SEL_GROUP)); }
 };
 
 // Element i of a pass as it is stored (past the end another one), the pair it sorts by, and whether it takes part.  FIRST: losses.
@@ -503,6 +508,39 @@ __global__ __launch_bounds__(THREADS) void radix_count_kernel(const uint2* __res
     }
 }
 
+// More than SEL_GROUPS_MAX groups: every row of sums becomes that of the groups before it, and row `total_row` that of all of them
+// (a scatter that adds up the rows itself reads as much as the square of the pool).  A workgroup takes 16 digits, a thread a 64th
+// of the groups of one.
+template <class Shape, bool FIRST>
+__global__ __launch_bounds__(1024) void radix_scan_kernel(const SelInfo* __restrict__ info, int64_t N, int shift, uint32_t* __restrict__ group, int total_row) {
+    __shared__ uint32_t part[64][16];
+    if ((uint32_t)(shift >> 3) >= info->n_passes) return;
+    const int groups = Shape::groups(FIRST ? N : (int64_t)info->M);
+    if (groups <= SEL_GROUPS_MAX) return;
+    const int c = threadIdx.x & 15, sl = threadIdx.x >> 4, per = (groups + 63) >> 6;
+    const int g0 = min(sl * per, groups), g1 = min(g0 + per, groups);
+    uint32_t* col = group + blockIdx.x * 16 + c;
+    uint32_t sum = 0;
+#pragma unroll 8
+    for (int g = g0; g < g1; ++g) sum += col[(int64_t)g * 256];
+    part[sl][c] = sum;
+    __syncthreads();
+    uint32_t run = 0;
+    for (int s = 0; s < sl; ++s) run += part[s][c];
+    if (sl == 63) col[(int64_t)total_row * 256] = run + sum;
+    for (int g = g0; g < g1; g += 8) {
+        uint32_t v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = g + j < g1 ? col[(int64_t)(g + j) * 256] : 0u;
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            if (g + j < g1) {
+                col[(int64_t)(g + j) * 256] = run;
+                run += v[j];
+            }
+    }
+}
+
 // Each wave owns RITER * 64 consecutive elements of the tile and ranks them 64 at a time with ballots, counting every digit as it
 // goes, so the order of equal digits is the input order (stable).  The pairs are then put in digit order in LDS and written out
 // position by position: neighbouring lanes write neighbouring slots of a digit's run, and key and index travel as one 8-byte
@@ -511,7 +549,7 @@ __global__ __launch_bounds__(THREADS) void radix_count_kernel(const uint2* __res
 template <int THREADS, int RITER, bool FIRST>
 __global__ __launch_bounds__(THREADS, 4) void radix_scatter_kernel(const uint2* __restrict__ in, uint2* __restrict__ out, int64_t N,
                                                                 const SelInfo* __restrict__ info, int shift, const uint32_t* __restrict__ table,
-                                                                const uint32_t* __restrict__ group, const float* __restrict__ losses, int64_t k,
+                                                                const uint32_t* __restrict__ group, int total_row, const float* __restrict__ losses, int64_t k,
                                                                 int32_t* __restrict__ idx_out, float* __restrict__ val_out) {
     constexpr int TILE = RadixShape<THREADS, RITER>::TILE, WAVES = RadixShape<THREADS, RITER>::WAVES;
     __shared__ uint32_t cnt[WAVES][256];
@@ -534,15 +572,19 @@ __global__ __launch_bounds__(THREADS, 4) void radix_scatter_kernel(const uint2* 
     {   // a digit's elements in all tiles, and in those before this one
         constexpr int SLICES = WAVES / 4;
         const int d = threadIdx.x & 255, g0 = threadIdx.x >> 8, tile = blockIdx.x;
-        const int64_t elements = FIRST ? N : (int64_t)M;
-        const int groups = (int)((elements + (int64_t)TILE * SEL_GROUP - 1) / ((int64_t)TILE * SEL_GROUP)), own = tile / SEL_GROUP;
+        const int groups = RadixShape<THREADS, RITER>::groups(FIRST ? N : (int64_t)M), own = tile / SEL_GROUP;
         uint32_t v[SEL_GROUP / SLICES], all = 0, left = 0;
 #pragma unroll
         for (int j = 0; j < SEL_GROUP / SLICES; ++j) {
             const int t = own * SEL_GROUP + g0 + SLICES * j;
             v[j] = t < tile ? table[(int64_t)t * 256 + d] : 0u;
         }
-        for (int q = g0; q < groups; q += 16 * SLICES) {
+        const bool scanned = RadixShape<THREADS, RITER>::SCANS && groups > SEL_GROUPS_MAX;
+        if (scanned && g0 == 0) {
+            all = group[(int64_t)total_row * 256 + d];
+            left = group[(int64_t)own * 256 + d];
+        }
+        for (int q = scanned ? groups : g0; q < groups; q += 16 * SLICES) {
             uint32_t w[16];
 #pragma unroll
             for (int j = 0; j < 16; ++j) w[j] = q + SLICES * j < groups ? group[(int64_t)(q + SLICES * j) * 256 + d] : 0u;
@@ -664,7 +706,7 @@ __global__ __launch_bounds__(THREADS, 4) void radix_scatter_kernel(const uint2* 
 }
 
 struct TopkScratch {
-    uint32_t *hist, *hist2, *sums, *table;   // the first three are cleared together; sums: of groups, per pass
+    uint32_t *hist, *hist2, *sums, *table;   // the first three are cleared together; sums: of groups, and of all of them, per pass
     uint2 *a, *b;
     SelInfo* info;
     int64_t cleared;
@@ -676,8 +718,8 @@ static TopkScratch carve_topk(Carver& c, int64_t N) {
     TopkScratch t;
     t.big = N >= (int64_t(1) << 22);
     t.tiles = (int)ceil_div(N, t.big ? RadixShape<512, 16>::TILE : RadixShape<256, 8>::TILE);
-    t.groups = (int)ceil_div(t.tiles, SEL_GROUP);
-    t.cleared = SEL_BINS + SEL_BINS2 + (int64_t)4 * t.groups * 256;
+    t.groups = (int)ceil_div(t.tiles, SEL_GROUP);   // at most SEL_GROUPS_MAX unless big
+    t.cleared = SEL_BINS + SEL_BINS2 + (int64_t)4 * (t.groups + 1) * 256;
     t.hist = c.take<uint32_t>(t.cleared);
     t.hist2 = t.hist + SEL_BINS;
     t.sums = t.hist2 + SEL_BINS2;
@@ -690,15 +732,19 @@ static TopkScratch carve_topk(Carver& c, int64_t N) {
 
 template <int THREADS, int RITER>
 static void launch_radix(hipStream_t s, const TopkScratch& t, const float* losses, int64_t N, int64_t k, int32_t* idx_out, float* val_out) {
+    using Shape = RadixShape<THREADS, RITER>;
     const dim3 grid(t.tiles), threads(THREADS);
     uint2 *from = t.b, *to = t.a;
     for (int pass = 0; pass < 4; ++pass) {
-        uint32_t* group = t.sums + (int64_t)pass * t.groups * 256;
+        uint32_t* group = t.sums + (int64_t)pass * (t.groups + 1) * 256;
 #define RADIX_PASS(FIRST)                                                                                                                       \
     do {                                                                                                                                        \
         hipLaunchKernelGGL((radix_count_kernel<THREADS, RITER, FIRST>), grid, threads, 0, s, from, losses, N, t.info, pass * 8, t.table, group); \
+        if constexpr (Shape::SCANS)                                                                                                             \
+            if (t.groups > SEL_GROUPS_MAX)                                                                                                      \
+                hipLaunchKernelGGL((radix_scan_kernel<Shape, FIRST>), dim3(16), dim3(1024), 0, s, t.info, N, pass * 8, group, t.groups);        \
         hipLaunchKernelGGL((radix_scatter_kernel<THREADS, RITER, FIRST>), grid, threads, 0, s, from, to, N, t.info, pass * 8, t.table, group,   \
-                           losses, k, idx_out, val_out);                                                                                        \
+                           t.groups, losses, k, idx_out, val_out);                                                                              \
     } while (0)
         if (pass == 0) RADIX_PASS(true);
         else RADIX_PASS(false);

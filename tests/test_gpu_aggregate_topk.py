@@ -191,6 +191,44 @@ def test_topk_selects_through_coarse_and_fine_bins(env, kind, n):
         np.testing.assert_array_equal(idx.cpu().numpy(), ranked[:k])
 
 
+@pytest.mark.parametrize("kind", ["halfnormal", "ties16"])
+@pytest.mark.parametrize("n", [(1 << 24) + 1, 130 * 32 * 8192 - 8191])
+def test_topk_with_scanned_groups(env, kind, n):
+    """More groups of tiles than a scatter adds up itself: the first such pool, and one whose last tile holds one sample.  With a
+    50th selected the first pass scans and the others do not."""
+    torch, bls, ctx = env
+    arr = synth.loss_array(kind, n)
+    d = torch.from_numpy(arr).cuda()
+    ranked = oracle.topk_by_loss(arr, n)
+    for k in (n // 50, n):
+        idx = torch.full((k,), -1, dtype=torch.int32, device="cuda")
+        val = torch.zeros(k, dtype=torch.float32, device="cuda")
+        bls.topk_by_loss(ctx, d, k, idx, val)
+        ctx.synchronize()
+        np.testing.assert_array_equal(idx.cpu().numpy(), ranked[:k])
+        np.testing.assert_array_equal(val.cpu().numpy().view(np.uint32), arr[ranked[:k]].view(np.uint32))
+
+
+def test_topk_time_grows_with_the_pool(env):
+    """Eight times the losses take about eight times as long (6.2 measured, the smaller pool being bound by launches); fifteen times
+    where every tile adds up the digit counts of all groups."""
+    torch, bls, ctx = env
+    best = {}
+    for n in (1 << 25, 1 << 28):
+        d = torch.randn(n, device="cuda", generator=torch.Generator(device="cuda").manual_seed(1)).abs_()
+        idx = torch.empty(n // 50, dtype=torch.int32, device="cuda")
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        times = []
+        for _ in range(6):
+            a.record()
+            bls.topk_by_loss(ctx, d, n // 50, idx)
+            b.record()
+            b.synchronize()
+            times.append(a.elapsed_time(b))
+        best[n] = min(times)
+    assert best[1 << 28] <= 10.0 * best[1 << 25], best
+
+
 def test_topk_of_scores_then_smaller_pool(env):
     # scratch is reused between calls of different sizes
     torch, bls, ctx = env
