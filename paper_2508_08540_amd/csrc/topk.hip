@@ -14,7 +14,8 @@
 
 // Ranking by counting needs no scratch and costs 24.6 us at 16384 (four sorting passes: 22 us at 16385).  Sorting whole / selecting
 // first, k = N / 50 and k = N: 200 000 samples 45 / 48 and 54 us, 262 144 (the last that four rounds of a tile hold) 51 / 48 and 55,
-// 400 000 64 / 49 and 58.  (Several selections in one go, TOPK_SORT_MAX, are another matter: they share the sort's launches.)
+// 400 000 64 / 49 and 58.  (Where the keys selected range over four digits: all of 262 145 half-normal losses 57 / 61, half of 400 000 of which
+// three quarters are zero 68 / 75.  Several selections in one go, TOPK_SORT_MAX, are another matter: they share the sort's launches.)
 #define TOPK_RANK_MAX 16384
 #define TOPK_WHOLE_MAX (1 << 18)
 
@@ -284,8 +285,8 @@ static int launch_topk_medium(bls_ctx* ctx, char* scratch_base, SelJobs jobs, in
 
 // ---- large pools ----------------------------------------------------------------------------------
 //
-// 1. Select: a histogram of the top 15 key bits gives the bin that holds the k-th largest key.  Where that bin holds more than
-//    N / 32 elements too many (they would all be sorted), a second histogram of the next 11 bits over its members gives a 26-bit
+// 1. Select: a histogram of the top 14 key bits gives the bin that holds the k-th largest key.  Where that bin holds more than
+//    N / 32 elements too many (they would all be sorted), a second histogram of the next 12 bits over its members gives a 26-bit
 //    prefix.  The M elements with key >= thr are selected (M >= k).
 // 2. Stable LSD radix sort of the M elements, 8 bits per pass, with as many passes as the range of their keys needs (the later
 //    ones exit at once).  The sort key is hi - key (hi bounds every key), so that ascending order is rank order and the keys
@@ -302,13 +303,16 @@ static int launch_topk_medium(bls_ctx* ctx, char* scratch_base, SelJobs jobs, in
 // up the groups would grow with the square of the pool, one launch scans their sums (SEL_GROUPS_MAX; 2 % and all of 2^25 half-normal
 // losses 185 -> 163 and 928 -> 831 us, 2 % of 2^28 2.85 -> 1.01 ms, of 2^30 35.9 -> 3.9).  A compaction of
 // the selected pairs before the sort (count, scan, gather: 41 us for 16 M keys) is gone too: the first pass skips what is not selected.
-// 4 M of 16 M half-normal losses: 24 launches and 201 us before, 13 and 157; all of 16 M 436 -> 330; 84 000 of 4.2 M 119 -> 77; all of
-// 600 000 96 -> 64.
+// 4 M of 16 M half-normal losses above ln 10: 24 launches and 201 us before, 13 and 155; all of 16 M 436 -> 330; 84 000 of 4.2 M 119 -> 74; all of
+// 600 000 96 -> 59.  Pools that did better with the compaction: 2 % of 2^26 and 2^28 losses of 2.30 +- 0.03, 285 -> 325 and 1010 -> 1180 us.
 
-#define SEL_BINS 32768       // level 1
-#define SEL_SHIFT 17
-#define SEL_BINS2 2048       // level 2
-#define SEL_SHIFT2 6
+#define SEL_BITS 14          // level 1
+#define SEL_BINS (1 << SEL_BITS)
+#define SEL_SUB 2            // counters of a bin in LDS
+#define SEL_SHIFT (32 - SEL_BITS)
+#define SEL_BITS2 12         // level 2
+#define SEL_BINS2 (1 << SEL_BITS2)
+#define SEL_SHIFT2 (SEL_SHIFT - SEL_BITS2)
 #define SEL_GROUP 32         // tiles of a group of digit counts
 #define SEL_GROUPS_MAX 64    // up to this many groups a scatter adds them up itself; more are scanned by a launch between
 #define SEL_EXCESS 32        // level 2 runs where more than N / SEL_EXCESS elements too many would be selected
@@ -344,42 +348,62 @@ __device__ __forceinline__ void load_keys4(const float* __restrict__ losses, int
     }
 }
 
-// LEVEL 1: bins of the top 15 bits over all elements, 128 KB of LDS.  (Losses crowd into a few octaves, but an octave has 64 of
-// these bins: the lanes of a wave mostly add to different words.)  LEVEL 2: bins of the next 11 bits over the members of one.
-// One workgroup of 1024 threads per compute unit: the loop waits for memory, while every further histogram costs a clear and a
-// fold of its bins.
+// LEVEL 1: bins of the top 14 bits over all elements, 128 KB of LDS.  An octave has 32 of these bins, so that most pools do without
+// level 2 (with 12 bits 4 M of 16 M half-normal losses above ln 10 need it: 157 -> 174 us).  LEVEL 2: bins of the next 12 bits over the
+// members of one.
+// Lanes that meet in a word are served one after the other, and losses may lie in a few bins (an untrained network's, around ln C) or be
+// equal, so every bin has two counters, for odd and even lanes, and a thread adds the elements of a run in one bin at once.  2 % of
+// 2^24 losses against 2^15 bins with one counter: half-normal 117 -> 116 us, 2.30 +- 0.03 151 -> 140, three quarters zero 150 -> 116, all
+// within 1e-4 170 -> 124, all equal 400 -> 230.  Merging the lanes of a bin before the atomic costs every wave its ballots: the launch
+// over 2^28 spread losses 250 -> 392 us.
+// Workgroups of 1024 threads, one per compute unit at level 1 and two at level 2 as soon as each has eight quads a thread (2^28 losses 237 ->
+// 181 us): the loop waits for memory, while every further histogram costs a clear and a fold of its bins.
 #define HIST_THREADS 1024
 template <int LEVEL, bool VEC>
 __global__ __launch_bounds__(HIST_THREADS) void sel_hist_kernel(const float* __restrict__ losses, int64_t N, const SelInfo* __restrict__ info,
                                                        uint32_t* __restrict__ hist) {
-    constexpr int BINS = LEVEL == 1 ? SEL_BINS : SEL_BINS2, DEPTH = 4;
+    constexpr int BINS = LEVEL == 1 ? SEL_BINS : SEL_BINS2, SUB = LEVEL == 1 ? SEL_SUB : 1, DEPTH = 2;
     extern __shared__ __align__(16) uint32_t sel_lds[];
     if (LEVEL == 2 && !info->refine) return;
-    const uint32_t b1 = LEVEL == 2 ? info->thr >> SEL_SHIFT : 0u;
-    for (int i = threadIdx.x; i < BINS / 4; i += HIST_THREADS) reinterpret_cast<uint4*>(sel_lds)[i] = make_uint4(0u, 0u, 0u, 0u);
+    const uint32_t b1 = LEVEL == 2 ? info->thr >> SEL_SHIFT : 0u, sub = threadIdx.x & (SUB - 1);
+    for (int i = threadIdx.x; i < BINS * SUB / 4; i += HIST_THREADS) reinterpret_cast<uint4*>(sel_lds)[i] = make_uint4(0u, 0u, 0u, 0u);
     __syncthreads();
-    const int64_t quads = (N + 3) >> 2, stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < quads; q += DEPTH * stride) {
+    uint32_t run_bin = 0, run = 0;   // level 1: elements of the thread since its bin last changed
+    const int64_t quads = (N + 3) >> 2;
+    constexpr int STRIDE = HIST_THREADS;
+    for (int64_t q = (int64_t)blockIdx.x * (DEPTH * STRIDE) + threadIdx.x; q < quads; q += (int64_t)gridDim.x * (DEPTH * STRIDE)) {
         uint32_t key[DEPTH][4];
         bool ok[DEPTH][4];
 #pragma unroll
         for (int u = 0; u < DEPTH; ++u) {
 #pragma unroll
             for (int j = 0; j < 4; ++j) ok[u][j] = false;
-            if (q + u * stride < quads) load_keys4<VEC>(losses, N, q + u * stride, key[u], ok[u]);
+            if (q + u * STRIDE < quads) load_keys4<VEC>(losses, N, q + u * STRIDE, key[u], ok[u]);
         }
 #pragma unroll
         for (int u = 0; u < DEPTH; ++u)
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 if (!ok[u][j]) continue;
-                if (LEVEL == 1) atomicAdd(&sel_lds[key[u][j] >> SEL_SHIFT], 1u);
-                else if ((key[u][j] >> SEL_SHIFT) == b1) atomicAdd(&sel_lds[(key[u][j] >> SEL_SHIFT2) & (SEL_BINS2 - 1)], 1u);
+                if (LEVEL == 1) {
+                    const uint32_t bin = key[u][j] >> SEL_SHIFT;
+                    if (bin != run_bin) {
+                        atomicAdd(&sel_lds[run_bin * SUB + sub], run);
+                        run_bin = bin;
+                        run = 0;
+                    }
+                    ++run;
+                } else if ((key[u][j] >> SEL_SHIFT) == b1) {
+                    atomicAdd(&sel_lds[(key[u][j] >> SEL_SHIFT2) & (SEL_BINS2 - 1)], 1u);
+                }
             }
     }
+    if (LEVEL == 1) atomicAdd(&sel_lds[run_bin * SUB + sub], run);
     __syncthreads();
     for (int i = threadIdx.x; i < BINS; i += HIST_THREADS) {
-        const uint32_t c = sel_lds[i];
+        uint32_t c = 0;
+#pragma unroll
+        for (int u = 0; u < SUB; ++u) c += sel_lds[i * SUB + u];
         if (c) atomicAdd(&hist[i], c);
     }
 }
@@ -390,28 +414,16 @@ template <int LEVEL>
 __global__ __launch_bounds__(1024) void sel_threshold_kernel(const uint32_t* __restrict__ hist, uint32_t k, int64_t N, SelInfo* __restrict__ info) {
     constexpr int PER = (LEVEL == 1 ? SEL_BINS : SEL_BINS2) / 1024;   // bins per thread
     __shared__ uint32_t wave_total[16], top_bin;
-    extern __shared__ __align__(16) uint32_t sel_lds[];   // level 1: the bins, a word left out after every 32
     if (LEVEL == 2 && !info->refine) return;
     const uint32_t want = LEVEL == 1 ? k : k - info->above, first = LEVEL == 2 ? info->thr : 0u, hi_before = LEVEL == 2 ? info->hi : 0u,
                    above_before = LEVEL == 2 ? info->above : 0u;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     uint32_t mine[PER], tot = 0;
     if (threadIdx.x == 0) top_bin = 0u;
-    if constexpr (LEVEL == 1) {
-        uint4 v[PER / 4];
 #pragma unroll
-        for (int j = 0; j < PER / 4; ++j) v[j] = reinterpret_cast<const uint4*>(hist)[j * 1024 + threadIdx.x];
-#pragma unroll
-        for (int j = 0; j < PER / 4; ++j) {
-            const int b = 4 * (j * 1024 + threadIdx.x), at = b + (b >> 5);
-            sel_lds[at] = v[j].x; sel_lds[at + 1] = v[j].y; sel_lds[at + 2] = v[j].z; sel_lds[at + 3] = v[j].w;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < PER; ++j) mine[j] = sel_lds[threadIdx.x * (PER + 1) + j];
-    } else {
-#pragma unroll
-        for (int j = 0; j < PER; ++j) mine[j] = hist[threadIdx.x * PER + j];
+    for (int j = 0; j < PER; j += 4) {
+        const uint4 v = reinterpret_cast<const uint4*>(hist)[(threadIdx.x * PER + j) / 4];
+        mine[j] = v.x; mine[j + 1] = v.y; mine[j + 2] = v.z; mine[j + 3] = v.w;
     }
 #pragma unroll
     for (int j = 0; j < PER; ++j) tot += mine[j];
@@ -423,14 +435,12 @@ __global__ __launch_bounds__(1024) void sel_threshold_kernel(const uint32_t* __r
     }
     if (lane == 0) wave_total[wave] = incl;
     __syncthreads();
-    if (LEVEL == 1) {
-        int top = -1;
+    int top = -1;
 #pragma unroll
-        for (int j = 0; j < PER; ++j)
-            if (mine[j]) top = j;
-        if (top >= 0) atomicMax(&top_bin, (uint32_t)(threadIdx.x * PER + top));
-        __syncthreads();
-    }
+    for (int j = 0; j < PER; ++j)
+        if (mine[j]) top = j;
+    if (top >= 0) atomicMax(&top_bin, (uint32_t)(threadIdx.x * PER + top));
+    __syncthreads();
     uint32_t above = incl - tot;
     for (int w = wave + 1; w < 16; ++w) above += wave_total[w];
 #pragma unroll
@@ -439,7 +449,9 @@ __global__ __launch_bounds__(1024) void sel_threshold_kernel(const uint32_t* __r
         if (above < want && with >= want) {
             const uint32_t b = threadIdx.x * PER + j;
             const uint32_t thr = LEVEL == 1 ? b << SEL_SHIFT : first | (b << SEL_SHIFT2);
-            const uint32_t hi = LEVEL == 1 ? ((top_bin + 1u) << SEL_SHIFT) - 1u : hi_before;   // the last bin: 2^32 - 1
+            // level 1: the end of the last bin (2^32 - 1 for the largest); level 2: that of its last sub-bin where no bin is above it
+            const uint32_t hi = LEVEL == 1 ? ((top_bin + 1u) << SEL_SHIFT) - 1u
+                                : above_before ? hi_before : first | (((top_bin + 1u) << SEL_SHIFT2) - 1u);
             const uint32_t range = hi - thr;   // sort keys lie in [0, range]
             info->thr = thr;
             info->hi = hi;
@@ -771,15 +783,19 @@ static int launch_topk_large(bls_ctx* ctx, char* scratch_base, const float* loss
     Carver c(scratch_base);
     TopkScratch t = carve_topk(c, N);
     hipStream_t s = ctx->stream;
-    const int64_t hist_want = ceil_div(ceil_div(N, 4), HIST_THREADS);
-    const int hist_blocks = (int)(hist_want < ctx->num_cus ? hist_want : ctx->num_cus);
+    const int64_t hist_most = ceil_div(ceil_div(N, 4), HIST_THREADS);
+    auto hist_blocks = [&](int level) {
+        int64_t n = ctx->num_cus;
+        if (level == 2 && hist_most > 8 * n) n = hist_most < 16 * n ? hist_most / 8 : 2 * n;
+        return (unsigned)(hist_most < n ? hist_most : n);
+    };
     const bool vec = reinterpret_cast<uintptr_t>(losses) % 16 == 0;   // 16-byte loads where the array allows them
     hipLaunchKernelGGL(zero_u32_kernel, dim3(256), dim3(256), 0, s, t.hist, t.cleared);
 #define SEL_HIST(LEVEL, VEC, HIST) \
-    hipLaunchKernelGGL((sel_hist_kernel<LEVEL, VEC>), dim3(hist_blocks), dim3(HIST_THREADS), 4 * (LEVEL == 1 ? SEL_BINS : SEL_BINS2), s, losses, N, t.info, HIST)
+    hipLaunchKernelGGL((sel_hist_kernel<LEVEL, VEC>), dim3(hist_blocks(LEVEL)), dim3(HIST_THREADS), 4 * (LEVEL == 1 ? SEL_BINS * SEL_SUB : SEL_BINS2), s, losses, N, t.info, HIST)
     if (vec) SEL_HIST(1, true, t.hist);
     else SEL_HIST(1, false, t.hist);
-    hipLaunchKernelGGL(sel_threshold_kernel<1>, dim3(1), dim3(1024), 4 * (SEL_BINS + SEL_BINS / 32), s, t.hist, (uint32_t)k, N, t.info);
+    hipLaunchKernelGGL(sel_threshold_kernel<1>, dim3(1), dim3(1024), 0, s, t.hist, (uint32_t)k, N, t.info);
     if (vec) SEL_HIST(2, true, t.hist2);
     else SEL_HIST(2, false, t.hist2);
 #undef SEL_HIST
