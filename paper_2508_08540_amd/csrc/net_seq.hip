@@ -48,6 +48,7 @@ struct LayerAct {
 };
 
 // Packs of a weight matrix W[rows][cols] at `off` of the parameters: over cols (the projection) and over rows (its input gradient).
+#define NO_PACK (~size_t(0))
 struct SplitWeight {
     int64_t off;
     int rows, cols;
@@ -87,7 +88,8 @@ struct SeqScratch {
     int64_t acc_count;
     // fp32 mode, training: the factors that gemm_split.hip reads as packs (empty: no packs)
     std::vector<SplitWeight> packs;
-    uint16_t *pack_f, *pack_t, *pack_x;   // weights as second factor of a projection, of its input gradient; of the product at hand on the side stream
+    uint16_t *pack_f, *pack_t;      // weights as second factor of a projection, of its input gradient
+    uint16_t* pack_x;               // second factor of the weight gradient at hand on the side stream
 };
 
 // Splits of the token contraction of a weight gradient so that about one workgroup per compute unit is in flight: the products
@@ -116,14 +118,27 @@ int dgrad_splits(bool bf, int64_t M, int N, int K) {
     return (int)(s > 1 ? s : 1);
 }
 
-// Training in fp32 takes the linear layers' products to gemm_split.hip from this many tokens a batch on: the packs of the weights
-// cost the same (0.6 GB of traffic at 35 million parameters) whatever the batch.  Two steps of the 6-layer encoder, fp32 products
-// against split ones: 256 tokens 4.41 / 4.61 ms, 400 tokens 5.15 / 5.00, three layers with 600 tokens 2.68 / 2.48, 1600 tokens
-// 7.77 / 6.34, 3100 tokens 15.93 / 11.59.  (Scoring keeps the fp32 products: a score is the same bits in a pool of any size.)
+// Which products of the linear layers a training step in fp32 takes to gemm_split.hip.  (Scoring keeps the fp32 products: a score is
+// the same bits in a pool of any size.)
+//
+// All weights are packed in both orders, in two launches, or none.  20 bytes a weight, whatever the batch, cost what 300 tokens gain
+// (32 000 x 512: 43 us; 135 saved at 512 tokens), hence the tokens.  A product of less work is bound by latency, not by the matrix
+// pipe (projection and input gradient, fp32 instruction / split, us: 1024 tokens x 512 x 512, 2.7e8, 29 / 29; 2048 x 256 x 1024, 5.4e8, 38 / 34; 2048
+// x 2048 x 512, 2.1e9, 103 / 67), while every weight gradient is one launch more, hence the work of the largest product.  Two steps of two
+// layers, feed-forward width four times the width, 1000 words, fp32 products / split: width 64, 8192 tokens (5.2e8) 1.19 / 1.25 ms; 128, 4096 tokens
+// (5.2e8) 1.08 / 1.09, 8192 tokens 1.56 / 1.48; 256, 1024 tokens 1.00 / 1.07, 2048 (5.4e8) 1.26 / 1.20; 512, 384 tokens 1.20 / 1.22, 512 (5.4e8) 1.26 / 1.25, 4096
+// 4.01 / 3.09.
 #define SPLIT_MIN_TOKENS 512
+#define SPLIT_MIN_WORK 530000000
 bool uses_packs(const bls_model* m, int64_t T) {
-    return m->desc.act_dtype != BLS_ACT_BF16 && T >= SPLIT_MIN_TOKENS && m->enc_D % 16 == 0 && m->enc_F % 4 == 0;
+    return m->desc.act_dtype != BLS_ACT_BF16 && T >= SPLIT_MIN_TOKENS && m->enc_D % 16 == 0 && m->enc_F % 4 == 0 &&
+           T * m->enc_D * std::max(m->enc_F, m->enc_V) >= SPLIT_MIN_WORK;
 }
+// Not split: the first feed-forward product of a width of 64 and less, which its GELU bounds and not its contraction (65 536 tokens, 2048 x 64:
+// 368 us, split 567); and a weight gradient of few rows, which packs its second factor for itself, T x n_in values that n_out rows
+// have to earn (65 536 tokens, 64 x 2048: 231 us, split 210 and the pack 235; 256 x 1024 366, 255 and 118).
+#define SPLIT_MIN_GELU_K 65
+#define SPLIT_MIN_WGRAD_OUT 128
 
 enum Kind { F32_ONLY, BOTH, FACTOR_ONLY };   // FACTOR_ONLY: fp32 in fp32 mode, bf16 alone in bf16 mode
 
@@ -237,20 +252,20 @@ SeqScratch carve(Carver& c, const bls_model* m, int B, bool train) {
     s.acc = c.take<fixsum_t>(s.acc_count);
     if (uses_packs(m, T)) {
         size_t f = 0, t = 0;
-        auto pack = [&](int64_t off, int rows, int cols) {
-            s.packs.push_back(SplitWeight{off, rows, cols, f, t});
-            f += split_pack_elems(rows, cols);
-            t += split_pack_elems(cols, rows);
+        auto pack = [&](int64_t off, int rows, int cols, bool with_f, bool with_t) {
+            s.packs.push_back(SplitWeight{off, rows, cols, with_f ? f : NO_PACK, with_t ? t : NO_PACK});
+            f += with_f ? split_pack_elems(rows, cols) : 0;
+            t += with_t ? split_pack_elems(cols, rows) : 0;
         };
         for (const EncLayer& e : m->enc_layers) {
-            for (int64_t w : {e.wq, e.wk, e.wv, e.wo}) pack(w, D, D);
-            pack(e.w1, F, D);
-            pack(e.w2, D, F);
+            for (int64_t w : {e.wq, e.wk, e.wv, e.wo}) pack(w, D, D, true, true);
+            pack(e.w1, F, D, D >= SPLIT_MIN_GELU_K, true);
+            pack(e.w2, D, F, true, true);
         }
-        pack(m->enc_head, V, D);
+        pack(m->enc_head, V, D, true, true);
         s.pack_f = c.take<uint16_t>(f);
         s.pack_t = c.take<uint16_t>(t);
-        s.pack_x = c.take<uint16_t>(split_pack_elems(std::max(D, F), T));
+        s.pack_x = c.take<uint16_t>(split_pack_elems(D >= SPLIT_MIN_WGRAD_OUT ? std::max(D, F) : D, T));
     }
     return s;
 }
@@ -348,7 +363,7 @@ struct Net {
     // pack of the weights at `off`, over its columns or (t) its rows; NULL where there are none
     const uint16_t* pack(int64_t off, bool t) const {
         for (const SplitWeight& w : s->packs)
-            if (w.off == off) return t ? s->pack_t + w.t : s->pack_f + w.f;
+            if (w.off == off && (t ? w.t : w.f) != NO_PACK) return t ? s->pack_t + w.t : s->pack_f + w.f;
         return nullptr;
     }
     void refresh_packs() const {
@@ -356,17 +371,19 @@ struct Net {
             SplitPackTable tab;
             tab.n = 0;
             for (const SplitWeight& w : s->packs) {
-                tab.j[tab.n++] = SplitPackJob{w.off, (int64_t)(t ? w.t : w.f), t ? w.cols : w.rows, t ? w.rows : w.cols, w.cols, 0};
-                if (tab.n == SPLIT_PACK_MAX || &w == &s->packs.back()) {
+                if ((t ? w.t : w.f) != NO_PACK)
+                    tab.j[tab.n++] = SplitPackJob{w.off, (int64_t)(t ? w.t : w.f), t ? w.cols : w.rows, t ? w.rows : w.cols, w.cols, 0};
+                if (tab.n == SPLIT_PACK_MAX || (tab.n && &w == &s->packs.back())) {
                     PROF(ctx, PROF_UPDATE, launch_split_pack(st, tab, t, params, t ? s->pack_t : s->pack_f));
                     tab.n = 0;
                 }
             }
         }
     }
-    // the second factor x[T][n_in] of a weight gradient as a pack over the tokens, in the side stream's buffer
-    const uint16_t* pack_tokens(Mat x, int64_t T, int n_in) const {
-        if (s->packs.empty()) return nullptr;
+    // the second factor x[T][n_in] of a weight gradient of n_out rows as a pack over the tokens, in the side stream's buffer; NULL
+    // where that does not pay
+    const uint16_t* pack_tokens(Mat x, int64_t T, int n_out, int n_in) const {
+        if (s->packs.empty() || n_out < SPLIT_MIN_WGRAD_OUT) return nullptr;
         SplitPackTable tab;
         tab.n = 1;
         tab.j[0] = SplitPackJob{0, 0, n_in, (int)T, n_in, 0};
@@ -457,7 +474,7 @@ struct Net {
         p.M = n_out; p.N = n_in; p.K = (int)T;
         p.splits = wgrad_splits(n_out, n_in, T);
         p.part = s->part;
-        if (split_takes(p)) p.Bs = pack_tokens(x, T, n_in);
+        if (split_takes(p)) p.Bs = pack_tokens(x, T, n_out, n_in);
         multiply(ctx, st, s, p, PROF_CONV_WGRAD);
     }
     // q, k, v = x Wq^T + bq, ... as one batch of three products where the three weights (and biases, and outputs) are
@@ -494,7 +511,7 @@ struct Net {
             p.batch = 3;
             p.splits = wgrad_splits(D, D, T, 3);
             p.part = s->part;
-            if (split_takes(p)) p.Bs = pack_tokens(x, T, D);
+            if (split_takes(p)) p.Bs = pack_tokens(x, T, D, D);
             multiply(ctx, st, s, p, PROF_CONV_WGRAD);
             return;
         }

@@ -1,0 +1,25 @@
+"""Scratch of the sequence model's training steps in fp32: copies of the weights for split products are kept only by batches whose
+products gain from them.  Everything else grows linearly with the batch."""
+import pytest
+
+import paper_2508_08540_amd as bls
+
+
+def _jump(batch, *model):
+    """Bytes by which the scratch of `batch` sequences exceeds what the two smaller batches let expect."""
+    m = bls.Model.transformer(*model)
+    w = [m.workspace_bytes(batch - i, True) for i in range(3)]
+    return (w[0] - w[1]) - (w[1] - w[2])
+
+
+@pytest.mark.parametrize("vocab,D,H,F", [(1000, 64, 2, 256), (1000, 128, 4, 512), (1000, 256, 8, 1024)])
+def test_narrow_encoders_of_512_tokens_keep_no_copies(vocab, D, H, F):
+    weights = 2 * (4 * D * D + 2 * D * F) + vocab * D
+    assert abs(_jump(4, vocab, 128, D, H, F, 2)) < 6 * weights   # one copy in three bf16
+
+
+@pytest.mark.parametrize("vocab,D,H,F,batch", [(32000, 64, 2, 256, 4), (1000, 256, 8, 1024, 17), (1000, 512, 8, 2048, 5)])
+def test_larger_products_keep_two_copies(vocab, D, H, F, batch):
+    weights = 2 * (4 * D * D + 2 * D * F) + vocab * D
+    sizes = [bls.Model.transformer(vocab, 128, D, H, F, 2).workspace_bytes(b, True) for b in (2, 3, batch)]
+    assert sizes[2] - sizes[1] - (batch - 3) * (sizes[1] - sizes[0]) > 12 * weights
