@@ -262,7 +262,7 @@ SeqScratch carve(Carver& c, const bls_model* m, int B, bool train) {
             pack(e.w1, F, D, D >= SPLIT_MIN_GELU_K, true);
             pack(e.w2, D, F, true, true);
         }
-        pack(m->enc_head, V, D, true, true);
+        pack(m->enc_head, V, D, true, gemm_split_takes(nullptr, V, 0, 0, false, V, 0));   // rows of V logits are the other factor
         s.pack_f = c.take<uint16_t>(f);
         s.pack_t = c.take<uint16_t>(t);
         s.pack_x = c.take<uint16_t>(split_pack_elems(D >= SPLIT_MIN_WGRAD_OUT ? std::max(D, F) : D, T));

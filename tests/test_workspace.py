@@ -23,3 +23,14 @@ def test_larger_products_keep_two_copies(vocab, D, H, F, batch):
     weights = 2 * (4 * D * D + 2 * D * F) + vocab * D
     sizes = [bls.Model.transformer(vocab, 128, D, H, F, 2).workspace_bytes(b, True) for b in (2, 3, batch)]
     assert sizes[2] - sizes[1] - (batch - 3) * (sizes[1] - sizes[0]) > 12 * weights
+
+
+def test_no_copy_of_the_vocabulary_projection_that_no_product_reads():
+    """Rows of 32 001 logits do not start on 16 bytes, so the input gradient of the projection keeps the fp32 instruction."""
+    layers = 2 * (4 * 512 * 512 + 2 * 512 * 2048)
+    extra = {}
+    for vocab in (32000, 32001):
+        sizes = [bls.Model.transformer(vocab, 128, 512, 8, 2048, 2).workspace_bytes(b, True) for b in (2, 3, 4)]
+        extra[vocab] = (sizes[2] - sizes[1]) - (sizes[1] - sizes[0])
+    assert extra[32000] >= 12 * (layers + 32000 * 512)
+    assert extra[32000] - extra[32001] >= 5 * 32000 * 512
