@@ -557,9 +557,13 @@ int launch_gemm_tiled(hipStream_t s, GemmDesc d) {
     if (d.k_seg && !direct) return BLS_EUNSUPPORTED;   // gemm_tiled_kernel reads one pair of matrices
     GdPlan plan{4, 4, d.splits};
     if (direct) plan = gd_plan(d.M, d.N, d.K, d.batch, d.splits);
-    // A contraction of a few steps is latency: as long as four workgroups of the smallest tile per compute unit hold the product, they
-    // run side by side (248 attention scores of 100 x 100 x 64: 21 us in tiles of 128, 12 in tiles of 64).
-    if (direct && plan.splits == 1 && d.K <= 8 * GT_K && (int64_t)d.batch * ceil_div(d.M, 64) * ceil_div(d.N, 64) <= 1024) plan = GdPlan{2, 2, 1};
+    // A contraction of up to eight steps is latency: workgroups of the smallest tile, of which more run side by side, beat the plan at
+    // every size (scores of 64 / 1500 sequences of 100 / 128 tokens, width 128, plan and smallest tile: 248 / 220 us, 4.32 / 4.08 ms; width 64, 256 sequences 347 / 326
+    // us; training 31 x 100 tokens, width 512, two layers 2.81 / 2.74 ms).  Contractions of one or two steps store more than they multiply, so from four
+    // workgroups per compute unit on the plan decides there (8192 tokens x 32 000 words, widths 16 and 32: scores 585 / 622 and 655 / 676 us).
+    if (direct && plan.splits == 1 && d.K <= 8 * GT_K &&
+        (d.K > 2 * GT_K || (int64_t)d.batch * ceil_div(d.M, 64) * ceil_div(d.N, 64) <= 1024))
+        plan = GdPlan{2, 2, 1};
     const int k_chunk = (int)ceil_div(ceil_div(d.K, plan.splits), GT_K) * GT_K;
     d.splits = (int)ceil_div(d.K, k_chunk);
     d.k_chunk = k_chunk;
