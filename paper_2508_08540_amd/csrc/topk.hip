@@ -849,8 +849,8 @@ int launch_topk_jobs(bls_ctx* ctx, char* scratch_base, SelJobs jobs, int n_jobs,
 
 // ---- selection without any allocation -----------------------------------------------------------------
 //
-// The large-pool path above needs device scratch (histogram, block counts, digit tables and two arrays of key and
-// index).  For callers that must not allocate, the same launches run on a fixed array in the library's device image.
+// The paths above need device scratch (histograms, digit tables and their sums, two arrays of key and index).  For callers that
+// must not allocate, the same launches run on a fixed array in the library's device image.
 // Every GPU the library is loaded on holds its own copy of the array at its own address, for the life of the process.
 
 #define TOPK_STATIC_BYTES (size_t(18) << 20)   // >= topk_scratch_bytes(BLS_TOPK_STATIC_MAX_N, .), checked on every call

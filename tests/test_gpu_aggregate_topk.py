@@ -122,7 +122,7 @@ def test_topk_matches_oracle_small(env, kind, n):
 @pytest.mark.parametrize("kind", synth.LOSS_ARRAY_KINDS)
 @pytest.mark.parametrize("n", [16385, 50000, 100000, (1 << 20) + 3])
 def test_topk_matches_oracle_large(env, kind, n):
-    # pools beyond one workgroup's LDS: radix select, ordered compaction, stable radix sort
+    # pools that are sorted whole in radix passes, and one that is selected before it is sorted
     torch, bls, ctx = env
     arr = synth.loss_array(kind, n)
     for k in sorted({1, n // 4, n}):
@@ -132,8 +132,9 @@ def test_topk_matches_oracle_large(env, kind, n):
 @pytest.mark.parametrize("kind", ["halfnormal", "ties16", "specials"])
 @pytest.mark.parametrize("n", [64, 65, 16383, 65536, 65537, 131073, 262144, 262145, 1 << 19, (1 << 19) + 1])
 def test_topk_at_the_edges_of_its_variants(env, kind, n):
-    # chunks of 64 and the last pool ranked by counting; 1, 2, 4 and 8 rounds per tile of the whole-pool sort, full and with a
-    # remainder of one; the first pool that is selected before it is sorted; from an address that is only 4-byte aligned
+    # chunks of 64 and the last pool ranked by counting; 1, 2 and 4 rounds per tile of the whole-pool sort, full and with a
+    # remainder of one (8 rounds occur in an epoch's draws only, whose tests reach 2^19); the first pool that is selected before it
+    # is sorted and larger ones; from an address that is only 4-byte aligned
     torch, bls, ctx = env
     arr = synth.loss_array(kind, n)
     d = torch.from_numpy(np.concatenate([np.zeros(1, np.float32), arr])).cuda()[1:]
@@ -179,16 +180,20 @@ def test_topk_selects_through_coarse_and_fine_bins(env, kind, n):
         arr = np.abs(rng.standard_normal(n)).astype(np.float32) + np.float32(2.3)
     if kind == "sorted":
         arr = np.sort(arr)
-    if kind == "split":   # n / 32 + 100 losses in a bin of their own, far above the others
+    if kind == "split":   # n / 32 + 100 losses in the bin of 64 (its top 14 bits), far above the others, two of each
         m = n // 32 + 100
-        arr[rng.permutation(n)[:m]] = np.float32(64.0) + np.arange(m, dtype=np.float32) * np.float32(2.0 ** -21 * 16)
+        arr[rng.permutation(n)[:m]] = np.float32(64.0) + (np.arange(m) // 2).astype(np.float32) * np.float32(2.0 ** -17)
+        in_bin = int((arr.view(np.uint32) >> 18 == np.float32(64.0).view(np.uint32) >> 18).sum())
+        assert in_bin == m == int((arr >= 64.0).sum()) and in_bin - 99 > n // 32 >= in_bin - 101
     ranked = oracle.topk_by_loss(arr, n)
     d = torch.from_numpy(arr).cuda()
     for k in (1, 99, 101, n // 3, n - 1):
         idx = torch.full((k,), -1, dtype=torch.int32, device="cuda")
-        bls.topk_by_loss(ctx, d, k, idx, None)
+        val = torch.zeros(k, dtype=torch.float32, device="cuda")
+        bls.topk_by_loss(ctx, d, k, idx, val)
         ctx.synchronize()
         np.testing.assert_array_equal(idx.cpu().numpy(), ranked[:k])
+        np.testing.assert_array_equal(val.cpu().numpy().view(np.uint32), arr[ranked[:k]].view(np.uint32))
 
 
 @pytest.mark.parametrize("kind", ["halfnormal", "ties16"])
