@@ -2,13 +2,15 @@
 // C[m][n] = alpha * sum_k A(m,k) B(n,k) [+ bias[n]] [+ R[m][n]], A as in gemm_tiled.hip, B packed (below).
 //
 // Every fp32 value is the exact sum of three bf16 values, h + m + l (3 x 8 bits; h is x rounded, m what is left rounded, l the
-// rest).  Of the nine partial products the six of at least 2^-18 are summed (l h, h l, m m, m h, h m, h h); the three left out
-// are 2^-27 and less of a product.  Six bf16 instructions take 3/8 of the matrix-pipe time of the fp32 instructions for the same
-// block, and round less often: the h h products have an accumulator of their own (one rounding per 16 values of k instead of
-// four per 16), the others, 2^-9 of its size, a second one.  Relative 2-norm error against 64 bits, normal factors, contraction of
-// 64 / 512 / 2048 / 32 000: fp32 instruction 1.4e-7 / 4.0e-7 / 8.1e-7 / 3.2e-6, this 5.0e-8 / 1.3e-7 / 2.7e-7 / 1.1e-6; one accumulator
-// for all six would be at 3.3e-7 for 512 and biased (the instruction truncates towards minus infinity).  Weight gradients
-// (A k-major) fold the first accumulator every GT_RUN steps: 3100 tokens 1.1e-7, fp32 instructions in the same runs 2.9e-7.
+// rest).  Of the nine partial products six are summed (l h, h l, m m, m h, h m, h h); the three left out, m l, l m and l l, are at most
+// 2^-24 of a product together, 2^-27.5 in the mean square.  Six bf16 instructions take 3/8 of the matrix-pipe time of the fp32
+// instructions for the same block, and round less often: the h h products have an accumulator of their own (one rounding per 16
+// values of k instead of four per 16), the others, 2^-8 of its size, a second one.  Relative 2-norm error against 64 bits, normal factors,
+// contraction of 16 / 32 / 64 / 512 / 2048 / 32 000: fp32 instruction 7.4e-8 / 1.0e-7 / 1.4e-7 / 4.0e-7 / 8.1e-7 / 3.2e-6, this 3.2e-8 / 3.9e-8 / 5.0e-8 /
+// 1.3e-7 / 2.7e-7 / 1.1e-6; one accumulator for all six would be at 3.3e-7 for 512 and biased (the instruction truncates towards minus
+// infinity).  Where one product of a sum dwarfs the others (factors spread over e^3, log-normal) the two are alike: 16 / 64 / 2048 2.6e-8 /
+// 7.0e-8 / 1.1e-7 and 4.1e-8 / 8.2e-8 / 1.3e-7.  Weight gradients (A k-major) fold the first accumulator every GT_RUN steps: 3100 tokens 1.1e-7,
+// fp32 instructions in the same runs 2.9e-7.
 // Values below 2^-110 lose the bits of l and m that bf16 cannot hold (2^-133).
 //
 // Infinities, NaN and values that round to a bf16 infinity: h + m + l is NaN or infinity minus infinity there, and h h may be beyond

@@ -394,7 +394,7 @@ __global__ __launch_bounds__(256) void gelu_bwd_kernel(float* __restrict__ dg, c
 
 // The same with the column sums of du on the way (the gradient of the bias added before the activation): a workgroup
 // owns GB_ROWS rows of 1024 adjacent columns, a thread four of those columns; part[blockIdx.y][n] = its rows' sum.
-// Eight rows: 3100 x 2048 are then 776 workgroups of a chain of loads and erf / exp each (32 rows: 194, 52 us; now 28).
+// Eight rows: 3100 x 2048 are then 776 workgroups of a chain of loads and erf / exp each (32 rows: 194, 52 us; now 27).
 #define GB_ROWS 8
 __global__ __launch_bounds__(256) void gelu_bwd_colsum_kernel(float* __restrict__ dg, const float* __restrict__ u, uint16_t* __restrict__ du16,
                                                               int64_t M, int N, float* __restrict__ part) {
