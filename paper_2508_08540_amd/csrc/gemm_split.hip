@@ -8,9 +8,10 @@
 // values of k instead of four per 16), the others, 2^-8 of its size, a second one.  Relative 2-norm error against 64 bits, normal factors,
 // contraction of 16 / 32 / 64 / 512 / 2048 / 32 000: fp32 instruction 7.4e-8 / 1.0e-7 / 1.4e-7 / 4.0e-7 / 8.1e-7 / 3.2e-6, this 3.2e-8 / 3.9e-8 / 5.0e-8 /
 // 1.3e-7 / 2.7e-7 / 1.1e-6; one accumulator for all six would be at 3.3e-7 for 512 and biased (the instruction truncates towards minus
-// infinity).  Where one product of a sum dwarfs the others (factors spread over e^3, log-normal) the two are alike: 16 / 64 / 2048 2.6e-8 /
-// 7.0e-8 / 1.1e-7 and 4.1e-8 / 8.2e-8 / 1.3e-7.  Weight gradients (A k-major) fold the first accumulator every GT_RUN steps: 3100 tokens 1.1e-7,
-// fp32 instructions in the same runs 2.9e-7.
+// infinity).  Where one product of a sum dwarfs the others that truncation is what is left, and the fp32 instruction is closer: factors
+// spread log-normally over e^3, 16 / 64 / 2048 values 2.6e-8 / 7.0e-8 / 1.1e-7, this 4.1e-8 / 8.2e-8 / 1.3e-7 (gradients of encoders: half its
+// error in the median, a third in the worst tensor).  Weight gradients (A k-major) fold the first accumulator every GT_RUN steps: 3100 tokens
+// 1.1e-7, fp32 instructions in the same runs 2.9e-7.
 // Values below 2^-110 lose the bits of l and m that bf16 cannot hold (2^-133).
 //
 // Infinities, NaN and values that round to a bf16 infinity: h + m + l is NaN or infinity minus infinity there, and h h may be beyond
